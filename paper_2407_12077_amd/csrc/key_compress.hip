@@ -5,7 +5,8 @@
 // by the HBM read of x; all arithmetic is on the matrix cores (v_mfma_f32_16x16x32_bf16, fp32
 // accumulation, bf16 products are exact in fp32).
 //
-// One workgroup owns 128 tokens x kBN output columns (kBN = 128 up to D = 2048, 256 above, so that
+// Two kernels.  With enough tokens to fill the chip with large tiles (the rule is at the launch): one workgroup
+// owns 128 tokens x kBN output columns (kBN = 128 up to D = 2048, 256 above, so that
 // up to D = 4096 a workgroup has all columns and x passes through a compute unit's vector memory
 // path once; fewer columns in the last tile when D/16 is not a multiple of kBN) and walks the D
 // axis in steps of 64 channels (cyclically, from a start that differs between workgroups).  Its
@@ -331,20 +332,178 @@ __global__ __launch_bounds__(Tile<kBN>::kThreads, 256 / kBN) void key_compress_k
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// Few tokens (a decode batch, short prompts): the contraction split over the waves.  Bound by latency up to a
+// few hundred tokens (launch, two rounds of loads, the reduction: 4 to 6 us), then by W through L2.
+// ------------------------------------------------------------------------------------------
+// The tiles above need 128 tokens per workgroup to be worth their loads: with a few row tiles most
+// compute units have nothing to do and the others walk D / 64 dependent steps.  Here a workgroup owns a
+// small tile, 16 kTB tokens x 16 kNB columns, and its sixteen waves take the 32-channel blocks of D in
+// turn (wave w: blocks w, w + 16, ...), so that a walk is D / 512 steps long, with the loads of
+// kFewDepth of them in flight, and needs no barrier: a wave reads its x fragment straight into the MFMA
+// operand layout (16 tokens, 16 bytes per lane) and passes its W block through a piece of LDS of its
+// own for the transposing read.  The sixteen partial results are added in wave order, in fp32, at the end.
+constexpr int kFewWaves = 16;
+constexpr int kFewDepth = 2;
+
+template <int kTB, int kNB>
+struct FewTile {
+    static constexpr int kWRow = 32 * kNB + 32;         // LDS row stride of a wave's W block [32][16 kNB] bf16
+    static constexpr int kWBlock = 32 * kWRow;
+    static constexpr int kPRow = 16 * kNB + 4;          // row stride (floats) of a wave's partial result
+    static constexpr int kPart = 16 * kTB * kPRow;      // floats per wave
+    static constexpr int kWBytes = kFewWaves * kWBlock, kPBytes = kFewWaves * kPart * 4;
+    static constexpr int kLds = kWBytes > kPBytes ? kWBytes : kPBytes;
+    static_assert(kLds <= 160 * 1024, "LDS budget");
+};
+
+template <int kTB, int kNB, bool kOutF32>
+__global__ __launch_bounds__(64 * kFewWaves) void key_compress_few_kernel(KcArgs a) {
+    using TL = FewTile<kTB, kNB>;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nct = (a.C + 16 * kNB - 1) / (16 * kNB);
+    const long long m0 = static_cast<long long>(blockIdx.x / nct) * (16 * kTB);
+    const int n0 = static_cast<int>(blockIdx.x % nct) * (16 * kNB);
+    const long long rows_left = a.M - m0;
+    const int rows = rows_left < 16 * kTB ? static_cast<int>(rows_left) : 16 * kTB;
+    const long long x_row_bytes = static_cast<long long>(a.D) * 2, w_row_bytes = static_cast<long long>(a.C) * 2;
+    const char* x_base = static_cast<const char*>(a.x) + m0 * x_row_bytes;
+    const long long x_bytes = rows * x_row_bytes, w_bytes = static_cast<long long>(a.D) * w_row_bytes;
+    const int nkb = a.D / 32;
+
+    // W block: 2 kNB lanes per row piece of 16 kNB columns, 32 / kNB rows per pass; columns past C (a
+    // partial last column tile) lie at an offset that no descriptor covers
+    constexpr int kLanesPerRow = 2 * kNB, kRowsPerPass = 64 / kLanesPerRow;
+    const int wr = lane / kLanesPerRow, wg = lane % kLanesPerRow;
+    const int w_voff = n0 + 8 * wg < a.C ? static_cast<int>(wr * w_row_bytes + (n0 + 8 * wg) * 2) : 0x7ffffff0;
+    const int w_pass = n0 + 8 * wg < a.C ? static_cast<int>(kRowsPerPass * w_row_bytes) : 0;
+    int x_voff[kTB];
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb) x_voff[tb] = static_cast<int>((16 * tb + l16) * x_row_bytes + 16 * g4);
+
+    struct Regs {
+        uint4v x[kTB], w[kNB];
+    };
+    auto fetch = [&](Regs& s, int kb) {
+        const bool live = kb < nkb;                    // uniform; past the end the descriptors are empty
+        const long long xs = static_cast<long long>(kb) * 64, ws = static_cast<long long>(kb) * 32 * w_row_bytes;
+        const __amdgpu_buffer_rsrc_t rx = rsrc_of(x_base + (live ? xs : 0), live ? x_bytes - xs : 0);
+        const __amdgpu_buffer_rsrc_t rw = rsrc_of(static_cast<const char*>(a.w) + (live ? ws : 0), live ? w_bytes - ws : 0);
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb)
+            s.w[nb] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(rw, w_voff + nb * w_pass, 0, 0));
+#pragma unroll
+        for (int tb = 0; tb < kTB; ++tb)
+            s.x[tb] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(rx, x_voff[tb], 0, 0));
+    };
+
+    float4v acc[kTB][kNB];
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb)
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb) acc[tb][nb] = float4v{0.f, 0.f, 0.f, 0.f};
+    char* mine = lds + wave * TL::kWBlock;
+    const int b_lane = (8 * g4 + (l16 >> 2)) * TL::kWRow + 8 * (l16 & 3);
+    auto step = [&](const Regs& s) {
+        // the wave alone touches its piece: the fences keep the order of its own accesses
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb)
+            *reinterpret_cast<uint4v*>(mine + (wr + kRowsPerPass * nb) * TL::kWRow + 16 * wg) = s.w[nb];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb) {
+            // columns as the rows of the product: a lane ends with four neighbouring columns of its token
+            const bf16x8 wt = lds_read_tr8<TL::kWRow>(mine, b_lane + 32 * nb);
+#pragma unroll
+            for (int tb = 0; tb < kTB; ++tb)
+                acc[tb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt, __builtin_bit_cast(bf16x8, s.x[tb]), acc[tb][nb], 0, 0, 0);
+        }
+    };
+    Regs ring[kFewDepth];
+#pragma unroll
+    for (int i = 0; i < kFewDepth; ++i) fetch(ring[i], wave + kFewWaves * i);
+#pragma clang loop unroll(disable)
+    for (int kb = wave; kb < nkb; kb += kFewWaves * kFewDepth) {
+#pragma unroll
+        for (int i = 0; i < kFewDepth; ++i) {          // blocks past the end add products of zeros
+            step(ring[i]);
+            fetch(ring[i], kb + kFewWaves * (kFewDepth + i));
+        }
+    }
+
+    // the partial results meet in LDS
+    float* part = reinterpret_cast<float*>(lds);
+    __syncthreads();                                   // every wave is done with its W blocks
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb)
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb)
+            *reinterpret_cast<float4v*>(part + wave * TL::kPart + (16 * tb + l16) * TL::kPRow + 16 * nb + 4 * g4) = acc[tb][nb];
+    __syncthreads();
+    constexpr int kPairs = 16 * kTB * 8 * kNB;         // two neighbouring columns per thread
+    for (int i = tid; i < kPairs; i += 64 * kFewWaves) {
+        const int row = i / (8 * kNB), col = 2 * (i % (8 * kNB));
+        const float* src = part + row * TL::kPRow + col;
+        float lo = 0.f, hi = 0.f;
+#pragma unroll
+        for (int w = 0; w < kFewWaves; ++w) {
+            const float2 p = *reinterpret_cast<const float2*>(src + w * TL::kPart);
+            lo += p.x;
+            hi += p.y;
+        }
+        if (row < rows && n0 + col < a.C) {            // C is a multiple of 16
+            const long long e = (m0 + row) * a.C + n0 + col;
+            if constexpr (kOutF32)
+                *reinterpret_cast<float2*>(static_cast<float*>(a.c) + e) = make_float2(lo, hi);
+            else
+                *reinterpret_cast<unsigned*>(static_cast<unsigned short*>(a.c) + e) =
+                    static_cast<unsigned>(__builtin_bit_cast(unsigned short, static_cast<__bf16>(lo))) |
+                    (static_cast<unsigned>(__builtin_bit_cast(unsigned short, static_cast<__bf16>(hi))) << 16);
+        }
+    }
+}
+
 }  // namespace
 
 namespace {
+
+template <int kTB, int kNB, bool kOutF32>
+hipError_t launch_few(const KcArgs& a, hipStream_t stream) {
+    using TL = FewTile<kTB, kNB>;
+    const long long row_tiles = (a.M + 16 * kTB - 1) / (16 * kTB);
+    const dim3 grid(static_cast<unsigned>(row_tiles * ((a.C + 16 * kNB - 1) / (16 * kNB))));
+    hipLaunchKernelGGL((key_compress_few_kernel<kTB, kNB, kOutF32>), grid, dim3(64 * kFewWaves), TL::kLds, stream, a);
+    return hipGetLastError();
+}
 
 template <int kBN, bool kOutF32>
 hipError_t launch_tile(const KcArgs& a, hipStream_t stream) {
     using TL = Tile<kBN>;
     const long long row_tiles = (a.M + kBM - 1) / kBM;
     const dim3 grid(static_cast<unsigned>((row_tiles + 7) / 8 * 8 * ((a.C + kBN - 1) / kBN)));
-    struct Tag {};
-    const hipError_t err = set_lds_limit_once<Tag>(&key_compress_kernel<kBN, kOutF32>, TL::kLds);
-    if (err != hipSuccess) return err;
     hipLaunchKernelGGL((key_compress_kernel<kBN, kOutF32>), grid, dim3(TL::kThreads), TL::kLds, stream, a);
     return hipGetLastError();
+}
+
+}  // namespace
+
+namespace {
+
+template <bool kOutF32>
+hipError_t raise_lds_limits() {
+    hipError_t err = set_lds_limit(&key_compress_few_kernel<1, 1, kOutF32>, FewTile<1, 1>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_few_kernel<1, 2, kOutF32>, FewTile<1, 2>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_few_kernel<1, 4, kOutF32>, FewTile<1, 4>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_few_kernel<2, 4, kOutF32>, FewTile<2, 4>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, kOutF32>, Tile<128>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<256, kOutF32>, Tile<256>::kLds);
+    return err;
 }
 
 }  // namespace
@@ -354,6 +513,30 @@ hipError_t launch_key_compress(long long M, int D, const void* x, const void* w,
     KcArgs a;
     a.M = M; a.D = D; a.C = D / 16;
     a.x = x; a.w = w; a.c = c;
+    struct Tag {};
+    const hipError_t err = once_per_device<Tag>([] {
+        const hipError_t e = raise_lds_limits<false>();
+        return e == hipSuccess ? raise_lds_limits<true>() : e;
+    });
+    if (err != hipSuccess) return err;
+    // The contraction-split form while it fits the chip once: then a call takes as long as one workgroup, and
+    // its walk of D / 512 steps is shorter than the D / 64 of the large tiles.  The smallest tile that still
+    // gives at most one workgroup per compute unit, since a workgroup's time grows with its tile.  Measured, D
+    // = 2048, microseconds, large tiles -> this form: 19.7 -> 4.4 at 1 token, 20.9 -> 5.6 at 512, 21.0 -> 5.7 at
+    // 1024, 21.0 -> 7.3 at 2048, 21.0 -> 11.1 at 4096 (256 workgroups of the largest tile); at 8192 both take 21
+    // and beyond that the W traffic of the small tiles (all of W per 32 tokens) loses: 39.5 against 22 at 16384.
+    // D = 1024: 11.5 -> 3.8 at 16 tokens, 12.3 -> 7.4 at 8192, level at 16384.  Above D = 2048 a large tile's walk is so
+    // long (56 at D = 4096 for any few tokens) that two rounds still win: 34.5 against 58 at 4096 tokens, 66 against 59
+    // at 8192.
+    const int cus = compute_units();
+    auto groups = [&](int tb, int nb) {
+        return (M + 16 * tb - 1) / (16 * tb) * ((a.C + 16 * nb - 1) / (16 * nb));
+    };
+    if (groups(1, 1) <= cus) return out_f32 ? launch_few<1, 1, true>(a, stream) : launch_few<1, 1, false>(a, stream);
+    if (groups(1, 2) <= cus) return out_f32 ? launch_few<1, 2, true>(a, stream) : launch_few<1, 2, false>(a, stream);
+    if (groups(1, 4) <= cus) return out_f32 ? launch_few<1, 4, true>(a, stream) : launch_few<1, 4, false>(a, stream);
+    if (groups(2, 4) <= (a.C > 128 ? 2 : 1) * cus)
+        return out_f32 ? launch_few<2, 4, true>(a, stream) : launch_few<2, 4, false>(a, stream);
     if (a.C > 128) return out_f32 ? launch_tile<256, true>(a, stream) : launch_tile<256, false>(a, stream);
     return out_f32 ? launch_tile<128, true>(a, stream) : launch_tile<128, false>(a, stream);
 }

@@ -93,21 +93,33 @@ hipError_t launch_decay_input(int B, int T, int D, const void* x, const void* x_
                               const float* lambda_d, const void* a_d, const void* b_d, const void* a_omega, void* y,
                               bool out_f32, hipStream_t stream);
 
-// Raises a kernel's dynamic LDS limit once per device and kernel instantiation (the attribute
-// belongs to the loaded function on a device, so it need not be set again at every launch, and must
-// not be set under stream capture: a process that captures should make its first call to an entry
-// point outside the capture).  `Tag` makes one flag set per kernel.
-template <typename Tag, typename Kernel>
-inline hipError_t set_lds_limit_once(Kernel kernel, int bytes) {
+// Runs `f` (returning hipError_t) once per device; a call that fails is tried again by the next one.
+// `Tag` makes one flag set per use.
+template <typename Tag, typename F>
+inline hipError_t once_per_device(F f) {
     static std::atomic<unsigned long long> done{0};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
     const unsigned long long bit = 1ull << dev;
     if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
-    const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    const hipError_t err = f();
     if (err == hipSuccess) done.fetch_or(bit, std::memory_order_release);
     return err;
+}
+
+template <typename Kernel>
+inline hipError_t set_lds_limit(Kernel kernel, int bytes) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
+// Raises a kernel's dynamic LDS limit once per device and kernel instantiation (the attribute
+// belongs to the loaded function on a device, so it need not be set again at every launch, and must
+// not be set under stream capture: a process that captures should make its first call to an entry
+// point outside the capture).  An entry point whose sizes choose between kernels sets the limits of all of
+// them on its first call, so that the size of that call does not matter.
+template <typename Tag, typename Kernel>
+inline hipError_t set_lds_limit_once(Kernel kernel, int bytes) {
+    return once_per_device<Tag>([&] { return set_lds_limit(kernel, bytes); });
 }
 
 // Compute units of the current device (256 on an MI355X), read once per device; 256 if the
