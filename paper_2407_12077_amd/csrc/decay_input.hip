@@ -7,6 +7,7 @@
 // which wkv6_finch_c2_prefill_lora_bf16 turns into decay logits per head.  Per token this is a chain
 // of three skinny matrix products (D -> 32, 32 -> D, D -> 64) bound by the one HBM read of x.
 //
+// Two kernels; the rule is at the launch.  With enough tokens to fill the chip:
 // One workgroup owns 128 consecutive tokens of one sequence and walks the D axis twice in steps of 128
 // channels (the second walk needs tanh(q A_d) of the whole first one; its reads of x are served by
 // L2 / the last-level cache).  Sixteen waves in two roles, one barrier per step; the steps are this
@@ -377,6 +378,328 @@ __global__ __launch_bounds__(kDiThreads) void decay_input_kernel(DiArgs a) {
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// The contraction split over the waves, for fewer tokens than fill the chip with the tiles above
+// ------------------------------------------------------------------------------------------
+// A workgroup owns 16 kTB consecutive rows of the flattened [B * T] tokens (so sequences of a token or two share a
+// tile) and its waves take the 32-channel blocks of D in turn; the partial sums of q A_d and of z A_omega meet
+// through LDS, once each.  No barrier and no shared stage inside the walks: a wave brings its block's x rows and weight
+// slices from global memory in whole 64-byte pieces, passes them through a piece of LDS of its own into the operand
+// layouts, and has the loads of the next block (two for the small tiles) in flight.  A token's predecessor is an
+// LDS row as well: the row above it, or the carried row where a sequence starts.  Bound by the compute unit's L1
+// path (every workgroup takes all weights, 512 KB at D = 2048) and, at 64 rows, by the conversions and interpolations in the
+// vector ALU.  Straight operand loads from global memory (sixteen lines per quarter wave) took 26.4 us where this takes 16.6,
+// bf16 weights with the other operand as two bf16 values the same time, six waves instead of twelve 17.0, and 64
+// rows with four waves, two workgroups per compute unit, 36 instead of 31 (24 sequences of one token; 16384 tokens; D = 2048).
+template <int kTB, int kSplitWaves>
+struct SplitTile {
+    static constexpr int kRows = 16 * kTB;
+    static constexpr int kWaves = kSplitWaves;
+    static constexpr int kThreads = 64 * kWaves;
+    static constexpr int kDepth = kTB == 4 ? 1 : 2;      // blocks of a wave in flight beside the one it works on
+    static constexpr int kCarry = kTB == 1 ? 16 : 1;     // rows of a tile that can start a sequence (kTB > 1: T >= kRows)
+    // a wave's piece of LDS: rows of 32 channels (64 bytes + 32 pad: full-rate 16-byte reads)
+    static constexpr int kRow = 96;
+    static constexpr int kXRows = 1 + kRows + kCarry;    // the row before the tile, the tile, the carried rows
+    static constexpr int kOffA = kXRows * kRow;          // walk 1: A_d slice [32 columns]; walk 2: A_omega slice [64 columns]
+    static constexpr int kOffB = kOffA + kOuterRank * kRow;   // walk 2: B_d slice [32 channels][32 ranks]
+    static constexpr int kOffV = kOffB + 32 * kRow;      // mu_x or lambda_d slice, 32 fp32
+    static constexpr int kPiece = kOffV + 128;
+    static constexpr int kPRow = kInnerRank + 4;         // row strides (floats) of the waves' partial sums
+    static constexpr int kYRow = kOuterRank + 4;
+    static constexpr int kPtRow = kInnerRank * 2 + 16;   // row stride (bytes) of tanh(q A_d)
+    static constexpr int kYPart = kWaves * kRows * kYRow * 4;
+    static constexpr int kPtOff = kWaves * kPiece > kYPart ? kWaves * kPiece : kYPart;
+    static constexpr int kLds = kPtOff + kRows * kPtRow;
+    static_assert(kLds <= 160 * 1024, "LDS budget");
+};
+
+__device__ __forceinline__ void wave_lds_order() {       // a wave's own LDS writes before its own reads, and back
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int kTB, int kSplitWaves, bool kOutF32>
+__global__ __launch_bounds__(64 * kSplitWaves) void decay_input_split_kernel(DiArgs a) {
+    using TL = SplitTile<kTB, kSplitWaves>;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    char* mine = lds + wave * TL::kPiece;
+    const long long M = static_cast<long long>(a.B) * a.T;
+    const long long m0 = static_cast<long long>(blockIdx.x) * TL::kRows;
+    const int rows = M - m0 < TL::kRows ? static_cast<int>(M - m0) : TL::kRows;
+    const long long row_bytes = static_cast<long long>(a.D) * 2;
+    const int nkb = a.D / 32;
+    const long long b0 = m0 / a.T;                             // sequence of the tile's first row
+    const unsigned T = static_cast<unsigned>(a.T), t0 = static_cast<unsigned>(m0 - b0 * a.T);
+    const unsigned first_start = t0 == 0 ? 0 : 1;              // first sequence, counted from b0, whose start can lie in the tile
+    const bool has_start = t0 == 0 || t0 + rows > T;           // some row starts a sequence
+
+    constexpr int kNowhere = 0x7ffffff0;                       // an offset that no descriptor covers: reads zero
+    auto load = [](const char* base, int bytes, int voff, int soff) {
+        return __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(
+                                              __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, bytes, 0x00020000),
+                                              voff, soff, 0));
+    };
+    auto store = [&](int off, uint4v q) { *reinterpret_cast<uint4v*>(mine + off) = q; };
+    // Global loads go by rows, four lanes to the 64 bytes of a row's 32 channels (sixteen different lines per
+    // quarter wave, as the operand layout would have it, cost four times as much in the L1's tag lookups).
+    const int lr = lane >> 2, lp = 16 * (lane & 3);
+    const char* x_base = a.x + m0 * row_bytes;
+    const int x_bytes = static_cast<int>(rows * row_bytes), x_voff = static_cast<int>(lr * row_bytes) + lp;
+    const int x_pass = static_cast<int>(16 * row_bytes);
+    const char* p_base = t0 > 0 ? x_base - row_bytes : a.x;    // the row before the tile, if it belongs to the sequence
+    const int p_bytes = t0 > 0 ? static_cast<int>(row_bytes) : 0, p_voff = lane < 4 ? lp : kNowhere;
+    const long long c0 = b0 + first_start;                     // carried rows of the sequences that start in the tile
+    const long long c_rows = a.B - c0 < TL::kCarry ? a.B - c0 : TL::kCarry;
+    const char* c_base = a.x_prev && c_rows > 0 ? a.x_prev + c0 * row_bytes : a.x;
+    const int c_bytes = a.x_prev && c_rows > 0 ? static_cast<int>(c_rows * row_bytes) : 0;
+    const int w_voff = static_cast<int>(lr * row_bytes) + lp;  // columns of A_d, A_omega
+
+    struct X {
+        uint4v x[kTB], p, c;
+    };
+    auto fetch_x = [&](X& s, bool live, int soff) {            // live: uniform; dead: empty descriptors
+#pragma unroll
+        for (int tb = 0; tb < kTB; ++tb) s.x[tb] = load(x_base, live ? x_bytes : 0, x_voff + tb * x_pass, soff);
+        s.p = load(p_base, live ? p_bytes : 0, p_voff, soff);
+        s.c = uint4v{0u, 0u, 0u, 0u};
+        if (has_start) s.c = load(c_base, live ? c_bytes : 0, lr < TL::kCarry ? x_voff : kNowhere, soff);
+    };
+    auto park_x = [&](const X& s) {
+#pragma unroll
+        for (int tb = 0; tb < kTB; ++tb) store((1 + 16 * tb + lr) * TL::kRow + lp, s.x[tb]);
+        if (lane < 4) store(lp, s.p);
+        if (has_start && lr < TL::kCarry) store((1 + TL::kRows + lr) * TL::kRow + lp, s.c);
+    };
+    // LDS rows of this lane's tokens and of their predecessors
+    int cur_off[kTB], prev_off[kTB];
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb) {
+        const unsigned row = 16 * tb + l16, db = (t0 + row) / T;
+        const bool start = t0 + row == db * T;
+        cur_off[tb] = (1 + row) * TL::kRow + 16 * g4;
+        // (a row past the end of the tile may find a sequence past the carried rows: its result is not stored)
+        const unsigned slot = db - first_start < TL::kCarry ? db - first_start : TL::kCarry - 1;
+        prev_off[tb] = (start ? 1 + TL::kRows + static_cast<int>(slot) : static_cast<int>(row)) * TL::kRow + 16 * g4;
+    }
+    auto interpolate = [](unsigned cur, unsigned prev, float w0, float w1) {   // two channels, fp32, rounded to fp16
+        const float c0 = lo_f(cur), c1 = hi_f(cur);
+        return pack_h2f(__builtin_fmaf(lo_f(prev) - c0, w0, c0), __builtin_fmaf(hi_f(prev) - c1, w1, c1));
+    };
+    auto read_half8 = [&](int off) { return *reinterpret_cast<const half8*>(mine + off); };
+    auto read_u4 = [&](int off) { return *reinterpret_cast<const uint4v*>(mine + off); };
+    auto read_f4 = [&](int off) { return *reinterpret_cast<const float4v*>(mine + off); };
+
+    // walk 1: this wave's share of q A_d
+    struct W1 {
+        X x;
+        uint4v wgt[2], mu;
+    };
+    auto fetch1 = [&](W1& s, int kb) {
+        const bool live = kb < nkb;
+        const int soff = live ? kb * 64 : 0;
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+            s.wgt[nb] = load(a.a_d + nb * 16 * row_bytes, live ? static_cast<int>(16 * row_bytes) : 0, w_voff, soff);
+        s.mu = load(a.mu_x, live ? a.D * 4 : 0, lane < 8 ? 16 * lane : kNowhere, 2 * soff);
+        fetch_x(s.x, live, soff);
+    };
+    float4v pacc[kTB][2];
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb) pacc[tb][0] = pacc[tb][1] = float4v{0.f, 0.f, 0.f, 0.f};
+    auto park1 = [&](const W1& s) {
+        wave_lds_order();
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) store(TL::kOffA + (16 * nb + lr) * TL::kRow + lp, bf16x8_to_f16x8(s.wgt[nb]));
+        if (lane < 8) store(TL::kOffV + 16 * lane, s.mu);
+        park_x(s.x);
+        wave_lds_order();
+    };
+    auto step1 = [&] {
+        half8 wgt[2];
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) wgt[nb] = read_half8(TL::kOffA + (16 * nb + l16) * TL::kRow + 16 * g4);
+        const float4v mu[2] = {read_f4(TL::kOffV + 32 * g4), read_f4(TL::kOffV + 32 * g4 + 16)};
+#pragma unroll
+        for (int tb = 0; tb < kTB; ++tb) {
+            const uint4v cur = read_u4(cur_off[tb]), prev = read_u4(prev_off[tb]);
+            uint4v q;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) q[i] = interpolate(cur[i], prev[i], mu[i >> 1][2 * (i & 1)], mu[i >> 1][2 * (i & 1) + 1]);
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+                pacc[tb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wgt[nb], __builtin_bit_cast(half8, q), pacc[tb][nb], 0, 0, 0);
+        }
+    };
+    {
+        W1 ring[TL::kDepth];
+#pragma unroll
+        for (int i = 0; i < TL::kDepth; ++i) fetch1(ring[i], wave + i * TL::kWaves);
+#pragma clang loop unroll(disable)
+        for (int kb = wave; kb < nkb; kb += TL::kDepth * TL::kWaves) {   // blocks past the end add products of zeros
+#pragma unroll
+            for (int i = 0; i < TL::kDepth; ++i) {
+                park1(ring[i]);
+                fetch1(ring[i], kb + (TL::kDepth + i) * TL::kWaves);
+                step1();
+            }
+        }
+    }
+
+    // walk 2's first blocks do not wait for the exchange
+    struct W2 {
+        X x;
+        uint4v bd[2], wo[4], lam;
+    };
+    auto fetch2 = [&](W2& s, int kb) {
+        const bool live = kb >= 0;
+        const int soff = live ? kb * 64 : 0;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)                            // 32 channels x 64 bytes: one contiguous piece
+            s.bd[i] = load(a.b_d, live ? a.D * kInnerRank * 2 : 0, 1024 * i + 16 * lane, kInnerRank * soff);
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+            s.wo[nb] = load(a.a_omega + nb * 16 * row_bytes, live ? static_cast<int>(16 * row_bytes) : 0, w_voff, soff);
+        s.lam = load(a.lambda_d, live ? a.D * 4 : 0, lane < 8 ? 16 * lane : kNowhere, 2 * soff);
+        fetch_x(s.x, live, soff);
+    };
+    const int last = wave < nkb ? wave + (nkb - 1 - wave) / TL::kWaves * TL::kWaves : -1;   // this wave's last block
+    W2 ring[TL::kDepth];
+#pragma unroll
+    for (int i = 0; i < TL::kDepth; ++i) fetch2(ring[i], last - i * TL::kWaves);
+
+    // the waves' shares of q A_d meet; p = tanh of the sum, as fp16
+    float* part = reinterpret_cast<float*>(lds);
+    __syncthreads();                                           // every wave is done with its piece
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+            *reinterpret_cast<float4v*>(part + (wave * TL::kRows + 16 * tb + l16) * TL::kPRow + 16 * nb + 4 * g4) = pacc[tb][nb];
+    __syncthreads();
+    for (int i = tid; i < TL::kRows * (kInnerRank / 4); i += TL::kThreads) {
+        const int row = i / (kInnerRank / 4), c4 = 4 * (i % (kInnerRank / 4));
+        float4v sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < TL::kWaves; ++w)
+            sum += *reinterpret_cast<const float4v*>(part + (w * TL::kRows + row) * TL::kPRow + c4);
+        *reinterpret_cast<uint2v*>(lds + TL::kPtOff + row * TL::kPtRow + 2 * c4) =
+            uint2v{pack_h2f(fast_tanh(sum[0]), fast_tanh(sum[1])), pack_h2f(fast_tanh(sum[2]), fast_tanh(sum[3]))};
+    }
+    __syncthreads();
+    half8 pt[kTB];                                             // ranks 8*g4 .. +7 of this lane's tokens
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb)
+        pt[tb] = *reinterpret_cast<const half8*>(lds + TL::kPtOff + (16 * tb + l16) * TL::kPtRow + 16 * g4);
+
+    // walk 2: this wave's share of z A_omega, from the blocks most recently brought into the caches down
+    float4v yacc[kTB][4];
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb)
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) yacc[tb][nb] = float4v{0.f, 0.f, 0.f, 0.f};
+    auto park2 = [&](const W2& s) {
+        wave_lds_order();
+#pragma unroll
+        for (int i = 0; i < 2; ++i) store(TL::kOffB + (16 * i + lr) * TL::kRow + lp, bf16x8_to_f16x8(s.bd[i]));
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) store(TL::kOffA + (16 * nb + lr) * TL::kRow + lp, bf16x8_to_f16x8(s.wo[nb]));
+        if (lane < 8) store(TL::kOffV + 16 * lane, s.lam);
+        park_x(s.x);
+        wave_lds_order();
+    };
+    auto step2 = [&] {
+        // Which channel sits in which row of the B_d^T operand is free as long as z and A_omega agree: with row m of
+        // block `half` holding channel 8*(m>>2) + 4*half + (m&3) a lane's results are its own channels 8*g4 .. +7
+        half8 bd[2], wo[4];
+        float4v lam[2];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            bd[half] = read_half8(TL::kOffB + (8 * (l16 >> 2) + 4 * half + (l16 & 3)) * TL::kRow + 16 * g4);
+            lam[half] = read_f4(TL::kOffV + 32 * g4 + 16 * half);
+        }
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) wo[nb] = read_half8(TL::kOffA + (16 * nb + l16) * TL::kRow + 16 * g4);
+#pragma unroll
+        for (int tb = 0; tb < kTB; ++tb) {
+            const uint4v cur = read_u4(cur_off[tb]), prev = read_u4(prev_off[tb]);
+            uint4v z;
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                // mix[e] = lambda_d + sum_k B_d[k][channel 8*g4 + 4*half + e] p[token][k]
+                const float4v mix = __builtin_amdgcn_mfma_f32_16x16x32_f16(bd[half], pt[tb], lam[half], 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    z[2 * half + i] = interpolate(cur[2 * half + i], prev[2 * half + i], mix[2 * i], mix[2 * i + 1]);
+            }
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb)
+                yacc[tb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wo[nb], __builtin_bit_cast(half8, z), yacc[tb][nb], 0, 0, 0);
+        }
+    };
+#pragma clang loop unroll(disable)
+    for (int kb = last; kb >= 0; kb -= TL::kDepth * TL::kWaves) {   // blocks before the first add products with zero weights
+#pragma unroll
+        for (int i = 0; i < TL::kDepth; ++i) {
+            park2(ring[i]);
+            fetch2(ring[i], kb - (TL::kDepth + i) * TL::kWaves);
+            step2();
+        }
+    }
+
+    __syncthreads();                                           // every wave is done with its piece
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb)
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+            *reinterpret_cast<float4v*>(part + (wave * TL::kRows + 16 * tb + l16) * TL::kYRow + 16 * nb + 4 * g4) = yacc[tb][nb];
+    __syncthreads();
+    for (int i = tid; i < TL::kRows * (kOuterRank / 4); i += TL::kThreads) {
+        const int row = i / (kOuterRank / 4), c4 = 4 * (i % (kOuterRank / 4));
+        float4v sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < TL::kWaves; ++w)
+            sum += *reinterpret_cast<const float4v*>(part + (w * TL::kRows + row) * TL::kYRow + c4);
+        if (row < rows) {
+            const long long e = (m0 + row) * kOuterRank + c4;
+#pragma unroll
+            for (int i2 = 0; i2 < 4; ++i2) sum[i2] = fast_tanh(sum[i2]);
+            if constexpr (kOutF32) {
+                *reinterpret_cast<float4v*>(static_cast<float*>(a.y) + e) = sum;
+            } else {
+                typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+                *reinterpret_cast<uint2v*>(static_cast<unsigned short*>(a.y) + e) =
+                    __builtin_bit_cast(uint2v, __builtin_convertvector(sum, bf16x4));
+            }
+        }
+    }
+}
+
+}  // namespace
+
+namespace {
+
+template <int kTB, int kSplitWaves, bool kOutF32>
+hipError_t launch_split(const DiArgs& a, hipStream_t stream) {
+    using TL = SplitTile<kTB, kSplitWaves>;
+    const long long M = static_cast<long long>(a.B) * a.T;
+    hipLaunchKernelGGL((decay_input_split_kernel<kTB, kSplitWaves, kOutF32>), dim3(static_cast<unsigned>((M + TL::kRows - 1) / TL::kRows)),
+                       dim3(TL::kThreads), TL::kLds, stream, a);
+    return hipGetLastError();
+}
+
+template <bool kOutF32>
+hipError_t raise_lds_limits() {
+    hipError_t err = set_lds_limit(&decay_input_split_kernel<1, 12, kOutF32>, SplitTile<1, 12>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&decay_input_split_kernel<2, 8, kOutF32>, SplitTile<2, 8>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&decay_input_split_kernel<4, 8, kOutF32>, SplitTile<4, 8>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&decay_input_kernel<kOutF32>, kDiLds);
+    return err;
+}
+
 }  // namespace
 
 hipError_t launch_decay_input(int B, int T, int D, const void* x, const void* x_prev, const float* mu_x,
@@ -395,19 +718,33 @@ hipError_t launch_decay_input(int B, int T, int D, const void* x, const void* x_
     a.b_d = static_cast<const char*>(b_d);
     a.a_omega = static_cast<const char*>(a_omega);
     a.y = y;
+    struct Tag {};
+    const hipError_t err = once_per_device<Tag>([] {
+        const hipError_t e = raise_lds_limits<false>();
+        return e == hipSuccess ? raise_lds_limits<true>() : e;
+    });
+    if (err != hipSuccess) return err;
+    // Which kernel: rounds of one workgroup per compute unit, times what a round takes.  A 128-token workgroup
+    // takes as long with one token as with 128 (46 us at D = 2048, 20 at 768, 88 at 4096) and serves one sequence, so
+    // it is the better one only when it fills the chip; the split tiles take rows of any sequences.  Measured at
+    // D = 2048, microseconds a round: 128 tokens 47 to 58; split 64 rows 28 to 31, 32 rows 19 to 22, 16 rows 16.6 to 18.8 (D = 768:
+    // 20 to 24; 14 to 16, 12.4, 9.2; D = 4096: 88 to 110; 50 to 64, 33 to 37, 26 to 30); the weights 16, 10, 7, 6
+    // are these, rounded.  At D = 2048: 24 sequences of one token 45.8 -> 16.6, 300 of them 90 -> 16.8, 8192 tokens 46.6 ->
+    // 22, 16384 tokens 47 -> 31; at 24000 the 64-row tiles need a second round and lose (59 against 48).
+    const long long cus = compute_units(), rows = static_cast<long long>(B) * T;
+    auto rounds = [&](long long groups) { return (groups + cus - 1) / cus; };
+    const long long whole = 16 * rounds(static_cast<long long>(B) * a.tiles_per_seq);
+    const long long r64 = T >= 64 ? 10 * rounds((rows + 63) / 64) : whole;
+    const long long r32 = T >= 32 ? 7 * rounds((rows + 31) / 32) : whole;
+    const long long r16 = 6 * rounds((rows + 15) / 16);
+    if (r16 < whole && r16 <= r32 && r16 <= r64) return out_f32 ? launch_split<1, 12, true>(a, stream) : launch_split<1, 12, false>(a, stream);
+    if (r32 < whole && r32 <= r64) return out_f32 ? launch_split<2, 8, true>(a, stream) : launch_split<2, 8, false>(a, stream);
+    if (r64 < whole) return out_f32 ? launch_split<4, 8, true>(a, stream) : launch_split<4, 8, false>(a, stream);
     const dim3 grid(static_cast<unsigned>(static_cast<long long>(B) * a.tiles_per_seq));
-    struct TagF32 {};
-    struct TagBf16 {};
-    hipError_t err;
-    if (out_f32) {
-        err = set_lds_limit_once<TagF32>(&decay_input_kernel<true>, kDiLds);
-        if (err != hipSuccess) return err;
+    if (out_f32)
         hipLaunchKernelGGL(decay_input_kernel<true>, grid, dim3(kDiThreads), kDiLds, stream, a);
-    } else {
-        err = set_lds_limit_once<TagBf16>(&decay_input_kernel<false>, kDiLds);
-        if (err != hipSuccess) return err;
+    else
         hipLaunchKernelGGL(decay_input_kernel<false>, grid, dim3(kDiThreads), kDiLds, stream, a);
-    }
     return hipGetLastError();
 }
 

@@ -165,3 +165,19 @@ def test_input_beyond_four_gib(gpu_device):
         assert err <= TOL_BF16
     del x, y
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("B,T,H", [(24, 1, 32), (17, 1, 2), (40, 2, 6), (9, 15, 4), (9, 16, 12), (9, 17, 2), (130, 31, 2),
+                                   (131, 33, 2), (4, 1100, 2), (70, 60, 2), (256, 32, 2), (2, 4097, 2), (3, 5461, 2), (128, 127, 2),
+                                   (1, 16385, 2)])
+def test_split_contraction_tiles(gpu_device, B, T, H):
+    """Every tile of the wave-split form (16, 32 and 64 rows) and the change to the 128-token form, with sequence starts at
+    every place of a tile (T below, at and above the tile's rows), ragged last tiles, widths that leave waves without a
+    block, and both kinds of first token.  The bar is the one of the 128-token form: fp16 operands, 2e-3 of the
+    largest |y|."""
+    fi = make_decay_front_inputs(scaled(CONFIGS[2], B=B, T=T, H=H), seed=1300 + T)
+    for with_prev in (True, False):
+        y32 = run_front(fi, torch.float32, with_prev).cpu().numpy()
+        assert max_norm_err(y32, oracle_front(fi, with_prev)) <= TOL_BF16
+        y16 = run_front(fi, torch.bfloat16, with_prev).float().cpu().numpy()
+        assert np.array_equal(y16, round_to_bf16(y32))
