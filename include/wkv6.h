@@ -83,7 +83,13 @@ typedef enum {
     WKV6_DTYPE_F32 = 1
 } wkv6_dtype;
 
-/* bf16 r,k,v,x; fp32 u and state; bf16 out.  Chunked matrix-core kernel. */
+/*
+ * bf16 r,k,v,x; fp32 u and state; bf16 out.  Chunked matrix-core kernel.  Shapes with so few (batch, head)
+ * units that they would leave most compute units idle, and enough tokens (this and every other prefill and append
+ * entry point but the explicit split ones), are cut along the tokens as described at wkv6_prefill_bf16_split, by a rule
+ * on the shape alone; the passes hand their states over in `out` itself, in rows that the last pass overwrites, so
+ * nothing but `out` and state_out is written, and `out` holds no partial result after the call's last kernel.
+ */
 int wkv6_prefill_bf16(int B, int T, int H, int N,
                       const void *r, const void *k, const void *v, const void *x,
                       const float *u, const float *state_in,

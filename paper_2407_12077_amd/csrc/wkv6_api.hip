@@ -19,12 +19,78 @@ enum class Path { kChunked, kRecurrent, kBySize };
 // window each at these lengths).
 constexpr int kRecurrentMaxTokens = 6;
 
+struct SplitPlan {
+    int segs;        // segments actually used
+    int seg_len;     // tokens per segment (multiple of 32), last one shorter
+};
+
+SplitPlan plan_split(int T, int segments) {
+    SplitPlan p;
+    if (segments < 1) segments = 1;
+    long long len = (static_cast<long long>(T) + segments - 1) / segments;
+    len = (len + 31) / 32 * 32;
+    if (len < 32) len = 32;
+    p.seg_len = static_cast<int>(len);
+    p.segs = static_cast<int>((T + len - 1) / len);
+    if (p.segs < 1) p.segs = 1;
+    return p;
+}
+
+// The split that an entry point without a workspace makes by itself when its (batch, head) units leave compute units
+// idle: as many segments as fill the 256 of an MI355X once.  The hand-over between the passes lies in
+// the first rows of every segment of `out`, which the last pass overwrites, so every segment needs that many
+// tokens.  A function of the shape alone, the same for every form and output type, so that forms that agree bit for
+// bit still do.
+// The two passes in front cost about 12 us and, in the last pass, every chunk that a workgroup no longer walks saves 0.75
+// us: the split pays from about 20 chunks on.  Measured, microseconds, whole -> split (Finch, H = 32): 700 tokens 21.9 -> 22.4,
+// 1024 29.0 -> 22.7, 4096 97 -> 38, 32 768 727 -> 221; Finch-C2 with two sequences 700 tokens 27.1 -> 28.3, 1024
+// 35.7 -> 29.9, 4096 121 -> 70.  Two segments never pay: what they save the state pass takes (Finch-C2, four sequences of 4096:
+// 128 -> 124; of 2048 67 -> 68).
+SplitPlan plan_own_split(int B, int T, int H) {
+    const SplitPlan whole{1, T};
+    const long long units = static_cast<long long>(B) * H;
+    long long segs = 256 / units;
+    if (segs > T / wkv6::kSegPlaceTokens) segs = T / wkv6::kSegPlaceTokens;
+    for (; segs > 2; --segs) {
+        const SplitPlan p = plan_split(T, static_cast<int>(segs));
+        if (p.segs < 3 || T - p.seg_len < 20 * 32) return whole;
+        if (p.seg_len >= wkv6::kSegPlaceTokens && T - static_cast<long long>(p.segs - 1) * p.seg_len >= wkv6::kSegPlaceTokens)
+            return p;
+    }
+    return whole;
+}
+
+// Fills in the segments of `p` with their hand-over in the segments' own rows of out.
+void split_into_out(wkv6::Args& a, const SplitPlan& p, bool out_f32) {
+    a.segs = p.segs;
+    a.seg_len = p.seg_len;
+    const long long elem = out_f32 ? 4 : 2;
+    const long long row = static_cast<long long>(a.H) * wkv6::kHeadSize * elem;      // H < 256 here: fits an int
+    a.place.base = static_cast<char*>(a.out);
+    a.place.batch = a.batch_stride * elem;
+    a.place.seg = p.seg_len * row;
+    a.place.head = wkv6::kHeadSize * elem;
+    a.place.row = static_cast<int>(out_f32 ? row : 2 * row);
+    a.place.half = static_cast<int>(out_f32 ? 128 : row);
+}
+
+// The passes of a prefill whose Args are complete but for the segments.
+hipError_t launch_prefill(wkv6::Args& a, wkv6::ChunkedMode mode, bool own_split, hipStream_t s) {
+    const bool lora = mode == wkv6::ChunkedMode::kBf16OutLora || mode == wkv6::ChunkedMode::kBf16OutLoraMoments;
+    if (own_split) {
+        const SplitPlan p = plan_own_split(a.B, a.T, a.H);
+        if (p.segs > 1) split_into_out(a, p, mode == wkv6::ChunkedMode::kF32Out);
+    }
+    const hipError_t err = wkv6::launch_segment_states(a, lora, s);
+    return err == hipSuccess ? wkv6::launch_chunked(a, mode, s) : err;
+}
+
 // `uprime` selects the form: nullptr = Finch (bonus u), otherwise Finch-C2 (u unused, may be null).
 int run(int B, int T, int H, int N, const void* r, const void* k, const void* v, const void* x,
         const float* u, const float* state_in, void* out, float* state_out,
         long long batch_stride, bool in_bf16, bool out_f32, Path path, void* stream,
         const void* uprime = nullptr, bool finch_c2 = false, float* moments = nullptr,
-        bool want_moments = false) {
+        bool want_moments = false, bool own_split = true) {
     if (N != wkv6::kHeadSize) return WKV6_ERR_UNSUPPORTED;
     if (B < 0 || T < 0 || H < 1 || H > 262144) return WKV6_ERR_SHAPE;   // 32-bit row offsets in the kernels
     if (!finch_c2 && !u) return WKV6_ERR_NULL;
@@ -52,7 +118,7 @@ int run(int B, int T, int H, int N, const void* r, const void* k, const void* v,
     a.uprime = finch_c2 ? uprime : nullptr;
     a.state_in = state_in; a.out = out; a.state_out = state_out;
     a.batch_stride = batch_stride;
-    a.segs = 1; a.T_last = T; a.seg_stride = 0; a.decay_out = nullptr; a.unit_stride = 0;
+    a.segs = 1; a.seg_len = T; a.unit_stride = 0;
     a.moments = moments;
     a.y = nullptr; a.lambda = nullptr; a.bw = nullptr;
 
@@ -63,9 +129,9 @@ int run(int B, int T, int H, int N, const void* r, const void* k, const void* v,
     else if (path == Path::kRecurrent || (path == Path::kBySize && T <= kRecurrentMaxTokens))
         err = wkv6::launch_recurrent(a, in_bf16, in_bf16 && !out_f32, s);
     else if (want_moments)
-        err = wkv6::launch_chunked(a, wkv6::ChunkedMode::kBf16OutMoments, s);
+        err = launch_prefill(a, wkv6::ChunkedMode::kBf16OutMoments, own_split, s);
     else
-        err = wkv6::launch_chunked(a, out_f32 ? wkv6::ChunkedMode::kF32Out : wkv6::ChunkedMode::kBf16Out, s);
+        err = launch_prefill(a, out_f32 ? wkv6::ChunkedMode::kF32Out : wkv6::ChunkedMode::kBf16Out, own_split, s);
     return err == hipSuccess ? WKV6_OK : WKV6_ERR_LAUNCH;
 }
 
@@ -158,13 +224,13 @@ int run_lora(int B, int T, int H, int N, int R, const void* r, const void* k, co
     a.uprime = finch_c2 ? uprime : nullptr;
     a.state_in = state_in; a.out = out; a.state_out = state_out;
     a.batch_stride = static_cast<long long>(T) * H * N;
-    a.segs = 1; a.T_last = T; a.seg_stride = 0; a.decay_out = nullptr; a.unit_stride = 0;
+    a.segs = 1; a.seg_len = T; a.unit_stride = 0;
     a.moments = moments;
     a.y = y; a.lambda = lambda; a.bw = b_omega;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const hipError_t err = T == 0 ? wkv6::launch_state_passthrough(a, s)
-                                  : wkv6::launch_chunked(a, moments ? wkv6::ChunkedMode::kBf16OutLoraMoments
-                                                                    : wkv6::ChunkedMode::kBf16OutLora, s);
+                                  : launch_prefill(a, moments ? wkv6::ChunkedMode::kBf16OutLoraMoments
+                                                              : wkv6::ChunkedMode::kBf16OutLora, true, s);
     return err == hipSuccess ? WKV6_OK : WKV6_ERR_LAUNCH;
 }
 
@@ -321,29 +387,6 @@ int wkv6_version(void) { return 500; }
 
 // ---- token-split variant: three enqueued passes over caller-provided workspace
 
-namespace {
-
-struct SplitPlan {
-    int segs;        // segments actually used
-    int seg_len;     // tokens per segment (multiple of 32), last one shorter
-    int last_len;
-};
-
-SplitPlan plan_split(int T, int segments) {
-    SplitPlan p;
-    if (segments < 1) segments = 1;
-    long long len = (static_cast<long long>(T) + segments - 1) / segments;
-    len = (len + 31) / 32 * 32;
-    if (len < 32) len = 32;
-    p.seg_len = static_cast<int>(len);
-    p.segs = static_cast<int>((T + len - 1) / len);
-    if (p.segs < 1) p.segs = 1;
-    p.last_len = T - (p.segs - 1) * p.seg_len;
-    return p;
-}
-
-}  // namespace
-
 extern "C" {
 
 int wkv6_split_segments(int B, int T, int H, int N) {
@@ -406,7 +449,7 @@ int run_split(int B, int T, int H, int N, const void* r, const void* k, const vo
     if (T == 0 || B == 0 || p.segs == 1)
         return run(B, T, H, N, r, k, v, x, u, state_in, out, state_out,
                    static_cast<long long>(T) * H * N, true, out_dtype == WKV6_DTYPE_F32,
-                   Path::kChunked, stream, uprime, finch_c2);
+                   Path::kChunked, stream, uprime, finch_c2, nullptr, false, false);
     if ((!finch_c2 && !u) || (finch_c2 && !uprime) || !r || !k || !v || !x || !out || !workspace)
         return WKV6_ERR_NULL;
     if (misaligned(r) || misaligned(k) || misaligned(v) || misaligned(x) || misaligned(out) ||
@@ -416,34 +459,28 @@ int run_split(int B, int T, int H, int N, const void* r, const void* k, const vo
     if (workspace_bytes < wkv6_split_workspace_bytes(B, T, H, N, segments)) return WKV6_ERR_SHAPE;
     if (static_cast<long long>(B) * p.segs * H > 0x7fffffffLL) return WKV6_ERR_SHAPE;
 
-    float* seg_state = static_cast<float*>(workspace);
-    float* seg_decay = seg_state + static_cast<long long>(B) * p.segs * H * 4096;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-
     wkv6::Args a;
-    a.B = B; a.T = p.seg_len; a.H = H;
+    a.B = B; a.T = T; a.H = H;
     a.r = r; a.k = k; a.v = v; a.x = x; a.u = u;
     a.finch_c2 = finch_c2;
     a.uprime = finch_c2 ? uprime : nullptr;
+    a.state_in = state_in; a.out = out; a.state_out = state_out;
     a.batch_stride = static_cast<long long>(T) * H * N;
-    a.segs = p.segs; a.T_last = p.last_len; a.unit_stride = 0; a.moments = nullptr;
+    a.segs = p.segs; a.seg_len = p.seg_len; a.unit_stride = 0; a.moments = nullptr;
     a.y = nullptr; a.lambda = nullptr; a.bw = nullptr;
-    a.seg_stride = static_cast<long long>(p.seg_len) * H * N;
-    // pass 1: every segment but the last (nothing follows it) from a zero state, no output: its
-    // local state and total decay
-    a.state_in = nullptr; a.out = nullptr; a.state_out = seg_state; a.decay_out = seg_decay;
-    a.segs_launched = p.segs - 1;
-    if (wkv6::launch_chunked(a, wkv6::ChunkedMode::kStateOnly, s) != hipSuccess) return WKV6_ERR_LAUNCH;
-    // pass 2: the state entering every segment (in place)
-    if (wkv6::launch_combine_segments(B, H, p.segs, state_in, seg_state, seg_decay, nullptr, false, s) != hipSuccess)
-        return WKV6_ERR_LAUNCH;
-    // pass 3: the full computation of every segment from its true entering state; the last
-    // segment's workgroups leave the sequence's final state
-    a.segs_launched = 0;
-    a.state_in = seg_state; a.out = out; a.state_out = state_out; a.state_out_final = true; a.decay_out = nullptr;
+    // pass 1: every segment but the last (nothing follows it) from a zero state, no output: its local state and
+    // total decay; pass 2: the state entering every segment (in place); pass 3: the full computation of every
+    // segment from its true entering state; the last segment's workgroups leave the sequence's final state
+    constexpr long long kPlaceBytes = (wkv6::kHeadSize * wkv6::kHeadSize + wkv6::kHeadSize) * 4;
+    a.place.base = static_cast<char*>(workspace);
+    a.place.head = kPlaceBytes;
+    a.place.seg = H * kPlaceBytes;
+    a.place.batch = p.segs * a.place.seg;
+    a.place.row = 256;
+    a.place.half = 128;
     const wkv6::ChunkedMode mode = out_dtype == WKV6_DTYPE_F32 ? wkv6::ChunkedMode::kF32Out
                                                                : wkv6::ChunkedMode::kBf16Out;
-    if (wkv6::launch_chunked(a, mode, s) != hipSuccess) return WKV6_ERR_LAUNCH;
+    if (launch_prefill(a, mode, false, static_cast<hipStream_t>(stream)) != hipSuccess) return WKV6_ERR_LAUNCH;
     return WKV6_OK;
 }
 

@@ -40,12 +40,14 @@
 // the level-1 tiles, the diagonal of the scores is zero, and the second value u' is added to the
 // fp32-staged rows before the store.
 //
-// Modes (template parameter kMode): 0 bf16 output, 1 fp32 output, 2 state only (no r, no scores,
-// no output: final state and total decay of the unit, for the token split), 3 bf16 output plus
+// Modes (template parameter kMode): 0 bf16 output, 1 fp32 output, 3 bf16 output plus
 // the per-head partial sums of the LayerNorm over all heads (Finch-C2 output equation) taken in
 // the store phase, 4 bf16 output with the decay logits formed in the kernel from the low-rank
 // decay path (d = lambda + y B, consumers' MFMAs, handed to phase D through LDS) instead of
 // read as x, 5 both.
+//
+// A workgroup may also own one token segment of a sequence (the token split): its entering state then
+// comes from where the segment passes left it (wkv6_segments.hip).
 //
 // LDS tiles whose contraction index is the channel (scores, inter-chunk read) are [token][channel]
 // fp16 with a 160-byte row stride; the two tiles whose contraction index is the token (k^T V, A V:
@@ -59,6 +61,7 @@
 // the operands of the consumers' MFMAs, so that a lane holds four consecutive value channels of
 // one token and stages them with one store.
 #include "wkv6_launch.h"
+#include "wkv6_math.h"
 #include "wkv6_windows.h"
 
 #include <type_traits>
@@ -68,7 +71,6 @@ namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef unsigned uint4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -114,49 +116,12 @@ constexpr int kDx = kLdsBytes;
 constexpr int kLdsBytesLora = kLdsBytes + 2 * kDxBuf;
 static_assert(kLdsBytesLora <= 160 * 1024, "LDS budget");
 
-constexpr float kLog2e = 1.4426950408889634f;
-
-__device__ __forceinline__ float bf16_lo(unsigned bits) { return __uint_as_float(bits << 16); }
-__device__ __forceinline__ float bf16_hi(unsigned bits) { return __uint_as_float(bits & 0xffff0000u); }
-
-__device__ __forceinline__ unsigned pack_h2(float a, float b) {
-    half2v p;
-    p.x = static_cast<_Float16>(a);
-    p.y = static_cast<_Float16>(b);
-    return __builtin_bit_cast(unsigned, p);
-}
-
-// packed fp16 multiply of two channel pairs
-__device__ __forceinline__ unsigned mul_h2(unsigned a, unsigned b) {
-    return __builtin_bit_cast(unsigned, __builtin_bit_cast(half2v, a) * __builtin_bit_cast(half2v, b));
-}
-
 // two floats to a bf16 pair (round to nearest even), one packed conversion
 __device__ __forceinline__ unsigned pack_bf2(float a, float b) {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     typedef float float2v __attribute__((ext_vector_type(2)));
     const float2v f = {a, b};
     return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));
-}
-
-// w = exp(-exp(x)) through two base-2 exponentials (x=-inf -> 1, x=+inf -> 0):
-// log2(e) * exp(x) = exp2(x * log2(e) + log2(log2(e))), so the factor of the second exponential
-// rides in the argument of the first.
-// Also hands back the scaled inner exponential log2(e) * exp(x), which the Finch-C2 key factor needs.
-__device__ __forceinline__ float decay_of(float x, float& e_log2e) {
-    constexpr float kLog2Log2e = 0.5287663729448977f;
-    e_log2e = __builtin_amdgcn_exp2f(__builtin_fmaf(x, kLog2e, kLog2Log2e));
-    return __builtin_amdgcn_exp2f(-e_log2e);
-}
-
-// Finch-C2 key factor 1 - w = 1 - exp(-e), e = exp(x), without the cancellation of the plain
-// subtraction for long-memory channels (w close to 1): below e = 2^-5 the alternating series
-// e (1 - e/2 + e^2/6 - e^3/24), whose first dropped term is under 1e-8 of the result there;
-// above it the subtraction loses at most five bits of an fp32 value.
-__device__ __forceinline__ float one_minus_decay(float e_log2e, float w) {
-    const float e = e_log2e * 0.6931471805599453f;      // exp(x) from the decay's own inner exponential
-    const float series = e * __builtin_fmaf(e, __builtin_fmaf(e, __builtin_fmaf(e, -1.f / 24.f, 1.f / 6.f), -0.5f), 1.f);
-    return e < 0.03125f ? series : 1.f - w;
 }
 
 __device__ __forceinline__ half8 lds_read_h8(const char* lds, int byte_off) {
@@ -215,25 +180,10 @@ struct Streams {
     long long span_bytes;      // bytes from the unit's first token row to the end of its last one
 };
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_rsrc(const char* base, long long off,
-                                                           long long span_bytes) {
-    long long left = span_bytes - off;
-    if (left < 0) left = 0;
-    if (left > 0x7fffffffLL) left = 0x7fffffffLL;
-    // raw buffer (stride 0), 32-bit data format
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base + off), 0,
-                                             static_cast<int>(left), 0x00020000);
-}
-
 // A chunk's loads are issued in two halves (x and r; k and v) so that two different phases can
 // share the cost of issuing them.
-// kPolicy: the cache policy of the loads.  Every mode streams (kStreamOnce), the state-only pass of the
-// token split included: running that split block by block with cached loads in its first pass, so that
-// the second read of k, v, x could come from the last-level cache, was measured and dropped (config 3:
-// 0.91 ms unblocked with cached first-pass loads, 0.90 to 1.10 ms in 4 to 16 blocks, against 0.78 ms
-// with streaming loads and one block; the byte counters of the L2, which cannot tell that cache from
-// HBM, did not move).
-template <bool kSkipR, bool kSkipX, int kPolicy>
+// kPolicy: the cache policy of the loads.  Every mode streams (kStreamOnce).
+template <bool kSkipX, int kPolicy>
 __device__ __forceinline__ void load_rows_xr(Raw& d, const Streams& st, long long unit_bytes, int t0,
                                              const int (&voff)[4]) {
     const long long off = static_cast<long long>(t0) * st.row_bytes;       // uniform
@@ -245,14 +195,9 @@ __device__ __forceinline__ void load_rows_xr(Raw& d, const Streams& st, long lon
 #pragma unroll
         for (int s = 0; s < 4; ++s) d.x[s] = 0u;
     }
-    if constexpr (!kSkipR) {
-        const __amdgpu_buffer_rsrc_t rr = chunk_rsrc(st.r + unit_bytes, off, st.span_bytes);
+    const __amdgpu_buffer_rsrc_t rr = chunk_rsrc(st.r + unit_bytes, off, st.span_bytes);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) d.r[s] = __builtin_amdgcn_raw_buffer_load_b32(rr, voff[s], 0, kPolicy);
-    } else {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) d.r[s] = 0u;
-    }
+    for (int s = 0; s < 4; ++s) d.r[s] = __builtin_amdgcn_raw_buffer_load_b32(rr, voff[s], 0, kPolicy);
 }
 
 template <int kPolicy>
@@ -274,13 +219,17 @@ __device__ __forceinline__ void load_rows_kv(Raw& d, const Streams& st, long lon
 // the pipeline once per unit.  All units of a workgroup share the head (the stride between them
 // is a multiple of H), have the same length T, and lie `step` elements apart.
 struct Units {
-    int first;            // unit index of the first one: selects state_in / state_out / decay_out
+    int first;            // index (batch * H + head) of the first one: selects state_in / state_out / moments
     int stride;           // unit index stride
     int count;            // how many
     int nchunks;          // chunks per unit
     long long base0;      // element offset of the first unit's token 0 in r,k,v,x,out
     long long step;       // element offset between consecutive units of this workgroup
     float* state_out;     // where final states go, indexed like state_in (nullptr: not written)
+    int t0;               // the sequence's token that is token 0 here (a token segment's start, else 0)
+    int tokens;           // tokens of a unit
+    const char* entering; // segment's entering state ([64][64] fp32 with the pitches below), or nullptr: state_in
+    int pitch_row, pitch_half;
 };
 
 // Sum over the 8 lanes of an aligned group of 8 (every lane gets the total): neighbours, pairs,
@@ -337,7 +286,6 @@ template <int kMode, bool kC2, bool kMulti>
 __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, int pg, int wq, int h,
                                          const Units& un, long long tok_stride, int T) {
     constexpr bool kOutF32 = kMode == 1;
-    constexpr bool kStateOnly = kMode == 2;
     constexpr bool kMoments = kMode == 3 || kMode == 5;   // bf16 out plus the per-head LayerNorm partials
     constexpr bool kLora = kMode >= 4;           // decay logits from the consumers (LDS), not from x
     constexpr bool kStageF32 = kOutF32 || kC2;   // staging precision of the finished rows
@@ -367,7 +315,7 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
 
     // the score block above the diagonal that the A.V product still touches, (t-block 0,
     // i-block 1), stays zero for good in both partial score tiles: 2 x 16x16 halfs = 256 dwords
-    if (!kStateOnly && pg < 2) {
+    if (pg < 2) {
         char* lds = lds_all + pg * kBuf;
         const int which = gtid >> 7;                 // A0 / A1
         const int e = gtid & 127;                    // row = e>>3, column pair = e&7
@@ -520,14 +468,12 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
         const int tr1 = tile_t_off(2 * cp + 1, wq) + 8 * hl;
         lds_write_u64(lds, kVT + tr0, pr.vt[0], pr.vt[1]);
         lds_write_u64(lds, kVT + tr1, pr.vt[2], pr.vt[3]);
-        if constexpr (!kStateOnly) {
-            // level 4: the even group of an 8-block holds keys, the odd one queries
-            put4(kZ4, q4 ? pr.rp[0] : pr.ks[0], q4 ? pr.rp[1] : pr.ks[1], q4 ? pr.rp[2] : pr.ks[2],
-                 q4 ? pr.rp[3] : pr.ks[3]);
-            put4(kZ2, pr.z2[0], pr.z2[1], pr.z2[2], pr.z2[3]);
-            put4(kQ1, pr.q1[0], pr.q1[1], pr.q1[2], pr.q1[3]);
-            if constexpr (!kC2) put4(kK1, pr.k1[0], pr.k1[1], pr.k1[2], pr.k1[3]);
-        }
+        // level 4: the even group of an 8-block holds keys, the odd one queries
+        put4(kZ4, q4 ? pr.rp[0] : pr.ks[0], q4 ? pr.rp[1] : pr.ks[1], q4 ? pr.rp[2] : pr.ks[2],
+             q4 ? pr.rp[3] : pr.ks[3]);
+        put4(kZ2, pr.z2[0], pr.z2[1], pr.z2[2], pr.z2[3]);
+        put4(kQ1, pr.q1[0], pr.q1[1], pr.q1[2], pr.q1[3]);
+        if constexpr (!kC2) put4(kK1, pr.k1[0], pr.k1[1], pr.k1[2], pr.k1[3]);
         __builtin_amdgcn_sched_barrier(0);       // keep these writes ahead of the wait for the totals
 #pragma unroll
         for (int ch = 0; ch < 2; ++ch) {
@@ -563,14 +509,12 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
             lds_write_u64(lds, kKT + tr0, lo_halves(k0, k1), lo_halves(k2, k3));
             lds_write_u64(lds, kKT + tr1, hi_halves(k0, k1), hi_halves(k2, k3));
         }
-        if constexpr (!kStateOnly) {
-            const unsigned* z16 = kQ16 ? pr.rp : pr.ks;
-            const unsigned* z8 = kQ8 ? pr.rp : pr.ks;
-            put4(kZ16, mul_h2(z16[0], h16), mul_h2(z16[1], h16), mul_h2(z16[2], h16), mul_h2(z16[3], h16));
-            put4(kZ8, mul_h2(z8[0], h8), mul_h2(z8[1], h8), mul_h2(z8[2], h8), mul_h2(z8[3], h8));
-            put4(kRT + (rt_col - 2 * cp) * 2, mul_h2(pr.rp[0], h_rt), mul_h2(pr.rp[1], h_rt),
-                 mul_h2(pr.rp[2], h_rt), mul_h2(pr.rp[3], h_rt));
-        }
+        const unsigned* z16 = kQ16 ? pr.rp : pr.ks;
+        const unsigned* z8 = kQ8 ? pr.rp : pr.ks;
+        put4(kZ16, mul_h2(z16[0], h16), mul_h2(z16[1], h16), mul_h2(z16[2], h16), mul_h2(z16[3], h16));
+        put4(kZ8, mul_h2(z8[0], h8), mul_h2(z8[1], h8), mul_h2(z8[2], h8), mul_h2(z8[3], h8));
+        put4(kRT + (rt_col - 2 * cp) * 2, mul_h2(pr.rp[0], h_rt), mul_h2(pr.rp[1], h_rt),
+             mul_h2(pr.rp[2], h_rt), mul_h2(pr.rp[3], h_rt));
     };
     auto write_tiles = [&](int c) {
         switch (wq) {                             // wave-uniform
@@ -636,7 +580,7 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
     [[maybe_unused]] const int up_voff = static_cast<int>(srow * st.row_bytes + scol * 2);
     [[maybe_unused]] const char* up_base = kC2 ? static_cast<const char*>(a.uprime) + un.base0 * 2 : nullptr;
     auto load_uprime = [&](const Cursor<kMulti>& at) {
-        if constexpr (kC2 && !kStateOnly) {
+        if constexpr (kC2) {
             // unconditional (exact wait counts): before the start it re-reads chunk 0, past the
             // end the descriptor is empty
             const int cc = at.c < 0 ? 0 : at.c;
@@ -699,7 +643,7 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
                         // short units against a plain store)
                         typedef float float2v __attribute__((ext_vector_type(2)));
                         const float2v pair = {s, m2};
-                        __builtin_nontemporal_store(pair, reinterpret_cast<float2v*>(a.moments + (unit_index * T + t) * 2));
+                        __builtin_nontemporal_store(pair, reinterpret_cast<float2v*>(a.moments + (unit_index * a.T + un.t0 + t) * 2));
                     }
                 }
                 if constexpr (kOutF32) {
@@ -749,7 +693,7 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
     stc.advance(0, un.nchunks);
     auto fetch_xr = [&](Raw& buf, const Cursor<kMulti>& at) {
         const bool live = at.live(un);                // uniform; dead: offset past the span = empty descriptor
-        load_rows_xr<kStateOnly, kLora, kStreamOnce>(buf, st, live ? at.unit_elems(un) * 2 : 0, live ? at.c * kChunk : T + kChunk, voff);
+        load_rows_xr<kLora, kStreamOnce>(buf, st, live ? at.unit_elems(un) * 2 : 0, live ? at.c * kChunk : T + kChunk, voff);
     };
     auto fetch_kv = [&](Raw& buf, const Cursor<kMulti>& at) {
         const bool live = at.live(un);
@@ -768,11 +712,9 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
         if (live) write_tiles(g);
         fetch_kv(buf, ld);                        // the other half: issued a window later, measured best here
         __syncthreads();                                                        // window barrier
-        if constexpr (!kStateOnly) {
-            __builtin_amdgcn_s_setprio(3);
-            if (live) scores(g);
-            if (stc.c >= 0 && stc.live(un)) store_rows(g - 2, stc);
-        }
+        __builtin_amdgcn_s_setprio(3);
+        if (live) scores(g);
+        if (stc.c >= 0 && stc.live(un)) store_rows(g - 2, stc);
         __syncthreads();                                                        // window barrier
         cur.advance(3, un.nchunks);
         ld.advance(3, un.nchunks);
@@ -811,7 +753,6 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
 template <int kMode, bool kC2, bool kMulti>
 __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane, int cw, const Units& un) {
     constexpr bool kOutF32 = kMode == 1;
-    constexpr bool kStateOnly = kMode == 2;
     constexpr bool kLora = kMode >= 4;
     const int l16 = lane & 15;
     const int g4 = lane >> 4;
@@ -844,12 +785,23 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
             for (int nb = 0; nb < 4; ++nb) dst[nb] = float4v{0.f, 0.f, 0.f, 0.f};
         }
     };
-    if constexpr (kMulti)
+    if constexpr (kMulti) {
         fetch_state(Snext, 0);
-    else
+    } else if (un.entering) {
+        // A token segment: its entering state, rows and half rows at the pitches of where it was left.  When
+        // that is the segment's own rows of `out`, this load has returned before the first of them is
+        // overwritten: chunk 0's read-out takes S, and its rows leave after a barrier behind that.
+        const int voff = 4 * g4 * un.pitch_row + (j >> 5) * un.pitch_half + (j & 31) * 4;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(un.entering), 0, 64 * un.pitch_row, 0x00020000);
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                S[nb][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, (16 * nb + e) * un.pitch_row, 0));
+    } else {
         fetch_state(S, 0);
+    }
 
-    float dtot = 1.f;   // product of all decays so far, key channel `lane` (only with decay_out)
     // Output of the chunk whose state chain ran last, transposed: o[tq][e] belongs to token
     // 16*tq + l16 and value channel 16*cw + 4*g4 + e (the state is the A operand and the token rows
     // the B operand of the MFMAs below), so a lane's four values are contiguous in the output row.
@@ -885,9 +837,9 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
     }
     auto y_fetch = [&](const Cursor<kMulti>& dn) {
         const long long batch = y_b0 + (kMulti ? static_cast<long long>(dn.ui) * y_bstep : 0);
-        const long long seq_bytes = static_cast<long long>(a.T) * (kLoraRank * 2);
-        const __amdgpu_buffer_rsrc_t ry = chunk_rsrc(static_cast<const char*>(a.y) + batch * seq_bytes,
-                                                     static_cast<long long>(dn.c) * kChunk * (kLoraRank * 2), seq_bytes);
+        const __amdgpu_buffer_rsrc_t ry = chunk_rsrc(static_cast<const char*>(a.y) + (batch * a.T + un.t0) * (kLoraRank * 2),
+                                                     static_cast<long long>(dn.c) * kChunk * (kLoraRank * 2),
+                                                     static_cast<long long>(un.tokens) * (kLoraRank * 2));
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
@@ -926,7 +878,7 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
         // first, then the matrix-core work of both chunks -- shortens the consumers' own chain from
         // 1430 to 1260 clocks and lengthens the window from 1850 to 1960: their reads then arrive at
         // the LDS queue in one burst at the highest priority and the producers wait behind them.)
-        if (!kStateOnly && n >= 3 && n - 3 < total) {
+        if (n >= 3 && n - 3 < total) {
             // chunk n-3: o += A V (two partial score tiles), then stage for the producers' stores
             char* lds = lds_all + ((n - 3) & 1) * kBuf;
 #pragma unroll
@@ -954,28 +906,24 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
                     for (int nb = 0; nb < 4; ++nb) S[nb] = Snext[nb];
                     fetch_state(Snext, at.ui + 1);
                 }
-                dtot = 1.f;
             }
             // inter-chunk read: o[t][j] = sum_n (r_t W(t,-1))[n] S[n][j]; the state registers,
             // rounded to fp16, are the A operand (k-slot order = the r tile's column permutation)
-            if constexpr (!kStateOnly) {
-                half8 sh[2];
+            half8 sh[2];
 #pragma unroll
-                for (int kk = 0; kk < 2; ++kk)
+            for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        sh[kk][e] = static_cast<_Float16>(S[2 * kk + (e >> 2)][e & 3]);
+                for (int e = 0; e < 8; ++e)
+                    sh[kk][e] = static_cast<_Float16>(S[2 * kk + (e >> 2)][e & 3]);
 #pragma unroll
-                for (int tq = 0; tq < 2; ++tq) {
-                    o[tq] = float4v{0.f, 0.f, 0.f, 0.f};
+            for (int tq = 0; tq < 2; ++tq) {
+                o[tq] = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int kk = 0; kk < 2; ++kk) {
-                        const half8 rt = lds_read_h8(lds, kRT + (16 * tq + l16) * kRow + (32 * kk + 8 * g4) * 2);
-                        o[tq] = mfma(sh[kk], rt, o[tq]);
-                    }
+                for (int kk = 0; kk < 2; ++kk) {
+                    const half8 rt = lds_read_h8(lds, kRT + (16 * tq + l16) * kRow + (32 * kk + 8 * g4) * 2);
+                    o[tq] = mfma(sh[kk], rt, o[tq]);
                 }
             }
-            if (a.decay_out) dtot *= *reinterpret_cast<const float*>(lds + kD + lane * 4);
             // state update: S = diag(W(32,-1)) S + (k W(32,i))^T V over the chunk's 32 tokens
             vt = lds_read_h8(lds, kVT + tile_t_off(16 * cw + l16, g4));
 #pragma unroll
@@ -989,8 +937,7 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
                 S[nb] = mfma(kt, vt, S[nb]);
             }
             if (at.c == un.nchunks - 1) {
-                // the unit ends: its final state and, if asked for, its total decay
-                const long long unit = static_cast<long long>(un.first) + static_cast<long long>(at.ui) * un.stride;
+                // the unit ends: its final state
                 if (un.state_out) {
                     const __amdgpu_buffer_rsrc_t rs = state_rsrc(un.state_out, at.ui);
 #pragma unroll
@@ -1002,7 +949,6 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
                                                                   (16 * nb + e) * 256, 0);
                         }
                 }
-                if (a.decay_out && cw == 0) a.decay_out[unit * kHeadSize + lane] = dtot;
             }
             at.advance(1, un.nchunks);
         }
@@ -1019,10 +965,7 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
 template <int kMode, bool kC2, bool kMulti>
 __global__ __launch_bounds__(kThreads) void chunked_kernel(Args a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    // MODE.FP16_OVFL = 1 (hwreg id 1, bit 23, one bit): fp16 results that overflow, conversions
-    // included, are clamped to +-65504 instead of becoming infinite, so operands beyond the fp16
-    // range saturate as the header promises; true infinities are preserved.
-    __builtin_amdgcn_s_setreg(1 | (23 << 6) | (0 << 11), 1);
+    clamp_fp16_overflow();
     const int tid = threadIdx.x;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     int unit = blockIdx.x;                       // (batch * segs + segment) * H + head
@@ -1035,25 +978,25 @@ __global__ __launch_bounds__(kThreads) void chunked_kernel(Args a) {
     }
     const int bs = unit / a.H;
     const int h = unit - bs * a.H;
-    const int segs_launched = a.segs_launched > 0 ? a.segs_launched : a.segs;
-    const int b = bs / segs_launched;
-    const int seg = bs - b * segs_launched;
+    const int b = bs / a.segs;
+    const int seg = bs - b * a.segs;
     const long long tok_stride = static_cast<long long>(a.H) * kHeadSize;
-    const long long unit_base = static_cast<long long>(b) * a.batch_stride +
-                                static_cast<long long>(seg) * a.seg_stride +
-                                static_cast<long long>(h) * kHeadSize;
-    const int T = (seg == a.segs - 1) ? a.T_last : a.T;
     // The workgroup's units: this one and, when the launch gave a stride (a multiple of H, whole
     // sequences only), every stride-th unit after it: same head, batch index advancing.
     Units un;
-    un.first = (b * a.segs + seg) * a.H + h;     // = unit when every segment has a workgroup
+    un.t0 = seg * a.seg_len;
+    const int T = a.T - un.t0 < a.seg_len ? a.T - un.t0 : a.seg_len;
+    un.tokens = T;
+    un.first = b * a.H + h;
     un.stride = a.unit_stride;
-    un.state_out = a.state_out;
-    if (a.state_out_final)                       // [B][H] states, written by the last segment only
-        un.state_out = a.state_out && seg == a.segs - 1 ? a.state_out - static_cast<long long>(un.first - (b * a.H + h)) * 4096 : nullptr;
+    un.state_out = seg == a.segs - 1 ? a.state_out : nullptr;      // only the last segment leaves the sequence's state
+    un.entering = nullptr;
+    if (a.segs > 1) un.entering = a.place.base + b * a.place.batch + seg * a.place.seg + h * a.place.head;
+    un.pitch_row = a.place.row;
+    un.pitch_half = a.place.half;
     un.count = 1;
     un.nchunks = (T + kChunk - 1) / kChunk;
-    un.base0 = unit_base;
+    un.base0 = static_cast<long long>(b) * a.batch_stride + un.t0 * tok_stride + static_cast<long long>(h) * kHeadSize;
     un.step = 0;
     if constexpr (kMulti) {
         const long long total = static_cast<long long>(a.B) * a.H;
@@ -1066,59 +1009,14 @@ __global__ __launch_bounds__(kThreads) void chunked_kernel(Args a) {
         consumer<kMode, kC2, kMulti>(a, lds, tid & 63, wid - 4 * kProducerGroups, un);
 }
 
-// Sequential fold over the segments of one (batch, head): 256 threads x 16 state entries.
-__global__ __launch_bounds__(256) void combine_kernel(int H, int segs, const float* state_in,
-                                                      float* seg_state, const float* seg_decay,
-                                                      float* state_out, bool fold_last) {
-    const int unit = blockIdx.x;                 // batch * H + head
-    const int b = unit / H;
-    const int h = unit - b * H;
-    const int t = threadIdx.x;
-    const int row = t >> 2;                      // key channel of this thread's 16 entries
-    float4 S[4];
-    if (state_in) {
-        const float4* s0 = reinterpret_cast<const float4*>(state_in + static_cast<long long>(unit) * 4096) + 4 * t;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) S[q] = s0[q];
-    } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) S[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    for (int p = 0; p < segs; ++p) {
-        const long long su = (static_cast<long long>(b) * segs + p) * H + h;
-        float4* loc = reinterpret_cast<float4*>(seg_state + su * 4096) + 4 * t;
-        if (p == segs - 1 && !fold_last) {       // nothing follows: its pair was not produced
-#pragma unroll
-            for (int q = 0; q < 4; ++q) loc[q] = S[q];
-            break;
-        }
-        const float d = seg_decay[su * kHeadSize + row];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 l = loc[q];
-            loc[q] = S[q];                       // the state entering segment p
-            S[q] = make_float4(fmaf(d, S[q].x, l.x), fmaf(d, S[q].y, l.y), fmaf(d, S[q].z, l.z),
-                               fmaf(d, S[q].w, l.w));
-        }
-    }
-    if (state_out && fold_last) {
-        float4* so = reinterpret_cast<float4*>(state_out + static_cast<long long>(unit) * 4096) + 4 * t;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) so[q] = S[q];
-    }
-}
-
-template <int kMode, bool kC2, bool kMulti>
-struct ChunkedTag {};
-
 template <int kMode, bool kC2>
 hipError_t launch_mode(const Args& args, hipStream_t stream) {
     Args a = args;
-    long long units = static_cast<long long>(a.B) * (a.segs_launched > 0 ? a.segs_launched : a.segs) * a.H;
+    long long units = static_cast<long long>(a.B) * a.segs * a.H;
     a.unit_stride = 0;
     // With more (batch, head) units than compute units each workgroup takes several of them back to back.
     const int cus = compute_units();
-    if (kMode != 2 && a.segs == 1 && a.H <= cus) {
+    if (a.segs == 1 && a.H <= cus) {
         const int per_round = a.H * (cus / a.H);                 // a multiple of H: the head stays fixed
         if (units > per_round) {
             a.unit_stride = per_round;
@@ -1127,16 +1025,17 @@ hipError_t launch_mode(const Args& args, hipStream_t stream) {
     }
     const dim3 grid(static_cast<unsigned>(units));
     constexpr int lds_bytes = kMode >= 4 ? kLdsBytesLora : kLdsBytes;
-    auto go = [&](auto tag, auto kernel) {
-        const hipError_t err = set_lds_limit_once<decltype(tag)>(kernel, lds_bytes);
-        if (err != hipSuccess) return err;
-        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds_bytes, stream, a);
-        return hipGetLastError();
-    };
-    if constexpr (kMode != 2) {
-        if (a.unit_stride > 0) return go(ChunkedTag<kMode, kC2, true>{}, &chunked_kernel<kMode, kC2, true>);
-    }
-    return go(ChunkedTag<kMode, kC2, false>{}, &chunked_kernel<kMode, kC2, false>);
+    struct Tag {};
+    const hipError_t err = once_per_device<Tag>([] {
+        const hipError_t e = set_lds_limit(&chunked_kernel<kMode, kC2, false>, lds_bytes);
+        return e == hipSuccess ? set_lds_limit(&chunked_kernel<kMode, kC2, true>, lds_bytes) : e;
+    });
+    if (err != hipSuccess) return err;
+    if (a.unit_stride > 0)
+        hipLaunchKernelGGL((chunked_kernel<kMode, kC2, true>), grid, dim3(kThreads), lds_bytes, stream, a);
+    else
+        hipLaunchKernelGGL((chunked_kernel<kMode, kC2, false>), grid, dim3(kThreads), lds_bytes, stream, a);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -1146,24 +1045,16 @@ hipError_t launch_chunked(const Args& a, ChunkedMode mode, hipStream_t stream) {
     switch (mode) {
         case ChunkedMode::kBf16Out: return c2 ? launch_mode<0, true>(a, stream) : launch_mode<0, false>(a, stream);
         case ChunkedMode::kF32Out: return c2 ? launch_mode<1, true>(a, stream) : launch_mode<1, false>(a, stream);
-        case ChunkedMode::kStateOnly: return c2 ? launch_mode<2, true>(a, stream) : launch_mode<2, false>(a, stream);
         case ChunkedMode::kBf16OutMoments:
-            if (!c2 || a.segs != 1 || !a.moments) return hipErrorInvalidValue;
+            if (!c2 || !a.moments) return hipErrorInvalidValue;
             return launch_mode<3, true>(a, stream);
         default:
-            if (a.segs != 1 || !a.y || !a.lambda || !a.bw) return hipErrorInvalidValue;
+            if (!a.y || !a.lambda || !a.bw) return hipErrorInvalidValue;
             if (mode == ChunkedMode::kBf16OutLora)
                 return c2 ? launch_mode<4, true>(a, stream) : launch_mode<4, false>(a, stream);
             if (!c2 || !a.moments) return hipErrorInvalidValue;
             return launch_mode<5, true>(a, stream);
     }
-}
-
-hipError_t launch_combine_segments(int B, int H, int segs, const float* state_in, float* seg_state,
-                                   const float* seg_decay, float* state_out, bool fold_last, hipStream_t stream) {
-    hipLaunchKernelGGL(combine_kernel, dim3(static_cast<unsigned>(B) * static_cast<unsigned>(H)),
-                       dim3(256), 0, stream, H, segs, state_in, seg_state, seg_decay, state_out, fold_last);
-    return hipGetLastError();
 }
 
 }  // namespace wkv6

@@ -8,8 +8,21 @@ namespace wkv6 {
 
 constexpr int kHeadSize = 64;   // N: the only head size the kernels are built for
 
+// Where the token split keeps what a segment hands over: the [64][64] fp32 state and, in the row behind
+// it, the 64 total decays.  A row is two halves of 32 values.  Byte strides; either a workspace (rows of
+// 256 bytes) or the first rows of the segment in `out` itself (which the last pass overwrites): a bf16 token
+// row of a head holds half a state row, an fp32 one a whole.
+struct SegPlace {
+    char* base = nullptr;
+    long long batch = 0, seg = 0, head = 0;
+    int row = 0, half = 0;
+};
+
+// Tokens of `out` that a segment's hand-over covers: 65 rows of two 128-byte halves.
+constexpr int kSegPlaceTokens = 130;
+
 struct Args {
-    int B, T, H;
+    int B, T, H;              // T: tokens of a sequence
     const void* r;
     const void* k;
     const void* v;
@@ -18,24 +31,19 @@ struct Args {
     bool finch_c2;            // false: Finch form (bonus u).  true: Finch-C2 form: k is the key before its
                               // (1 - w) factor, no bonus, and the second value uprime is added to the read-out
     const void* uprime;       // Finch-C2 only: [B][T][H][N] bf16, laid out like out; not read by the
-                              // state-only pass
+                              // segments' first pass
     const float* state_in;    // may be nullptr (zero state)
     void* out;
     float* state_out;         // may be nullptr (not written)
     long long batch_stride;   // elements between consecutive batches of r,k,v,x,out
-    // Token-axis segments (chunked kernel only).  Each sequence is cut into `segs` segments of T
-    // tokens (the last one T_last), seg_stride elements apart; a workgroup handles one
-    // (batch, segment, head) and indexes state_in / state_out / decay_out by
-    // (batch*segs + segment)*H + head.  segs == 1: T_last == T and the plain layout.
+    // Token-axis segments (chunked kernel only).  Each sequence is cut into `segs` segments of seg_len
+    // tokens (a multiple of 32; the last one may be shorter); a workgroup handles one (batch, segment,
+    // head), takes its entering state from `place`, and the last segment's writes state_out.  segs == 1:
+    // seg_len == T and the plain layout.
     int segs;
-    int T_last;
-    long long seg_stride;
-    int segs_launched = 0;    // 0: every segment has a workgroup.  n > 0: only the first n segments of each
-                              // sequence have one (the indexing by all `segs` stays)
-    bool state_out_final = false;   // with segs > 1: state_out is [B][H][N][N] and only the last segment's
-                              // workgroup writes it (the state the whole sequence leaves behind)
-    float* decay_out;         // may be nullptr; [B*segs][H][N] product of all decays of the unit
-    float* moments;           // kBf16OutMoments only: [B][H][T][2] per (batch, head, token): the sum of
+    int seg_len;
+    SegPlace place;
+    float* moments;           // with the LayerNorm partials only: [B][H][T][2] per (batch, head, token): the sum of
                               // the head's N output values and their squared deviations from the
                               // head's own mean (taken before the rounding to bf16)
     // kBf16OutLora / kBf16OutLoraMoments only (x unused): the decay logit is formed in the kernel as
@@ -47,7 +55,7 @@ struct Args {
                               // handles units w, w + unit_stride, ... (a multiple of H, segs == 1 only)
 };
 
-enum class ChunkedMode { kBf16Out, kF32Out, kStateOnly, kBf16OutMoments, kBf16OutLora, kBf16OutLoraMoments };
+enum class ChunkedMode { kBf16Out, kF32Out, kBf16OutMoments, kBf16OutLora, kBf16OutLoraMoments };
 
 constexpr int kLoraRank = 64;   // R: the only rank of the decay path the fused kernel is built for
 
@@ -55,21 +63,16 @@ constexpr int kLoraRank = 64;   // R: the only rank of the decay path the fused 
 // with bf16 inputs the output is fp32 or bf16 and a.finch_c2 selects the form.
 hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStream_t stream);
 
-// Chunked matrix-core kernel; inputs bf16, out bf16 or fp32, or (kStateOnly) no output at all:
-// only state_out and decay_out of every unit, from r-independent work.  kBf16OutMoments: bf16 out
-// plus a.moments, Finch-C2 form and segs == 1 only.  kBf16OutLora: bf16 out with the decay
-// logits formed in the kernel from a.y, a.lambda, a.bw instead of read from a.x (either form,
-// segs == 1); kBf16OutLoraMoments: that plus a.moments (Finch-C2 form).
+// Chunked matrix-core kernel; inputs bf16, out bf16 or fp32.  kBf16OutMoments: bf16 out
+// plus a.moments, Finch-C2 form only.  kBf16OutLora: bf16 out with the decay
+// logits formed in the kernel from a.y, a.lambda, a.bw instead of read from a.x (either form);
+// kBf16OutLoraMoments: that plus a.moments (Finch-C2 form).
 hipError_t launch_chunked(const Args& a, ChunkedMode mode, hipStream_t stream);
 
-// Token-split support: folds the per-segment (decay, local state) pairs of every (batch, head)
-// into the state entering each segment, in place in `seg_state` ([B*segs][H][N][N]).  The pair of
-// the last segment is not read (nothing follows it): the first pass need not produce it, and the
-// final state of the sequence comes from the full pass over the last segment (state_out_final).
-// state_out, when not nullptr, receives the state entering the last segment's successor only if
-// `fold_last` is set (then the last pair is read too).
-hipError_t launch_combine_segments(int B, int H, int segs, const float* state_in, float* seg_state,
-                                   const float* seg_decay, float* state_out, bool fold_last, hipStream_t stream);
+// The two passes in front of it when a.segs > 1: the local state and total decay of every segment but the
+// last, from a zero state (k, v and x, or y, lambda and bw when `lora`), left in a.place; then, in place, the state
+// entering every segment (from a.state_in on).
+hipError_t launch_segment_states(const Args& a, bool lora, hipStream_t stream);
 
 // GOLD key compression c = x W: x [M][D] bf16, w [D][D/16] bf16, c [M][D/16] bf16 or fp32.
 // D must be a multiple of 256 (16 output columns per MFMA block, an even number of 64-channel steps).
