@@ -8,9 +8,13 @@
 // is why the chunked kernel exists; this one serves the decode / short-append shapes (one or a
 // few tokens per sequence, many sequences), where the work is streaming the fp32 state through
 // once: 64 row loads of 256 contiguous bytes per wave, all in flight together.  Long sequences
-// of the fp32 and cross-check entry points take the four-wave form further down.
+// of the fp32 and cross-check entry points take the four-wave form or, with few units, the form that spreads a
+// unit's columns over the chip, both further down.
 // Finch-C2 form (template flag): k = kbar (1 - w), no bonus, second value u' added to o.
 #include "wkv6_launch.h"
+#include "wkv6_math.h"
+
+#include <type_traits>
 
 #include <hip/hip_bf16.h>
 
@@ -270,6 +274,176 @@ __global__ __launch_bounds__(256) void recurrent_wide_kernel(Args a) {
     }
 }
 
+// The same for few (batch, head) units: the columns of a state do not depend on one another, so a unit's 64 are
+// dealt to 64 / kCols waves, four to a workgroup, and every SIMD of the chip gets work.  Lane i owns key row i of the
+// wave's kCols columns: r, k, w and u k of its row are one 16-byte LDS read per token, the wave's v values one
+// broadcast, and a token costs 4 kCols multiply-adds with no exchange between lanes.  The sums over the
+// rows wait until 64 of them are due (64 / kCols tokens): a reduce-scatter over the 64 lanes then leaves each lane one finished
+// value, in 141 instructions where folding each by itself would take 12 x 64.  Tokens are staged as in the
+// kernel above, one block of 64 / kCols tokens ahead with the loads of the next in flight, each unit's w formed once per workgroup.
+// Bound by the instruction issue of one or two waves per SIMD (two columns: 196 clocks a token at 32 units of 512 tokens).
+template <int kCtrl>
+__device__ __forceinline__ float dpp_lanes(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kCtrl, 0xf, 0xf, false));
+}
+// One step inside rows of 16 lanes: kCount pairs (v[i], v[i + kCount]); lanes with `high` unset keep the first of
+// a pair and give the second to their partner, the others the reverse.
+template <int kCount, int kCtrl>
+__device__ __forceinline__ void fold_pairs(float (&v)[64], bool high) {
+#pragma unroll
+    for (int i = 0; i < kCount; ++i) {
+        const float keep = high ? v[i + kCount] : v[i], give = high ? v[i] : v[i + kCount];
+        v[i] = keep + dpp_lanes<kCtrl>(give);
+    }
+}
+// v[0 .. 63] of 64 lanes -> in v[0] of lane l, the sum over all lanes of v[slot(l)], slot as scatter_slot below
+__device__ __forceinline__ float reduce_scatter(float (&v)[64], int lane) {
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {                 // halves: lanes 0..31 take v[i], 32..63 v[i + 32]
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 32]), false, false);
+        v[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {                 // rows of 16: even rows take v[i], odd ones v[i + 16]
+        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 16]), false, false);
+        v[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    }
+    fold_pairs<8, 0x128>(v, lane & 8);             // row_ror:8: lane ^ 8
+    fold_pairs<4, 0x141>(v, lane & 4);             // row_half_mirror: 7 - lane of each 8
+    fold_pairs<2, 0x1B>(v, lane & 2);              // quad_perm [3,2,1,0]
+    fold_pairs<1, 0xB1>(v, lane & 1);              // quad_perm [1,0,3,2]
+    return v[0];
+}
+__device__ __forceinline__ int scatter_slot(int lane) {
+    return (lane & 32) + (lane & 16) + (lane & 8) + (lane & 4) + (lane & 2) + (lane & 1);
+}
+
+// 4 to 32 bytes of a row: what a thread loads at once
+template <int kBytes>
+struct Piece;
+template <>
+struct Piece<4> {
+    typedef unsigned type __attribute__((ext_vector_type(1)));
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int voff) { return type{__builtin_amdgcn_raw_buffer_load_b32(r, voff, 0, 0)}; }
+};
+template <>
+struct Piece<8> {
+    typedef unsigned type __attribute__((ext_vector_type(2)));
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int voff) { return __builtin_bit_cast(type, __builtin_amdgcn_raw_buffer_load_b64(r, voff, 0, 0)); }
+};
+template <>
+struct Piece<16> {
+    typedef unsigned type __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int voff) { return __builtin_bit_cast(type, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0)); }
+};
+template <>
+struct Piece<32> {
+    typedef unsigned type __attribute__((ext_vector_type(8)));
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int voff) {
+        const auto lo = Piece<16>::load(r, voff), hi = Piece<16>::load(r, voff + 16);
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+};
+template <bool kInBf16, typename T>
+__device__ __forceinline__ float piece_value(const T& q, int i) {
+    if constexpr (!kInBf16) return __uint_as_float(q[i]);
+    else return __uint_as_float(i & 1 ? q[i >> 1] & 0xffff0000u : q[i >> 1] << 16);
+}
+
+template <int kCols, bool kInBf16>
+__global__ __launch_bounds__(256) void recurrent_columns_kernel(Args a) {
+    constexpr int N = kHeadSize;
+    constexpr int kTokens = 64 / kCols;            // tokens of a block
+    constexpr int kPer = kTokens / 4;              // channels a thread stages
+    constexpr int kGroups = N / (4 * kCols);       // workgroups of a unit
+    const int unit = blockIdx.x / kGroups;         // b * H + h
+    const int b = unit / a.H, h = unit - b * a.H;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int j0 = (blockIdx.x - unit * kGroups) * (4 * kCols);      // the workgroup's first column
+    const int jw = j0 + kCols * wave;                                // the wave's
+
+    __shared__ __attribute__((aligned(16))) float4 s_rows[2][kTokens][N];        // r, k, w, u k of a key row
+    __shared__ __attribute__((aligned(16))) float s_v[2][kTokens][4 * kCols];
+
+    float S[kCols];
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) S[c] = 0.f;
+    if (a.state_in) {
+        const float* s0 = a.state_in + static_cast<long long>(unit) * N * N + lane * N + jw;
+#pragma unroll
+        for (int c = 0; c < kCols; ++c) S[c] = s0[c];
+    }
+    const long long tok_stride = static_cast<long long>(a.H) * N;
+    const long long base = static_cast<long long>(b) * a.batch_stride + static_cast<long long>(h) * N;
+    const int st = tid / (N / kPer), sc = kPer * (tid % (N / kPer));             // staged token and first channel
+    const int vt = tid / (4 * kCols), vc = tid % (4 * kCols);                    // 256 = kTokens * 4 kCols values of v
+    float u[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) u[i] = a.u[h * N + sc + i];
+
+    // Loads through raw buffer descriptors that end with the sequence: rows past the end read as zero with no
+    // branch (r = k = v = 0; w is set to 1 when staged), so a block is one straight line.
+    constexpr int kElem = kInBf16 ? 2 : 4;
+    const long long row_bytes = tok_stride * kElem, span = static_cast<long long>(a.T - 1) * row_bytes + N * kElem;
+    const int voff = static_cast<int>(st * row_bytes) + sc * kElem, v_voff = static_cast<int>(vt * row_bytes) + (j0 + vc) * kElem;
+    typedef typename Piece<kPer * kElem>::type Raw;
+    Raw raw_r, raw_k, raw_x;
+    float raw_v = 0.f;
+    auto fetch = [&](int t0) {
+        const long long off = t0 * row_bytes;
+        raw_r = Piece<kPer * kElem>::load(chunk_rsrc(static_cast<const char*>(a.r) + base * kElem, off, span), voff);
+        raw_k = Piece<kPer * kElem>::load(chunk_rsrc(static_cast<const char*>(a.k) + base * kElem, off, span), voff);
+        raw_x = Piece<kPer * kElem>::load(chunk_rsrc(static_cast<const char*>(a.x) + base * kElem, off, span), voff);
+        const __amdgpu_buffer_rsrc_t rv = chunk_rsrc(static_cast<const char*>(a.v) + base * kElem, off, span);
+        if constexpr (kInBf16)
+            raw_v = __uint_as_float(static_cast<unsigned>(__builtin_amdgcn_raw_buffer_load_b16(rv, v_voff, 0, 0)) << 16);
+        else
+            raw_v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rv, v_voff, 0, 0));
+    };
+    auto stage = [&](int t0, int parity) {
+        const bool past = t0 + st >= a.T;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const float rr = piece_value<kInBf16>(raw_r, i), kk = piece_value<kInBf16>(raw_k, i), xx = piece_value<kInBf16>(raw_x, i);
+            const float w = expf(-expf(xx));
+            s_rows[parity][st][sc + i] = make_float4(rr, kk, past ? 1.f : w, u[i] * kk);
+        }
+        s_v[parity][vt][vc] = raw_v;
+    };
+
+    if (a.T > 0) {
+        fetch(0);
+        stage(0, 0);
+        fetch(kTokens);
+    }
+    const int slot = scatter_slot(lane), ot = slot / kCols, oc = slot % kCols;   // the value this lane ends up with
+    int parity = 0;
+    for (int t0 = 0; t0 < a.T; t0 += kTokens, parity ^= 1) {
+        __syncthreads();                           // this block is staged; the other slot has been read
+        stage(t0 + kTokens, parity ^ 1);
+        fetch(t0 + 2 * kTokens);
+        float part[64];
+#pragma unroll
+        for (int t = 0; t < kTokens; ++t) {
+            const float4 q = s_rows[parity][t][lane];
+            const float* v = &s_v[parity][t][kCols * wave];
+#pragma unroll
+            for (int c = 0; c < kCols; ++c) {
+                part[t * kCols + c] = q.x * fmaf(q.w, v[c], S[c]);
+                S[c] = fmaf(q.z, S[c], q.y * v[c]);
+            }
+        }
+        const float o = reduce_scatter(part, lane);
+        if (t0 + ot < a.T) static_cast<float*>(a.out)[base + static_cast<long long>(t0 + ot) * tok_stride + jw + oc] = o;
+    }
+
+    if (a.state_out) {
+        float* so = a.state_out + static_cast<long long>(unit) * N * N + lane * N + jw;
+#pragma unroll
+        for (int c = 0; c < kCols; ++c) so[c] = S[c];
+    }
+}
+
 __global__ __launch_bounds__(256) void state_passthrough_kernel(const float* in, float* out,
                                                                 long long n4) {
     const long long i = static_cast<long long>(blockIdx.x) * 256 + threadIdx.x;
@@ -289,6 +463,24 @@ constexpr int kWideMinTokens = 16;
 hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStream_t stream) {
     const dim3 grid(static_cast<unsigned>(a.B) * static_cast<unsigned>(a.H));
     const bool c2 = a.finch_c2;
+    if (a.T >= kWideMinTokens && !c2 && !out_bf16) {
+        // A unit's columns over as many workgroups as the chip has room for: one round of 256 with two columns a wave,
+        // two with four or eight.  Measured, fp32, microseconds, four waves a unit -> here (2, 4, 8 columns): 4 units x 256 tokens 77
+        // -> 22, 31, 45; 32 x 512 154 -> 44, 60, 90; 96 x 300 100 -> 75, 46, 56; 256 x 300 101 -> 151, 82, 74; 512 x 1024 382
+        // -> 855, 492, 426: from there the four-wave form, whose waves hold all rows of a column, issues fewer instructions.
+        const long long units = grid.x;
+        auto columns = [&](auto bf16) {
+            constexpr bool kIn = decltype(bf16)::value;
+            if (units <= 32)
+                hipLaunchKernelGGL((recurrent_columns_kernel<2, kIn>), dim3(grid.x * 8), dim3(256), 0, stream, a);
+            else if (units <= 128)
+                hipLaunchKernelGGL((recurrent_columns_kernel<4, kIn>), dim3(grid.x * 4), dim3(256), 0, stream, a);
+            else
+                hipLaunchKernelGGL((recurrent_columns_kernel<8, kIn>), dim3(grid.x * 2), dim3(256), 0, stream, a);
+            return hipGetLastError();
+        };
+        if (units <= 256) return in_bf16 ? columns(std::true_type{}) : columns(std::false_type{});
+    }
     if (a.T >= kWideMinTokens && !c2) {
         if (!in_bf16)
             hipLaunchKernelGGL((recurrent_wide_kernel<false, false>), grid, dim3(256), 0, stream, a);

@@ -531,3 +531,21 @@ def test_split_result_does_not_depend_on_placement(gpu_device):
         results.append((out.clone(), s_out))
     assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
     assert torch.isfinite(results[0][0].float()).all() and torch.isfinite(results[0][1]).all()
+
+
+@pytest.mark.parametrize("B,T,H", [(1, 16, 1), (1, 31, 4), (2, 32, 16), (1, 33, 32), (1, 65, 33), (4, 47, 32), (3, 16, 43), (1, 70, 256), (2, 40, 128),
+                                   (1, 41, 257)])
+@pytest.mark.parametrize("entry,tol,dt", [("wkv6_prefill_f32", TOL_F32, torch.float32),
+                                          ("wkv6_prefill_bf16_recurrent", TOL_F32, torch.bfloat16)])
+def test_columns_of_a_unit_over_several_workgroups(gpu_device, entry, tol, dt, B, T, H):
+    """Token-by-token entries on both sides of every change of the columns per wave (32, 128 and 256 units) and of the
+    token block (32, 16 and 8), with and without an entering state, and with the state updated in place.  Sums of
+    fp32 products either way: the fp32 bar."""
+    inp = make_inputs(scaled(CONFIGS[4], B=B, T=T, H=H), seed=5 + T)
+    for state in (True, False):
+        if not state:
+            inp["state_in"] = None
+        o_ref, s_ref = wkv6_oracle(**inp)
+        for in_place in ((False, True) if state else (False,)):
+            o, s = run_entry(entry, inp, in_dtype=dt, inplace_state=in_place)
+            assert max_norm_err(o, o_ref) <= tol and max_norm_err(s, s_ref) <= tol
