@@ -49,6 +49,29 @@ __global__ __launch_bounds__(256) void layernorm_finalize_kernel(int T, int H, c
     }
 }
 
+// Sequences of a few tokens: a wave per token with the heads on its lanes, since a lane per token would leave
+// most lanes without one.  Partial results meet in pairs over the lanes (the order of the fold is free).
+__global__ __launch_bounds__(256) void layernorm_finalize_few_kernel(long long tokens, int T, int H, const float2* moments,
+                                                                     float eps, float2* mean_rstd) {
+    const int lane = threadIdx.x & 63;
+    const long long token = static_cast<long long>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    if (token >= tokens) return;
+    const long long b = token / T;
+    const float2* src = moments + b * H * T + (token - b * T);
+    Group g{0.f, 0.f, 0.f};
+    for (int h = lane; h < H; h += 64) {
+        const float2 p = src[static_cast<long long>(h) * T];
+        g = combine(g, Group{static_cast<float>(kHeadSize), p.x * (1.f / kHeadSize), p.y});
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        const Group other{__shfl_xor(g.count, m, 64), __shfl_xor(g.mean, m, 64), __shfl_xor(g.m2, m, 64)};
+        // the same order of the pair on both sides, so that every lane ends with the same values
+        g = lane & m ? combine(other, g) : combine(g, other);
+    }
+    if (lane == 0) mean_rstd[token] = make_float2(g.mean, 1.f / sqrtf(g.m2 / g.count + eps));
+}
+
 // The normalisation itself, for callers whose projection GEMM has no row-scaling epilogue:
 // y = (o - mean) * rstd * gamma + beta over the D = H*N values of each token; 8 channels (16 bytes
 // of bf16) per item, every tensor touched once, fp32 arithmetic, one rounding of the result.  A thread
@@ -184,6 +207,14 @@ hipError_t launch_layernorm_apply(long long tokens, int D, const void* o, const 
 
 hipError_t launch_layernorm_finalize(int B, int T, int H, const float* moments, float eps, float* mean_rstd,
                                      hipStream_t stream) {
+    // Below 16 tokens a sequence the lane-per-token form uses fewer than a quarter of its lanes and one workgroup per
+    // sequence: 24 sequences of one token 4.6 -> 3.9 us.
+    const long long tokens = static_cast<long long>(B) * T;
+    if (T < 16) {
+        hipLaunchKernelGGL(layernorm_finalize_few_kernel, dim3(static_cast<unsigned>((tokens + 3) / 4)), dim3(256), 0, stream, tokens, T, H,
+                           reinterpret_cast<const float2*>(moments), eps, reinterpret_cast<float2*>(mean_rstd));
+        return hipGetLastError();
+    }
     const dim3 grid(static_cast<unsigned>((T + 63) / 64), static_cast<unsigned>(B));
     hipLaunchKernelGGL(layernorm_finalize_kernel, grid, dim3(256), 0, stream, T, H,
                        reinterpret_cast<const float2*>(moments), eps, reinterpret_cast<float2*>(mean_rstd));

@@ -228,9 +228,15 @@ int run_lora(int B, int T, int H, int N, int R, const void* r, const void* k, co
     a.moments = moments;
     a.y = y; a.lambda = lambda; a.bw = b_omega;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const hipError_t err = T == 0 ? wkv6::launch_state_passthrough(a, s)
-                                  : launch_prefill(a, moments ? wkv6::ChunkedMode::kBf16OutLoraMoments
-                                                              : wkv6::ChunkedMode::kBf16OutLora, true, s);
+    // A few tokens: as for the append entries, streaming the states once is the work.  24 sequences of one token, 32
+    // heads: 12.7 -> 7.5 us.
+    hipError_t err;
+    if (T == 0)
+        err = wkv6::launch_state_passthrough(a, s);
+    else if (T <= kRecurrentMaxTokens)
+        err = wkv6::launch_recurrent(a, true, true, s);
+    else
+        err = launch_prefill(a, moments ? wkv6::ChunkedMode::kBf16OutLoraMoments : wkv6::ChunkedMode::kBf16OutLora, true, s);
     return err == hipSuccess ? WKV6_OK : WKV6_ERR_LAUNCH;
 }
 

@@ -60,7 +60,8 @@ enum class ChunkedMode { kBf16Out, kF32Out, kBf16OutMoments, kBf16OutLora, kBf16
 constexpr int kLoraRank = 64;   // R: the only rank of the decay path the fused kernel is built for
 
 // Token-by-token fp32 kernel; inputs bf16 or fp32 (fp32 inputs: fp32 out, Finch form only);
-// with bf16 inputs the output is fp32 or bf16 and a.finch_c2 selects the form.
+// with bf16 inputs the output is fp32 or bf16 and a.finch_c2 selects the form.  With a.y the decay logits are formed
+// from a.y, a.lambda, a.bw (bf16 in and out) and a.moments, if set, is written (Finch-C2 form).
 hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStream_t stream);
 
 // Chunked matrix-core kernel; inputs bf16, out bf16 or fp32.  kBf16OutMoments: bf16 out

@@ -37,7 +37,10 @@ __device__ __forceinline__ float wave_sum(float a) {
     return a;
 }
 
-template <bool kInBf16, bool kOutBf16, bool kC2>
+// kLora: the decay logit is formed here, lambda + y B, from the token's 64 low-rank activations and this channel's column of
+// B (32 registers of bf16 pairs; products exact and sums in fp32, as on the matrix cores).  With a.moments
+// (Finch-C2) the wave also leaves the head's LayerNorm partials of every token.
+template <bool kInBf16, bool kOutBf16, bool kC2, bool kLora>
 __global__ __launch_bounds__(64) void recurrent_kernel(Args a) {
     constexpr int N = kHeadSize;
     const int unit = blockIdx.x;           // b * H + h
@@ -48,6 +51,19 @@ __global__ __launch_bounds__(64) void recurrent_kernel(Args a) {
     __shared__ __attribute__((aligned(16))) float s_r[N];
     __shared__ __attribute__((aligned(16))) float s_k[N];
     __shared__ __attribute__((aligned(16))) float s_w[N];
+    __shared__ __attribute__((aligned(16))) float s_y[kLora ? N : 4];
+    static_assert(!kLora || kLoraRank == kHeadSize, "a lane brings in one activation");
+
+    [[maybe_unused]] unsigned bw[kLora ? N / 2 : 1];
+    [[maybe_unused]] float lam = 0.f;
+    if constexpr (kLora) {
+        const long long width = static_cast<long long>(a.H) * N;
+        const unsigned short* col = static_cast<const unsigned short*>(a.bw) + h * N + j;
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i)
+            bw[i] = static_cast<unsigned>(col[2 * i * width]) | (static_cast<unsigned>(col[(2 * i + 1) * width]) << 16);
+        lam = a.lambda[h * N + j];
+    }
 
     float S[N];
     if (a.state_in) {
@@ -63,28 +79,47 @@ __global__ __launch_bounds__(64) void recurrent_kernel(Args a) {
     const long long tok_stride = static_cast<long long>(a.H) * N;
     long long idx = static_cast<long long>(b) * a.batch_stride + static_cast<long long>(h) * N + j;
 
+    // x (or, with kLora, the token's activation y_j) of a token
+    auto load_x = [&](int t, long long e) {
+        if constexpr (kLora) return load_in<true>(a.y, (static_cast<long long>(b) * a.T + t) * kLoraRank + j);
+        else return load_in<kInBf16>(a.x, e);
+    };
     float rj = 0.f, kj = 0.f, vj = 0.f, xj = 0.f, pj = 0.f;
     if (a.T > 0) {
         rj = load_in<kInBf16>(a.r, idx);
         kj = load_in<kInBf16>(a.k, idx);
         vj = load_in<kInBf16>(a.v, idx);
-        xj = load_in<kInBf16>(a.x, idx);
+        xj = load_x(0, idx);
         if constexpr (kC2) pj = load_in<kInBf16>(a.uprime, idx);
     }
     for (int t = 0; t < a.T; ++t) {
-        const float r_cur = rj, v_cur = vj, p_cur = pj;
-        const float w_cur = expf(-expf(xj));
-        // Finch-C2 key factor 1 - w = -expm1(-exp(x)): no cancellation for decays close to 1
-        const float k_cur = kC2 ? kj * -expm1f(-expf(xj)) : kj;
+        const float r_cur = rj, v_cur = vj, p_cur = pj, x_cur = xj, kraw = kj;
         const long long idx_cur = idx;
         idx += tok_stride;
         if (t + 1 < a.T) {                     // next token's loads overlap this token's math
             rj = load_in<kInBf16>(a.r, idx);
             kj = load_in<kInBf16>(a.k, idx);
             vj = load_in<kInBf16>(a.v, idx);
-            xj = load_in<kInBf16>(a.x, idx);
+            xj = load_x(t + 1, idx);
             if constexpr (kC2) pj = load_in<kInBf16>(a.uprime, idx);
         }
+        float logit = x_cur;
+        if constexpr (kLora) {
+            s_y[j] = x_cur;                    // (the last token's reads are behind its second barrier)
+            __syncthreads();
+            logit = lam;
+#pragma unroll
+            for (int i = 0; i < N; i += 4) {
+                const float4 y4 = *reinterpret_cast<const float4*>(&s_y[i]);
+                logit = fmaf(y4.x, __uint_as_float(bw[i / 2] << 16), logit);
+                logit = fmaf(y4.y, __uint_as_float(bw[i / 2] & 0xffff0000u), logit);
+                logit = fmaf(y4.z, __uint_as_float(bw[i / 2 + 1] << 16), logit);
+                logit = fmaf(y4.w, __uint_as_float(bw[i / 2 + 1] & 0xffff0000u), logit);
+            }
+        }
+        const float w_cur = expf(-expf(logit));
+        // Finch-C2 key factor 1 - w = -expm1(-exp(x)): no cancellation for decays close to 1
+        const float k_cur = kC2 ? kraw * -expm1f(-expf(logit)) : kraw;
         __syncthreads();                       // previous token's LDS reads are done
         s_r[j] = r_cur;
         s_k[j] = k_cur;
@@ -112,6 +147,13 @@ __global__ __launch_bounds__(64) void recurrent_kernel(Args a) {
                 __builtin_bit_cast(unsigned short, static_cast<__bf16>(o));
         else
             static_cast<float*>(a.out)[idx_cur] = o;
+        if constexpr (kLora && kC2) {
+            if (a.moments) {                   // uniform
+                const float sum = wave_sum(o), dev = o - sum * (1.f / N);
+                const float m2 = wave_sum(dev * dev);
+                if (j == 0) *reinterpret_cast<float2*>(a.moments + (static_cast<long long>(unit) * a.T + t) * 2) = make_float2(sum, m2);
+            }
+        }
     }
 
     if (a.state_out) {
@@ -463,6 +505,13 @@ constexpr int kWideMinTokens = 16;
 hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStream_t stream) {
     const dim3 grid(static_cast<unsigned>(a.B) * static_cast<unsigned>(a.H));
     const bool c2 = a.finch_c2;
+    if (a.y) {                                 // fused decay path: bf16 in and out
+        if (c2)
+            hipLaunchKernelGGL((recurrent_kernel<true, true, true, true>), grid, dim3(64), 0, stream, a);
+        else
+            hipLaunchKernelGGL((recurrent_kernel<true, true, false, true>), grid, dim3(64), 0, stream, a);
+        return hipGetLastError();
+    }
     if (a.T >= kWideMinTokens && !c2 && !out_bf16) {
         // A unit's columns over as many workgroups as the chip has room for: one round of 256 with two columns a wave,
         // two with four or eight.  Measured, fp32, microseconds, four waves a unit -> here (2, 4, 8 columns): 4 units x 256 tokens 77
@@ -491,15 +540,15 @@ hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStrea
         return hipGetLastError();
     }
     if (!in_bf16)
-        hipLaunchKernelGGL((recurrent_kernel<false, false, false>), grid, dim3(64), 0, stream, a);
+        hipLaunchKernelGGL((recurrent_kernel<false, false, false, false>), grid, dim3(64), 0, stream, a);
     else if (!out_bf16 && !c2)
-        hipLaunchKernelGGL((recurrent_kernel<true, false, false>), grid, dim3(64), 0, stream, a);
+        hipLaunchKernelGGL((recurrent_kernel<true, false, false, false>), grid, dim3(64), 0, stream, a);
     else if (!out_bf16 && c2)
-        hipLaunchKernelGGL((recurrent_kernel<true, false, true>), grid, dim3(64), 0, stream, a);
+        hipLaunchKernelGGL((recurrent_kernel<true, false, true, false>), grid, dim3(64), 0, stream, a);
     else if (!c2)
-        hipLaunchKernelGGL((recurrent_kernel<true, true, false>), grid, dim3(64), 0, stream, a);
+        hipLaunchKernelGGL((recurrent_kernel<true, true, false, false>), grid, dim3(64), 0, stream, a);
     else
-        hipLaunchKernelGGL((recurrent_kernel<true, true, true>), grid, dim3(64), 0, stream, a);
+        hipLaunchKernelGGL((recurrent_kernel<true, true, true, false>), grid, dim3(64), 0, stream, a);
     return hipGetLastError();
 }
 

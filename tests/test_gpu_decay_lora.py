@@ -227,3 +227,20 @@ def test_finch_form_validation(gpu_device):
         wkv.wkv6_prefill_lora_bf16(B, T, H, N, R, z, z, z, y, lam, bo, None, None, out, None)
     with pytest.raises(wkv.Wkv6Error):                         # rank
         wkv.wkv6_prefill_lora_bf16(B, T, H, N, 128, z, z, z, y, lam, bo, lam, None, out, None)
+
+
+@pytest.mark.parametrize("B,T,H", [(24, 1, 32), (3, 2, 4), (1, 5, 3), (2, 6, 12), (2, 7, 12), (700, 1, 2)])
+def test_few_tokens_on_both_sides_of_the_kernel_switch(gpu_device, B, T, H):
+    """Up to six tokens the token-by-token kernel forms the logits, above that the chunked one: both forms, with and
+    without the LayerNorm partials, against the oracles at the same bars."""
+    inp = inputs(scaled(CONFIGS[4], B=B, T=T, H=H))
+    check(inp)
+    check_finch(inp)
+    o_ref, _ = oracle(inp)
+    o, s, mom = run_lora(inp, want_moments=True)
+    o2, s2, _ = run_lora(inp)
+    assert np.array_equal(o, o2) and np.array_equal(s, s2)
+    sum_ref, m2_ref = head_moments_numpy(o_ref)
+    delta = TOL_BF16 * np.abs(o_ref).max()
+    assert np.abs(mom[..., 0] - sum_ref).max() <= 64 * delta
+    assert (np.abs(mom[..., 1] - m2_ref) <= 4 * delta * np.sqrt(64 * m2_ref) + 4 * 64 * delta ** 2).all()

@@ -245,3 +245,21 @@ def test_layernorm_apply_validation(gpu_device):
         with pytest.raises(wkv.Wkv6Error) as e:
             wkv.wkv6_layernorm_apply_bf16(*args)
         assert e.value.status == status
+
+
+@pytest.mark.parametrize("B,T,H", [(1, 1, 1), (24, 1, 32), (3, 15, 12), (3, 16, 12), (5, 7, 64), (2, 3, 65), (1, 2, 200)])
+def test_fold_of_short_sequences(gpu_device, B, T, H):
+    """The wave-per-token fold (below 16 tokens a sequence) and the lane-per-token fold, head counts below, at and above
+    the 64 lanes, against float64 on the same pairs.  fp32 folds of at most 200 pairs: 1e-5 for the mean, of the standard
+    deviation, and 3e-5 for its reciprocal, the bars of the fold elsewhere."""
+    rng = np.random.default_rng(B * 1000 + T * 10 + H)
+    mom = np.stack([rng.standard_normal((B, H, T)) * 8, rng.random((B, H, T)) * 64 + 1], axis=-1).astype(np.float32)
+    got = torch.empty((B, T, 2), device="cuda")
+    wkv.wkv6_layernorm_finalize(B, T, H, 64, to_dev(mom, torch.float32), EPS, got)
+    torch.cuda.synchronize()
+    m = mom.astype(np.float64)
+    mean = m[..., 0].sum(1) / (64 * H)
+    var = (m[..., 1] + 64 * (m[..., 0] / 64 - mean[:, None]) ** 2).sum(1) / (64 * H)
+    got = got.cpu().numpy()
+    assert (np.abs(got[..., 0] - mean) <= 1e-5 * np.sqrt(var)).all()
+    assert (np.abs(got[..., 1] * np.sqrt(var + EPS) - 1) <= 3e-5).all()
