@@ -6,9 +6,9 @@
 // accumulation, bf16 products are exact in fp32).
 //
 // Two kernels.  With enough tokens to fill the chip with large tiles (the rule is at the launch): one workgroup
-// owns 128 tokens x kBN output columns (kBN = 128 up to D = 2048, 256 above, so that
-// up to D = 4096 a workgroup has all columns and x passes through a compute unit's vector memory
-// path once; fewer columns in the last tile when D/16 is not a multiple of kBN) and walks the D
+// owns 128 tokens x kBN output columns (kBN = 128 up to D = 2048, 256 above that if there are more tiles than
+// compute units, so that up to D = 4096 a workgroup has all columns and x passes through a compute unit's vector
+// memory path once; fewer columns in the last tile when D/16 is not a multiple of kBN) and walks the D
 // axis in steps of 64 channels (cyclically, from a start that differs between workgroups).  Its
 // waves split into two roles that meet at one barrier per step:
 //   kBN/32 LOADER waves (the last ones): fetch the x tile (128 x 64: full 128-byte row pieces, 8
@@ -18,9 +18,9 @@
 //               Rows past M and steps past D go through shrunk raw buffer descriptors and read
 //               as zero without touching memory, so no load is predicated and the wait counters
 //               stay exact.
-//   kBN/32 MFMA waves: each owns a 64 x 64 block of the result in 64 accumulator registers;
-//               per step 8 row reads of x (row stride 160 B: full-rate 16-byte LDS reads), 16
-//               transposing reads of W (its contraction index is the tile's row) and 32 MFMAs.
+//   kBN/32 MFMA waves (or twice as many): each owns a 64 x 64 (64 x 32) block of the result in accumulator
+//               registers; per step 8 row reads of x (row stride 160 B: full-rate 16-byte LDS reads), 16 (8)
+//               transposing reads of W (its contraction index is the tile's row) and 32 (16) MFMAs.
 //               They issue no global loads, so nothing but LDS latency sits between their MFMAs.
 // With kBN = 128 registers and LDS are sized so that two workgroups share a compute unit: the
 // waits, prologue and epilogue of one overlap the steady state of the other.  With kBN = 256 a
@@ -42,21 +42,22 @@ constexpr int kXRow = 160;          // LDS row stride of the x tile (64 bf16 + 3
 constexpr int kXTile = kBM * kXRow; // 20480
 constexpr int kCRow = 128 * 4 + 16; // staging row of 128 columns of the fp32 result tile
 
-// per width of the workgroup's column tile (kBN = 128 or 256)
-template <int kBN>
+// per width of the workgroup's column tile (kBN = 128 or 256) and 16-column blocks of an MFMA wave (kWNB = 4 or 2)
+template <int kBN, int kWNB>
 struct Tile {
     static constexpr int kWRow = kBN * 2 + 32;          // LDS row stride of the W tile (kBN bf16 + 32 B pad)
     static constexpr int kWTile = kBK * kWRow;
     static constexpr int kStage = kXTile + kWTile;
     static constexpr int kLds = 2 * kStage;
-    static constexpr int kMfmaWaves = kBN / 32;         // 2 x kBN/64 blocks of 64 x 64
-    static constexpr int kLoaders = 2 * kBN;            // loader threads: as many waves as MFMA waves
+    static constexpr int kMfmaWaves = 2 * kBN / (16 * kWNB);     // blocks of 64 rows x 16 kWNB columns
+    static constexpr int kLoaders = 2 * kBN;            // loader threads
     static constexpr int kThreads = 64 * kMfmaWaves + kLoaders;
     static constexpr int kXLoads = kBM * 8 / kLoaders;  // 16-byte loads per loader thread and step: x,
     static constexpr int kWLoads = kBK * kBN / 8 / kLoaders;   // W
     // steps a loader has in flight: two when two workgroups share a compute unit (they overlap each
     // other's waits), four when one workgroup has it alone
     static constexpr int kDepth = kBN == 128 ? 2 : 4;
+    static constexpr int kPerCu = kBN == 128 && kWNB == 4 ? 2 : 1;
     static constexpr int kHalves = kBN / 128;           // the result leaves through LDS 128 columns at a time
     static_assert(kLds >= kBM * kCRow, "result staging reuses the operand buffers");
 };
@@ -92,18 +93,18 @@ struct KcArgs {
     void* c;
 };
 
-template <int kBN>
+template <typename TL>
 struct StepRegs {          // a loader thread's share of one step, 16 bytes each
-    uint4v x[Tile<kBN>::kXLoads], w[Tile<kBN>::kWLoads];
+    uint4v x[TL::kXLoads], w[TL::kWLoads];
 };
 
 // ------------------------------------------------------------------------------------------
 // loader waves (256 threads): tiles of step s+2 into registers, tiles of step s+1 into LDS
 // ------------------------------------------------------------------------------------------
-template <int kBN>
+template <int kBN, int kWNB>
 __device__ __forceinline__ void kc_loader(const KcArgs& a, char* lds, int lt, long long m0, int n0, int rows,
                                           int nsteps, int first) {
-    using TL = Tile<kBN>;
+    using TL = Tile<kBN, kWNB>;
     constexpr int kWRow = TL::kWRow, kStage = TL::kStage, kXLoads = TL::kXLoads, kWLoads = TL::kWLoads;
     constexpr int kXRowsPerPass = TL::kLoaders / 8;
     constexpr int kLanesPerWRow = kBN / 8, kWRowsPerPass = TL::kLoaders / kLanesPerWRow;
@@ -128,7 +129,7 @@ __device__ __forceinline__ void kc_loader(const KcArgs& a, char* lds, int lt, lo
     const int x_lds = xr * kXRow + 16 * xg;
     const int w_lds = kXTile + wr * kWRow + 16 * wg;
 
-    auto fetch = [&](StepRegs<kBN>& s, int step) {
+    auto fetch = [&](StepRegs<TL>& s, int step) {
         const bool live = step < nsteps;                                          // uniform
         int ks = step + first;                                                    // this step's channel block
         if (ks >= nsteps) ks -= nsteps;
@@ -143,7 +144,7 @@ __device__ __forceinline__ void kc_loader(const KcArgs& a, char* lds, int lt, lo
         for (int p = 0; p < kXLoads; ++p)
             s.x[p] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(rx, x_voff[p], 0, 0));
     };
-    auto park = [&](const StepRegs<kBN>& s, int buf) {
+    auto park = [&](const StepRegs<TL>& s, int buf) {
         char* b = lds + buf * kStage;
 #pragma unroll
         for (int p = 0; p < kXLoads; ++p) *reinterpret_cast<uint4v*>(b + x_lds + kXRowsPerPass * p * kXRow) = s.x[p];
@@ -154,7 +155,7 @@ __device__ __forceinline__ void kc_loader(const KcArgs& a, char* lds, int lt, lo
     // D / 64 steps, a multiple of four; one barrier per step, as many as the MFMA waves pass
     if constexpr (TL::kDepth == 2) {
         // the tiles of two steps in flight per workgroup, and two workgroups share a compute unit
-        StepRegs<kBN> s0, s1;
+        StepRegs<TL> s0, s1;
         fetch(s0, 0);
         fetch(s1, 1);
         park(s0, 0);
@@ -171,7 +172,7 @@ __device__ __forceinline__ void kc_loader(const KcArgs& a, char* lds, int lt, lo
         }
     } else {
         // four steps in flight: with one workgroup per compute unit nothing else covers the latency
-        StepRegs<kBN> s0, s1, s2, s3;
+        StepRegs<TL> s0, s1, s2, s3;
         fetch(s0, 0);
         fetch(s1, 1);
         fetch(s2, 2);
@@ -204,37 +205,37 @@ __device__ __forceinline__ void kc_loader(const KcArgs& a, char* lds, int lt, lo
 // ------------------------------------------------------------------------------------------
 // MFMA waves (256 threads)
 // ------------------------------------------------------------------------------------------
-template <int kBN, bool kOutF32>
+template <int kBN, int kWNB, bool kOutF32>
 __device__ __forceinline__ void kc_worker(const KcArgs& a, char* lds, int tid, int wave, long long m0, int n0,
                                           int rows, int nsteps) {
-    using TL = Tile<kBN>;
-    constexpr int kWRow = TL::kWRow, kStage = TL::kStage, kColBlocks = kBN / 64;
+    using TL = Tile<kBN, kWNB>;
+    constexpr int kWRow = TL::kWRow, kStage = TL::kStage, kColBlocks = kBN / (16 * kWNB);
     const int lane = tid & 63;
     const int l16 = lane & 15;
     const int g4 = lane >> 4;
-    // wave (wr, wc) owns rows 64 wr .. +63 and columns 64 wc .. +63: 4 x 4 blocks of 16 x 16
+    // wave (wr, wc) owns rows 64 wr .. +63 and columns 16 kWNB wc ..: 4 x kWNB blocks of 16 x 16
     const int wr2 = wave / kColBlocks, wc2 = wave % kColBlocks;
-    float4v acc[4][4];
+    float4v acc[4][kWNB];
 #pragma unroll
     for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) acc[rb][nb] = float4v{0.f, 0.f, 0.f, 0.f};
+        for (int nb = 0; nb < kWNB; ++nb) acc[rb][nb] = float4v{0.f, 0.f, 0.f, 0.f};
 
     const int a_lane = (64 * wr2 + l16) * kXRow + 16 * g4;                                      // + 16*kXRow*rb + 64*kb
-    const int b_lane = kXTile + (8 * g4 + (l16 >> 2)) * kWRow + 8 * (l16 & 3) + 128 * wc2;     // + 32*kWRow*kb + 32*nb
+    const int b_lane = kXTile + (8 * g4 + (l16 >> 2)) * kWRow + 8 * (l16 & 3) + 32 * kWNB * wc2;     // + 32*kWRow*kb + 32*nb
     auto compute = [&](int buf) {
         const char* b = lds + buf * kStage;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
-            bf16x8 av[4], wt[4];
+            bf16x8 av[4], wt[kWNB];
 #pragma unroll
             for (int rb = 0; rb < 4; ++rb) av[rb] = lds_read_b8(b, a_lane + 16 * kXRow * rb + 64 * kb);
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb) wt[nb] = lds_read_tr8<kWRow>(b, b_lane + 32 * kWRow * kb + 32 * nb);
+            for (int nb = 0; nb < kWNB; ++nb) wt[nb] = lds_read_tr8<kWRow>(b, b_lane + 32 * kWRow * kb + 32 * nb);
 #pragma unroll
             for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-                for (int nb = 0; nb < 4; ++nb)
+                for (int nb = 0; nb < kWNB; ++nb)
                     acc[rb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[rb], wt[nb], acc[rb][nb], 0, 0, 0);
         }
     };
@@ -254,15 +255,15 @@ __device__ __forceinline__ void kc_worker(const KcArgs& a, char* lds, int tid, i
 #pragma unroll
     for (int hf = 0; hf < TL::kHalves; ++hf) {
         if (hf > 0) __syncthreads();                               // the previous half has been read
-        if ((wc2 >> 1) == hf) {
+        if (16 * kWNB * wc2 / 128 == hf) {
 #pragma unroll
             for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-                for (int nb = 0; nb < 4; ++nb)
+                for (int nb = 0; nb < kWNB; ++nb)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         *reinterpret_cast<float*>(lds + (64 * wr2 + 16 * rb + 4 * g4 + e) * kCRow +
-                                                  (64 * (wc2 & 1) + 16 * nb + l16) * 4) = acc[rb][nb][e];
+                                                  (16 * kWNB * wc2 % 128 + 16 * nb + l16) * 4) = acc[rb][nb][e];
         }
         __syncthreads();
         // A row's eight threads store one whole 128-byte line per instruction: thread cg takes the
@@ -295,9 +296,9 @@ __device__ __forceinline__ void kc_worker(const KcArgs& a, char* lds, int tid, i
     }
 }
 
-template <int kBN, bool kOutF32>
-__global__ __launch_bounds__(Tile<kBN>::kThreads, 256 / kBN) void key_compress_kernel(KcArgs a) {
-    using TL = Tile<kBN>;
+template <int kBN, int kWNB, bool kOutF32>
+__global__ __launch_bounds__((Tile<kBN, kWNB>::kThreads), (Tile<kBN, kWNB>::kPerCu)) void key_compress_kernel(KcArgs a) {
+    using TL = Tile<kBN, kWNB>;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -325,10 +326,10 @@ __global__ __launch_bounds__(Tile<kBN>::kThreads, 256 / kBN) void key_compress_k
     // priority is an issue-arbitration hint): measured 2-3 % on the benchmark shapes
     if (wave >= TL::kMfmaWaves) {
         __builtin_amdgcn_s_setprio(2);
-        kc_loader<kBN>(a, lds, tid - 64 * TL::kMfmaWaves, m0, n0, rows, nsteps, first);
+        kc_loader<kBN, kWNB>(a, lds, tid - 64 * TL::kMfmaWaves, m0, n0, rows, nsteps, first);
     } else {
         __builtin_amdgcn_s_setprio(1);
-        kc_worker<kBN, kOutF32>(a, lds, tid, wave, m0, n0, rows, nsteps);
+        kc_worker<kBN, kWNB, kOutF32>(a, lds, tid, wave, m0, n0, rows, nsteps);
     }
 }
 
@@ -482,12 +483,12 @@ hipError_t launch_few(const KcArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <int kBN, bool kOutF32>
+template <int kBN, int kWNB, bool kOutF32>
 hipError_t launch_tile(const KcArgs& a, hipStream_t stream) {
-    using TL = Tile<kBN>;
+    using TL = Tile<kBN, kWNB>;
     const long long row_tiles = (a.M + kBM - 1) / kBM;
     const dim3 grid(static_cast<unsigned>((row_tiles + 7) / 8 * 8 * ((a.C + kBN - 1) / kBN)));
-    hipLaunchKernelGGL((key_compress_kernel<kBN, kOutF32>), grid, dim3(TL::kThreads), TL::kLds, stream, a);
+    hipLaunchKernelGGL((key_compress_kernel<kBN, kWNB, kOutF32>), grid, dim3(TL::kThreads), TL::kLds, stream, a);
     return hipGetLastError();
 }
 
@@ -501,8 +502,9 @@ hipError_t raise_lds_limits() {
     if (err == hipSuccess) err = set_lds_limit(&key_compress_few_kernel<1, 2, kOutF32>, FewTile<1, 2>::kLds);
     if (err == hipSuccess) err = set_lds_limit(&key_compress_few_kernel<1, 4, kOutF32>, FewTile<1, 4>::kLds);
     if (err == hipSuccess) err = set_lds_limit(&key_compress_few_kernel<2, 4, kOutF32>, FewTile<2, 4>::kLds);
-    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, kOutF32>, Tile<128>::kLds);
-    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<256, kOutF32>, Tile<256>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, 4, kOutF32>, Tile<128, 4>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, 2, kOutF32>, Tile<128, 2>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<256, 4, kOutF32>, Tile<256, 4>::kLds);
     return err;
 }
 
@@ -537,8 +539,13 @@ hipError_t launch_key_compress(long long M, int D, const void* x, const void* w,
     if (groups(1, 4) <= cus) return out_f32 ? launch_few<1, 4, true>(a, stream) : launch_few<1, 4, false>(a, stream);
     if (groups(2, 4) <= (a.C > 128 ? 2 : 1) * cus)
         return out_f32 ? launch_few<2, 4, true>(a, stream) : launch_few<2, 4, false>(a, stream);
-    if (a.C > 128) return out_f32 ? launch_tile<256, true>(a, stream) : launch_tile<256, false>(a, stream);
-    return out_f32 ? launch_tile<128, true>(a, stream) : launch_tile<128, false>(a, stream);
+    // At most one large tile per compute unit: 128 columns a tile, also above D = 2048 (x then comes from L2 the second
+    // time), and eight MFMA waves instead of four, since no second workgroup is there to overlap with.  Microseconds, before -> here:
+    // D = 4096 6000 tokens 58.6 -> 37.1, 16 384 (256 tiles) 64.8 -> 50.8, and at 24 000 71 against 79; D = 8192 8192 tokens 116 -> 88;
+    // D = 2048 16 384 tokens 22.6 -> 21.5.
+    if ((M + kBM - 1) / kBM * ((a.C + 127) / 128) <= cus) return out_f32 ? launch_tile<128, 2, true>(a, stream) : launch_tile<128, 2, false>(a, stream);
+    if (a.C > 128) return out_f32 ? launch_tile<256, 4, true>(a, stream) : launch_tile<256, 4, false>(a, stream);
+    return out_f32 ? launch_tile<128, 4, true>(a, stream) : launch_tile<128, 4, false>(a, stream);
 }
 
 }  // namespace wkv6

@@ -111,3 +111,13 @@ def test_every_tile_of_the_split_contraction(gpu_device, M, D):
     c32 = run(x, w, torch.float32)
     assert max_norm_err(c32, key_compress_oracle(x, w)) <= 1e-5
     assert np.array_equal(run(x, w, torch.bfloat16), round_to_bf16(c32))
+
+
+@pytest.mark.parametrize("M,D", [(8193, 4096), (16384, 4096), (16385, 4096), (8192, 2048), (32768, 1024), (32769, 1024), (5000, 8192), (8321, 4352)])
+def test_large_tiles_around_one_per_compute_unit(gpu_device, M, D):
+    """Both sides of the change from 128-column tiles with eight MFMA waves (at most 256 tiles) to the wider or
+    narrower-staffed ones, with a ragged last row tile and a partial last column tile."""
+    x, w = make_key_compress_inputs(M, D, seed=77 + M)
+    c32 = run(x, w, torch.float32)
+    assert max_norm_err(c32, key_compress_oracle(x, w)) <= 1e-5
+    assert np.array_equal(run(x, w, torch.bfloat16), round_to_bf16(c32))
