@@ -341,19 +341,21 @@ __global__ __launch_bounds__((Tile<kBN, kWNB>::kThreads), (Tile<kBN, kWNB>::kPer
 // compute units have nothing to do and the others walk D / 64 dependent steps.  Here a workgroup owns a
 // small tile, 16 kTB tokens x 16 kNB columns, and its sixteen waves take the 32-channel blocks of D in
 // turn (wave w: blocks w, w + 16, ...), so that a walk is D / 512 steps long, with the loads of
-// kFewDepth of them in flight, and needs no barrier: a wave reads its x fragment straight into the MFMA
-// operand layout (16 tokens, 16 bytes per lane) and passes its W block through a piece of LDS of its
-// own for the transposing read.  The sixteen partial results are added in wave order, in fp32, at the end.
+// kFewDepth of them in flight, and needs no barrier: a wave passes its x and W blocks through a piece of LDS of its
+// own (x loaded straight into operand layout touches sixteen lines per quarter wave, which the L1's tag lookups
+// charge four times: D = 2048, 16 tokens 5.1 -> 4.5 us, 4096 tokens 11.1 -> 10.6).  The sixteen partial results are added in wave order, in fp32, at the end.
 constexpr int kFewWaves = 16;
 constexpr int kFewDepth = 2;
 
 template <int kTB, int kNB>
 struct FewTile {
     static constexpr int kWRow = 32 * kNB + 32;         // LDS row stride of a wave's W block [32][16 kNB] bf16
-    static constexpr int kWBlock = 32 * kWRow;
+    static constexpr int kXOff = 32 * kWRow;            // then its x block [16 kTB][32] bf16, 64-byte rows
+    static constexpr int kFewXRow = 96;
+    static constexpr int kPiece = kXOff + 16 * kTB * kFewXRow;
     static constexpr int kPRow = 16 * kNB + 4;          // row stride (floats) of a wave's partial result
     static constexpr int kPart = 16 * kTB * kPRow;      // floats per wave
-    static constexpr int kWBytes = kFewWaves * kWBlock, kPBytes = kFewWaves * kPart * 4;
+    static constexpr int kWBytes = kFewWaves * kPiece, kPBytes = kFewWaves * kPart * 4;
     static constexpr int kLds = kWBytes > kPBytes ? kWBytes : kPBytes;
     static_assert(kLds <= 160 * 1024, "LDS budget");
 };
@@ -380,9 +382,9 @@ __global__ __launch_bounds__(64 * kFewWaves) void key_compress_few_kernel(KcArgs
     const int wr = lane / kLanesPerRow, wg = lane % kLanesPerRow;
     const int w_voff = n0 + 8 * wg < a.C ? static_cast<int>(wr * w_row_bytes + (n0 + 8 * wg) * 2) : 0x7ffffff0;
     const int w_pass = n0 + 8 * wg < a.C ? static_cast<int>(kRowsPerPass * w_row_bytes) : 0;
-    int x_voff[kTB];
-#pragma unroll
-    for (int tb = 0; tb < kTB; ++tb) x_voff[tb] = static_cast<int>((16 * tb + l16) * x_row_bytes + 16 * g4);
+    // x block: 4 lanes per 64-byte row piece, 16 rows per pass
+    const int xr = lane >> 2, xg = 16 * (lane & 3);
+    const int x_voff = static_cast<int>(xr * x_row_bytes) + xg, x_pass = static_cast<int>(16 * x_row_bytes);
 
     struct Regs {
         uint4v x[kTB], w[kNB];
@@ -397,7 +399,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void key_compress_few_kernel(KcArgs
             s.w[nb] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(rw, w_voff + nb * w_pass, 0, 0));
 #pragma unroll
         for (int tb = 0; tb < kTB; ++tb)
-            s.x[tb] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(rx, x_voff[tb], 0, 0));
+            s.x[tb] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(rx, x_voff + tb * x_pass, 0, 0));
     };
 
     float4v acc[kTB][kNB];
@@ -405,7 +407,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void key_compress_few_kernel(KcArgs
     for (int tb = 0; tb < kTB; ++tb)
 #pragma unroll
         for (int nb = 0; nb < kNB; ++nb) acc[tb][nb] = float4v{0.f, 0.f, 0.f, 0.f};
-    char* mine = lds + wave * TL::kWBlock;
+    char* mine = lds + wave * TL::kPiece;
     const int b_lane = (8 * g4 + (l16 >> 2)) * TL::kWRow + 8 * (l16 & 3);
     auto step = [&](const Regs& s) {
         // the wave alone touches its piece: the fences keep the order of its own accesses
@@ -414,16 +416,22 @@ __global__ __launch_bounds__(64 * kFewWaves) void key_compress_few_kernel(KcArgs
 #pragma unroll
         for (int nb = 0; nb < kNB; ++nb)
             *reinterpret_cast<uint4v*>(mine + (wr + kRowsPerPass * nb) * TL::kWRow + 16 * wg) = s.w[nb];
+#pragma unroll
+        for (int tb = 0; tb < kTB; ++tb)
+            *reinterpret_cast<uint4v*>(mine + TL::kXOff + (16 * tb + xr) * TL::kFewXRow + xg) = s.x[tb];
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        bf16x8 xv[kTB];
+#pragma unroll
+        for (int tb = 0; tb < kTB; ++tb) xv[tb] = lds_read_b8(mine, TL::kXOff + (16 * tb + l16) * TL::kFewXRow + 16 * g4);
 #pragma unroll
         for (int nb = 0; nb < kNB; ++nb) {
             // columns as the rows of the product: a lane ends with four neighbouring columns of its token
             const bf16x8 wt = lds_read_tr8<TL::kWRow>(mine, b_lane + 32 * nb);
 #pragma unroll
             for (int tb = 0; tb < kTB; ++tb)
-                acc[tb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt, __builtin_bit_cast(bf16x8, s.x[tb]), acc[tb][nb], 0, 0, 0);
+                acc[tb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt, xv[tb], acc[tb][nb], 0, 0, 0);
         }
     };
     Regs ring[kFewDepth];
@@ -524,12 +532,11 @@ hipError_t launch_key_compress(long long M, int D, const void* x, const void* w,
     // The contraction-split form while it fits the chip once: then a call takes as long as one workgroup, and
     // its walk of D / 512 steps is shorter than the D / 64 of the large tiles.  The smallest tile that still
     // gives at most one workgroup per compute unit, since a workgroup's time grows with its tile.  Measured, D
-    // = 2048, microseconds, large tiles -> this form: 19.7 -> 4.4 at 1 token, 20.9 -> 5.6 at 512, 21.0 -> 5.7 at
-    // 1024, 21.0 -> 7.3 at 2048, 21.0 -> 11.1 at 4096 (256 workgroups of the largest tile); at 8192 both take 21
-    // and beyond that the W traffic of the small tiles (all of W per 32 tokens) loses: 39.5 against 22 at 16384.
-    // D = 1024: 11.5 -> 3.8 at 16 tokens, 12.3 -> 7.4 at 8192, level at 16384.  Above D = 2048 a large tile's walk is so
-    // long (56 at D = 4096 for any few tokens) that two rounds still win: 34.5 against 58 at 4096 tokens, 66 against 59
-    // at 8192.
+    // = 2048, microseconds, large tiles -> this form: 19.7 -> 4.4 at 1 token, 20.9 -> 5.2 at 512, 21.0 -> 5.5 at
+    // 1024, 21.0 -> 6.8 at 2048, 21.0 -> 10.6 at 4096 (256 workgroups of the largest tile); D = 1024: 11.5 -> 3.8 at 16 tokens, 12.3
+    // -> 7.4 at 8192, level at 16 384.  From D = 2048 on a large tile's walk is so long that two rounds of these still win
+    // or tie: 18.2 against 19.9 at 6000 tokens, 19.7 against 20.2 at 8192; D = 4096 32.7 against 58 at 4096.  Beyond
+    // that the W traffic of the small tiles (all of W per 32 tokens) loses: D = 2048, 16 384 tokens 37 against 21.
     const int cus = compute_units();
     auto groups = [&](int tb, int nb) {
         return (M + 16 * tb - 1) / (16 * tb) * ((a.C + 16 * nb - 1) / (16 * nb));
@@ -537,7 +544,7 @@ hipError_t launch_key_compress(long long M, int D, const void* x, const void* w,
     if (groups(1, 1) <= cus) return out_f32 ? launch_few<1, 1, true>(a, stream) : launch_few<1, 1, false>(a, stream);
     if (groups(1, 2) <= cus) return out_f32 ? launch_few<1, 2, true>(a, stream) : launch_few<1, 2, false>(a, stream);
     if (groups(1, 4) <= cus) return out_f32 ? launch_few<1, 4, true>(a, stream) : launch_few<1, 4, false>(a, stream);
-    if (groups(2, 4) <= (a.C > 128 ? 2 : 1) * cus)
+    if (groups(2, 4) <= (a.C >= 128 ? 2 : 1) * cus)
         return out_f32 ? launch_few<2, 4, true>(a, stream) : launch_few<2, 4, false>(a, stream);
     // At most one large tile per compute unit: 128 columns a tile, also above D = 2048 (x then comes from L2 the second
     // time), and eight MFMA waves instead of four, since no second workgroup is there to overlap with.  Microseconds, before -> here:
