@@ -2,6 +2,7 @@
 // Every step of the computation runs in the kernels this file launches.
 #include "../../include/wkv6.h"
 #include "wkv6_launch.h"
+#include "wkv6_split_plan.h"
 
 #include <cstdint>
 #include <mutex>
@@ -19,49 +20,8 @@ enum class Path { kChunked, kRecurrent, kBySize };
 // window each at these lengths).
 constexpr int kRecurrentMaxTokens = 6;
 
-struct SplitPlan {
-    int segs;        // segments actually used
-    int seg_len;     // tokens per segment (multiple of 32), last one shorter
-};
-
-SplitPlan plan_split(int T, int segments) {
-    SplitPlan p;
-    if (segments < 1) segments = 1;
-    long long len = (static_cast<long long>(T) + segments - 1) / segments;
-    len = (len + 31) / 32 * 32;
-    if (len < 32) len = 32;
-    p.seg_len = static_cast<int>(len);
-    p.segs = static_cast<int>((T + len - 1) / len);
-    if (p.segs < 1) p.segs = 1;
-    return p;
-}
-
-// The split that an entry point without a workspace makes by itself when its (batch, head) units leave compute units
-// idle: as many segments as fill the 256 of an MI355X once.  The hand-over between the passes lies in
-// the first rows of every segment of `out`, which the last pass overwrites, so every segment needs that many
-// tokens.  A function of the shape alone, the same for every form and output type, so that forms that agree bit for
-// bit still do.
-// The two passes in front cost about 12 us and, in the last pass, every chunk that a workgroup no longer walks saves 0.75
-// us: the split pays from about 20 chunks on.  Measured, microseconds, whole -> split (Finch, H = 32): 700 tokens 21.9 -> 22.4,
-// 1024 29.0 -> 22.7, 4096 97 -> 38, 32 768 727 -> 221; Finch-C2 with two sequences 700 tokens 27.1 -> 28.3, 1024
-// 35.7 -> 29.9, 4096 121 -> 70.  Two segments never pay: what they save the state pass takes (Finch-C2, four sequences of 4096:
-// 128 -> 124; of 2048 67 -> 68).
-SplitPlan plan_own_split(int B, int T, int H) {
-    const SplitPlan whole{1, T};
-    const long long units = static_cast<long long>(B) * H;
-    long long segs = 256 / units;
-    if (segs > T / wkv6::kSegPlaceTokens) segs = T / wkv6::kSegPlaceTokens;
-    for (; segs > 2; --segs) {
-        const SplitPlan p = plan_split(T, static_cast<int>(segs));
-        if (p.segs < 3 || T - p.seg_len < 20 * 32) return whole;
-        if (p.seg_len >= wkv6::kSegPlaceTokens && T - static_cast<long long>(p.segs - 1) * p.seg_len >= wkv6::kSegPlaceTokens)
-            return p;
-    }
-    return whole;
-}
-
 // Fills in the segments of `p` with their hand-over in the segments' own rows of out.
-void split_into_out(wkv6::Args& a, const SplitPlan& p, bool out_f32) {
+void split_into_out(wkv6::Args& a, const wkv6::SplitPlan& p, bool out_f32) {
     a.segs = p.segs;
     a.seg_len = p.seg_len;
     const long long elem = out_f32 ? 4 : 2;
@@ -78,7 +38,7 @@ void split_into_out(wkv6::Args& a, const SplitPlan& p, bool out_f32) {
 hipError_t launch_prefill(wkv6::Args& a, wkv6::ChunkedMode mode, bool own_split, hipStream_t s) {
     const bool lora = mode == wkv6::ChunkedMode::kBf16OutLora || mode == wkv6::ChunkedMode::kBf16OutLoraMoments;
     if (own_split) {
-        const SplitPlan p = plan_own_split(a.B, a.T, a.H);
+        const wkv6::SplitPlan p = wkv6::plan_own_split(a.B, a.T, a.H);
         if (p.segs > 1) split_into_out(a, p, mode == wkv6::ChunkedMode::kF32Out);
     }
     const hipError_t err = wkv6::launch_segment_states(a, lora, s);
@@ -409,7 +369,7 @@ int wkv6_split_segments(int B, int T, int H, int N) {
 
 long long wkv6_split_workspace_bytes(int B, int T, int H, int N, int segments) {
     if (N != wkv6::kHeadSize || B < 0 || T < 0 || H < 1 || segments < 1) return -1;
-    const SplitPlan p = plan_split(T > 0 ? T : 1, segments);
+    const wkv6::SplitPlan p = wkv6::plan_split(T > 0 ? T : 1, segments);
     return static_cast<long long>(B) * p.segs * H * (wkv6::kHeadSize * wkv6::kHeadSize + wkv6::kHeadSize) * 4;
 }
 
@@ -451,7 +411,7 @@ int run_split(int B, int T, int H, int N, const void* r, const void* k, const vo
     if (out_dtype != WKV6_DTYPE_BF16 && out_dtype != WKV6_DTYPE_F32) return WKV6_ERR_UNSUPPORTED;
     if (N != wkv6::kHeadSize) return WKV6_ERR_UNSUPPORTED;
     if (B < 0 || T < 0 || H < 1 || H > 262144 || segments < 1) return WKV6_ERR_SHAPE;
-    const SplitPlan p = plan_split(T > 0 ? T : 1, segments);
+    const wkv6::SplitPlan p = wkv6::plan_split(T > 0 ? T : 1, segments);
     if (T == 0 || B == 0 || p.segs == 1)
         return run(B, T, H, N, r, k, v, x, u, state_in, out, state_out,
                    static_cast<long long>(T) * H * N, true, out_dtype == WKV6_DTYPE_F32,

@@ -18,9 +18,6 @@ struct SegPlace {
     int row = 0, half = 0;
 };
 
-// Tokens of `out` that a segment's hand-over covers: 65 rows of two 128-byte halves.
-constexpr int kSegPlaceTokens = 130;
-
 struct Args {
     int B, T, H;              // T: tokens of a sequence
     const void* r;
