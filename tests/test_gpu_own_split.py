@@ -132,3 +132,24 @@ def test_replays_in_a_graph(gpu_device):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want) and torch.equal(s_out, s_want)
+
+
+def test_moments_of_a_split_prefill_are_those_of_its_output(gpu_device):
+    """The LayerNorm partials carry the sequence's token index, not the segment's: the plain entry's bits for out and state,
+    and sums and squared deviations of the head's read-outs (fp32 out of the same split, so 64 fp32 sums: 1e-5)."""
+    B, T, H = 2, 1531, 12
+    _, inp = inputs(B, T, H)
+    r, k, v, x, up = (to_dev(inp[n], torch.bfloat16) for n in ("r", "k", "v", "x", "uprime"))
+    s_in = to_dev(inp["state_in"], torch.float32)
+    out, s_out, mom = torch.empty_like(r), torch.empty_like(s_in), torch.full((B, H, T, 2), float("nan"), device="cuda")
+    wkv.wkv6_finch_c2_prefill_bf16_moments(B, T, H, 64, r, k, v, x, up, s_in, out, mom, s_out)
+    out0, s0 = torch.empty_like(r), torch.empty_like(s_in)
+    wkv.wkv6_finch_c2_prefill_bf16(B, T, H, 64, r, k, v, x, up, s_in, out0, s0)
+    assert torch.equal(out, out0) and torch.equal(s_out, s0)
+    o32 = torch.empty((B, T, H, 64), device="cuda")
+    wkv.wkv6_finch_c2_prefill_bf16_f32out(B, T, H, 64, r, k, v, x, up, s_in, o32, s0)
+    o = o32.double().permute(0, 2, 1, 3)
+    mean = o.mean(-1, keepdim=True)
+    assert (mom[..., 0].double() - o.sum(-1)).abs().max() <= 1e-5 * o.abs().sum(-1).max()
+    m2 = ((o - mean) ** 2).sum(-1)
+    assert ((mom[..., 1].double() - m2).abs() <= 1e-5 * m2.max()).all()
