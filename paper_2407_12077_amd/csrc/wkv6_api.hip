@@ -45,6 +45,14 @@ hipError_t launch_prefill(wkv6::Args& a, wkv6::ChunkedMode mode, bool own_split,
     return err == hipSuccess ? wkv6::launch_chunked(a, mode, s) : err;
 }
 
+// A call that the token-by-token kernel takes because it is short: its entry point launches the kernels of
+// launch_prefill at other sizes, so their limits are raised here as well.
+hipError_t launch_short(const wkv6::Args& a, wkv6::ChunkedMode mode, hipStream_t s) {
+    hipError_t err = wkv6::raise_segment_limits();
+    if (err == hipSuccess) err = wkv6::raise_chunked_limits(a, mode);
+    return err == hipSuccess ? wkv6::launch_recurrent(a, true, true, s) : err;
+}
+
 // `uprime` selects the form: nullptr = Finch (bonus u), otherwise Finch-C2 (u unused, may be null).
 int run(int B, int T, int H, int N, const void* r, const void* k, const void* v, const void* x,
         const float* u, const float* state_in, void* out, float* state_out,
@@ -86,8 +94,10 @@ int run(int B, int T, int H, int N, const void* r, const void* k, const void* v,
     hipError_t err;
     if (T == 0)
         err = wkv6::launch_state_passthrough(a, s);
-    else if (path == Path::kRecurrent || (path == Path::kBySize && T <= kRecurrentMaxTokens))
+    else if (path == Path::kRecurrent)
         err = wkv6::launch_recurrent(a, in_bf16, in_bf16 && !out_f32, s);
+    else if (path == Path::kBySize && T <= kRecurrentMaxTokens)          // bf16 in and out
+        err = launch_short(a, wkv6::ChunkedMode::kBf16Out, s);
     else if (want_moments)
         err = launch_prefill(a, wkv6::ChunkedMode::kBf16OutMoments, own_split, s);
     else
@@ -190,13 +200,14 @@ int run_lora(int B, int T, int H, int N, int R, const void* r, const void* k, co
     hipStream_t s = static_cast<hipStream_t>(stream);
     // A few tokens: as for the append entries, streaming the states once is the work.  24 sequences of one token, 32
     // heads: 12.7 -> 7.5 us.
+    const wkv6::ChunkedMode mode = moments ? wkv6::ChunkedMode::kBf16OutLoraMoments : wkv6::ChunkedMode::kBf16OutLora;
     hipError_t err;
     if (T == 0)
         err = wkv6::launch_state_passthrough(a, s);
     else if (T <= kRecurrentMaxTokens)
-        err = wkv6::launch_recurrent(a, true, true, s);
+        err = launch_short(a, mode, s);
     else
-        err = launch_prefill(a, moments ? wkv6::ChunkedMode::kBf16OutLoraMoments : wkv6::ChunkedMode::kBf16OutLora, true, s);
+        err = launch_prefill(a, mode, true, s);
     return err == hipSuccess ? WKV6_OK : WKV6_ERR_LAUNCH;
 }
 

@@ -1015,7 +1015,19 @@ __global__ __launch_bounds__(kThreads) void chunked_kernel(Args a) {
 }
 
 template <int kMode, bool kC2>
+hipError_t raise_mode_limits() {
+    constexpr int lds_bytes = kMode >= 4 ? kLdsBytesLora : kLdsBytes;
+    struct Tag {};
+    return once_per_device<Tag>([] {
+        const hipError_t e = set_lds_limit(&chunked_kernel<kMode, kC2, false>, lds_bytes);
+        return e == hipSuccess ? set_lds_limit(&chunked_kernel<kMode, kC2, true>, lds_bytes) : e;
+    });
+}
+
+template <int kMode, bool kC2>
 hipError_t launch_mode(const Args& args, hipStream_t stream) {
+    const hipError_t err = raise_mode_limits<kMode, kC2>();
+    if (err != hipSuccess) return err;
     Args a = args;
     long long units = static_cast<long long>(a.B) * a.segs * a.H;
     a.unit_stride = 0;
@@ -1030,12 +1042,6 @@ hipError_t launch_mode(const Args& args, hipStream_t stream) {
     }
     const dim3 grid(static_cast<unsigned>(units));
     constexpr int lds_bytes = kMode >= 4 ? kLdsBytesLora : kLdsBytes;
-    struct Tag {};
-    const hipError_t err = once_per_device<Tag>([] {
-        const hipError_t e = set_lds_limit(&chunked_kernel<kMode, kC2, false>, lds_bytes);
-        return e == hipSuccess ? set_lds_limit(&chunked_kernel<kMode, kC2, true>, lds_bytes) : e;
-    });
-    if (err != hipSuccess) return err;
     if (a.unit_stride > 0)
         hipLaunchKernelGGL((chunked_kernel<kMode, kC2, true>), grid, dim3(kThreads), lds_bytes, stream, a);
     else
@@ -1045,21 +1051,36 @@ hipError_t launch_mode(const Args& args, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_chunked(const Args& a, ChunkedMode mode, hipStream_t stream) {
-    const bool c2 = a.finch_c2;
+namespace {
+
+// f(mode, form) with the two as compile-time constants
+template <typename F>
+hipError_t with_mode(const Args& a, ChunkedMode mode, F f) {
+    constexpr std::true_type c2;
+    constexpr std::false_type finch;
     switch (mode) {
-        case ChunkedMode::kBf16Out: return c2 ? launch_mode<0, true>(a, stream) : launch_mode<0, false>(a, stream);
-        case ChunkedMode::kF32Out: return c2 ? launch_mode<1, true>(a, stream) : launch_mode<1, false>(a, stream);
+        case ChunkedMode::kBf16Out: return a.finch_c2 ? f(std::integral_constant<int, 0>{}, c2) : f(std::integral_constant<int, 0>{}, finch);
+        case ChunkedMode::kF32Out: return a.finch_c2 ? f(std::integral_constant<int, 1>{}, c2) : f(std::integral_constant<int, 1>{}, finch);
         case ChunkedMode::kBf16OutMoments:
-            if (!c2 || !a.moments) return hipErrorInvalidValue;
-            return launch_mode<3, true>(a, stream);
+            if (!a.finch_c2 || !a.moments) return hipErrorInvalidValue;
+            return f(std::integral_constant<int, 3>{}, c2);
         default:
             if (!a.y || !a.lambda || !a.bw) return hipErrorInvalidValue;
             if (mode == ChunkedMode::kBf16OutLora)
-                return c2 ? launch_mode<4, true>(a, stream) : launch_mode<4, false>(a, stream);
-            if (!c2 || !a.moments) return hipErrorInvalidValue;
-            return launch_mode<5, true>(a, stream);
+                return a.finch_c2 ? f(std::integral_constant<int, 4>{}, c2) : f(std::integral_constant<int, 4>{}, finch);
+            if (!a.finch_c2 || !a.moments) return hipErrorInvalidValue;
+            return f(std::integral_constant<int, 5>{}, c2);
     }
+}
+
+}  // namespace
+
+hipError_t raise_chunked_limits(const Args& a, ChunkedMode mode) {
+    return with_mode(a, mode, [](auto m, auto c2) { return raise_mode_limits<decltype(m)::value, decltype(c2)::value>(); });
+}
+
+hipError_t launch_chunked(const Args& a, ChunkedMode mode, hipStream_t stream) {
+    return with_mode(a, mode, [&](auto m, auto c2) { return launch_mode<decltype(m)::value, decltype(c2)::value>(a, stream); });
 }
 
 }  // namespace wkv6

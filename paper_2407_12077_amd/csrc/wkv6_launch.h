@@ -67,10 +67,16 @@ hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStrea
 // kBf16OutLoraMoments: that plus a.moments (Finch-C2 form).
 hipError_t launch_chunked(const Args& a, ChunkedMode mode, hipStream_t stream);
 
+// Raises the dynamic LDS limits that launch_chunked needs for this form and mode, without launching.
+hipError_t raise_chunked_limits(const Args& a, ChunkedMode mode);
+
 // The two passes in front of it when a.segs > 1: the local state and total decay of every segment but the
 // last, from a zero state (k, v and x, or y, lambda and bw when `lora`), left in a.place; then, in place, the state
 // entering every segment (from a.state_in on).
 hipError_t launch_segment_states(const Args& a, bool lora, hipStream_t stream);
+
+// Raises the dynamic LDS limits that launch_segment_states needs for any form, without launching.
+hipError_t raise_segment_limits();
 
 // GOLD key compression c = x W: x [M][D] bf16, w [D][D/16] bf16, c [M][D/16] bf16 or fp32.
 // D must be a multiple of 256 (16 output columns per MFMA block, an even number of 64-channel steps).
@@ -108,20 +114,15 @@ inline hipError_t once_per_device(F f) {
     return err;
 }
 
+// A kernel's dynamic LDS limit.  The attribute belongs to the loaded function on a device, so it is set once per
+// device and not at every launch, and it is no stream operation: a process that captures should make its first call to an
+// entry point outside the capture.  An entry point whose sizes choose between kernels sets the limits of all of
+// them on its first call, so that the size of that call does not matter.
 template <typename Kernel>
 inline hipError_t set_lds_limit(Kernel kernel, int bytes) {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-// Raises a kernel's dynamic LDS limit once per device and kernel instantiation (the attribute
-// belongs to the loaded function on a device, so it need not be set again at every launch, and must
-// not be set under stream capture: a process that captures should make its first call to an entry
-// point outside the capture).  An entry point whose sizes choose between kernels sets the limits of all of
-// them on its first call, so that the size of that call does not matter.
-template <typename Tag, typename Kernel>
-inline hipError_t set_lds_limit_once(Kernel kernel, int bytes) {
-    return once_per_device<Tag>([&] { return set_lds_limit(kernel, bytes); });
-}
 
 // Compute units of the current device (256 on an MI355X), read once per device; 256 if the
 // query fails.

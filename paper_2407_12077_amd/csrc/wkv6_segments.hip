@@ -302,9 +302,9 @@ __global__ __launch_bounds__(256) void segment_fold_kernel(Args a) {
 
 }  // namespace
 
-hipError_t launch_segment_states(const Args& a, bool lora, hipStream_t stream) {
+hipError_t raise_segment_limits() {
     struct Tag {};
-    const hipError_t err = once_per_device<Tag>([] {
+    return once_per_device<Tag>([] {
         hipError_t e = set_lds_limit(&segment_state_kernel<false, false, 0>, kSegLds);
         if (e == hipSuccess) e = set_lds_limit(&segment_state_kernel<true, false, 0>, kSegLds);
         if (e == hipSuccess) e = set_lds_limit(&segment_state_kernel<false, true, 0>, kSegLds);
@@ -315,6 +315,10 @@ hipError_t launch_segment_states(const Args& a, bool lora, hipStream_t stream) {
         if (e == hipSuccess) e = set_lds_limit(&segment_state_kernel<true, true, 2>, kSegLds);
         return e;
     });
+}
+
+hipError_t launch_segment_states(const Args& a, bool lora, hipStream_t stream) {
+    const hipError_t err = raise_segment_limits();
     if (err != hipSuccess || a.segs < 2) return err;      // (a call with one segment only raises the limits)
     const dim3 grid(static_cast<unsigned>(a.B) * static_cast<unsigned>(a.segs - 1) * static_cast<unsigned>(a.H));
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(64 * kWaves), kSegLds, stream, a); };
