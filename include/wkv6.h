@@ -271,8 +271,8 @@ int wkv6_layernorm_apply_bf16(int B, int T, int H, int N, const void *o, const f
  * rows to four (y is 128 bytes per token for all heads together).  `moments` may be NULL; if
  * not, the per-head LayerNorm partials are written as by wkv6_finch_c2_prefill_bf16_moments.
  * Everything else (kbar, uprime, layouts, state, T and B edge cases, value range, errors) is as
- * for wkv6_finch_c2_prefill_bf16; the chunked kernel, or up to 6 tokens per sequence the token-by-token
- * fp32 one, as for wkv6_finch_c2_append_bf16.
+ * for wkv6_finch_c2_prefill_bf16; the chunked kernel, or for at most 2 to 4 tokens per sequence (by the
+ * number of (batch, head) units) the token-by-token fp32 one, as for wkv6_finch_c2_append_bf16.
  */
 int wkv6_finch_c2_prefill_lora_bf16(int B, int T, int H, int N, int R,
                                     const void *r, const void *kbar, const void *v,

@@ -169,6 +169,22 @@ int wkv6_finch_c2_prefill_bf16_moments(int B, int T, int H, int N, const void* r
 
 namespace {
 
+// Fused decay path: sequences at most this long go to the token-by-token kernel.  It streams the states once, as for the
+// append entries, but a token costs it 64 more multiply-adds and a barrier, while the chunked kernel takes any of these
+// lengths in the time of one window per round of workgroups.  So the line lies the further out the more rounds that
+// would be, until the token-by-token kernel needs several rounds of waves itself (from one unit per SIMD on, sooner
+// with the registers of the Finch-C2 form).  Measured, microseconds, chunked against token by token, Finch-C2 with moments:
+// 256 units 2 tokens 6.9 : 7.0, 3 tokens 6.9 : 8.6; 512 units 3 tokens 9.7 : 9.4, 4 tokens 9.7 : 11.1; 1024 units 4 tokens
+// 15.2 : 13.5, 5 tokens 15.3 : 15.5; 2048 units 1 token 22.0 : 14.6, 2 tokens 22.1 : 18.7, 3 tokens 22.4 : 22.4; 8192 units 2
+// tokens 74.8 : 69.4, 3 tokens 74.9 : 85.6.  Finch: 256 units 2 tokens 6.4 : 6.1, 3 tokens 6.4 : 7.5; 512 units 3 tokens 9.0 : 8.1, 4
+// tokens 9.0 : 9.5; 768 units 4 tokens 12.2 : 10.5; 8192 units 4 tokens 73.7 : 68.2, 6 tokens 74.1 : 81.8.
+int fused_short_tokens(int B, int H, bool finch_c2) {
+    const long long units = static_cast<long long>(B) * H;
+    if (units <= 256) return 2;
+    if (units <= 512) return 3;
+    return units <= 1024 || !finch_c2 ? 4 : 2;
+}
+
 // Both forms of the prefill with the decay logits formed in the kernel; `uprime` non-null selects
 // the Finch-C2 form (then `u` is unused), otherwise `u` is the Finch bonus.
 int run_lora(int B, int T, int H, int N, int R, const void* r, const void* k, const void* v, const void* y,
@@ -198,13 +214,11 @@ int run_lora(int B, int T, int H, int N, int R, const void* r, const void* k, co
     a.moments = moments;
     a.y = y; a.lambda = lambda; a.bw = b_omega;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // A few tokens: as for the append entries, streaming the states once is the work.  24 sequences of one token, 32
-    // heads: 12.7 -> 7.5 us.
     const wkv6::ChunkedMode mode = moments ? wkv6::ChunkedMode::kBf16OutLoraMoments : wkv6::ChunkedMode::kBf16OutLora;
     hipError_t err;
     if (T == 0)
         err = wkv6::launch_state_passthrough(a, s);
-    else if (T <= kRecurrentMaxTokens)
+    else if (T <= fused_short_tokens(B, H, finch_c2))
         err = launch_short(a, mode, s);
     else
         err = launch_prefill(a, mode, true, s);

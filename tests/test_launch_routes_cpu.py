@@ -31,3 +31,13 @@ def test_first_call_raises_every_limit_of_its_entry(fake, make):
             assert not [e for e in ev if e.kind == "attribute"], (first, size)
             for e in ev:
                 assert e.bytes <= max(65536, limit.get(e.kernel, 0)), (first, size, e.kernel)
+
+
+@pytest.mark.parametrize("B,H,c2,longest", [(1, 4, True, 2), (8, 32, True, 2), (8, 32, False, 2), (9, 32, True, 3), (16, 32, False, 3),
+                                            (17, 32, True, 4), (32, 32, True, 4), (33, 32, True, 2), (256, 32, True, 2), (17, 32, False, 4),
+                                            (33, 32, False, 4), (256, 32, False, 4)])
+def test_fused_decay_calls_are_token_by_token_only_while_that_is_faster(fake, B, H, c2, longest):
+    """Up to 2 to 4 tokens by the number of units; 6 tokens of 32 units took twice as long token by token."""
+    make = (lambda T: lu.fused_c2(B, T, H)) if c2 else (lambda T: lu.fused_finch(B, T, H))
+    for T, kernels in zip(range(1, 9), lu.launched(fake, [make(T) for T in range(1, 9)])):
+        assert kernels == ["recurrent_kernel" if T <= longest else "chunked_kernel"], T
