@@ -14,11 +14,16 @@
 // roundings of a scaled key.  The states that the segments hand on therefore differ from those of an unsplit walk by the
 // rounding of fp32 sums alone (a few 1e-7), not by the rounding of operands, whatever the segments are.
 //
-// Bound by HBM when the segments fill the chip (7 segments of 16 384 tokens, 32 heads: 1.41 GB in 247 us, 5.7 TB/s) and by
-// the latency of a few chunks when they are short (7 segments of 512 tokens, 32 heads: 11 us).  The chunked kernel's own
-// pipeline, which made this pass before, needs five windows of 0.5 us to fill and drain: whole calls, before -> after: one
-// sequence of 131 072 tokens and 16 heads, Finch-C2, 16 segments 502 -> 484 us, 50 000 x 32 heads x 2 750 -> 722, 131 072 x 32
-// 819 -> 823.
+// Bound by HBM when the segments fill the chip (7 segments of 16 384 tokens, 32 heads: 1.41 GB) and by the latency of a few
+// chunks when they are short (7 segments of 512 tokens, 32 heads: 11 us).  The chunked kernel's own pipeline, which made this
+// pass before, needs five windows of 0.5 us to fill and drain.  Whole calls of the explicit split, microseconds, before ->
+// now, with the tensors spread over address bits 7..9 and, in brackets, equally aligned: Finch 131 072 tokens x 32 heads
+// 748 -> 701 (814 -> 817), 131 072 x 16 382 -> 356 (419 -> 413), 8192 x 24 86 -> 81 (87 -> 84); Finch-C2 131 072 x 32
+// 907 -> 858 (983 -> 952), 131 072 x 16 466 -> 426 (500 -> 478).  Equally aligned Finch inputs are where it loses: up to 1.3 %
+// at 32 heads, and more where a token's rows lie a multiple of 5 KiB apart (40 heads: 8192 tokens 97 -> 100, 131 072
+// 1082 -> 1129).  The earlier pass, brought back for comparison, has the better figure there and loses 2 to 6 % with tensors
+// that are spread out; the two add up in another order, and the bits of a result must not depend on where its tensors lie,
+// so the choice cannot follow the alignment.
 #include "wkv6_launch.h"
 #include "wkv6_math.h"
 
@@ -214,25 +219,29 @@ __global__ __launch_bounds__(64 * kWaves) void segment_state_kernel(Args a) {
             fetch_values(s, c + 1);
         }
     } else {
+        // The next chunk's keys and logits are requested in front of this one's scaling, its values behind it: all 24 loads
+        // at once reach the memory as one burst, which is worst where k, v and x start at equally aligned addresses
+        // (whole calls, Finch: one sequence of 131 072 tokens and 32 heads, spread out 707.7 -> 700.9 us, equally
+        // aligned 818.6 -> 817.3, 8192 tokens and 40 heads 102.8 -> 99.8).
         SegRegs s0, s1;
-        auto fetch = [&](SegRegs& s, int c) {
-            fetch_keys(s, c);
-            fetch_values(s, c);
-        };
-        auto digest = [&](const SegRegs& s) {
-            scale_keys(s);
-            accumulate(s);
-        };
-        fetch(s0, c_lo);
+        fetch_keys(s0, c_lo);
+        fetch_values(s0, c_lo);
         int c = c_lo;
 #pragma clang loop unroll(disable)
         for (; c + 1 < c_hi; c += 2) {
-            fetch(s1, c + 1);
-            digest(s0);
-            fetch(s0, c + 2);
-            digest(s1);
+            fetch_keys(s1, c + 1);
+            scale_keys(s0);
+            fetch_values(s1, c + 1);
+            accumulate(s0);
+            fetch_keys(s0, c + 2);
+            scale_keys(s1);
+            fetch_values(s0, c + 2);
+            accumulate(s1);
         }
-        if (c < c_hi) digest(s0);
+        if (c < c_hi) {
+            scale_keys(s0);
+            accumulate(s0);
+        }
     }
 
     // the waves' total decays (behind the barrier B is not read any more); each wave's state scaled by the later waves'
