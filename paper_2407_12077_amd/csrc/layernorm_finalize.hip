@@ -208,9 +208,14 @@ hipError_t launch_layernorm_apply(long long tokens, int D, const void* o, const 
 hipError_t launch_layernorm_finalize(int B, int T, int H, const float* moments, float eps, float* mean_rstd,
                                      hipStream_t stream) {
     // Below 16 tokens a sequence the lane-per-token form uses fewer than a quarter of its lanes and one workgroup per
-    // sequence: 24 sequences of one token 4.6 -> 3.9 us.
+    // sequence, but it reads a line of a head's pairs once where a wave per token reads it for every token again.  So
+    // the wave per token takes launches of up to 2048 tokens (one round of waves) and, with more, the lengths where the
+    // heads make the other form's chain the longer one.  Microseconds, lane per token : wave per token: 24 sequences of one
+    // token, 32 heads, 4.6 : 3.9 inside a layer's calls (4.5 : 4.6 repeated alone), 1024 x 8 tokens x 12 heads 4.5 : 6.5, x 15 4.5 :
+    // 10; 4096 x 2 x 32 8.8 : 7.1, x 4 8.8 : 11.8, x 15 8.9 : 38; 65 535 x 1 x 12 54 : 35, x 2 54 : 68; 4096 x 8 x 256 54 : 32,
+    // x 15 53 : 81.
     const long long tokens = static_cast<long long>(B) * T;
-    if (T < 16) {
+    if (T < 16 && (tokens <= 2048 || T <= 1 + H / 32)) {
         hipLaunchKernelGGL(layernorm_finalize_few_kernel, dim3(static_cast<unsigned>((tokens + 3) / 4)), dim3(256), 0, stream, tokens, T, H,
                            reinterpret_cast<const float2*>(moments), eps, reinterpret_cast<float2*>(mean_rstd));
         return hipGetLastError();
