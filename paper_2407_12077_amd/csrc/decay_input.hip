@@ -725,18 +725,20 @@ hipError_t launch_decay_input(int B, int T, int D, const void* x, const void* x_
     });
     if (err != hipSuccess) return err;
     // Which kernel: rounds of one workgroup per compute unit, times what a round takes.  A 128-token workgroup
-    // takes as long with one token as with 128 (46 us at D = 2048, 20 at 768, 88 at 4096) and serves one sequence, so
-    // it is the better one only when it fills the chip; the split tiles take rows of any sequences.  Measured at
-    // D = 2048, microseconds a round: 128 tokens 47 to 58; split 64 rows 28 to 31, 32 rows 19 to 22, 16 rows 16.6 to 18.8 (D = 768:
-    // 20 to 24; 14 to 16, 12.4, 9.2; D = 4096: 88 to 110; 50 to 64, 33 to 37, 26 to 30); the weights 16, 10, 7, 6
-    // are these, rounded.  At D = 2048: 24 sequences of one token 45.8 -> 16.6, 300 of them 90 -> 16.8, 8192 tokens 46.6 ->
-    // 22, 16384 tokens 47 -> 31; at 24000 the 64-row tiles need a second round and lose (59 against 48).
-    const long long cus = compute_units(), rows = static_cast<long long>(B) * T;
+    // takes as long with one token as with 128 and serves one sequence, so it is the better one only when it fills the
+    // chip; the split tiles take rows of any sequences, but every tile takes all weights and the launch, the two exchanges
+    // and the last reduction weigh more the narrower the model is.  Nanoseconds a round, a fixed part and one per 128
+    // channels, fitted to D = 128, 256, 768, 2048, 4096: 128 tokens 6.7, 9.5, 20.3, 46.5, 89 us; split 64 rows 6.8, 8, 14.5, 30,
+    // 56, 32 rows 7.4, 8.9, 12.9, 21.6, 39, 16 rows 7.0, 7.9, 9.0, 16.5, 25.5.  128 tokens against the split: D = 2048 24 sequences of
+    // one token 45.8 : 16.6, 300 of them 90 : 16.8, 8192 tokens 46.6 : 22, 16 384 tokens 47 : 31, 33 792 tokens 94 : 86, 24 000
+    // tokens (a second round of 64 rows) 48 : 59; D = 128 one token 6.3 : 6.9, 300 sequences of one token 12.2 : 7.2, 33 792 tokens
+    // 13.0 : 20.0; D = 256 33 792 tokens 19.3 : 23.6, 1000 sequences of 20 34.7 : 36.3; D = 768 49 152 tokens 41.0 : 42.6.
+    const long long cus = compute_units(), rows = static_cast<long long>(B) * T, blocks = D / 128;
     auto rounds = [&](long long groups) { return (groups + cus - 1) / cus; };
-    const long long whole = 16 * rounds(static_cast<long long>(B) * a.tiles_per_seq);
-    const long long r64 = T >= 64 ? 10 * rounds((rows + 63) / 64) : whole;
-    const long long r32 = T >= 32 ? 7 * rounds((rows + 31) / 32) : whole;
-    const long long r16 = 6 * rounds((rows + 15) / 16);
+    const long long whole = (4300 + 2640 * blocks) * rounds(static_cast<long long>(B) * a.tiles_per_seq);
+    const long long r64 = T >= 64 ? (5500 + 1550 * blocks) * rounds((rows + 63) / 64) : whole;
+    const long long r32 = T >= 32 ? (6500 + 1000 * blocks) * rounds((rows + 31) / 32) : whole;
+    const long long r16 = (6600 + 590 * blocks) * rounds((rows + 15) / 16);
     if (r16 < whole && r16 <= r32 && r16 <= r64) return out_f32 ? launch_split<1, 12, true>(a, stream) : launch_split<1, 12, false>(a, stream);
     if (r32 < whole && r32 <= r64) return out_f32 ? launch_split<2, 8, true>(a, stream) : launch_split<2, 8, false>(a, stream);
     if (r64 < whole) return out_f32 ? launch_split<4, 8, true>(a, stream) : launch_split<4, 8, false>(a, stream);

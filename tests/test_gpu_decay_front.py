@@ -181,3 +181,16 @@ def test_split_contraction_tiles(gpu_device, B, T, H):
         assert max_norm_err(y32, oracle_front(fi, with_prev)) <= TOL_BF16
         y16 = run_front(fi, torch.bfloat16, with_prev).float().cpu().numpy()
         assert np.array_equal(y16, round_to_bf16(y32))
+
+
+@pytest.mark.parametrize("B,T,H", [(17, 1, 4), (300, 1, 2), (600, 3, 2), (9, 17, 4), (130, 31, 4), (131, 33, 4), (4, 1100, 4), (70, 60, 4),
+                                   (256, 32, 4), (2, 4097, 4), (3, 5461, 4), (128, 127, 4), (1, 16385, 4)])
+def test_split_contraction_tiles_at_the_widths_that_take_them(gpu_device, B, T, H):
+    """The same places of a tile as above at D = 256, where 16-, 32- and 64-row tiles are taken (at D = 128 only many short
+    sequences take the split form).  Bar and rounding as above."""
+    fi = make_decay_front_inputs(scaled(CONFIGS[2], B=B, T=T, H=H), seed=1700 + T)
+    for with_prev in (True, False):
+        y32 = run_front(fi, torch.float32, with_prev).cpu().numpy()
+        assert max_norm_err(y32, oracle_front(fi, with_prev)) <= TOL_BF16
+        y16 = run_front(fi, torch.bfloat16, with_prev).float().cpu().numpy()
+        assert np.array_equal(y16, round_to_bf16(y32))

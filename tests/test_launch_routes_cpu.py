@@ -50,3 +50,19 @@ def test_fold_by_wave_per_token_only_for_few_tokens_or_many_heads(fake, B, T, H,
     """65 535 sequences of 15 tokens and 2 heads took nine times as long with a wave per token."""
     call = ("wkv6_layernorm_finalize", [B, T, H, 64, lu.at(0), 1e-5, lu.at(1), None])
     assert lu.launched(fake, [call])[0] == ["layernorm_finalize_few_kernel" if few else "layernorm_finalize_kernel"]
+
+
+@pytest.mark.parametrize("B,T,D,kernel", [
+    (1, 1, 128, "decay_input_kernel<"), (24, 1, 128, "decay_input_kernel<"), (300, 1, 128, "split_kernel<1, 12,"), (16, 1024, 128, "decay_input_kernel<"),
+    (33, 1024, 128, "decay_input_kernel<"), (1000, 20, 128, "decay_input_kernel<"), (1000, 40, 256, "decay_input_kernel<"), (33, 1024, 256, "decay_input_kernel<"),
+    (24, 1, 256, "split_kernel<1, 12,"), (300, 129, 256, "split_kernel<4, 8,"), (33, 1024, 768, "decay_input_kernel<"), (16, 1024, 768, "split_kernel<4, 8,"),
+    (24, 1, 2048, "split_kernel<1, 12,"), (8, 1000, 2048, "split_kernel<2, 8,"), (16, 1024, 2048, "split_kernel<4, 8,"), (24, 1000, 2048, "decay_input_kernel<"),
+    (33, 1024, 2048, "split_kernel<4, 8,"), (33, 1024, 4096, "split_kernel<4, 8,"), (32, 1024, 2048, "decay_input_kernel<"),
+    (130, 31, 256, "split_kernel<1, 12,"), (131, 33, 256, "split_kernel<2, 8,"), (256, 32, 256, "split_kernel<2, 8,"), (2, 4097, 256, "split_kernel<4, 8,"),
+    (3, 5461, 256, "split_kernel<4, 8,"), (1, 16385, 256, "decay_input_kernel<"), (600, 3, 128, "split_kernel<1, 12,"), (1000, 40, 2048, "split_kernel<2, 8,")])
+def test_decay_front_tiles_by_width(fake, B, T, D, kernel):
+    """What a round of each tile takes depends on the width: at D = 128, 33 x 1024 tokens in 64-row tiles took 20 us against 13."""
+    call = ("wkv6_decay_lora_input_bf16", [B, T, D, 32, 64] + [lu.at(i) for i in range(8)] + [0, None])
+    [ev] = lu.events(fake, [call])
+    [launch] = [e for e in ev if e.kind == "launch"]
+    assert kernel in launch.kernel, launch.kernel
