@@ -212,10 +212,11 @@ hipError_t launch_layernorm_finalize(int B, int T, int H, const float* moments, 
     // the wave per token takes launches of up to 2048 tokens (one round of waves) and, with more, the lengths where the
     // heads make the other form's chain the longer one.  Microseconds, lane per token : wave per token: 24 sequences of one
     // token, 32 heads, 4.6 : 3.9 inside a layer's calls (4.5 : 4.6 repeated alone), 1024 x 8 tokens x 12 heads 4.5 : 6.5, x 15 4.5 :
-    // 10; 4096 x 2 x 32 8.8 : 7.1, x 4 8.8 : 11.8, x 15 8.9 : 38; 65 535 x 1 x 12 54 : 35, x 2 54 : 68; 4096 x 8 x 256 54 : 32,
-    // x 15 53 : 81.
+    // 10; 4096 x 2 x 32 8.8 : 7.1, x 4 8.8 : 11.8, x 15 8.9 : 38; 65 535 x 1 x 12 54 : 35, x 2 54 : 68; 1024 x 4 x 64 5.8 : 5.1,
+    // x 6 5.8 : 6.6; 1024 x 8 x 128 9.9 : 8.3, x 11 9.4 : 12.6; 4096 x 8 x 256 54 : 32, x 15 53 : 81.
     const long long tokens = static_cast<long long>(B) * T;
-    if (T < 16 && (tokens <= 2048 || T <= 1 + H / 32)) {
+    const int longest = H / 16 < 8 ? H / 16 : 8;
+    if (T < 16 && (tokens <= 2048 || T == 1 || T <= longest)) {
         hipLaunchKernelGGL(layernorm_finalize_few_kernel, dim3(static_cast<unsigned>((tokens + 3) / 4)), dim3(256), 0, stream, tokens, T, H,
                            reinterpret_cast<const float2*>(moments), eps, reinterpret_cast<float2*>(mean_rstd));
         return hipGetLastError();

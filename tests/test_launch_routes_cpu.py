@@ -45,7 +45,8 @@ def test_fused_decay_calls_are_token_by_token_only_while_that_is_faster(fake, B,
 
 @pytest.mark.parametrize("B,T,H,few", [(1, 1, 1, True), (24, 1, 32, True), (136, 15, 32, True), (137, 15, 32, False), (3, 16, 12, False),
                                        (256, 8, 12, True), (257, 8, 12, False), (4096, 2, 32, True), (4096, 3, 32, False), (4096, 2, 31, False),
-                                       (65535, 1, 2, True), (65535, 2, 2, False), (4096, 9, 256, True), (4096, 10, 256, False)])
+                                       (65535, 1, 2, True), (65535, 2, 2, False), (4096, 8, 256, True), (4096, 9, 256, False), (1024, 4, 64, True), (1024, 5, 64, False),
+                                       (1024, 8, 128, True), (1024, 9, 128, False)])
 def test_fold_by_wave_per_token_only_for_few_tokens_or_many_heads(fake, B, T, H, few):
     """65 535 sequences of 15 tokens and 2 heads took nine times as long with a wave per token."""
     call = ("wkv6_layernorm_finalize", [B, T, H, 64, lu.at(0), 1e-5, lu.at(1), None])
