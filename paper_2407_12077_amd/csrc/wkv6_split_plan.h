@@ -28,11 +28,13 @@ inline SplitPlan plan_split(int T, int segments) {
 // the first rows of every segment of `out`, which the last pass overwrites, so every segment needs that many
 // tokens.  A function of the shape alone, the same for every form and output type, so that forms that agree bit for
 // bit still do.
-// The two passes in front cost about 12 us and, in the last pass, every chunk that a workgroup no longer walks saves 0.75
-// us: the split pays from about 20 chunks on.  Measured, microseconds, whole -> split (Finch, H = 32): 700 tokens 21.9 -> 22.4,
-// 1024 29.0 -> 22.7, 4096 97 -> 38, 32 768 727 -> 221; Finch-C2 with two sequences 700 tokens 27.1 -> 28.3, 1024
-// 35.7 -> 29.9, 4096 121 -> 70.  Two segments never pay: what they save the state pass takes (Finch-C2, four sequences of 4096:
-// 128 -> 124; of 2048 67 -> 68).
+// The two passes in front cost 11 to 17 us and, in the last pass, every chunk that a workgroup no longer walks saves 0.65 us
+// (Finch-C2 0.75): the split pays from about 20 chunks on, with three segments, whose state pass reads two thirds of
+// k, v and x again for the least gain, from 25 on.  Measured, microseconds, whole -> split: Finch 1 x 32 heads 700 tokens 21.9 -> 22.4,
+// 800 22.2 -> 19.3, 1100 29.6 -> 20.5, 4096 92 -> 37, 32 768 727 -> 221; 64 heads (four segments) 870 tokens 25.4 -> 23.3; 7 x 12 heads
+// (three) 1050 28.8 -> 29.0, 1100 30.1 -> 31.0, 1200 32.2 -> 31.9, 1300 34.2 -> 32.9, 4096 93 -> 70, 85 x 1 head 1100 29.7 -> 31.3, 1200
+// 31.9 -> 32.0; Finch-C2 2 x 32 heads 870 29.7 -> 25.5, 4096 113 -> 69, 7 x 12 heads 1100 34.7 -> 34.1, 1300 39.5 -> 37.2.  Two
+// segments never pay: what they save the state pass takes (Finch-C2, four sequences of 4096: 128 -> 124; of 2048 67 -> 68).
 inline SplitPlan plan_own_split(int B, int T, int H) {
     const SplitPlan whole{1, T};
     const long long units = static_cast<long long>(B) * H;
@@ -40,7 +42,7 @@ inline SplitPlan plan_own_split(int B, int T, int H) {
     if (segs > T / kSegPlaceTokens) segs = T / kSegPlaceTokens;
     for (; segs > 2; --segs) {
         const SplitPlan p = plan_split(T, static_cast<int>(segs));
-        if (p.segs < 3 || T - p.seg_len < 20 * 32) return whole;
+        if (p.segs < 3 || T - p.seg_len < 32 * (p.segs == 3 ? 25 : 20)) return whole;
         if (p.seg_len >= kSegPlaceTokens && T - static_cast<long long>(p.segs - 1) * p.seg_len >= kSegPlaceTokens)
             return p;
     }

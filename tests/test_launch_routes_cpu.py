@@ -4,6 +4,7 @@ pinned on both sides of its line."""
 import pytest
 
 import launch_util as lu
+from split_shapes import SPLIT, WHOLE
 
 
 @pytest.fixture(scope="module")
@@ -67,3 +68,24 @@ def test_decay_front_tiles_by_width(fake, B, T, D, kernel):
     [ev] = lu.events(fake, [call])
     [launch] = [e for e in ev if e.kind == "launch"]
     assert kernel in launch.kernel, launch.kernel
+
+
+# shapes of tests/test_gpu_own_split.py beside those of the list
+ALSO_SPLIT = [(1, 1100, 4), (2, 1531, 12), (2, 1201, 6), (1, 1000, 4), (1, 1300, 8)]
+
+
+@pytest.mark.parametrize("make", [lambda B, T, H: lu.time_mix("wkv6_prefill_bf16", B, T, H), lambda B, T, H: lu.time_mix("wkv6_finch_c2_append_bf16", B, T, H),
+                                  lambda B, T, H: lu.fused_c2(B, T, H), lambda B, T, H: lu.fused_finch(B, T, H)],
+                         ids=["prefill", "c2_append", "fused_c2", "fused_finch"])
+def test_own_split_where_it_is_said_to_be(fake, make):
+    """Three segments of 384 tokens (85 units of 1100) took 6 % longer than the whole walk."""
+    shapes = list(SPLIT) + ALSO_SPLIT + WHOLE
+    for (B, T, H), ev in zip(shapes, lu.events(fake, [make(*s) for s in shapes])):
+        run = [e for e in ev if e.kind == "launch"]
+        if (B, T, H) in WHOLE:
+            assert [e.base for e in run] == ["chunked_kernel"], (B, T, H)
+            continue
+        assert [e.base for e in run] == ["segment_state_kernel", "segment_fold_kernel", "chunked_kernel"], (B, T, H)
+        if (B, T, H) in SPLIT:
+            segs = SPLIT[B, T, H][0]
+            assert [e.grid[0] for e in run] == [B * (segs - 1) * H, 4 * B * H, B * segs * H], (B, T, H)

@@ -2,6 +2,8 @@
 import os
 import subprocess
 
+from split_shapes import SPLIT, WHOLE
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -9,5 +11,7 @@ def test_split_plan_covers_every_token_and_leaves_room(tmp_path):
     exe = str(tmp_path / "check_split")
     subprocess.check_call(["g++", "-std=c++17", "-O2", "-Wall", "-fsanitize=undefined", "-fno-sanitize-recover=all",
                            os.path.join(ROOT, "tests", "split_plan", "check_split.cpp"), "-o", exe])
-    out = subprocess.run([exe], capture_output=True, text=True)
+    pinned = {**SPLIT, **{(B, T, H): (1, T) for B, T, H in WHOLE}}
+    args = [str(n) for shape, plan in pinned.items() for n in (*shape, *plan)]
+    out = subprocess.run([exe, *args], capture_output=True, text=True)
     assert out.returncode == 0 and out.stdout.startswith("ok"), out.stdout + out.stderr
