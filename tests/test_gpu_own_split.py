@@ -10,12 +10,12 @@ from oracle import decay_logits_numpy, finch_c2_oracle, wkv6_oracle
 from paper_2407_12077_amd.workloads import CONFIGS, make_decay_lora_inputs, make_inputs, make_uprime, round_to_bf16, scaled
 
 from gpu_util import BF16_OUT_ROUNDING, TOL_BF16, max_norm_err, to_dev
+from split_shapes import SPLIT, WHOLE
 
 pytestmark = pytest.mark.gpu
 
-# (B, T, H): both sides of the rule (640 tokens saved, three segments), last segments of exactly and just above the 130 tokens of
-# the hand-over, ragged last chunks, one unit (most segments) and the most units that still split
-SHAPES = [(1, 831, 4), (1, 863, 4), (1, 960, 64), (1, 961, 85), (5, 1531, 12), (1, 4098, 1), (1, 2560, 16), (2, 1100, 40), (1, 3000, 3)]
+# both sides of the rule, with the plans that the CPU tests pin
+SHAPES = list(SPLIT) + WHOLE
 
 
 def inputs(B, T, H, state=True):
@@ -50,7 +50,9 @@ def test_matches_oracle_and_output_types_agree(gpu_device, B, T, H):
             assert np.array_equal(o16, round_to_bf16(o32)) and np.array_equal(s16, s32), entry
 
 
-@pytest.mark.parametrize("B,T,H", [(1, 1100, 4), (2, 1531, 12)])
+# the last three: a last segment of exactly the hand-over's tokens, and waves of the state pass with two or three (one or two)
+# chunks each, whose loop carries the state, its decay and the next chunk's loads from one chunk to the next
+@pytest.mark.parametrize("B,T,H", [(1, 1100, 4), (2, 1531, 12), (1, 898, 1), (1, 4200, 32), (2, 1300, 40)])
 def test_fused_decay_path_and_moments(gpu_device, B, T, H):
     cfg, inp = inputs(B, T, H)
     lo = make_decay_lora_inputs(cfg, 5)
@@ -153,3 +155,35 @@ def test_moments_of_a_split_prefill_are_those_of_its_output(gpu_device):
     assert (mom[..., 0].double() - o.sum(-1)).abs().max() <= 1e-5 * o.abs().sum(-1).max()
     m2 = ((o - mean) ** 2).sum(-1)
     assert ((mom[..., 1].double() - m2).abs() <= 1e-5 * m2.max()).all()
+
+
+@pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
+def test_segments_beyond_four_gib(gpu_device, out_dtype):
+    """85 heads and so many tokens that the third segment starts beyond 4 GiB in every tensor (fp32 out: beyond 8 GiB), which is
+    where the hand-over then lies: two heads against the oracle over the last segment and some tokens in front of it, and
+    the final state."""
+    H, T = 85, 620_000
+    seg_len = (T + 3 * 32 - 1) // (3 * 32) * 32
+    assert 2 * seg_len * H * 64 * 2 > 1 << 32
+    g = torch.Generator(device="cuda").manual_seed(77)
+    make = lambda scale: torch.randn((1, T, H, 64), generator=g, device="cuda", dtype=torch.bfloat16).mul_(scale)  # noqa: E731
+    r, k, v = make(0.125), make(0.125), make(0.125)
+    x = make(1.0).sub_(3.0)
+    u = torch.randn((H, 64), generator=g, device="cuda") * 0.5
+    out = torch.full((1, T, H, 64), float("nan"), dtype=out_dtype, device="cuda")
+    s_out = torch.full((1, H, 64, 64), float("nan"), device="cuda")
+    entry = wkv.wkv6_prefill_bf16 if out_dtype == torch.bfloat16 else wkv.wkv6_prefill_bf16_f32out
+    entry(1, T, H, 64, r, k, v, x, u, None, out, s_out)
+    torch.cuda.synchronize()
+    first = 2 * seg_len
+    heads = [0, H - 1]
+    # the decays forget (0.08 a token in the exponent on average): 20 000 tokens in front hold the segment's entering state
+    lead = 20_000
+    host = {n: np.ascontiguousarray(t[:, first - lead:, heads].float().cpu().numpy()) for n, t in zip("rkvx", (r, k, v, x))}
+    o_ref, s_ref = wkv6_oracle(host["r"], host["k"], host["v"], host["x"], np.ascontiguousarray(u[heads].cpu().numpy()), None)
+    bar = TOL_BF16 + (BF16_OUT_ROUNDING if out_dtype == torch.bfloat16 else 0.0)
+    assert max_norm_err(out[:, first:, heads].float().cpu().numpy(), o_ref[:, lead:]) <= bar
+    assert max_norm_err(s_out[:, heads].cpu().numpy(), s_ref) <= TOL_BF16
+    assert bool(torch.isfinite(out[:, :first:997].float()).all())
+    del r, k, v, x, out
+    torch.cuda.empty_cache()
