@@ -535,8 +535,11 @@ hipError_t launch_key_compress(long long M, int D, const void* x, const void* w,
     // = 2048, microseconds, large tiles -> this form: 19.7 -> 4.4 at 1 token, 20.9 -> 5.2 at 512, 21.0 -> 5.5 at
     // 1024, 21.0 -> 6.8 at 2048, 21.0 -> 10.6 at 4096 (256 workgroups of the largest tile); D = 1024: 11.5 -> 3.8 at 16 tokens, 12.3
     // -> 7.4 at 8192, level at 16 384.  From D = 2048 on a large tile's walk is so long that two rounds of these still win
-    // or tie: 18.2 against 19.9 at 6000 tokens, 19.7 against 20.2 at 8192; D = 4096 32.7 against 58 at 4096.  Beyond
-    // that the W traffic of the small tiles (all of W per 32 tokens) loses: D = 2048, 16 384 tokens 37 against 21.
+    // or tie: 18.5 against 19.9 at 4200 tokens, 19.5 against 20.1 at 6200 and 19.8 against 20.1 at 6700, but 20.4 against 20.1
+    // at 7200 and 21.6 against 20.2 at 8192, so up to five thirds of a round there (six to seven thousand tokens); wider models
+    // the whole second round: D = 2304 20.5 against 22.0 at 3000 tokens, 3072 24.0 against 28.2 at 4096 and 25.0 against 28.3 at 5200,
+    // 4096 33.6 against 36.4 at 4096.  Beyond that the W traffic of the small tiles (all of W per 32 tokens) loses: D = 2048,
+    // 16 384 tokens 37 against 21.
     const int cus = compute_units();
     auto groups = [&](int tb, int nb) {
         return (M + 16 * tb - 1) / (16 * tb) * ((a.C + 16 * nb - 1) / (16 * nb));
@@ -544,7 +547,7 @@ hipError_t launch_key_compress(long long M, int D, const void* x, const void* w,
     if (groups(1, 1) <= cus) return out_f32 ? launch_few<1, 1, true>(a, stream) : launch_few<1, 1, false>(a, stream);
     if (groups(1, 2) <= cus) return out_f32 ? launch_few<1, 2, true>(a, stream) : launch_few<1, 2, false>(a, stream);
     if (groups(1, 4) <= cus) return out_f32 ? launch_few<1, 4, true>(a, stream) : launch_few<1, 4, false>(a, stream);
-    if (groups(2, 4) <= (a.C >= 128 ? 2 : 1) * cus)
+    if (3 * groups(2, 4) <= (a.C > 128 ? 6 : a.C == 128 ? 5 : 3) * cus)
         return out_f32 ? launch_few<2, 4, true>(a, stream) : launch_few<2, 4, false>(a, stream);
     // At most one large tile per compute unit: 128 columns a tile, also above D = 2048 (x then comes from L2 the second
     // time), and eight MFMA waves instead of four, since no second workgroup is there to overlap with.  Microseconds, before -> here:

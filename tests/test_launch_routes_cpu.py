@@ -99,3 +99,14 @@ def test_columns_of_few_units_over_workgroups(fake, entry, bf16, units, T, colum
     [ev] = lu.events(fake, [lu.time_mix(entry, 1, T, units)])
     want = "recurrent_columns_kernel<%d, %s>" % (columns, str(bf16).lower()) if columns else "recurrent_wide_kernel<%s, false>" % str(bf16).lower()
     assert [e.kernel for e in ev] == [want]
+
+
+@pytest.mark.parametrize("M,D,kernel", [
+    (16, 2048, "few_kernel<1, 1,"), (4096, 2048, "few_kernel<2, 4,"), (4097, 2048, "few_kernel<2, 4,"), (6816, 2048, "few_kernel<2, 4,"), (6817, 2048, "key_compress_kernel<128, 2,"),
+    (8192, 2048, "key_compress_kernel<128, 2,"), (4096, 1792, "few_kernel<2, 4,"), (4097, 1792, "key_compress_kernel<128, 2,"), (5440, 2304, "few_kernel<2, 4,"), (5461, 2304, "key_compress_kernel<128, 2,"),
+    (4096, 4096, "few_kernel<2, 4,"), (4097, 4096, "key_compress_kernel<128, 2,"), (16384, 4096, "key_compress_kernel<128, 2,"), (16385, 4096, "key_compress_kernel<256, 4,"), (32769, 2048, "key_compress_kernel<128, 4,")])
+def test_key_compression_tiles(fake, M, D, kernel):
+    """At D = 2048 the second round of small tiles pays up to five thirds of a round (8192 tokens: 21.6 us against 20.2)."""
+    call = ("wkv6_key_compress_bf16", [M, D, lu.at(0), lu.at(1), lu.at(2), 0, None])
+    [launch] = [e for e in lu.events(fake, [call])[0] if e.kind == "launch"]
+    assert kernel in launch.kernel, launch.kernel
