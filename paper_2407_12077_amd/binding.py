@@ -145,13 +145,13 @@ def wkv6_prefill_bf16_f32out(B, T, H, N, r, k, v, x, u, state_in, out, state_out
 def wkv6_prefill_bf16_strided(B, T, H, N, r, k, v, x, u, state_in, out, state_out,
                               batch_stride, out_dtype, stream=None):
     _call("wkv6_prefill_bf16_strided", B, T, H, N, r, k, v, x, u, state_in, out, state_out,
-          stream, int(batch_stride), int(out_dtype))
+          stream, ctypes.c_longlong(batch_stride), int(out_dtype))
 
 
 def wkv6_prefill_bf16_split(B, T, H, N, r, k, v, x, u, state_in, out, state_out, out_dtype,
                             segments, workspace, workspace_bytes, stream=None):
     _call("wkv6_prefill_bf16_split", B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream,
-          int(out_dtype), int(segments), _ptr(workspace), int(workspace_bytes))
+          int(out_dtype), int(segments), _ptr(workspace), ctypes.c_longlong(workspace_bytes))
 
 
 def wkv6_prefill_bf16_split_noalloc(B, T, H, N, r, k, v, x, u, state_in, out, state_out, out_dtype,
@@ -163,7 +163,7 @@ def wkv6_prefill_bf16_split_noalloc(B, T, H, N, r, k, v, x, u, state_in, out, st
 def wkv6_finch_c2_prefill_bf16_split(B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out,
                                      out_dtype, segments, workspace, workspace_bytes, stream=None):
     _call("wkv6_finch_c2_prefill_bf16_split", B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out,
-          stream, int(out_dtype), int(segments), _ptr(workspace), int(workspace_bytes))
+          stream, int(out_dtype), int(segments), _ptr(workspace), ctypes.c_longlong(workspace_bytes))
 
 
 def wkv6_split_workspace_bytes(B, T, H, N, segments):
@@ -204,7 +204,7 @@ def wkv6_finch_c2_prefill_bf16_f32out(B, T, H, N, r, kbar, v, x, uprime, state_i
 def wkv6_finch_c2_prefill_bf16_strided(B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out,
                                        batch_stride, out_dtype, stream=None):
     _call("wkv6_finch_c2_prefill_bf16_strided", B, T, H, N, r, kbar, v, x, uprime, state_in, out,
-          state_out, stream, int(batch_stride), int(out_dtype))
+          state_out, stream, ctypes.c_longlong(batch_stride), int(out_dtype))
 
 
 def wkv6_finch_c2_prefill_bf16_moments(B, T, H, N, r, kbar, v, x, uprime, state_in, out, moments, state_out,
