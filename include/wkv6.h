@@ -85,10 +85,12 @@ typedef enum {
 
 /*
  * bf16 r,k,v,x; fp32 u and state; bf16 out.  Chunked matrix-core kernel.  Shapes with so few (batch, head)
- * units that they would leave most compute units idle, and enough tokens (this and every other prefill and append
- * entry point but the explicit split ones), are cut along the tokens as described at wkv6_prefill_bf16_split, by a rule
- * on the shape alone; the passes hand their states over in `out` itself, in rows that the last pass overwrites, so
- * nothing but `out` and state_out is written, and `out` holds no partial result after the call's last kernel.
+ * units that they would leave most compute units idle (at most 85), and enough tokens (from about 800 on), are cut
+ * along the tokens as described at wkv6_prefill_bf16_split, by a rule on the shape alone; the passes hand their states
+ * over in `out` itself, in rows that the last pass overwrites, so nothing but `out` and state_out is written, and `out`
+ * holds no partial result after the call's last kernel.  So are all entry points that run the chunked kernel, but for the
+ * explicit split ones; wkv6_prefill_f32, wkv6_prefill_bf16_recurrent and the short calls that the token-by-token kernel
+ * takes are not.
  */
 int wkv6_prefill_bf16(int B, int T, int H, int N,
                       const void *r, const void *k, const void *v, const void *x,
@@ -217,8 +219,8 @@ int wkv6_finch_c2_prefill_bf16_split(int B, int T, int H, int N,
  * token the normalisation becomes a row scaling and a rank-one correction in the epilogue of
  * the projection GEMM, LayerNorm(o_t) W = rstd_t (o_t (diag(gamma) W)) - rstd_t mean_t
  * (gamma W) + beta W, and no separate pass over `out` is needed.
- * Everything else is as for wkv6_finch_c2_prefill_bf16 (always the chunked kernel; `moments` must
- * not be NULL when T > 0; T == 0 writes nothing to it).
+ * Everything else is as for wkv6_finch_c2_prefill_bf16 (the chunked kernel at every length, behind the segment
+ * passes where the shape is cut; `moments` must not be NULL when T > 0; T == 0 writes nothing to it).
  */
 int wkv6_finch_c2_prefill_bf16_moments(int B, int T, int H, int N,
                                        const void *r, const void *kbar, const void *v, const void *x,

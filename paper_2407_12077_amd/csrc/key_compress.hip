@@ -302,7 +302,7 @@ __global__ __launch_bounds__((Tile<kBN, kWNB>::kThreads), (Tile<kBN, kWNB>::kPer
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Block -> tile map.  With more than one column tile (D > 4096) the column tiles of one row tile
+    // Block -> tile map.  With more than one column tile (D > 16 kBN: 2048 or 4096) the column tiles of one row tile
     // must meet in the same L2 so that x comes from HBM once: consecutive block ids go round the
     // 8 XCDs, so the id is read as (slot, xcd) and the column tiles of a row tile take consecutive
     // slots of one XCD.

@@ -338,7 +338,8 @@ __device__ __forceinline__ void fold_pairs(float (&v)[64], bool high) {
         v[i] = keep + dpp_lanes<kCtrl>(give);
     }
 }
-// v[0 .. 63] of 64 lanes -> in v[0] of lane l, the sum over all lanes of v[slot(l)], slot as scatter_slot below
+// v[0 .. 63] of 64 lanes -> in v[0] of lane l, the sum over all lanes of v[l] (every step keeps, of a pair 2^n apart, the one
+// that bit n of the lane's number selects)
 __device__ __forceinline__ float reduce_scatter(float (&v)[64], int lane) {
 #pragma unroll
     for (int i = 0; i < 32; ++i) {                 // halves: lanes 0..31 take v[i], 32..63 v[i + 32]
@@ -355,9 +356,6 @@ __device__ __forceinline__ float reduce_scatter(float (&v)[64], int lane) {
     fold_pairs<2, 0x1B>(v, lane & 2);              // quad_perm [3,2,1,0]
     fold_pairs<1, 0xB1>(v, lane & 1);              // quad_perm [1,0,3,2]
     return v[0];
-}
-__device__ __forceinline__ int scatter_slot(int lane) {
-    return (lane & 32) + (lane & 16) + (lane & 8) + (lane & 4) + (lane & 2) + (lane & 1);
 }
 
 // 4 to 32 bytes of a row: what a thread loads at once
@@ -458,7 +456,7 @@ __global__ __launch_bounds__(256) void recurrent_columns_kernel(Args a) {
         stage(0, 0);
         fetch(kTokens);
     }
-    const int slot = scatter_slot(lane), ot = slot / kCols, oc = slot % kCols;   // the value this lane ends up with
+    const int ot = lane / kCols, oc = lane % kCols;              // token and column of the value this lane ends up with
     int parity = 0;
     for (int t0 = 0; t0 < a.T; t0 += kTokens, parity ^= 1) {
         __syncthreads();                           // this block is staged; the other slot has been read
