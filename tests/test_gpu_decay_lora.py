@@ -229,9 +229,10 @@ def test_finch_form_validation(gpu_device):
         wkv.wkv6_prefill_lora_bf16(B, T, H, N, 128, z, z, z, y, lam, bo, lam, None, out, None)
 
 
-@pytest.mark.parametrize("B,T,H", [(24, 1, 32), (3, 2, 4), (1, 5, 3), (2, 6, 12), (2, 7, 12), (700, 1, 2)])
+@pytest.mark.parametrize("B,T,H", [(24, 1, 32), (3, 2, 4), (3, 3, 4), (1, 5, 3), (2, 6, 12), (2, 7, 12), (700, 1, 2), (9, 3, 32), (9, 4, 32),
+                                   (24, 4, 32), (24, 5, 32), (35, 2, 32), (35, 3, 32), (35, 5, 32)])
 def test_few_tokens_on_both_sides_of_the_kernel_switch(gpu_device, B, T, H):
-    """Up to six tokens the token-by-token kernel forms the logits, above that the chunked one: both forms, with and
+    """Up to two to four tokens, by units and form, the token-by-token kernel forms the logits, above that the chunked one: both forms, with and
     without the LayerNorm partials, against the oracles at the same bars."""
     inp = inputs(scaled(CONFIGS[4], B=B, T=T, H=H))
     check(inp)

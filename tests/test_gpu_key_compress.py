@@ -101,10 +101,10 @@ def test_input_beyond_four_gib(gpu_device):
 
 @pytest.mark.parametrize("M,D", [(1, 256), (15, 256), (17, 768), (16, 4096), (512, 2048), (513, 2048), (1023, 2048), (1024, 2048),
                                  (1025, 2048), (2048, 2048), (2049, 2048), (4096, 2048), (4097, 2048), (2047, 768),
-                                 (4095, 768), (8191, 768), (8193, 768), (8193, 2048), (4096, 4096), (4097, 4096), (40, 8192)])
+                                 (4095, 768), (8191, 768), (8193, 768), (8193, 2048), (4096, 4096), (4097, 4096), (40, 8192), (6816, 2048), (6817, 2048), (5440, 2304)])
 def test_every_tile_of_the_split_contraction(gpu_device, M, D):
-    """Both sides of every change of tile (256 workgroups of 16 x 16, 16 x 32, 16 x 64 and 32 x 64, twice that from
-    D = 2048 on), ragged token and column tails and one to sixteen of a workgroup's waves with work.  fp32 sums of bf16 products
+    """Both sides of every change of tile (256 workgroups of 16 x 16, 16 x 32, 16 x 64 and 32 x 64, five thirds of
+    that at D = 2048 and twice that above), ragged token and column tails and one to sixteen of a workgroup's waves with work.  fp32 sums of bf16 products
     that are exact in fp32: 1e-5 of the largest value, as for the large tiles; a bf16 result is the fp32 result
     rounded once."""
     x, w = make_key_compress_inputs(M, D, seed=900 + M)

@@ -247,9 +247,10 @@ def test_layernorm_apply_validation(gpu_device):
         assert e.value.status == status
 
 
-@pytest.mark.parametrize("B,T,H", [(1, 1, 1), (24, 1, 32), (3, 15, 12), (3, 16, 12), (5, 7, 64), (2, 3, 65), (1, 2, 200)])
+@pytest.mark.parametrize("B,T,H", [(1, 1, 1), (24, 1, 32), (3, 15, 12), (3, 16, 12), (5, 7, 64), (2, 3, 65), (1, 2, 200),
+                                   (2049, 1, 3), (700, 3, 12), (1025, 2, 32), (1025, 2, 31), (513, 4, 64), (411, 5, 64)])
 def test_fold_of_short_sequences(gpu_device, B, T, H):
-    """The wave-per-token fold (below 16 tokens a sequence) and the lane-per-token fold, head counts below, at and above
+    """The wave-per-token fold (below 16 tokens a sequence, few tokens or many heads) and the lane-per-token fold, head counts below, at and above
     the 64 lanes, against float64 on the same pairs.  fp32 folds of at most 200 pairs: 1e-5 for the mean, of the standard
     deviation, and 3e-5 for its reciprocal, the bars of the fold elsewhere."""
     rng = np.random.default_rng(B * 1000 + T * 10 + H)

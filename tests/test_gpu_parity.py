@@ -534,7 +534,7 @@ def test_split_result_does_not_depend_on_placement(gpu_device):
 
 
 @pytest.mark.parametrize("B,T,H", [(1, 16, 1), (1, 31, 4), (2, 32, 16), (1, 33, 32), (1, 65, 33), (4, 47, 32), (3, 16, 43), (1, 70, 256), (2, 40, 128),
-                                   (1, 41, 257)])
+                                   (1, 41, 257), (1, 17, 128), (1, 17, 129), (1, 20, 129)])
 @pytest.mark.parametrize("entry,tol,dt", [("wkv6_prefill_f32", TOL_F32, torch.float32),
                                           ("wkv6_prefill_bf16_recurrent", TOL_F32, torch.bfloat16)])
 def test_columns_of_a_unit_over_several_workgroups(gpu_device, entry, tol, dt, B, T, H):
