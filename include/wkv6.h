@@ -159,7 +159,16 @@ int wkv6_prefill_bf16_split_noalloc(int B, int T, int H, int N,
 /* Bytes of workspace wkv6_prefill_bf16_split needs for this shape (-1 for invalid arguments). */
 long long wkv6_split_workspace_bytes(int B, int T, int H, int N, int segments);
 
-/* Segment count this library would pick for the shape on a 256-CU MI355X (1 = do not split). */
+/*
+ * Segment count recommended for the explicit split entry points on a 256-CU MI355X (1 = do not split): as many
+ * segments of at least 2048 tokens as fill the compute units once, for at most 192 (batch, head) units.  It is not the
+ * plan by which the entry points without a workspace cut a shape by themselves (see wkv6_prefill_bf16): those take
+ * shorter segments, from about 800 tokens on, and at most 85 units.  So with at most 85 units call wkv6_prefill_bf16 or
+ * wkv6_finch_c2_prefill_bf16: they need no workspace and are as fast where segments are long (131 072 tokens, 32 heads:
+ * 0.82 ms either way) and faster below (1024 tokens, 1 recommended segment: 20 against 27 us; 4096, 2 segments: 36 against
+ * 76; 8192, 4 segments: 58 against 83).  With 86 to 192 units only the explicit entries split (20 000 tokens, 100 heads: 364
+ * against 432 us).
+ */
 int wkv6_split_segments(int B, int T, int H, int N);
 
 /*

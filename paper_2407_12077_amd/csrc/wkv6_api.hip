@@ -380,6 +380,7 @@ int wkv6_version(void) { return 500; }
 
 extern "C" {
 
+// The recommendation for the explicit split entries; the entry points that split by themselves follow plan_own_split.
 int wkv6_split_segments(int B, int T, int H, int N) {
     if (N != wkv6::kHeadSize || B < 1 || T < 1 || H < 1) return 1;
     const long long units = static_cast<long long>(B) * H;
