@@ -924,13 +924,13 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
                     o[tq] = mfma(sh[kk], rt, o[tq]);
                 }
             }
-            // The scheduler must not mix the two halves: with the reads and products of the state update pulled up
-            // between those of the read-out, the Finch form's window is 2 to 3 % longer (a unit of 10 218 tokens, 144 of
-            // them: 234.9 -> 227.7 us; the last pass of a token split with spread-out tensors 10 %: one sequence of
-            // 131 072 tokens and 32 heads, 796 -> 719 us).
-            __builtin_amdgcn_sched_barrier(0);
             // state update: S = diag(W(32,-1)) S + (k W(32,i))^T V over the chunk's 32 tokens
             vt = lds_read_h8(lds, kVT + tile_t_off(16 * cw + l16, g4));
+            // The scheduler must not mix the two halves: with the reads and products of the state update pulled up between
+            // those of the read-out, the Finch form's window is 2 to 3 % longer (12 sequences of 10 218 tokens and 12 heads:
+            // 234.9 -> 226.9 us; the last pass of a token split with spread-out tensors 10 %: one sequence of 131 072 tokens and 32
+            // heads, 796 -> 719 us).  In front of the read of vt 0.3 % slower than behind it.
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int nb = 0; nb < 4; ++nb) {
                 const float4 d = *reinterpret_cast<const float4*>(lds + kD + (16 * nb + 4 * g4) * 4);
