@@ -100,14 +100,24 @@ hipError_t launch_decay_input(int B, int T, int D, const void* x, const void* x_
                               const float* lambda_d, const void* a_d, const void* b_d, const void* a_omega, void* y,
                               bool out_f32, hipStream_t stream);
 
+// The current device as an index below 64.  With one visible device there is nothing to ask (a short append of one user, where the
+// host bounds the call, checks two flags: 5.12 -> 5.00 us).
+inline int device_index() {
+    static const bool one = [] {
+        int n = 0;
+        return hipGetDeviceCount(&n) == hipSuccess && n == 1;
+    }();
+    int dev = 0;
+    if (!one && (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)) dev = 0;
+    return dev;
+}
+
 // Runs `f` (returning hipError_t) once per device; a call that fails is tried again by the next one.
 // `Tag` makes one flag set per use.
 template <typename Tag, typename F>
 inline hipError_t once_per_device(F f) {
     static std::atomic<unsigned long long> done{0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-    const unsigned long long bit = 1ull << dev;
+    const unsigned long long bit = 1ull << device_index();
     if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
     const hipError_t err = f();
     if (err == hipSuccess) done.fetch_or(bit, std::memory_order_release);
@@ -128,8 +138,7 @@ inline hipError_t set_lds_limit(Kernel kernel, int bytes) {
 // query fails.
 inline int compute_units() {
     static std::atomic<int> cached[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
+    const int dev = device_index();
     int n = cached[dev].load(std::memory_order_relaxed);
     if (n <= 0) {
         if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;

@@ -69,6 +69,10 @@ int hipGetDevice(int* device) {
     *device = 0;
     return 0;
 }
+int hipGetDeviceCount(int* count) {
+    *count = 1;
+    return 0;
+}
 int hipDeviceGetAttribute(int* value, int, int) {      // the library asks for the number of compute units only
     *value = 256;
     return 0;
