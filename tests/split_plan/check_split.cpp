@@ -36,7 +36,7 @@ int main(int argc, char** argv) {
                 if (p.segs < 3 || units * p.segs > 256) return fail("too few or too many workgroups", B, T, H, p);
                 if (p.seg_len % 32 != 0 || last < 1 || last > p.seg_len) return fail("tokens left out or twice", B, T, H, p);
                 if (p.seg_len < wkv6::kSegPlaceTokens || last < wkv6::kSegPlaceTokens) return fail("no room for the hand-over", B, T, H, p);
-                if (T - p.seg_len < (p.segs == 3 ? 800 : 640)) return fail("too little saved", B, T, H, p);
+                if (T - p.seg_len < (units > 80 ? 800 : 640)) return fail("too little saved", B, T, H, p);
             }
     for (int T = 1; T < 3000; ++T)
         for (int segments = 1; segments < 70; ++segments) {

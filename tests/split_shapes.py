@@ -14,6 +14,8 @@ SPLIT = {
     (1, 3000, 3): (12, 256),
     (1, 4200, 32): (8, 544),        # 17 chunks a segment: two or three for each wave of the state pass
     (2, 1300, 40): (3, 448),        # 14 chunks: one or two
+    (2, 1100, 40): (3, 384),        # three segments of 80 units
+    (5, 1050, 16): (3, 352),
 }
-# left whole: too little saved (four segments of 224 tokens; three of 384), or one unit too many for a third segment
-WHOLE = [(1, 831, 4), (1, 863, 4), (1, 1215, 85), (1, 961, 85), (2, 1100, 40), (1, 4096, 86)]
+# left whole: too little saved (four segments of 224 tokens; three, with more than 80 units), or one unit too many for a third segment
+WHOLE = [(1, 831, 4), (1, 863, 4), (1, 1215, 85), (1, 961, 85), (7, 1100, 12), (1, 4096, 86)]
