@@ -928,8 +928,8 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
             vt = lds_read_h8(lds, kVT + tile_t_off(16 * cw + l16, g4));
             // The scheduler must not mix the two halves: with the reads and products of the state update pulled up between
             // those of the read-out, the Finch form's window is 2 to 3 % longer (12 sequences of 10 218 tokens and 12 heads:
-            // 234.9 -> 226.9 us; the last pass of a token split with spread-out tensors 10 %: one sequence of 131 072 tokens and 32
-            // heads, 796 -> 719 us).  In front of the read of vt 0.3 % slower than behind it.
+            // 234.9 -> 226.9 us; one sequence of 4096 tokens and 32 heads, split, 36.0 -> 35.0).  In front of the read of vt
+            // 0.3 % slower than behind it.
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int nb = 0; nb < 4; ++nb) {
