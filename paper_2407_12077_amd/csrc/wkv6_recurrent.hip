@@ -516,8 +516,8 @@ hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStrea
         // -> 22, 31, 45; 32 x 512 154 -> 44, 60, 90; 96 x 300 100 -> 75, 46, 56; 256 x 300 101 -> 151, 82, 74; 512 x 1024 382
         // -> 855, 492, 426: from there the four-wave form, whose waves hold all rows of a column, issues fewer instructions.
         // Short sequences, four waves -> here: 32 units x 16 tokens 6.7 -> 5.6, 128 x 17 8.5 -> 7.5; eight columns (blocks of 8
-        // tokens) 256 units x 16 7.8 -> 7.2, x 17 9.0 -> 9.4, x 18 9.2 -> 9.4, x 20 9.7 -> 9.5, x 33 13.9 -> 13.7, 192 x 17 8.8 -> 9.0,
-        // x 18 9.0 -> 9.0: a third block for one or two tokens is what loses.
+        // tokens) 256 units x 16 7.8 -> 7.2, x 17 9.0 -> 9.4, x 18 9.2 -> 9.4, x 20 9.7 -> 9.5 to 10.0, x 22 10.1 -> 9.7, x 33 13.9 -> 13.7,
+        // 192 x 17 8.8 -> 9.0, x 18 9.0 -> 9.0: a third block for a few tokens is what loses.
         const long long units = grid.x;
         auto columns = [&](auto bf16) {
             constexpr bool kIn = decltype(bf16)::value;
@@ -529,7 +529,7 @@ hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStrea
                 hipLaunchKernelGGL((recurrent_columns_kernel<8, kIn>), dim3(grid.x * 2), dim3(256), 0, stream, a);
             return hipGetLastError();
         };
-        const bool third_block = a.T > kWideMinTokens && a.T < kWideMinTokens + 4;
+        const bool third_block = a.T > kWideMinTokens && a.T <= kWideMinTokens + 4;
         if (units <= 128 || (units <= 256 && !third_block)) return in_bf16 ? columns(std::true_type{}) : columns(std::false_type{});
     }
     if (a.T >= kWideMinTokens && !c2) {

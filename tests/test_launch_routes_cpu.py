@@ -91,11 +91,11 @@ def test_own_split_where_it_is_said_to_be(fake, make):
             assert [e.grid[0] for e in run] == [B * (segs - 1) * H, 4 * B * H, B * segs * H], (B, T, H)
 
 
-@pytest.mark.parametrize("units,T,columns", [(32, 16, 2), (33, 17, 4), (128, 17, 4), (129, 16, 8), (129, 17, 0), (256, 18, 0), (256, 19, 0),
-                                             (256, 20, 8), (256, 1000, 8), (257, 16, 0)])
+@pytest.mark.parametrize("units,T,columns", [(32, 16, 2), (33, 17, 4), (128, 17, 4), (129, 16, 8), (129, 17, 0), (256, 18, 0), (256, 20, 0),
+                                             (256, 21, 8), (256, 1000, 8), (257, 16, 0)])
 @pytest.mark.parametrize("entry,bf16", [("wkv6_prefill_f32", False), ("wkv6_prefill_bf16_recurrent", True)])
 def test_columns_of_few_units_over_workgroups(fake, entry, bf16, units, T, columns):
-    """From 129 units on, 17 and 18 tokens are faster by the four-wave form (0: 256 units x 17 tokens 9.0 against 9.4 us)."""
+    """From 129 units on, 17 to 20 tokens are faster or level by the four-wave form (0: 256 units x 17 tokens 9.0 against 9.4 us)."""
     [ev] = lu.events(fake, [lu.time_mix(entry, 1, T, units)])
     want = "recurrent_columns_kernel<%d, %s>" % (columns, str(bf16).lower()) if columns else "recurrent_wide_kernel<%s, false>" % str(bf16).lower()
     assert [e.kernel for e in ev] == [want]
