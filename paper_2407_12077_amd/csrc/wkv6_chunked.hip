@@ -924,13 +924,14 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
                     o[tq] = mfma(sh[kk], rt, o[tq]);
                 }
             }
+            // The scheduler must not mix the two halves: with the LDS reads and products of the state update pulled up
+            // between those of the read-out, the Finch form's window is 2 to 3 % longer (12 sequences of 10 218 tokens and 12
+            // heads: 234.5 -> 226.3 us; one sequence of 4096 tokens and 32 heads, split, 36.0 -> 35.0).  Vector and scalar ALU
+            // instructions may cross (mask 6: 100 sequences of 60 tokens and 64 heads, fp32 out, 81.9 -> 79.9 against a full
+            // barrier), but for fp32 rows with one unit per workgroup (28.9 -> 28.5 us at 5 x 961 tokens x 16 heads with a full one).
+            __builtin_amdgcn_sched_barrier(kOutF32 && !kMulti ? 0 : 6);
             // state update: S = diag(W(32,-1)) S + (k W(32,i))^T V over the chunk's 32 tokens
             vt = lds_read_h8(lds, kVT + tile_t_off(16 * cw + l16, g4));
-            // The scheduler must not mix the two halves: with the reads and products of the state update pulled up between
-            // those of the read-out, the Finch form's window is 2 to 3 % longer (12 sequences of 10 218 tokens and 12 heads:
-            // 234.9 -> 226.9 us; one sequence of 4096 tokens and 32 heads, split, 36.0 -> 35.0).  In front of the read of vt
-            // 0.3 % slower than behind it.
-            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int nb = 0; nb < 4; ++nb) {
                 const float4 d = *reinterpret_cast<const float4*>(lds + kD + (16 * nb + 4 * g4) * 4);
