@@ -387,7 +387,8 @@ int wkv6_finch_c2_append_bf16(int B, int T, int H, int N,
 int wkv6_key_compress_bf16(long long M, int D, const void *x, const void *w_kd, void *c,
                            int out_dtype, void *stream);
 
-/* All-fp32 tensors.  Token-by-token kernel with the state in fp32 registers. */
+/* All-fp32 tensors, fp32 arithmetic throughout: token by token, and from 24 to 97 tokens on (by the number of (batch, head)
+ * units) in chunks of 16 on the fp32 matrix cores. */
 int wkv6_prefill_f32(int B, int T, int H, int N,
                      const float *r, const float *k, const float *v, const float *x,
                      const float *u, const float *state_in,

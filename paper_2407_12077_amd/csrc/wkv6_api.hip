@@ -11,7 +11,7 @@ namespace {
 
 inline bool misaligned(const void* p) { return (reinterpret_cast<std::uintptr_t>(p) & 15u) != 0; }
 
-enum class Path { kChunked, kRecurrent, kBySize };
+enum class Path { kChunked, kRecurrent, kBySize, kF32 };
 
 // Sequences at most this long go to the token-by-token kernel when the caller leaves the
 // choice to the library (append / decode shapes): with thousands of (batch, head) units and
@@ -19,6 +19,17 @@ enum class Path { kChunked, kRecurrent, kBySize };
 // 8192 units: about 8 tokens (the chunked kernel runs the units of a workgroup back to back, one
 // window each at these lengths).
 constexpr int kRecurrentMaxTokens = 6;
+
+// fp32 tensors: sequences of at least this many tokens go to the chunked kernel.  It takes whole chunks of 16 tokens and a round to
+// fill, the token-by-token kernels blocks of 8 to 32, so the line follows the form that those take at this number of units.  Measured,
+// microseconds, token by token : chunked: 4 units 64 tokens 7.6 : 7.6, 96 9.9 : 10.2, 112 12.2 : 10.5; 16 units 96 10.6 : 10.4; 32 units 32
+// tokens 5.8 : 7.3, 40 8.6 : 7.6; 64 units 32 6.5 : 7.4, 40 8.4 : 7.7; 96 units 24 7.8 : 8.1, 32 8.4 : 8.2; 128 units 24 8.8 : 8.2;
+// 256 units 24 10.2 : 9.0; 320 units (two rounds of workgroups) 40 18.3 : 18.5, 48 21.1 : 18.8; 512 units 40 19.5 : 19.3, 48 22.3 : 19.9.
+int f32_chunked_tokens(long long units) {
+    if (units <= 24) return 97;
+    if (units <= 96) return 33;
+    return units <= 256 ? 24 : 48;
+}
 
 // Fills in the segments of `p` with their hand-over in the segments' own rows of out.
 void split_into_out(wkv6::Args& a, const wkv6::SplitPlan& p, bool out_f32) {
@@ -51,6 +62,14 @@ hipError_t launch_short(const wkv6::Args& a, wkv6::ChunkedMode mode, hipStream_t
     hipError_t err = wkv6::raise_segment_limits();
     if (err == hipSuccess) err = wkv6::raise_chunked_limits(a, mode);
     return err == hipSuccess ? wkv6::launch_recurrent(a, true, true, s) : err;
+}
+
+// All-fp32 tensors; the limits as in launch_short.
+hipError_t launch_f32(const wkv6::Args& a, hipStream_t s) {
+    const hipError_t err = wkv6::raise_chunked_f32_limits();
+    if (err != hipSuccess) return err;
+    const long long units = static_cast<long long>(a.B) * a.H;
+    return a.T >= f32_chunked_tokens(units) ? wkv6::launch_chunked_f32(a, s) : wkv6::launch_recurrent(a, false, false, s);
 }
 
 // `uprime` selects the form: nullptr = Finch (bonus u), otherwise Finch-C2 (u unused, may be null).
@@ -94,6 +113,8 @@ int run(int B, int T, int H, int N, const void* r, const void* k, const void* v,
     hipError_t err;
     if (T == 0)
         err = wkv6::launch_state_passthrough(a, s);
+    else if (path == Path::kF32)
+        err = launch_f32(a, s);
     else if (path == Path::kRecurrent)
         err = wkv6::launch_recurrent(a, in_bf16, in_bf16 && !out_f32, s);
     else if (path == Path::kBySize && T <= kRecurrentMaxTokens)          // bf16 in and out
@@ -304,7 +325,7 @@ int wkv6_prefill_f32(int B, int T, int H, int N, const float* r, const float* k,
                      const float* x, const float* u, const float* state_in, float* out,
                      float* state_out, void* stream) {
     return run(B, T, H, N, r, k, v, x, u, state_in, out, state_out,
-               static_cast<long long>(T) * H * N, false, true, Path::kRecurrent, stream);
+               static_cast<long long>(T) * H * N, false, true, Path::kF32, stream);
 }
 
 int wkv6_prefill_bf16_recurrent(int B, int T, int H, int N, const void* r, const void* k,

@@ -61,6 +61,12 @@ constexpr int kLoraRank = 64;   // R: the only rank of the decay path the fused 
 // from a.y, a.lambda, a.bw (bf16 in and out) and a.moments, if set, is written (Finch-C2 form).
 hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStream_t stream);
 
+// Chunked kernel of fp32 tensors (Finch form, fp32 throughout).
+hipError_t launch_chunked_f32(const Args& a, hipStream_t stream);
+
+// Raises the dynamic LDS limits that launch_chunked_f32 needs, without launching.
+hipError_t raise_chunked_f32_limits();
+
 // Chunked matrix-core kernel; inputs bf16, out bf16 or fp32.  kBf16OutMoments: bf16 out
 // plus a.moments, Finch-C2 form only.  kBf16OutLora: bf16 out with the decay
 // logits formed in the kernel from a.y, a.lambda, a.bw instead of read from a.x (either form);

@@ -97,8 +97,32 @@ def test_own_split_where_it_is_said_to_be(fake, make):
 def test_columns_of_few_units_over_workgroups(fake, entry, bf16, units, T, columns):
     """From 129 units on, 17 to 20 tokens are faster or level by the four-wave form (0: 256 units x 17 tokens 9.0 against 9.4 us)."""
     [ev] = lu.events(fake, [lu.time_mix(entry, 1, T, units)])
+    if not bf16 and (units, T) == (256, 1000):                # fp32 tensors: only short sequences token by token
+        assert [e.kernel for e in ev if e.kind == "launch"] == ["chunked_f32_kernel<4, 4>"]
+        return
+    ev = [e for e in ev if e.kind == "launch"]
     want = "recurrent_columns_kernel<%d, %s>" % (columns, str(bf16).lower()) if columns else "recurrent_wide_kernel<%s, false>" % str(bf16).lower()
     assert [e.kernel for e in ev] == [want]
+
+
+@pytest.mark.parametrize("units,shortest,column_blocks", [(1, 97, 1), (24, 97, 1), (25, 33, 1), (64, 33, 1), (65, 33, 2), (96, 33, 2), (97, 24, 2), (128, 24, 2),
+                                                          (129, 24, 4), (256, 24, 4), (257, 48, 4), (512, 48, 4)])
+def test_fp32_sequences_in_chunks_from_where_that_is_faster(fake, units, shortest, column_blocks):
+    calls = [lu.time_mix("wkv6_prefill_f32", 1, T, units) for T in (shortest - 1, shortest, 1024)]
+    below, *above = [[e for e in ev if e.kind == "launch"] for ev in lu.events(fake, calls)]
+    assert "recurrent" in below[0].kernel
+    for launch in above:
+        assert [e.kernel for e in launch] == ["chunked_f32_kernel<%d, 4>" % column_blocks]
+        assert launch[0].grid[0] == (units + 7) // 8 * 8 * (4 // column_blocks)
+
+
+@pytest.mark.parametrize("first", [(1, 1, 4), (2, 20, 16), (4, 100, 4), (40, 100, 4), (3, 100, 32), (300, 100, 4)])
+def test_first_fp32_call_raises_every_limit(fake, first):
+    sizes = [(4, 100, 4), (40, 100, 4), (3, 100, 32), (300, 100, 4)]
+    per_call = lu.events(fake, [lu.time_mix("wkv6_prefill_f32", *first)] + [lu.time_mix("wkv6_prefill_f32", *s) for s in sizes])
+    limit = {e.kernel: e.bytes for e in per_call[0] if e.kind == "attribute"}
+    for ev in per_call[1:]:
+        assert [e.kind for e in ev] == ["launch"] and ev[0].bytes <= limit[ev[0].kernel]
 
 
 @pytest.mark.parametrize("M,D,kernel", [
