@@ -15,9 +15,9 @@ enum class Path { kChunked, kRecurrent, kBySize, kF32 };
 
 // Sequences at most this long go to the token-by-token kernel when the caller leaves the
 // choice to the library (append / decode shapes): with thousands of (batch, head) units and
-// a few tokens each the work is streaming the state once.  Measured crossover on MI355X with
-// 8192 units: about 8 tokens (the chunked kernel runs the units of a workgroup back to back, one
-// window each at these lengths).
+// a few tokens each the work is streaming the state once, and the token-by-token kernel does it with fp32
+// operands.  (The line was drawn against the chunked kernel, which was level at about 8 tokens with 8192
+// units; the one-chunk kernel would be the faster one from 4 tokens on, with fp16 operands.)
 constexpr int kRecurrentMaxTokens = 6;
 
 // fp32 tensors: sequences of at least this many tokens go to the chunked kernel.  It takes whole chunks of 16 tokens and a round to
@@ -45,14 +45,20 @@ void split_into_out(wkv6::Args& a, const wkv6::SplitPlan& p, bool out_f32) {
     a.place.half = static_cast<int>(out_f32 ? 128 : row);
 }
 
-// The passes of a prefill whose Args are complete but for the segments.
+// The passes of a prefill whose Args are complete but for the segments.  Sequences of one chunk go to the kernel that runs several
+// units per compute unit and not several chunks of one: at no number of units is it the slower one (figures there), and the bits
+// are the same.  The limits of the other kernels behind the entry point are raised all the same.
 hipError_t launch_prefill(wkv6::Args& a, wkv6::ChunkedMode mode, bool own_split, hipStream_t s) {
     const bool lora = mode == wkv6::ChunkedMode::kBf16OutLora || mode == wkv6::ChunkedMode::kBf16OutLoraMoments;
     if (own_split) {
         const wkv6::SplitPlan p = wkv6::plan_own_split(a.B, a.T, a.H);
         if (p.segs > 1) split_into_out(a, p, mode == wkv6::ChunkedMode::kF32Out);
     }
-    const hipError_t err = wkv6::launch_segment_states(a, lora, s);
+    hipError_t err = wkv6::launch_segment_states(a, lora, s);
+    if (a.segs == 1 && a.T <= wkv6::kChunkTokens) {
+        if (err == hipSuccess) err = wkv6::raise_chunked_limits(a, mode);
+        return err == hipSuccess ? wkv6::launch_one_chunk(a, mode, s) : err;
+    }
     return err == hipSuccess ? wkv6::launch_chunked(a, mode, s) : err;
 }
 

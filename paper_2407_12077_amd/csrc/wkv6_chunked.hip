@@ -61,7 +61,7 @@
 // the operands of the consumers' MFMAs, so that a lane holds four consecutive value channels of
 // one token and stages them with one store.
 #include "wkv6_launch.h"
-#include "wkv6_math.h"
+#include "wkv6_tiles.h"
 #include "wkv6_windows.h"
 
 #include <type_traits>
@@ -69,21 +69,12 @@
 namespace wkv6 {
 namespace {
 
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-typedef float float4v __attribute__((ext_vector_type(4)));
-typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
-constexpr int kChunk = 32;                 // tokens per chunk
 constexpr int kProducerGroups = kWindowGroups;   // 4 waves each
 constexpr int kThreads = 64 * (4 * kProducerGroups + 4);
 constexpr int kRow = 160;                  // fp16 tile row stride in bytes (64 halfs + 16 pad)
 constexpr int kTile = kChunk * kRow;       // one [32 tokens][64 channels] tile
 constexpr int kRowT = 96;                  // transposed tile [channel][32 tokens]: 64 B + 32 pad
 constexpr int kTileT = 64 * kRowT;
-constexpr int kORowF32 = 68;               // output staging row stride, fp32 mode (floats)
-constexpr int kORowBf16 = 72;              // output staging row stride, bf16 mode (halfs)
 
 // LDS map (bytes).  Everything up to kBuf exists twice, once per chunk parity.
 enum : int {
@@ -116,21 +107,6 @@ constexpr int kDx = kLdsBytes;
 constexpr int kLdsBytesLora = kLdsBytes + 2 * kDxBuf;
 static_assert(kLdsBytesLora <= 160 * 1024, "LDS budget");
 
-// two floats to a bf16 pair (round to nearest even), one packed conversion
-__device__ __forceinline__ unsigned pack_bf2(float a, float b) {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    typedef float float2v __attribute__((ext_vector_type(2)));
-    const float2v f = {a, b};
-    return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));
-}
-
-__device__ __forceinline__ half8 lds_read_h8(const char* lds, int byte_off) {
-    return *reinterpret_cast<const half8*>(lds + byte_off);
-}
-__device__ __forceinline__ void lds_write_u32(char* lds, int byte_off, unsigned val) {
-    *reinterpret_cast<unsigned*>(lds + byte_off) = val;
-}
-
 // Byte offset, inside a transposed tile, of the 16-byte granule `granule` (tokens 8*granule .. +7)
 // of row `row` (a channel).  The XOR with two row bits makes the producers' 8-byte stores (32
 // lanes on 32 different rows, two lanes per granule) and the consumers' 16-byte reads (16
@@ -143,30 +119,6 @@ __device__ __forceinline__ int tile_t_off(int row, int granule) {
 __device__ __forceinline__ int score_off(int t, int granule) {
     return t * kRow + ((granule ^ ((t >> 2) & 1)) << 4);
 }
-__device__ __forceinline__ void lds_write_u64(char* lds, int byte_off, unsigned lo, unsigned hi) {
-    *reinterpret_cast<uint2*>(lds + byte_off) = make_uint2(lo, hi);
-}
-// low halves / high halves of two packed fp16 pairs as one pair
-__device__ __forceinline__ unsigned lo_halves(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
-__device__ __forceinline__ unsigned hi_halves(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
-
-__device__ __forceinline__ float4v mfma(half8 a, half8 b, float4v c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-}
-
-// Cache policy of the streams that are touched exactly once (r, k, v, x, u', out): the
-// non-temporal bit, so they do not displace each other in the caches on their way through.
-constexpr int kStreamOnce = 2;
-// Cache policy of the output rows: scope bit sc1 without the non-temporal bit, i.e. written
-// through the XCD's L2 as they are produced instead of lingering there as dirty lines.  Measured
-// with a streaming probe of this layout (four non-temporal input streams, one output stream of
-// 128-byte rows 4 KiB apart): 130.7 us against 135.8 us with non-temporal stores.
-constexpr int kStoreThrough = 16;
-
-struct Raw {           // one chunk's inputs of a producer thread: 4 tokens x one channel pair
-    unsigned r[4], k[4], v[4], x[4];
-};
-
 // The four input streams of one (batch, head) are read through raw buffer descriptors whose
 // base is the chunk's first token row (uniform, rebuilt per chunk with scalar adds) and whose
 // extent ends with the unit's last token, so rows past the end of the sequence read as zero
@@ -232,19 +184,6 @@ struct Units {
     int pitch_row, pitch_half;
 };
 
-// Sum over the 8 lanes of an aligned group of 8 (every lane gets the total): neighbours, pairs,
-// then the mirrored half-row, all as data-parallel-primitive moves inside the vector ALU.
-template <int kCtrl>
-__device__ __forceinline__ float dpp_move(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kCtrl, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float row8_sum(float v) {
-    v += dpp_move<0xB1>(v);       // quad_perm [1,0,3,2]
-    v += dpp_move<0x4E>(v);       // quad_perm [2,3,0,1]
-    v += dpp_move<0x141>(v);      // row_half_mirror: lane i <-> 7 - i of each 8
-    return v;
-}
-
 // Position in the workgroup's chunk sequence: unit ui, chunk c of it.  Advanced without
 // divisions; c < 0 (before the start) and ui >= count (past the end) mean "no chunk".
 // With a single unit per workgroup (kMulti false) ui stays 0 and "past the end" is c >= nchunks.
@@ -268,15 +207,6 @@ struct Cursor {
         if constexpr (kMulti) return ui * un.step;
         return 0;
     }
-};
-
-// What a producer thread carries from phase D (where it digests the raw inputs of its chunk)
-// to phase T (where the other groups' decay totals are known and the tiles are written).
-struct Prep {
-    unsigned z2[4], q1[4], k1[4];                         // finished fp16 pairs (two channels), one per token
-    unsigned vt[4];            // v as fp16 pairs of consecutive tokens: [2*channel + token pair]
-    unsigned rp[4];            // r * prefix product inside the group, fp16 pair (2 channels)
-    unsigned ks[4];            // k * suffix product inside the group, fp16 pair
 };
 
 // ------------------------------------------------------------------------------------------
@@ -364,72 +294,9 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
                 }
             }
         } else {
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                float e0 = 0.f, e1 = 0.f;
-                w[0][s] = decay_of(bf16_lo(cur.x[s]), e0);
-                w[1][s] = decay_of(bf16_hi(cur.x[s]), e1);
-                if constexpr (kC2) {
-                    omw[0][s] = one_minus_decay(e0, w[0][s]);
-                    omw[1][s] = one_minus_decay(e1, w[1][s]);
-                }
-            }
+            decays_of<kC2>(cur.x, w, omw);
         }
-        // products of decays inside the group, fp32: prefix of token 2 and 3, suffix of token 1
-        // and 0, and the group total
-        float p2[2], p3[2], s1[2], s0[2];
-#pragma unroll
-        for (int ch = 0; ch < 2; ++ch) {
-            p2[ch] = w[ch][0] * w[ch][1];
-            p3[ch] = p2[ch] * w[ch][2];
-            s1[ch] = w[ch][2] * w[ch][3];
-            s0[ch] = w[ch][1] * s1[ch];
-        }
-        *reinterpret_cast<float2*>(lds + kG + (g8 * 64 + 2 * cp) * 4) =
-            make_float2(p3[0] * w[0][3], p3[1] * w[1][3]);
-        // r, k, v as fp16 channel pairs (exact: bf16 has fewer significant bits); every scaled
-        // operand is one packed fp16 multiply with a multiplier rounded to fp16
-        unsigned rh[4], kh[4];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            rh[s] = pack_h2(bf16_lo(cur.r[s]), bf16_hi(cur.r[s]));
-            if constexpr (kC2)      // Finch-C2: k = kbar (1 - w), the factor applied in fp32
-                kh[s] = pack_h2(bf16_lo(cur.k[s]) * omw[0][s], bf16_hi(cur.k[s]) * omw[1][s]);
-            else
-                kh[s] = pack_h2(bf16_lo(cur.k[s]), bf16_hi(cur.k[s]));
-        }
-        // v goes to a transposed tile: pairs of consecutive tokens of one channel
-        pr.vt[0] = pack_h2(bf16_lo(cur.v[0]), bf16_lo(cur.v[1]));
-        pr.vt[1] = pack_h2(bf16_lo(cur.v[2]), bf16_lo(cur.v[3]));
-        pr.vt[2] = pack_h2(bf16_hi(cur.v[0]), bf16_hi(cur.v[1]));
-        pr.vt[3] = pack_h2(bf16_hi(cur.v[2]), bf16_hi(cur.v[3]));
-        pr.rp[0] = rh[0];
-        pr.rp[1] = mul_h2(rh[1], pack_h2(w[0][0], w[1][0]));
-        pr.rp[2] = mul_h2(rh[2], pack_h2(p2[0], p2[1]));
-        pr.rp[3] = mul_h2(rh[3], pack_h2(p3[0], p3[1]));
-        const unsigned hw3 = pack_h2(w[0][3], w[1][3]);
-        pr.ks[0] = mul_h2(kh[0], pack_h2(s0[0], s0[1]));
-        pr.ks[1] = mul_h2(kh[1], pack_h2(s1[0], s1[1]));
-        pr.ks[2] = mul_h2(kh[2], hw3);
-        pr.ks[3] = kh[3];
-        // level 2: tokens 0,1 of the group are keys, 2,3 queries
-        pr.z2[0] = mul_h2(kh[0], pack_h2(w[0][1], w[1][1]));
-        pr.z2[1] = kh[1];
-        pr.z2[2] = rh[2];
-        pr.z2[3] = mul_h2(rh[3], pack_h2(w[0][2], w[1][2]));
-        // level 1 (odd token t reads even token t-1, no decay between them) and the bonus on the
-        // diagonal share one query tile and one key tile: u rides on the query for even tokens
-        // and on the key for odd tokens, so the diagonal gets r.u.k and the pair gets plain r.k
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            if constexpr (kC2) {
-                // no diagonal term: one tile, keys in the even token rows, receptances in the odd ones
-                pr.q1[s] = (s & 1) ? rh[s] : kh[s];
-            } else {
-                pr.q1[s] = (s & 1) ? rh[s] : mul_h2(rh[s], hu);
-                pr.k1[s] = !(s & 1) ? kh[s] : mul_h2(kh[s], hu);
-            }
-        }
+        *reinterpret_cast<float2*>(lds + kG + (g8 * 64 + 2 * cp) * 4) = form_operands<kC2>(pr, cur, w, omw, hu);
     };
 
     // Phase T: multipliers from the other groups' decay totals, then every operand tile.  (Writing
@@ -545,17 +412,9 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
         const float4v acc4 = mfma(z4, z4, zero);
         const float4v acc2 = mfma(z2, z2, zero);
         const float4v acc1 = mfma(k1, q1, zero);     // pairs (odd t, t-1) and, on the diagonal, the bonus
-        float sel[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int i = 4 * g4 + e, t = l16;
-            const int d = i ^ t;
-            const float val = d >= 8 ? acc8[e] : d >= 4 ? acc4[e] : d >= 2 ? acc2[e] : acc1[e];
-            sel[e] = (kC2 ? i >= t : i > t) ? 0.f : val;    // Finch-C2 has no diagonal term
-        }
         // keys 16q + 4*g4 .. +3 of token row 16q + l16: half (g4 & 1) of granule 2q + (g4 >> 1)
         *reinterpret_cast<uint2*>(lds + at + score_off(16 * q + l16, 2 * q + (g4 >> 1)) + 8 * (g4 & 1)) =
-            make_uint2(pack_h2(sel[0], sel[1]), pack_h2(sel[2], sel[3]));
+            choose_levels<kC2>(acc8, acc4, acc2, acc1, l16, g4);
         if (q == 0) {
             const int rq = (16 + l16) * kRow + 16 * g4 + 64 * kk;
             const half8 zq = lds_read_h8(lds, kZ16 + rq);
@@ -615,34 +474,14 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
                 const float4* src = reinterpret_cast<const float4*>(
                     lds + kO + (srow * kORowF32 + (kSplitRow ? scol / 2 : scol)) * 4);
                 float4 q0 = src[0], q1 = src[kSplitRow ? 8 : 1];
-                if constexpr (kC2) {
-                    q0.x += bf16_lo(up_raw[0]); q0.y += bf16_hi(up_raw[0]);
-                    q0.z += bf16_lo(up_raw[1]); q0.w += bf16_hi(up_raw[1]);
-                    q1.x += bf16_lo(up_raw[2]); q1.y += bf16_hi(up_raw[2]);
-                    q1.z += bf16_lo(up_raw[3]); q1.w += bf16_hi(up_raw[3]);
-                }
+                if constexpr (kC2) add_uprime(q0, q1, up_raw);
                 if constexpr (kMoments) {
-                    // The 8 threads of a row hold the head's 64 finished values of this token: their
-                    // sum, then the squared deviations from the head's own mean, each folded over
-                    // the 8 lanes; the row's first thread writes the pair.
-                    const float s = row8_sum(((q0.x + q0.y) + (q0.z + q0.w)) + ((q1.x + q1.y) + (q1.z + q1.w)));
-                    const float m = s * (1.f / kHeadSize);
-                    float m2 = (q0.x - m) * (q0.x - m);
-                    m2 = fmaf(q0.y - m, q0.y - m, m2);
-                    m2 = fmaf(q0.z - m, q0.z - m, m2);
-                    m2 = fmaf(q0.w - m, q0.w - m, m2);
-                    m2 = fmaf(q1.x - m, q1.x - m, m2);
-                    m2 = fmaf(q1.y - m, q1.y - m, m2);
-                    m2 = fmaf(q1.z - m, q1.z - m, m2);
-                    m2 = fmaf(q1.w - m, q1.w - m, m2);
-                    m2 = row8_sum(m2);
+                    const float2v pair = row_moments(q0, q1);        // the row's first thread writes it
                     if (scol == 0) {
                         long long unit_index = un.first;
                         if constexpr (kMulti) unit_index += static_cast<long long>(at.ui) * un.stride;
                         // streamed like the output rows (measured: 7 % of the kernel's time on many
                         // short units against a plain store)
-                        typedef float float2v __attribute__((ext_vector_type(2)));
-                        const float2v pair = {s, m2};
                         __builtin_nontemporal_store(pair, reinterpret_cast<float2v*>(a.moments + (unit_index * a.T + un.t0 + t) * 2));
                     }
                 }
@@ -655,12 +494,7 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
                         put(__builtin_bit_cast(uint4v, q1), 16);
                     }
                 } else {
-                    uint4v q;
-                    q.x = pack_bf2(q0.x, q0.y);
-                    q.y = pack_bf2(q0.z, q0.w);
-                    q.z = pack_bf2(q1.x, q1.y);
-                    q.w = pack_bf2(q1.z, q1.w);
-                    put(q, 0);
+                    put(pack_row(q0, q1), 0);
                 }
             } else {
                 put(*reinterpret_cast<const uint4v*>(lds + kO + (srow * kORowBf16 + scol) * 2), 0);

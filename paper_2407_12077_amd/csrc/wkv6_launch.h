@@ -73,6 +73,10 @@ hipError_t raise_chunked_f32_limits();
 // kBf16OutLoraMoments: that plus a.moments (Finch-C2 form).
 hipError_t launch_chunked(const Args& a, ChunkedMode mode, hipStream_t stream);
 
+// The same, bit for bit, for sequences of at most kChunkTokens tokens.
+constexpr int kChunkTokens = 32;
+hipError_t launch_one_chunk(const Args& a, ChunkedMode mode, hipStream_t stream);
+
 // Raises the dynamic LDS limits that launch_chunked needs for this form and mode, without launching.
 hipError_t raise_chunked_limits(const Args& a, ChunkedMode mode);
 

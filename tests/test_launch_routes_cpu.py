@@ -105,6 +105,19 @@ def test_columns_of_few_units_over_workgroups(fake, entry, bf16, units, T, colum
     assert [e.kernel for e in ev] == [want]
 
 
+@pytest.mark.parametrize("B,H", [(1, 1), (8, 32), (9, 32), (256, 32)])
+@pytest.mark.parametrize("make,shortest", [
+    (lambda B, T, H: lu.time_mix("wkv6_append_bf16", B, T, H), 7), (lambda B, T, H: lu.time_mix("wkv6_finch_c2_append_bf16", B, T, H), 7),
+    (lambda B, T, H: lu.time_mix("wkv6_prefill_bf16", B, T, H), 1), (lambda B, T, H: lu.time_mix("wkv6_finch_c2_prefill_bf16_f32out", B, T, H), 1),
+    (lambda B, T, H: lu.fused_c2(B, T, H), 5), (lambda B, T, H: lu.fused_finch(B, T, H), 5)],
+    ids=["append", "c2_append", "prefill", "c2_prefill_f32out", "fused_c2", "fused_finch"])
+def test_sequences_of_one_chunk_take_four_waves_a_unit(fake, make, shortest, B, H):
+    for T, ev in zip((shortest, 32, 33), lu.events(fake, [make(B, T, H) for T in (shortest, 32, 33)])):
+        [run] = [e for e in ev if e.kind == "launch"]
+        assert run.base == "chunked_kernel" and (run.block, run.bytes <= 40 * 1024) == ((256, True) if T <= 32 else (1024, False))
+        assert T > 32 or run.grid[0] == B * H
+
+
 @pytest.mark.parametrize("units,shortest,column_blocks", [(1, 97, 1), (24, 97, 1), (25, 33, 1), (64, 33, 1), (65, 33, 2), (96, 33, 2), (97, 24, 2), (128, 24, 2),
                                                           (129, 24, 4), (256, 24, 4), (257, 48, 4), (512, 48, 4)])
 def test_fp32_sequences_in_chunks_from_where_that_is_faster(fake, units, shortest, column_blocks):
