@@ -119,6 +119,20 @@ __device__ __forceinline__ int tile_t_off(int row, int granule) {
 __device__ __forceinline__ int score_off(int t, int granule) {
     return t * kRow + ((granule ^ ((t >> 2) & 1)) << 4);
 }
+// Cache policies of a launch, by the bytes that it touches (once, all of them).
+//   kCached    While two or three such calls fit the 256 MB memory-side cache: rows that lie there from the kernel that wrote
+//              them are loaded temporally, and what is written (rows, states) is streamed past.
+//   kLarge     Rows streamed; output rows written through, states left to the L2s.
+//   kStreamed  The same with the output rows streamed as well: several calls' worth of cache, and with several units a
+//              workgroup from where kCached ends (fp32 rows of more than four chunks a unit excepted: 30 x 500 x 16 heads
+//              37.5 -> 42.0, but 64 x 100 x 32 46.5 -> 43.3).
+// Microseconds, rows streamed and written through (the only policy once) -> the one taken, separate tensors: 8 x 60 tokens x 32 heads
+// (17 MB) 7.05 -> 6.2, 16 x 64 (36 MB) 11.4 -> 10.1, Finch-C2 32 x 64 (80 MB) 18.4 -> 16.2, fused 8 x 500 (90 MB) 27.1 -> 24.2;
+// 17 x 2000 (680 MB) 191 -> 180, 64 x 300 (440 MB) 93.7 -> 86.6, Finch-C2 256 x 512 742 -> 705.  Beyond the lines: temporal rows
+// at 110 MB 25.8 -> 26.9, at 164 MB 36.7 -> 42.7; streamed output with one unit a workgroup at 164 MB 35.6 -> 37.2; streamed
+// states at 144 MB 28.9 -> 32.0.  (As run-time branches in the stores the choice costs 2 to 7 %.)
+enum class Traffic { kCached, kLarge, kStreamed };
+
 // The four input streams of one (batch, head) are read through raw buffer descriptors whose
 // base is the chunk's first token row (uniform, rebuilt per chunk with scalar adds) and whose
 // extent ends with the unit's last token, so rows past the end of the sequence read as zero
@@ -134,7 +148,7 @@ struct Streams {
 
 // A chunk's loads are issued in two halves (x and r; k and v) so that two different phases can
 // share the cost of issuing them.
-// kPolicy: the cache policy of the loads.  Every mode streams (kStreamOnce).
+// kPolicy: the cache policy of the loads, kStreamOnce or 0 (temporal).
 template <bool kSkipX, int kPolicy>
 __device__ __forceinline__ void load_rows_xr(Raw& d, const Streams& st, long long unit_bytes, int t0,
                                              const int (&voff)[4]) {
@@ -212,9 +226,11 @@ struct Cursor {
 // ------------------------------------------------------------------------------------------
 // Producer waves: group pg (0..2) = chunk index mod 3, wq = wave inside the group
 // ------------------------------------------------------------------------------------------
-template <int kMode, bool kC2, bool kMulti>
+template <int kMode, bool kC2, bool kMulti, Traffic kTraffic>
 __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, int pg, int wq, int h,
                                          const Units& un, long long tok_stride, int T) {
+    constexpr int kRows = kTraffic == Traffic::kCached ? 0 : kStreamOnce;
+    constexpr int kOutRows = kTraffic == Traffic::kLarge ? kStoreThrough : kStoreThrough | kStreamOnce;
     constexpr bool kOutF32 = kMode == 1;
     constexpr bool kMoments = kMode == 3 || kMode == 5;   // bf16 out plus the per-head LayerNorm partials
     constexpr bool kLora = kMode >= 4;           // decay logits from the consumers (LDS), not from x
@@ -436,7 +452,9 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
     const int srow = gtid >> 3;                  // token row inside the chunk this thread stores
     const int scol = 8 * (gtid & 7);             // first of its 8 channels
     [[maybe_unused]] uint4v up_raw = {0u, 0u, 0u, 0u};
-    [[maybe_unused]] const int up_voff = static_cast<int>(srow * st.row_bytes + scol * 2);
+    // fp32 rows (256 bytes): the row's 8 threads store its first 128 bytes, then its second (whole cache lines per
+    // instruction), so thread j holds channels 4j .. and 32 + 4j ..; a bf16 row's threads hold channels 8j ..
+    [[maybe_unused]] const int up_voff = static_cast<int>(srow * st.row_bytes + (kOutF32 ? scol : scol * 2));
     [[maybe_unused]] const char* up_base = kC2 ? static_cast<const char*>(a.uprime) + un.base0 * 2 : nullptr;
     auto load_uprime = [&](const Cursor<kMulti>& at) {
         if constexpr (kC2) {
@@ -445,10 +463,14 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
             const int cc = at.c < 0 ? 0 : at.c;
             const bool live = at.c < 0 || at.live(un);
             const long long off = static_cast<long long>(cc) * kChunk * st.row_bytes;
-            up_raw = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(
-                                                    chunk_rsrc(up_base + (live ? at.unit_elems(un) * 2 : 0), off,
-                                                               live ? st.span_bytes : 0),
-                                                    up_voff, 0, kStreamOnce));
+            const __amdgpu_buffer_rsrc_t ru = chunk_rsrc(up_base + (live ? at.unit_elems(un) * 2 : 0), off, live ? st.span_bytes : 0);
+            if constexpr (kOutF32) {
+                const uint2v lo = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(ru, up_voff, 0, kRows));
+                const uint2v hi = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(ru, up_voff + 64, 0, kRows));
+                up_raw = uint4v{lo[0], lo[1], hi[0], hi[1]};
+            } else {
+                up_raw = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(ru, up_voff, 0, kRows));
+            }
         }
     };
     // Output rows leave through a raw buffer descriptor that starts at the chunk's first row and ends
@@ -464,16 +486,13 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
         const __amdgpu_buffer_rsrc_t ro = chunk_rsrc(out_base + at.unit_elems(un) * kOutElem,
                                                      static_cast<long long>(at.c) * kChunk * out_row_bytes, out_span);
         auto put = [&](uint4v q, int byte) {
-            __builtin_amdgcn_raw_buffer_store_b128(q, ro, out_voff + byte, 0, kStoreThrough);
+            __builtin_amdgcn_raw_buffer_store_b128(q, ro, out_voff + byte, 0, kOutRows);
         };
         if (t < T) {
             if constexpr (kStageF32) {
-                // fp32 rows of the Finch form (256 bytes): the row's 8 threads store its first 128 bytes, then
-                // its second (whole cache lines per instruction): thread j holds floats 4j.. and 32 + 4j..
-                constexpr bool kSplitRow = kOutF32 && !kC2;
                 const float4* src = reinterpret_cast<const float4*>(
-                    lds + kO + (srow * kORowF32 + (kSplitRow ? scol / 2 : scol)) * 4);
-                float4 q0 = src[0], q1 = src[kSplitRow ? 8 : 1];
+                    lds + kO + (srow * kORowF32 + (kOutF32 ? scol / 2 : scol)) * 4);
+                float4 q0 = src[0], q1 = src[kOutF32 ? 8 : 1];
                 if constexpr (kC2) add_uprime(q0, q1, up_raw);
                 if constexpr (kMoments) {
                     const float2v pair = row_moments(q0, q1);        // the row's first thread writes it
@@ -486,13 +505,8 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
                     }
                 }
                 if constexpr (kOutF32) {
-                    if constexpr (kSplitRow) {
-                        put(__builtin_bit_cast(uint4v, q0), -scol * 2);            // byte 16 j of the row
-                        put(__builtin_bit_cast(uint4v, q1), 128 - scol * 2);      // byte 128 + 16 j
-                    } else {
-                        put(__builtin_bit_cast(uint4v, q0), 0);
-                        put(__builtin_bit_cast(uint4v, q1), 16);
-                    }
+                    put(__builtin_bit_cast(uint4v, q0), -scol * 2);               // byte 16 j of the row
+                    put(__builtin_bit_cast(uint4v, q1), 128 - scol * 2);          // byte 128 + 16 j
                 } else {
                     put(pack_row(q0, q1), 0);
                 }
@@ -527,11 +541,11 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
     stc.advance(0, un.nchunks);
     auto fetch_xr = [&](Raw& buf, const Cursor<kMulti>& at) {
         const bool live = at.live(un);                // uniform; dead: offset past the span = empty descriptor
-        load_rows_xr<kLora, kStreamOnce>(buf, st, live ? at.unit_elems(un) * 2 : 0, live ? at.c * kChunk : T + kChunk, voff);
+        load_rows_xr<kLora, kRows>(buf, st, live ? at.unit_elems(un) * 2 : 0, live ? at.c * kChunk : T + kChunk, voff);
     };
     auto fetch_kv = [&](Raw& buf, const Cursor<kMulti>& at) {
         const bool live = at.live(un);
-        load_rows_kv<kStreamOnce>(buf, st, live ? at.unit_elems(un) * 2 : 0, live ? at.c * kChunk : T + kChunk, voff);
+        load_rows_kv<kRows>(buf, st, live ? at.unit_elems(un) * 2 : 0, live ? at.c * kChunk : T + kChunk, voff);
     };
     // one chunk of this group through its three windows; `buf` holds its raw inputs and is
     // refilled with the group's chunk after next (six chunks ahead) right after the digest
@@ -584,8 +598,9 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
 // ------------------------------------------------------------------------------------------
 // Consumer waves
 // ------------------------------------------------------------------------------------------
-template <int kMode, bool kC2, bool kMulti>
+template <int kMode, bool kC2, bool kMulti, Traffic kTraffic>
 __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane, int cw, const Units& un) {
+    constexpr int kState = kTraffic == Traffic::kCached ? kStoreThrough | kStreamOnce : 0;
     constexpr bool kOutF32 = kMode == 1;
     constexpr bool kLora = kMode >= 4;
     const int l16 = lane & 15;
@@ -786,7 +801,7 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
                         for (int e = 0; e < 4; ++e) {
                             const float value = S[nb][e];        // (a bit cast straight from the vector element reads element 0)
                             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(value), rs, state_voff,
-                                                                  (16 * nb + e) * 256, 0);
+                                                                  (16 * nb + e) * 256, kState);
                         }
                 }
             }
@@ -802,7 +817,7 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
     }
 }
 
-template <int kMode, bool kC2, bool kMulti>
+template <int kMode, bool kC2, bool kMulti, Traffic kTraffic>
 __global__ __launch_bounds__(kThreads) void chunked_kernel(Args a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     clamp_fp16_overflow();
@@ -844,9 +859,9 @@ __global__ __launch_bounds__(kThreads) void chunked_kernel(Args a) {
         un.step = static_cast<long long>(a.unit_stride / a.H) * a.batch_stride;
     }
     if (wid < 4 * kProducerGroups)
-        producer<kMode, kC2, kMulti>(a, lds, tid, wid >> 2, wid & 3, h, un, tok_stride, T);
+        producer<kMode, kC2, kMulti, kTraffic>(a, lds, tid, wid >> 2, wid & 3, h, un, tok_stride, T);
     else
-        consumer<kMode, kC2, kMulti>(a, lds, tid & 63, wid - 4 * kProducerGroups, un);
+        consumer<kMode, kC2, kMulti, kTraffic>(a, lds, tid & 63, wid - 4 * kProducerGroups, un);
 }
 
 template <int kMode, bool kC2>
@@ -854,8 +869,12 @@ hipError_t raise_mode_limits() {
     constexpr int lds_bytes = kMode >= 4 ? kLdsBytesLora : kLdsBytes;
     struct Tag {};
     return once_per_device<Tag>([] {
-        const hipError_t e = set_lds_limit(&chunked_kernel<kMode, kC2, false>, lds_bytes);
-        return e == hipSuccess ? set_lds_limit(&chunked_kernel<kMode, kC2, true>, lds_bytes) : e;
+        hipError_t e = set_lds_limit(&chunked_kernel<kMode, kC2, false, Traffic::kCached>, lds_bytes);
+        if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, true, Traffic::kCached>, lds_bytes);
+        if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, false, Traffic::kLarge>, lds_bytes);
+        if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, false, Traffic::kStreamed>, lds_bytes);
+        if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, true, Traffic::kStreamed>, lds_bytes);
+        return e;
     });
 }
 
@@ -877,10 +896,17 @@ hipError_t launch_mode(const Args& args, hipStream_t stream) {
     }
     const dim3 grid(static_cast<unsigned>(units));
     constexpr int lds_bytes = kMode >= 4 ? kLdsBytesLora : kLdsBytes;
-    if (a.unit_stride > 0)
-        hipLaunchKernelGGL((chunked_kernel<kMode, kC2, true>), grid, dim3(kThreads), lds_bytes, stream, a);
+    const long long row_bytes = kHeadSize * 2 * (kMode >= 4 ? 3 : 4) + kHeadSize * (kMode == 1 ? 4 : 2) + (kC2 ? kHeadSize * 2 : 0);
+    const long long mib = static_cast<long long>(a.B) * a.H * (a.T * row_bytes + 2 * 4096 * 4) >> 20;     // the call's rows and states
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds_bytes, stream, a); };
+    if (kMode == 1 && a.unit_stride > 0 && mib >= 90 && mib < 400 && a.T > 128)
+        go(&chunked_kernel<kMode, kC2, true, Traffic::kLarge>);
+    else if (a.unit_stride > 0)
+        mib < 90 ? go(&chunked_kernel<kMode, kC2, true, Traffic::kCached>) : go(&chunked_kernel<kMode, kC2, true, Traffic::kStreamed>);
+    else if (mib < 90)
+        go(&chunked_kernel<kMode, kC2, false, Traffic::kCached>);
     else
-        hipLaunchKernelGGL((chunked_kernel<kMode, kC2, false>), grid, dim3(kThreads), lds_bytes, stream, a);
+        mib < 400 ? go(&chunked_kernel<kMode, kC2, false, Traffic::kLarge>) : go(&chunked_kernel<kMode, kC2, false, Traffic::kStreamed>);
     return hipGetLastError();
 }
 

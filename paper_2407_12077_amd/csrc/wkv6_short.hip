@@ -136,9 +136,17 @@ __global__ __launch_bounds__(256, 4) void chunked_kernel(Args a) {
     }
     const int srow = tid >> 3, scol = 8 * (tid & 7);         // row and first channel that this thread stores
     [[maybe_unused]] uint4v up_raw = {0u, 0u, 0u, 0u};
-    if constexpr (kC2)
-        up_raw = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(chunk_rsrc(static_cast<const char*>(a.uprime) + base * 2, 0, span),
-                                                                                  static_cast<int>(srow * row_bytes) + scol * 2, 0, kRows));
+    if constexpr (kC2) {
+        const __amdgpu_buffer_rsrc_t ru = chunk_rsrc(static_cast<const char*>(a.uprime) + base * 2, 0, span);
+        const int up_voff = static_cast<int>(srow * row_bytes) + (kOutF32 ? scol : scol * 2);
+        if constexpr (kOutF32) {                             // thread j of an fp32 row: channels 4 j .. and 32 + 4 j ..
+            const uint2v lo = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(ru, up_voff, 0, kRows));
+            const uint2v hi = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(ru, up_voff + 64, 0, kRows));
+            up_raw = uint4v{lo[0], lo[1], hi[0], hi[1]};
+        } else {
+            up_raw = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(ru, up_voff, 0, kRows));
+        }
+    }
 
     // ---- decays
     float w[2][4];
@@ -321,10 +329,9 @@ __global__ __launch_bounds__(256, 4) void chunked_kernel(Args a) {
     const int out_voff = static_cast<int>(srow * out_row) + scol * kOutElem;
     auto put = [&](uint4v q, int byte) { __builtin_amdgcn_raw_buffer_store_b128(q, ro, out_voff + byte, 0, kStoreThrough); };
     if constexpr (kStageF32) {
-        // fp32 rows of the Finch form: thread j holds floats 4 j .. and 32 + 4 j .., whole lines per instruction
-        constexpr bool kSplitRow = kOutF32 && !kC2;
-        const float4* src = reinterpret_cast<const float4*>(lds + L::kO + (srow * kORowF32 + (kSplitRow ? scol / 2 : scol)) * 4);
-        float4 q0 = src[0], q1 = src[kSplitRow ? 8 : 1];
+        // fp32 rows: thread j holds floats 4 j .. and 32 + 4 j .., whole lines per instruction
+        const float4* src = reinterpret_cast<const float4*>(lds + L::kO + (srow * kORowF32 + (kOutF32 ? scol / 2 : scol)) * 4);
+        float4 q0 = src[0], q1 = src[kOutF32 ? 8 : 1];
         if constexpr (kC2) add_uprime(q0, q1, up_raw);
         if constexpr (kMoments) {
             const float2v pair = row_moments(q0, q1);
@@ -333,8 +340,8 @@ __global__ __launch_bounds__(256, 4) void chunked_kernel(Args a) {
         if constexpr (!kOutF32) {
             put(pack_row(q0, q1), 0);
         } else {
-            put(__builtin_bit_cast(uint4v, q0), kSplitRow ? -scol * 2 : 0);
-            put(__builtin_bit_cast(uint4v, q1), kSplitRow ? 128 - scol * 2 : 16);
+            put(__builtin_bit_cast(uint4v, q0), -scol * 2);
+            put(__builtin_bit_cast(uint4v, q1), 128 - scol * 2);
         }
     } else {
         put(*reinterpret_cast<const uint4v*>(lds + L::kO + (srow * kORowBf16 + scol) * 2), 0);

@@ -1,0 +1,31 @@
+"""The chunked kernel's cache policies follow the bytes of a call: a batch on the far side of a line gives, sequence by sequence, the bits
+of calls small enough for the first policy.  (The split entries with one segment: they never split by themselves.)"""
+import pytest
+import torch
+
+import paper_2407_12077_amd as wkv
+
+pytestmark = pytest.mark.gpu
+
+
+# one unit a workgroup: 90 MiB and 400 MiB; several: 90 MiB, fp32 rows of more than four chunks
+@pytest.mark.parametrize("c2", [False, True])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("B,T,H", [(4, 1001, 64), (4, 3500, 50), (20, 300, 32), (40, 100, 32)])
+def test_bits_do_not_depend_on_the_size_of_the_batch(c2, dtype, B, T, H):
+    g = torch.Generator(device="cuda").manual_seed(B * T)
+    r, k, v, up = ((torch.randn((B, T, H, 64), generator=g, device="cuda") / 8).to(torch.bfloat16) for _ in range(4))
+    x = (torch.rand((B, T, H, 64), generator=g, device="cuda") * 7 - 6).to(torch.bfloat16)
+    extra = up if c2 else torch.randn((H, 64), generator=g, device="cuda") / 2
+    state = torch.randn((B, H, 64, 64), generator=g, device="cuda") / 10
+    entry = wkv.wkv6_finch_c2_prefill_bf16_split if c2 else wkv.wkv6_prefill_bf16_split
+    out = torch.full((B, T, H, 64), float("nan"), dtype=dtype, device="cuda")
+    s = torch.full_like(state, float("nan"))
+    code = wkv.WKV6_DTYPE_F32 if dtype == torch.float32 else wkv.WKV6_DTYPE_BF16
+    entry(B, T, H, 64, r, k, v, x, extra, state, out, s, code, 1, None, 0)
+    one, s1 = torch.empty((1, T, H, 64), dtype=dtype, device="cuda"), torch.empty((1, H, 64, 64), device="cuda")
+    for b in range(0, B, 3):
+        sl = slice(b, b + 1)
+        entry(1, T, H, 64, r[sl], k[sl], v[sl], x[sl], up[sl] if c2 else extra, state[sl], one, s1, code, 1, None, 0)
+        torch.cuda.synchronize()
+        assert torch.equal(one, out[sl]) and torch.equal(s1, s[sl]), b
