@@ -121,16 +121,17 @@ __device__ __forceinline__ int score_off(int t, int granule) {
 }
 // Cache policies of a launch, by the bytes that it touches (once, all of them).
 //   kCached    While two or three such calls fit the 256 MB memory-side cache: rows that lie there from the kernel that wrote
-//              them are loaded temporally, and what is written (rows, states) is streamed past.
-//   kLarge     Rows streamed; output rows written through, states left to the L2s.
-//   kStreamed  The same with the output rows streamed as well: several calls' worth of cache, and with several units a
-//              workgroup from where kCached ends (fp32 rows of more than four chunks a unit excepted: 30 x 500 x 16 heads
-//              37.5 -> 42.0, but 64 x 100 x 32 46.5 -> 43.3).
-// Microseconds, rows streamed and written through (the only policy once) -> the one taken, separate tensors: 8 x 60 tokens x 32 heads
-// (17 MB) 7.05 -> 6.2, 16 x 64 (36 MB) 11.4 -> 10.1, Finch-C2 32 x 64 (80 MB) 18.4 -> 16.2, fused 8 x 500 (90 MB) 27.1 -> 24.2;
-// 17 x 2000 (680 MB) 191 -> 180, 64 x 300 (440 MB) 93.7 -> 86.6, Finch-C2 256 x 512 742 -> 705.  Beyond the lines: temporal rows
-// at 110 MB 25.8 -> 26.9, at 164 MB 36.7 -> 42.7; streamed output with one unit a workgroup at 164 MB 35.6 -> 37.2; streamed
-// states at 144 MB 28.9 -> 32.0.  (As run-time branches in the stores the choice costs 2 to 7 %.)
+//              them are loaded temporally, and final states are streamed past.
+//   kLarge     Rows streamed, states left to the L2s.
+//   kStreamed  The same with the output rows, which the other two write through into the memory-side cache, streamed as well: from
+//              where that cannot hold them anyway.  (Below, streaming them gains as much in a loop of such calls as it loses in a
+//              first call, whose writes the cache would have taken in, and it takes them from the kernel that reads them next.)
+// Microseconds, kLarge (the only policy once) -> the one taken: 8 x 60 tokens x 32 heads (17 MB) 7.05 -> 6.2, 16 x 64 (36 MB) 11.4 ->
+// 10.1, Finch-C2 32 x 64 (80 MB) 18.4 -> 16.2; Finch-C2 256 x 512 (3.3 GB) 742 -> 677, first calls 757 -> 728; 64 x 1000 (1.3 GB) 274 -> 252, first
+// 291 -> 284.  Not taken: temporal rows at 110 MB 25.8 -> 26.9, at 164 MB 36.7 -> 42.7; streamed output at 680 MB 191 -> 180 but first calls
+// 188 -> 206; streamed states at 144 MB 28.9 -> 32.0.  The modes with LayerNorm partials or fused logits stand in a chain with kernels that read
+// and write as much again: temporal rows at 90 MB make the prefill 27 -> 24 but the chain 67.9 -> 68.6, streamed output the chain of
+// 20 x 900 216 -> 219.  (As run-time branches in the stores the choice costs 2 to 7 %.)
 enum class Traffic { kCached, kLarge, kStreamed };
 
 // The four input streams of one (batch, head) are read through raw buffer descriptors whose
@@ -230,7 +231,7 @@ template <int kMode, bool kC2, bool kMulti, Traffic kTraffic>
 __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, int pg, int wq, int h,
                                          const Units& un, long long tok_stride, int T) {
     constexpr int kRows = kTraffic == Traffic::kCached ? 0 : kStreamOnce;
-    constexpr int kOutRows = kTraffic == Traffic::kLarge ? kStoreThrough : kStoreThrough | kStreamOnce;
+    constexpr int kOutRows = kTraffic == Traffic::kStreamed ? kStoreThrough | kStreamOnce : kStoreThrough;
     constexpr bool kOutF32 = kMode == 1;
     constexpr bool kMoments = kMode == 3 || kMode == 5;   // bf16 out plus the per-head LayerNorm partials
     constexpr bool kLora = kMode >= 4;           // decay logits from the consumers (LDS), not from x
@@ -873,8 +874,9 @@ hipError_t raise_mode_limits() {
         hipError_t e = set_lds_limit(&chunked_kernel<kMode, kC2, false, Traffic::kCached>, lds_bytes);
         if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, true, Traffic::kCached>, lds_bytes);
         if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, false, Traffic::kLarge>, lds_bytes);
-        if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, false, Traffic::kStreamed>, lds_bytes);
-        if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, true, Traffic::kStreamed>, lds_bytes);
+        if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, true, Traffic::kLarge>, lds_bytes);
+        if constexpr (kMode < 3)
+            if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, true, Traffic::kStreamed>, lds_bytes);
         return e;
     });
 }
@@ -900,14 +902,18 @@ hipError_t launch_mode(const Args& args, hipStream_t stream) {
     const long long row_bytes = kHeadSize * 2 * (kMode >= 4 ? 3 : 4) + kHeadSize * (kMode == 1 ? 4 : 2) + (kC2 ? kHeadSize * 2 : 0);
     const long long mib = static_cast<long long>(a.B) * a.H * (a.T * row_bytes + 2 * 4096 * 4) >> 20;     // the call's rows and states
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds_bytes, stream, a); };
-    if (kMode == 1 && a.unit_stride > 0 && mib >= 90 && mib < 400 && a.T > 128)
-        go(&chunked_kernel<kMode, kC2, true, Traffic::kLarge>);
-    else if (a.unit_stride > 0)
-        mib < 90 ? go(&chunked_kernel<kMode, kC2, true, Traffic::kCached>) : go(&chunked_kernel<kMode, kC2, true, Traffic::kStreamed>);
-    else if (mib < 90)
-        go(&chunked_kernel<kMode, kC2, false, Traffic::kCached>);
-    else
-        mib < 400 ? go(&chunked_kernel<kMode, kC2, false, Traffic::kLarge>) : go(&chunked_kernel<kMode, kC2, false, Traffic::kStreamed>);
+    const bool cached = mib < (kMode >= 3 ? 64 : 90);
+    if (a.unit_stride == 0) {
+        cached ? go(&chunked_kernel<kMode, kC2, false, Traffic::kCached>) : go(&chunked_kernel<kMode, kC2, false, Traffic::kLarge>);
+        return hipGetLastError();
+    }
+    if constexpr (kMode < 3) {
+        if (mib >= 1024) {
+            go(&chunked_kernel<kMode, kC2, true, Traffic::kStreamed>);
+            return hipGetLastError();
+        }
+    }
+    cached ? go(&chunked_kernel<kMode, kC2, true, Traffic::kCached>) : go(&chunked_kernel<kMode, kC2, true, Traffic::kLarge>);
     return hipGetLastError();
 }
 

@@ -120,14 +120,20 @@ def test_sequences_of_one_chunk_take_four_waves_a_unit(fake, make, shortest, B, 
 
 @pytest.mark.parametrize("entry,B,T,H,multi,traffic", [
     ("wkv6_prefill_bf16", 8, 33, 32, False, 0), ("wkv6_prefill_bf16", 8, 520, 32, False, 0), ("wkv6_prefill_bf16", 8, 530, 32, False, 1),
-    ("wkv6_prefill_bf16", 8, 2500, 32, False, 1), ("wkv6_prefill_bf16", 8, 2600, 32, False, 2), ("wkv6_prefill_bf16", 16, 230, 32, True, 0), ("wkv6_prefill_bf16", 16, 240, 32, True, 2),
-    ("wkv6_prefill_bf16_f32out", 16, 110, 32, True, 0), ("wkv6_prefill_bf16_f32out", 32, 80, 32, True, 2), ("wkv6_prefill_bf16_f32out", 32, 128, 32, True, 2),
-    ("wkv6_prefill_bf16_f32out", 32, 129, 32, True, 1), ("wkv6_prefill_bf16_f32out", 32, 480, 32, True, 1), ("wkv6_prefill_bf16_f32out", 32, 500, 32, True, 2),
+    ("wkv6_prefill_bf16", 8, 8000, 32, False, 1), ("wkv6_prefill_bf16", 16, 230, 32, True, 0), ("wkv6_prefill_bf16", 16, 240, 32, True, 1),
+    ("wkv6_prefill_bf16", 64, 760, 32, True, 1), ("wkv6_prefill_bf16", 64, 790, 32, True, 2), ("wkv6_prefill_bf16_f32out", 16, 110, 32, True, 0),
+    ("wkv6_prefill_bf16_f32out", 64, 620, 32, True, 1), ("wkv6_prefill_bf16_f32out", 64, 660, 32, True, 2),
     ("wkv6_finch_c2_prefill_bf16", 16, 190, 32, True, 0), ("wkv6_finch_c2_prefill_bf16", 256, 512, 32, True, 2), ("wkv6_finch_c2_prefill_bf16", 1, 4096, 32, False, 1)])
 def test_cache_policies_by_the_bytes_of_a_call(fake, entry, B, T, H, multi, traffic):
-    """0: less than 90 MiB of rows and states; 2: several calls' worth of the memory-side cache, or several units a workgroup."""
+    """0: less than 90 MiB of rows and states; 2: several units a workgroup and more than a GiB."""
     run = [e for e in lu.events(fake, [lu.time_mix(entry, B, T, H)])[0] if e.kind == "launch"][-1]
     assert run.base == "chunked_kernel" and run.kernel.endswith("%s, (Traffic)%d>" % (str(multi).lower(), traffic)), run.kernel
+
+
+@pytest.mark.parametrize("B,T,multi,traffic", [(8, 340, False, 0), (8, 390, False, 1), (16, 150, True, 0), (16, 170, True, 1), (256, 512, True, 1)])
+def test_cache_policies_of_a_call_inside_a_layer(fake, B, T, multi, traffic):
+    run = [e for e in lu.events(fake, [lu.fused_c2(B, T, 32)])[0] if e.kind == "launch"][-1]
+    assert run.kernel.endswith("%s, (Traffic)%d>" % (str(multi).lower(), traffic)), run.kernel
 
 
 @pytest.mark.parametrize("units,shortest,column_blocks", [(1, 97, 1), (24, 97, 1), (25, 33, 1), (64, 33, 1), (65, 33, 2), (96, 33, 2), (97, 24, 2), (128, 24, 2),
