@@ -83,9 +83,16 @@ __global__ __launch_bounds__(256) void layernorm_finalize_few_kernel(long long t
 typedef unsigned uint4v __attribute__((ext_vector_type(4)));
 constexpr int kInFlight = 4;
 
-template <bool kOutF32>
+// Cache policy of the stores.  bf16 rows of up to 64 MiB leave through the L2 (sc1), as those of the prefill do, but not
+// non-temporal: the product that reads them next finds them in the memory-side cache.  Microseconds, five calls of a layer in a row:
+// 16 x 700 tokens, D = 2048 134 -> 133, 8 x 100 42.8 -> 41.6, 4 x 500 55.5 -> 54.0, 8 x 2048 (64 MiB)
+// 164.2 -> 162.8; alone 16 x 700 17.7 -> 16.2, 8 x 4096 46.9 -> 47.7.  fp32 rows, which leave half a line at a time, stay non-temporal (92 -> 206 written through).
+constexpr int kStoreThrough = 16, kStoreStreamed = 2;
+
+// item `item` of the `items` from `first` on
+template <bool kOutF32, int kStore>
 __device__ __forceinline__ void normalise_item(const uint4v raw, const float2 ms, const float4 g0, const float4 g1,
-                                               const float4 b0, const float4 b1, void* y, long long item) {
+                                               const float4 b0, const float4 b1, void* y, long long first, long long items, int item) {
     const float gm[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
     const float bt[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
     float v[8];
@@ -98,7 +105,7 @@ __device__ __forceinline__ void normalise_item(const uint4v raw, const float2 ms
     for (int i = 0; i < 8; ++i) v[i] = fmaf((v[i] - ms.x) * ms.y, gm[i], bt[i]);
     if constexpr (kOutF32) {
         typedef float float4v __attribute__((ext_vector_type(4)));
-        float4v* dst = static_cast<float4v*>(y) + 2 * item;
+        float4v* dst = static_cast<float4v*>(y) + 2 * (first + item);
         __builtin_nontemporal_store(float4v{v[0], v[1], v[2], v[3]}, dst);
         __builtin_nontemporal_store(float4v{v[4], v[5], v[6], v[7]}, dst + 1);
     } else {
@@ -108,12 +115,14 @@ __device__ __forceinline__ void normalise_item(const uint4v raw, const float2 ms
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             q[i] = __builtin_bit_cast(unsigned, __builtin_convertvector(float2v{v[2 * i], v[2 * i + 1]}, bf16x2));
-        __builtin_nontemporal_store(q, static_cast<uint4v*>(y) + item);
+        const __amdgpu_buffer_rsrc_t rows =
+            __builtin_amdgcn_make_buffer_rsrc(static_cast<uint4v*>(y) + first, 0, static_cast<int>(items * 16), 0x00020000);
+        __builtin_amdgcn_raw_buffer_store_b128(q, rows, 16 * item, 0, kStore);
     }
 }
 
 // grid (token runs, strips of 256 item columns); items_per_token is a multiple of 256
-template <bool kOutF32>
+template <bool kOutF32, int kStore>
 __global__ __launch_bounds__(256) void layernorm_apply_strip_kernel(long long tokens, int tokens_per_block,
                                                                     int items_per_token, const uint4v* o,
                                                                     const float2* mean_rstd, const float4* gamma,
@@ -133,12 +142,12 @@ __global__ __launch_bounds__(256) void layernorm_apply_strip_kernel(long long to
             }
 #pragma unroll
         for (int j = 0; j < kInFlight; ++j)
-            if (t + j < t1) normalise_item<kOutF32>(raw[j], ms[j], g0, g1, b0, b1, y, (t + j) * items_per_token + column);
+            if (t + j < t1) normalise_item<kOutF32, kStore>(raw[j], ms[j], g0, g1, b0, b1, y, (t + j) * items_per_token, items_per_token, column);
     }
 }
 
 // any items_per_token: block b owns items [b * items_per_block, (b + 1) * items_per_block), a multiple of 1024
-template <bool kOutF32>
+template <bool kOutF32, int kStore>
 __global__ __launch_bounds__(256) void layernorm_apply_kernel(long long items, long long items_per_block,
                                                               int items_per_token, const uint4v* o,
                                                               const float2* mean_rstd, const float4* gamma,
@@ -156,8 +165,8 @@ __global__ __launch_bounds__(256) void layernorm_apply_kernel(long long items, l
             if (item < i1) {
                 const long long token = item / items_per_token;
                 const int c8 = static_cast<int>(item - token * items_per_token);
-                normalise_item<kOutF32>(raw[j], mean_rstd[token], gamma[2 * c8], gamma[2 * c8 + 1], beta[2 * c8],
-                                        beta[2 * c8 + 1], y, item);
+                normalise_item<kOutF32, kStore>(raw[j], mean_rstd[token], gamma[2 * c8], gamma[2 * c8 + 1], beta[2 * c8],
+                                        beta[2 * c8 + 1], y, i0, i1 - i0, static_cast<int>(item - i0));
             }
         }
     }
@@ -169,6 +178,7 @@ hipError_t launch_layernorm_apply(long long tokens, int D, const void* o, const 
                                   const float* beta, void* y, bool out_f32, hipStream_t stream) {
     const int items_per_token = D / 8;
     const long long items = tokens * items_per_token;
+    const bool small = items * 16 <= 64ll << 20;
     const int cus = compute_units();
     const uint4v* src = static_cast<const uint4v*>(o);
     const float2* ms = reinterpret_cast<const float2*>(mean_rstd);
@@ -183,12 +193,11 @@ hipError_t launch_layernorm_apply(long long tokens, int D, const void* o, const 
         const int tokens_per_block = static_cast<int>((tokens + runs - 1) / runs);
         const dim3 grid(static_cast<unsigned>((tokens + tokens_per_block - 1) / tokens_per_block),
                         static_cast<unsigned>(strips));
-        if (out_f32)
-            hipLaunchKernelGGL(layernorm_apply_strip_kernel<true>, grid, dim3(256), 0, stream, tokens, tokens_per_block,
-                               items_per_token, src, ms, gm, bt, y);
-        else
-            hipLaunchKernelGGL(layernorm_apply_strip_kernel<false>, grid, dim3(256), 0, stream, tokens, tokens_per_block,
-                               items_per_token, src, ms, gm, bt, y);
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, tokens, tokens_per_block, items_per_token, src, ms, gm, bt, y);
+        };
+        out_f32 ? go(&layernorm_apply_strip_kernel<true, kStoreStreamed>)
+                : small ? go(&layernorm_apply_strip_kernel<false, kStoreThrough>) : go(&layernorm_apply_strip_kernel<false, kStoreStreamed>);
         return hipGetLastError();
     }
     const long long step = kInFlight * 256;
@@ -196,12 +205,11 @@ hipError_t launch_layernorm_apply(long long tokens, int D, const void* o, const 
     long long items_per_block = ((items + blocks - 1) / blocks + step - 1) / step * step;
     blocks = (items + items_per_block - 1) / items_per_block;
     const dim3 grid(static_cast<unsigned>(blocks));
-    if (out_f32)
-        hipLaunchKernelGGL(layernorm_apply_kernel<true>, grid, dim3(256), 0, stream, items, items_per_block,
-                           items_per_token, src, ms, gm, bt, y);
-    else
-        hipLaunchKernelGGL(layernorm_apply_kernel<false>, grid, dim3(256), 0, stream, items, items_per_block,
-                           items_per_token, src, ms, gm, bt, y);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, items, items_per_block, items_per_token, src, ms, gm, bt, y);
+    };
+    out_f32 ? go(&layernorm_apply_kernel<true, kStoreStreamed>)
+            : small ? go(&layernorm_apply_kernel<false, kStoreThrough>) : go(&layernorm_apply_kernel<false, kStoreStreamed>);
     return hipGetLastError();
 }
 
