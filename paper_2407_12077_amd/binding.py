@@ -1,11 +1,13 @@
-"""Thin ctypes binding of ``libwkv6.so``: argument marshalling only.
+"""Thin binding of ``libwkv6.so``: argument marshalling only.
 
 Every entry point has the name and argument order of ``include/wkv6.h``.  Tensors are
 PyTorch-ROCm tensors used purely as device memory (``data_ptr``) and the current HIP
-stream; nothing is computed here.  There is no fallback: if the library is missing,
-loading raises.
+stream; nothing is computed here.  Calls that enqueue work go through the extension ``_call``
+(csrc/binding_call.cpp), the others through ctypes.  There is no fallback: if the library or the
+extension is missing, loading raises.
 """
 import ctypes
+import importlib
 import os
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
@@ -27,6 +29,7 @@ EXPORTS = ("wkv6_prefill_bf16", "wkv6_prefill_bf16_f32out", "wkv6_prefill_bf16_s
            "wkv6_version")
 
 _lib = None
+_call = None               # the extension, bound to _lib
 
 
 class Wkv6Error(RuntimeError):
@@ -35,9 +38,13 @@ class Wkv6Error(RuntimeError):
         self.status = status
 
 
+class _BadNumber(ctypes.ArgumentError, TypeError):
+    pass
+
+
 def load():
     """Load the C-ABI library built by ``paper_2407_12077_amd.build`` (no fallback)."""
-    global _lib
+    global _lib, _call
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise FileNotFoundError(
@@ -90,7 +97,9 @@ def load():
         lib.wkv6_status_string.argtypes = [i]
         lib.wkv6_version.restype = i
         lib.wkv6_version.argtypes = []
-        _lib = lib
+        call = importlib.import_module(__package__ + "._call")
+        call.bind(lib._handle, _check, _current_stream, _BadNumber)
+        _call, _lib = call, lib
     return _lib
 
 
@@ -98,28 +107,23 @@ def status_string(status):
     return load().wkv6_status_string(int(status)).decode()
 
 
-# A call's host time is what a decode step of a few users costs, so marshalling stays small: addresses go
-# through argtypes as plain integers (no ctypes object each), and the current stream's handle comes from torch's
-# raw accessor, which builds no Stream object.  Decode step of one user: 7.8 -> 4.6 us a call.
-def _ptr(t):
-    return None if t is None else t.data_ptr()
+def _bound():
+    load()
+    return _call
 
 
-_raw_stream = None
+def _current_stream():
+    """Handle of torch's current stream.  Once torch has initialised the GPU the extension asks its raw accessors itself;
+    a forked child starts over."""
+    import torch
+    handle = torch.cuda.current_stream().cuda_stream
+    get, device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+    if get is not None and device is not None and torch.cuda.is_initialized():
+        _call.stream_source(get, device)
+    return handle
 
 
-def _stream(stream):
-    global _raw_stream
-    if stream is not None:
-        return int(stream)
-    if _raw_stream is None:
-        import torch
-        get, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), torch.cuda.current_device
-        if get is None:
-            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
-        else:
-            _raw_stream = lambda: get(device())  # noqa: E731
-    return _raw_stream()
+os.register_at_fork(after_in_child=lambda: _call and _call.stream_source(None, None))
 
 
 def _check(status):
@@ -127,43 +131,37 @@ def _check(status):
         raise Wkv6Error(status, status_string(status))
 
 
-def _call(name, B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream, *extra):
-    status = getattr(_lib or load(), name)(B, T, H, N, _ptr(r), _ptr(k), _ptr(v), _ptr(x), _ptr(u), _ptr(state_in),
-                                           _ptr(out), _ptr(state_out), *extra, _stream(stream))
-    if status != WKV6_OK:
-        raise Wkv6Error(status, status_string(status))
-
-
 def wkv6_prefill_bf16(B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream=None):
-    _call("wkv6_prefill_bf16", B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream)
+    (_call or _bound()).wkv6_prefill_bf16(B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream)
 
 
 def wkv6_prefill_bf16_f32out(B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream=None):
-    _call("wkv6_prefill_bf16_f32out", B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream)
+    (_call or _bound()).wkv6_prefill_bf16_f32out(B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream)
 
 
 def wkv6_prefill_bf16_strided(B, T, H, N, r, k, v, x, u, state_in, out, state_out,
                               batch_stride, out_dtype, stream=None):
-    _call("wkv6_prefill_bf16_strided", B, T, H, N, r, k, v, x, u, state_in, out, state_out,
-          stream, ctypes.c_longlong(batch_stride), int(out_dtype))
+    (_call or _bound()).wkv6_prefill_bf16_strided(B, T, H, N, r, k, v, x, u, state_in, out, state_out, batch_stride,
+                                                  int(out_dtype), stream)
 
 
 def wkv6_prefill_bf16_split(B, T, H, N, r, k, v, x, u, state_in, out, state_out, out_dtype,
                             segments, workspace, workspace_bytes, stream=None):
-    _call("wkv6_prefill_bf16_split", B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream,
-          int(out_dtype), int(segments), _ptr(workspace), ctypes.c_longlong(workspace_bytes))
+    (_call or _bound()).wkv6_prefill_bf16_split(B, T, H, N, r, k, v, x, u, state_in, out, state_out, int(out_dtype),
+                                                int(segments), workspace, workspace_bytes, stream)
 
 
 def wkv6_prefill_bf16_split_noalloc(B, T, H, N, r, k, v, x, u, state_in, out, state_out, out_dtype,
                                     segments, stream=None):
-    _call("wkv6_prefill_bf16_split_noalloc", B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream,
-          int(out_dtype), int(segments))
+    (_call or _bound()).wkv6_prefill_bf16_split_noalloc(B, T, H, N, r, k, v, x, u, state_in, out, state_out,
+                                                        int(out_dtype), int(segments), stream)
 
 
 def wkv6_finch_c2_prefill_bf16_split(B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out,
                                      out_dtype, segments, workspace, workspace_bytes, stream=None):
-    _call("wkv6_finch_c2_prefill_bf16_split", B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out,
-          stream, int(out_dtype), int(segments), _ptr(workspace), ctypes.c_longlong(workspace_bytes))
+    (_call or _bound()).wkv6_finch_c2_prefill_bf16_split(B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out,
+                                                         int(out_dtype), int(segments), workspace, workspace_bytes,
+                                                         stream)
 
 
 def wkv6_split_workspace_bytes(B, T, H, N, segments):
@@ -184,85 +182,77 @@ def wkv6_arena_layout(sizes):
 
 
 def wkv6_prefill_f32(B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream=None):
-    _call("wkv6_prefill_f32", B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream)
+    (_call or _bound()).wkv6_prefill_f32(B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream)
 
 
 def wkv6_prefill_bf16_recurrent(B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream=None):
-    _call("wkv6_prefill_bf16_recurrent", B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream)
+    (_call or _bound()).wkv6_prefill_bf16_recurrent(B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream)
 
 
 def wkv6_finch_c2_prefill_bf16(B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out, stream=None):
-    _call("wkv6_finch_c2_prefill_bf16", B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out, stream)
+    (_call or _bound()).wkv6_finch_c2_prefill_bf16(B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out, stream)
 
 
 def wkv6_finch_c2_prefill_bf16_f32out(B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out,
                                       stream=None):
-    _call("wkv6_finch_c2_prefill_bf16_f32out", B, T, H, N, r, kbar, v, x, uprime, state_in, out,
-          state_out, stream)
+    (_call or _bound()).wkv6_finch_c2_prefill_bf16_f32out(B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out,
+                                                          stream)
 
 
 def wkv6_finch_c2_prefill_bf16_strided(B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out,
                                        batch_stride, out_dtype, stream=None):
-    _call("wkv6_finch_c2_prefill_bf16_strided", B, T, H, N, r, kbar, v, x, uprime, state_in, out,
-          state_out, stream, ctypes.c_longlong(batch_stride), int(out_dtype))
+    (_call or _bound()).wkv6_finch_c2_prefill_bf16_strided(B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out,
+                                                           batch_stride, int(out_dtype), stream)
 
 
 def wkv6_finch_c2_prefill_bf16_moments(B, T, H, N, r, kbar, v, x, uprime, state_in, out, moments, state_out,
                                        stream=None):
-    _check((_lib or load()).wkv6_finch_c2_prefill_bf16_moments(
-        B, T, H, N, _ptr(r), _ptr(kbar), _ptr(v), _ptr(x), _ptr(uprime), _ptr(state_in), _ptr(out),
-        _ptr(moments), _ptr(state_out), _stream(stream)))
+    (_call or _bound()).wkv6_finch_c2_prefill_bf16_moments(B, T, H, N, r, kbar, v, x, uprime, state_in, out, moments,
+                                                           state_out, stream)
 
 
 def wkv6_finch_c2_prefill_lora_bf16(B, T, H, N, R, r, kbar, v, y, lam, b_omega, uprime, state_in, out, moments,
                                     state_out, stream=None):
-    _check((_lib or load()).wkv6_finch_c2_prefill_lora_bf16(
-        B, T, H, N, R, _ptr(r), _ptr(kbar), _ptr(v), _ptr(y), _ptr(lam), _ptr(b_omega), _ptr(uprime),
-        _ptr(state_in), _ptr(out), _ptr(moments), _ptr(state_out), _stream(stream)))
+    (_call or _bound()).wkv6_finch_c2_prefill_lora_bf16(B, T, H, N, R, r, kbar, v, y, lam, b_omega, uprime, state_in,
+                                                        out, moments, state_out, stream)
 
 
 def wkv6_prefill_lora_bf16(B, T, H, N, R, r, k, v, y, lam, b_omega, u, state_in, out, state_out, stream=None):
-    _check((_lib or load()).wkv6_prefill_lora_bf16(
-        B, T, H, N, R, _ptr(r), _ptr(k), _ptr(v), _ptr(y), _ptr(lam), _ptr(b_omega), _ptr(u), _ptr(state_in),
-        _ptr(out), _ptr(state_out), _stream(stream)))
+    (_call or _bound()).wkv6_prefill_lora_bf16(B, T, H, N, R, r, k, v, y, lam, b_omega, u, state_in, out, state_out,
+                                               stream)
 
 
 def wkv6_decay_lora_input_bf16(B, T, D, R_d, R, x, x_prev, mu_x, lambda_d, a_d, b_d, a_omega, y, out_dtype, stream=None):
-    _check((_lib or load()).wkv6_decay_lora_input_bf16(B, T, D, R_d, R, _ptr(x), _ptr(x_prev), _ptr(mu_x), _ptr(lambda_d),
-                                             _ptr(a_d), _ptr(b_d), _ptr(a_omega), _ptr(y), int(out_dtype),
-                                             _stream(stream)))
+    (_call or _bound()).wkv6_decay_lora_input_bf16(B, T, D, R_d, R, x, x_prev, mu_x, lambda_d, a_d, b_d, a_omega, y,
+                                                   int(out_dtype), stream)
 
 
 def wkv6_layernorm_apply_bf16(B, T, H, N, o, mean_rstd, gamma, beta, y, out_dtype, stream=None):
-    _check((_lib or load()).wkv6_layernorm_apply_bf16(B, T, H, N, _ptr(o), _ptr(mean_rstd), _ptr(gamma), _ptr(beta), _ptr(y),
-                                            int(out_dtype), _stream(stream)))
+    (_call or _bound()).wkv6_layernorm_apply_bf16(B, T, H, N, o, mean_rstd, gamma, beta, y, int(out_dtype), stream)
 
 
 def wkv6_layernorm_finalize(B, T, H, N, moments, eps, mean_rstd, stream=None):
-    _check((_lib or load()).wkv6_layernorm_finalize(B, T, H, N, _ptr(moments), eps, _ptr(mean_rstd),
-                                          _stream(stream)))
+    (_call or _bound()).wkv6_layernorm_finalize(B, T, H, N, moments, eps, mean_rstd, stream)
 
 
 def wkv6_append_bf16(B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream=None):
-    _call("wkv6_append_bf16", B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream)
+    (_call or _bound()).wkv6_append_bf16(B, T, H, N, r, k, v, x, u, state_in, out, state_out, stream)
 
 
 def wkv6_finch_c2_append_bf16(B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out, stream=None):
-    _call("wkv6_finch_c2_append_bf16", B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out, stream)
+    (_call or _bound()).wkv6_finch_c2_append_bf16(B, T, H, N, r, kbar, v, x, uprime, state_in, out, state_out, stream)
 
 
 def wkv6_decode_bf16(B, H, N, r, k, v, x, u, state, out, stream=None):
-    _check((_lib or load()).wkv6_decode_bf16(B, H, N, _ptr(r), _ptr(k), _ptr(v), _ptr(x), _ptr(u), _ptr(state),
-                                   _ptr(out), _stream(stream)))
+    (_call or _bound()).wkv6_decode_bf16(B, H, N, r, k, v, x, u, state, out, stream)
 
 
 def wkv6_finch_c2_decode_bf16(B, H, N, r, kbar, v, x, uprime, state, out, stream=None):
-    _check((_lib or load()).wkv6_finch_c2_decode_bf16(B, H, N, _ptr(r), _ptr(kbar), _ptr(v), _ptr(x), _ptr(uprime),
-                                            _ptr(state), _ptr(out), _stream(stream)))
+    (_call or _bound()).wkv6_finch_c2_decode_bf16(B, H, N, r, kbar, v, x, uprime, state, out, stream)
 
 
 def wkv6_key_compress_bf16(M, D, x, w_kd, c, out_dtype, stream=None):
-    _check((_lib or load()).wkv6_key_compress_bf16(M, D, _ptr(x), _ptr(w_kd), _ptr(c), int(out_dtype), _stream(stream)))
+    (_call or _bound()).wkv6_key_compress_bf16(M, D, x, w_kd, c, int(out_dtype), stream)
 
 
 def wkv6_version():
