@@ -388,7 +388,8 @@ int wkv6_key_compress_bf16(long long M, int D, const void *x, const void *w_kd, 
                            int out_dtype, void *stream);
 
 /* All-fp32 tensors, fp32 arithmetic throughout: token by token, and from 24 to 97 tokens on (by the number of (batch, head)
- * units) in chunks of 16 on the fp32 matrix cores. */
+ * units) in chunks of 16 on the fp32 matrix cores.  With at most 64 units, from some 210 to 330 tokens on, two kernels: the first leaves
+ * the chunks' scores in rows of `out` that the second overwrites; `out` holds no partial result after it. */
 int wkv6_prefill_f32(int B, int T, int H, int N,
                      const float *r, const float *k, const float *v, const float *x,
                      const float *u, const float *state_in,

@@ -17,6 +17,12 @@
 // of a round (one per producer) while the producers make the next round's: one barrier per round, two slots per producer.
 // With kCB < 4 the partial read-outs of the key parts are added, and stored, by the producers one round later.
 //
+// Few units and many tokens (the rule is at the launch): a kernel of its own makes the scores first, a wave a chunk over the whole
+// chip, and leaves them in the rows of `out` that the column groups write later, a copy for each: 16 scores a token are
+// the 16 columns of a group.  The producers then only read them.  The same bits: 32 units x 512 tokens 31.7 -> 25.2 us, x 2048 112 -> 76; what is
+// left per chunk is the producers' decays and the consumers' state products, 1100 clocks of a SIMD, vector and matrix
+// instructions in turn.  (Rows fetched two rounds ahead instead of one: no gain, 25.9.)
+//
 // Bound by the vector ALUs: the fp32 matrix instructions run at twice their rate but do not overlap with them.  Per chunk a
 // workgroup issues about 2900 clocks of vector work, 1024 of scores and 1152 kCB / 4 of state work per wave, over four
 // SIMDs; a unit's column groups repeat the producers' part, so columns are spread only while compute units are idle.  The token-by-token
@@ -121,10 +127,108 @@ __device__ __forceinline__ int here(int v) {
     return v;
 }
 
-template <int kCB, int kProducers>
+// The scores of a chunk, bonus on the diagonal, into the slot (which has zeros above the diagonal); the level tiles pass through
+// the r W and k W of the slot.  kStaged: the compiler keeps the stages apart.  Without it registers are short where the
+// next chunk's rows have their own, and the addresses are formed here (kept from outside, 16 registers spill: 32 -> 39 us).
+template <bool kStaged>
+__device__ __forceinline__ void chunk_scores(const float (&r)[kChunk], const float (&k)[kChunk], const float (&ex)[kChunk],
+                                             const float (&w)[kChunk], float u, char* slot, int lane) {
+    const int ln = kStaged ? lane : here(lane);
+    const int l16 = ln & 15, g4 = ln >> 4;
+    auto put = [&](int row, float v) { *reinterpret_cast<float*>(slot + row * kRow + 4 * ln) = v; };     // this lane's channel of a row
+    auto stage_end = [] {
+        if constexpr (kStaged) __builtin_amdgcn_sched_barrier(0);
+    };
+    // decays between a token and the middle of its 8-token half's block: behind a key, in front of a query
+    float behind[8], before[8];
+    behind[7] = before[0] = 1.f;
+    float after = 0.f, until = 0.f;
+#pragma unroll
+    for (int i = 6; i >= 0; --i) behind[i] = decay_over(after += ex[i + 1]);
+#pragma unroll
+    for (int i = 1; i < 8; ++i) before[i] = decay_over(until += ex[7 + i]);
+    // levels 8 and 4: query rows 0..7 are tokens 8.., rows 8..15 tokens 4..7 and 12..15; key rows (16 on) 0..7 and 0..3, 8..11
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        put(j, r[8 + j] * before[j]);
+        put(16 + j, k[j] * behind[j]);
+    }
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        const int b = 8 * half;
+        const float s2 = w[b + 3], s1 = w[b + 2] * s2, s0 = w[b + 1] * s1;
+        const float q1 = w[b + 4], q2 = q1 * w[b + 5], q3 = q2 * w[b + 6];
+        put(24 + 4 * half, k[b] * s0);
+        put(25 + 4 * half, k[b + 1] * s1);
+        put(26 + 4 * half, k[b + 2] * s2);
+        put(27 + 4 * half, k[b + 3]);
+        put(8 + 4 * half, r[b + 4]);
+        put(9 + 4 * half, r[b + 5] * q1);
+        put(10 + 4 * half, r[b + 6] * q2);
+        put(11 + 4 * half, r[b + 7] * q3);
+    }
+    wave_lds_order();
+    // product of the tile: rows (registers) are keys, columns (lanes) queries
+    auto scores = [&] {
+        float4v sum[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4v qv = *reinterpret_cast<const float4v*>(slot + l16 * kRow + 64 * q + 16 * g4);
+            const float4v kv = *reinterpret_cast<const float4v*>(slot + (16 + l16) * kRow + 64 * q + 16 * g4);
+            sum[q] = four(kv, qv);
+        }
+        return (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    };
+    const float4v s84 = scores();
+    wave_lds_order();
+    stage_end();
+    // levels 2 and 1: query rows 0..7 are tokens 2, 3, 6, 7, .., rows 8..15 the odd ones; keys 0, 1, 4, 5, .. and the even ones
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        put(2 * b, r[4 * b + 2]);
+        put(2 * b + 1, r[4 * b + 3] * w[4 * b + 2]);
+        put(16 + 2 * b, k[4 * b] * w[4 * b + 1]);
+        put(16 + 2 * b + 1, k[4 * b + 1]);
+    }
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        put(8 + m, r[2 * m + 1]);
+        put(24 + m, k[2 * m]);
+    }
+    wave_lds_order();
+    const float4v s21 = scores();
+    wave_lds_order();
+    stage_end();
+    // bonus on the diagonal
+    float diag[kChunk];
+#pragma unroll
+    for (int t = 0; t < kChunk; ++t) diag[t] = r[t] * u * k[t];
+    const float dg = sum_scatter16(diag, lane);
+    // the scores where the two of a pair meet: a lane has four keys of its query
+    auto put_score = [&](int t, int i, float v) { *reinterpret_cast<float*>(slot + kOffA + token_off(t, i & 3) + 4 * (i >> 2)) = v; };
+    if (l16 < 8 && g4 < 2) {                         // level 8
+#pragma unroll
+        for (int e = 0; e < 4; ++e) put_score(8 + l16, 4 * g4 + e, s84[e]);
+    }
+    if (l16 >= 8 && g4 == 2 + ((l16 >> 2) & 1)) {    // level 4
+#pragma unroll
+        for (int e = 0; e < 4; ++e) put_score(l16 < 12 ? l16 - 4 : l16, (l16 < 12 ? 0 : 8) + e, s84[e]);
+    }
+    if (l16 < 8 && g4 == (l16 >> 2)) {               // level 2
+        const int blk = l16 >> 1;
+        put_score(4 * blk + 2 + (l16 & 1), 4 * blk, blk & 1 ? s21[2] : s21[0]);
+        put_score(4 * blk + 2 + (l16 & 1), 4 * blk + 1, blk & 1 ? s21[3] : s21[1]);
+    }
+    if (l16 >= 8 && g4 == (l16 >> 2)) {              // level 1
+        const int m = l16 - 8, e = l16 & 3;
+        put_score(2 * m + 1, 2 * m, e == 0 ? s21[0] : e == 1 ? s21[1] : e == 2 ? s21[2] : s21[3]);
+    }
+    if ((lane & 3) == 0) put_score(lane >> 2, lane >> 2, dg);
+}
+
+template <int kCB, int kProducers, bool kScored>
 __device__ __forceinline__ void producer(const Args& a, char* lds, int lane, int p, int h, long long base, int col0, int nrounds) {
     using SH = Shape<kCB, kProducers>;
-    const int l16 = lane & 15, g4 = lane >> 4;
     const long long row_bytes = static_cast<long long>(a.H) * (kHeadSize * 4);
     const long long span = static_cast<long long>(a.T - 1) * row_bytes + kHeadSize * 4;
     const int nchunks = (a.T + kChunk - 1) / kChunk;
@@ -144,6 +248,14 @@ __device__ __forceinline__ void producer(const Args& a, char* lds, int lane, int
     };
     struct Raw {
         float r[kChunk], k[kChunk], x[kChunk];
+        float4v score;                                       // token lane >> 2, granule lane & 3
+    };
+    auto fetch_score = [&](float4v& d, int c) {
+        if constexpr (kScored) {
+            const __amdgpu_buffer_rsrc_t rs = chunk_rsrc(static_cast<const char*>(a.out) + base * 4, c < nchunks ? c * (kChunk * row_bytes) : span, span);
+            d = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(
+                                                rs, static_cast<int>((lane >> 2) * row_bytes) + (col0 + 4 * (lane & 3)) * 4, 0, 0));
+        }
     };
     auto round = [&](int rd, Raw& raw, Raw& next) {
         float(&r)[kChunk] = raw.r, (&k)[kChunk] = raw.k, (&x)[kChunk] = raw.x;
@@ -171,6 +283,7 @@ __device__ __forceinline__ void producer(const Args& a, char* lds, int lane, int
                 fetch(next.x, a.x, c + kProducers);
                 fetch(next.r, a.r, c + kProducers);
                 fetch(next.k, a.k, c + kProducers);
+                fetch_score(next.score, c + kProducers);
             }
             float ex[kChunk], w[kChunk];                     // w = 2^-ex
 #pragma unroll
@@ -181,92 +294,9 @@ __device__ __forceinline__ void producer(const Args& a, char* lds, int lane, int
             }
             if constexpr (!kTwoSets) fetch(x, a.x, c + kProducers);
             stage_end();
-            // decays between a token and the middle of its 8-token half's block: behind a key, in front of a query
-            float behind[8], before[8];
-            behind[7] = before[0] = 1.f;
-            float after = 0.f, until = 0.f;
-#pragma unroll
-            for (int i = 6; i >= 0; --i) behind[i] = decay_over(after += ex[i + 1]);
-#pragma unroll
-            for (int i = 1; i < 8; ++i) before[i] = decay_over(until += ex[7 + i]);
-            // levels 8 and 4: query rows 0..7 are tokens 8.., rows 8..15 tokens 4..7 and 12..15; key rows (16 on) 0..7 and 0..3, 8..11
+            if constexpr (kScored) *reinterpret_cast<float4v*>(slot + kOffA + token_off(lane >> 2, lane & 3)) = raw.score;
+            else chunk_scores<!kTwoSets>(r, k, ex, w, u, slot, lane);
             auto put = [&](int row, float v) { *reinterpret_cast<float*>(slot + row * kRow + 4 * lane) = v; };     // this lane's channel of a row
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                put(j, r[8 + j] * before[j]);
-                put(16 + j, k[j] * behind[j]);
-            }
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const int b = 8 * half;
-                const float s2 = w[b + 3], s1 = w[b + 2] * s2, s0 = w[b + 1] * s1;
-                const float q1 = w[b + 4], q2 = q1 * w[b + 5], q3 = q2 * w[b + 6];
-                put(24 + 4 * half, k[b] * s0);
-                put(25 + 4 * half, k[b + 1] * s1);
-                put(26 + 4 * half, k[b + 2] * s2);
-                put(27 + 4 * half, k[b + 3]);
-                put(8 + 4 * half, r[b + 4]);
-                put(9 + 4 * half, r[b + 5] * q1);
-                put(10 + 4 * half, r[b + 6] * q2);
-                put(11 + 4 * half, r[b + 7] * q3);
-            }
-            wave_lds_order();
-            // product of the tile: rows (registers) are keys, columns (lanes) queries
-            auto scores = [&] {
-                float4v sum[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float4v qv = *reinterpret_cast<const float4v*>(slot + l16 * kRow + 64 * q + 16 * g4);
-                    const float4v kv = *reinterpret_cast<const float4v*>(slot + (16 + l16) * kRow + 64 * q + 16 * g4);
-                    sum[q] = four(kv, qv);
-                }
-                return (sum[0] + sum[1]) + (sum[2] + sum[3]);
-            };
-            const float4v s84 = scores();
-            wave_lds_order();
-            stage_end();
-            // levels 2 and 1: query rows 0..7 are tokens 2, 3, 6, 7, .., rows 8..15 the odd ones; keys 0, 1, 4, 5, .. and the even ones
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                put(2 * b, r[4 * b + 2]);
-                put(2 * b + 1, r[4 * b + 3] * w[4 * b + 2]);
-                put(16 + 2 * b, k[4 * b] * w[4 * b + 1]);
-                put(16 + 2 * b + 1, k[4 * b + 1]);
-            }
-#pragma unroll
-            for (int m = 0; m < 8; ++m) {
-                put(8 + m, r[2 * m + 1]);
-                put(24 + m, k[2 * m]);
-            }
-            wave_lds_order();
-            const float4v s21 = scores();
-            wave_lds_order();
-            stage_end();
-            // bonus on the diagonal
-            float diag[kChunk];
-#pragma unroll
-            for (int t = 0; t < kChunk; ++t) diag[t] = r[t] * u * k[t];
-            const float dg = sum_scatter16(diag, lane);
-            // the scores where the two of a pair meet: a lane has four keys of its query
-            auto put_score = [&](int t, int i, float v) { *reinterpret_cast<float*>(slot + kOffA + token_off(t, i & 3) + 4 * (i >> 2)) = v; };
-            if (l16 < 8 && g4 < 2) {                         // level 8
-#pragma unroll
-                for (int e = 0; e < 4; ++e) put_score(8 + l16, 4 * g4 + e, s84[e]);
-            }
-            if (l16 >= 8 && g4 == 2 + ((l16 >> 2) & 1)) {    // level 4
-#pragma unroll
-                for (int e = 0; e < 4; ++e) put_score(l16 < 12 ? l16 - 4 : l16, (l16 < 12 ? 0 : 8) + e, s84[e]);
-            }
-            if (l16 < 8 && g4 == (l16 >> 2)) {               // level 2
-                const int blk = l16 >> 1;
-                put_score(4 * blk + 2 + (l16 & 1), 4 * blk, blk & 1 ? s21[2] : s21[0]);
-                put_score(4 * blk + 2 + (l16 & 1), 4 * blk + 1, blk & 1 ? s21[3] : s21[1]);
-            }
-            if (l16 >= 8 && g4 == (l16 >> 2)) {              // level 1
-                const int m = l16 - 8, e = l16 & 3;
-                put_score(2 * m + 1, 2 * m, e == 0 ? s21[0] : e == 1 ? s21[1] : e == 2 ? s21[2] : s21[3]);
-            }
-            if ((lane & 3) == 0) put_score(lane >> 2, lane >> 2, dg);
             // r W(t,-1), k W(16,i) and the chunk's decay
             stage_end();
             // each decay from the sum of its exponents: one rounding that matters where a product of 15 has 14
@@ -290,6 +320,7 @@ __device__ __forceinline__ void producer(const Args& a, char* lds, int lane, int
                 stage_end();
                 fetch(r, a.r, c + kProducers);
                 fetch(k, a.k, c + kProducers);
+                fetch_score(raw.score, c + kProducers);
             }
         }
         __syncthreads();                                     // round barrier
@@ -298,6 +329,7 @@ __device__ __forceinline__ void producer(const Args& a, char* lds, int lane, int
     fetch(raw0.x, a.x, p);
     fetch(raw0.r, a.r, p);
     fetch(raw0.k, a.k, p);
+    fetch_score(raw0.score, p);
     int rd = 0;
     if constexpr (kTwoSets) {
         Raw raw1;
@@ -440,10 +472,9 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds, int lane, int
     }
 }
 
-template <int kCB, int kProducers>
-__global__ __launch_bounds__((Shape<kCB, kProducers>::kThreads)) void chunked_f32_kernel(Args a) {
+template <int kCB, int kProducers, bool kScored>
+__device__ __forceinline__ void chunks_of_a_unit(const Args& a, char* lds) {
     using SH = Shape<kCB, kProducers>;
-    extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroups go round the 8 XCDs by index: a unit's column groups take consecutive turns of one XCD, so that r, k and x
@@ -459,19 +490,90 @@ __global__ __launch_bounds__((Shape<kCB, kProducers>::kThreads)) void chunked_f3
     const int nrounds = (nchunks + kProducers - 1) / kProducers + (SH::kKeyParts > 1 ? 2 : 1);
     if (wave < kProducers) {
         __syncthreads();                                     // start barrier
-        producer<kCB, kProducers>(a, lds, lane, wave, h, base, col0, nrounds);
+        producer<kCB, kProducers, kScored>(a, lds, lane, wave, h, base, col0, nrounds);
     } else {
         consumer<kCB, kProducers>(a, lds, lane, wave - kProducers, unit, base, col0, nrounds);
+    }
+}
+
+template <int kCB, int kProducers>
+__global__ __launch_bounds__((Shape<kCB, kProducers>::kThreads)) void chunked_f32_kernel(Args a) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    chunks_of_a_unit<kCB, kProducers, false>(a, lds);
+}
+
+// Few units and many tokens: the scores come from a kernel of their own, below, that all compute units share in
+template <int kCB, int kProducers>
+__global__ __launch_bounds__((Shape<kCB, kProducers>::kThreads)) void chunked_f32_scored_kernel(Args a) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    chunks_of_a_unit<kCB, kProducers, true>(a, lds);
+}
+
+// The scores of every chunk of every unit, a wave a chunk, into `out`: row t of a chunk holds its 16 scores in the granules of
+// token_off, once for each column group that will read them (and then write its outputs over them).
+constexpr int kScoreWaves = 4;
+constexpr long long kMaxScoreGroups = 1 << 20;       // workgroups; their waves go on to further chunks
+__global__ __launch_bounds__(64 * kScoreWaves) void chunked_f32_scores_kernel(Args a, int group_columns) {
+    __shared__ __attribute__((aligned(16))) char lds[kScoreWaves * kSlotBytes];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    char* slot = lds + wave * kSlotBytes;
+    const int t = lane >> 2, quad = lane & 3;
+    *reinterpret_cast<float4v*>(slot + kOffA + token_off(t, quad)) = float4v{0.f, 0.f, 0.f, 0.f};
+    const int nchunks = (a.T + kChunk - 1) / kChunk;
+    const long long row_bytes = static_cast<long long>(a.H) * (kHeadSize * 4);
+    const long long span = static_cast<long long>(a.T - 1) * row_bytes + kHeadSize * 4;
+    const long long jobs = static_cast<long long>(a.B) * a.H * nchunks, step = static_cast<long long>(gridDim.x) * kScoreWaves;
+#pragma clang loop unroll(disable)
+    for (long long job = static_cast<long long>(blockIdx.x) * kScoreWaves + wave; job < jobs; job += step) {
+        const int unit = static_cast<int>(job / nchunks), c = static_cast<int>(job - static_cast<long long>(unit) * nchunks);
+        const int b = unit / a.H, h = unit - b * a.H;
+        const long long base = static_cast<long long>(b) * a.batch_stride + static_cast<long long>(h) * kHeadSize;
+        float r[kChunk], k[kChunk], x[kChunk], ex[kChunk], w[kChunk];
+        auto fetch = [&](float (&d)[kChunk], const void* src) {
+            const __amdgpu_buffer_rsrc_t rs = chunk_rsrc(static_cast<const char*>(src) + base * 4, c * (kChunk * row_bytes), span);
+#pragma unroll
+            for (int i = 0; i < kChunk; ++i) d[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, static_cast<int>(i * row_bytes) + 4 * lane, 0, 0));
+        };
+        fetch(x, a.x);
+        fetch(r, a.r);
+        fetch(k, a.k);
+        const float u = a.u[h * kHeadSize + lane];
+#pragma unroll
+        for (int i = 0; i < kChunk; ++i) {
+            ex[i] = exponent_of(x[i]);
+            if (c * kChunk + i >= a.T) ex[i] = 0.f;
+            w[i] = decay_over(ex[i]);
+        }
+        chunk_scores<false>(r, k, ex, w, u, slot, lane);
+        wave_lds_order();
+        const uint4v row = *reinterpret_cast<const uint4v*>(slot + kOffA + token_off(t, quad));
+        const __amdgpu_buffer_rsrc_t ro = chunk_rsrc(static_cast<const char*>(a.out) + base * 4, c * (kChunk * row_bytes), span);
+        for (int col = 0; col < kHeadSize; col += group_columns)
+            __builtin_amdgcn_raw_buffer_store_b128(row, ro, static_cast<int>(t * row_bytes) + (col + 4 * quad) * 4, 0, 0);
+        wave_lds_order();
     }
 }
 
 }  // namespace
 
 template <int kCB, int kProducers>
-hipError_t launch_cb(const Args& a, hipStream_t stream) {
+hipError_t launch_cb(const Args& a, bool scored, hipStream_t stream) {
     using SH = Shape<kCB, kProducers>;
     const unsigned units = (static_cast<unsigned>(a.B) * static_cast<unsigned>(a.H) + 7) / 8 * 8;
-    hipLaunchKernelGGL((chunked_f32_kernel<kCB, kProducers>), dim3(units * SH::kKeyParts), dim3(SH::kThreads), SH::kLds, stream, a);
+    const dim3 grid(units * SH::kKeyParts), block(SH::kThreads);
+    if constexpr (kCB == 1) {
+        if (scored) {
+            const long long groups = (static_cast<long long>(a.B) * a.H * ((a.T + kChunk - 1) / kChunk) + kScoreWaves - 1) / kScoreWaves;
+            hipLaunchKernelGGL(chunked_f32_scores_kernel, dim3(static_cast<unsigned>(groups < kMaxScoreGroups ? groups : kMaxScoreGroups)),
+                               dim3(64 * kScoreWaves), 0, stream, a, 16 * kCB);
+            const hipError_t err = hipGetLastError();
+            if (err != hipSuccess) return err;
+            hipLaunchKernelGGL((chunked_f32_scored_kernel<kCB, kProducers>), grid, block, SH::kLds, stream, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((chunked_f32_kernel<kCB, kProducers>), grid, block, SH::kLds, stream, a);
     return hipGetLastError();
 }
 
@@ -479,6 +581,7 @@ hipError_t raise_chunked_f32_limits() {
     struct Tag {};
     return once_per_device<Tag>([] {
         hipError_t e = set_lds_limit(&chunked_f32_kernel<1, 4>, Shape<1, 4>::kLds);
+        if (e == hipSuccess) e = set_lds_limit(&chunked_f32_scored_kernel<1, 4>, Shape<1, 4>::kLds);
         if (e == hipSuccess) e = set_lds_limit(&chunked_f32_kernel<2, 4>, Shape<2, 4>::kLds);
         if (e == hipSuccess) e = set_lds_limit(&chunked_f32_kernel<4, 4>, Shape<4, 4>::kLds);
         return e;
@@ -490,9 +593,14 @@ hipError_t launch_chunked_f32(const Args& a, hipStream_t stream) {
     if (err != hipSuccess) return err;
     // as many workgroups as fit the chip once
     const long long units = static_cast<long long>(a.B) * a.H;
-    if (units <= 64) return launch_cb<1, 4>(a, stream);
-    if (units <= 128) return launch_cb<2, 4>(a, stream);
-    return launch_cb<4, 4>(a, stream);
+    // Scores in a kernel of their own: a launch more (2 to 3 us) against 0.4 us a chunk, and the more units the longer that
+    // kernel takes itself.  Microseconds, one kernel : two: 4 units 192 tokens 14.1 : 14.4, 224 16.9 : 15.7; 16 units 192
+    // 14.4 : 14.7, 224 17.3 : 15.9; 32 units 224 17.4 : 16.5, 256 18.0 : 17.1, 512 31.7 : 25.3, 2048 112 : 76; 48 units 256 18.1 : 17.9,
+    // 320 21.5 : 20.1; 64 units 256 18.4 : 18.5, 320 21.7 : 22.1, 512 32.1 : 28.8, 2048 122 : 102.  With two or four column blocks a workgroup
+    // the producers' part is hardly repeated and one kernel is the better one: 128 units x 512 37.8 : 42.2, 256 x 512 52.5 : 75.
+    if (units <= 64) return launch_cb<1, 4>(a, a.T >= 200 + 2 * units, stream);
+    if (units <= 128) return launch_cb<2, 4>(a, false, stream);
+    return launch_cb<4, 4>(a, false, stream);
 }
 
 }  // namespace wkv6

@@ -34,6 +34,32 @@ def test_edges_of_chunks_and_rounds(B, H, T):
     assert max_norm_err(o, o_ref) <= TOL_F32 and max_norm_err(s, s_ref) <= TOL_F32
 
 
+# scores from a kernel of their own: the shortest such sequences of few units, chunks that end inside, rounds of four chunks
+@pytest.mark.parametrize("B,H,T", [(1, 1, 201), (1, 1, 202), (3, 1, 209), (2, 16, 264), (4, 8, 271), (32, 1, 319), (1, 64, 327), (1, 64, 328), (2, 32, 385), (1, 5, 1023)])
+@pytest.mark.parametrize("state", [False, True])
+def test_scores_handed_over_in_rows_of_out(B, H, T, state):
+    inp = inputs(B, T, H, T, state)
+    o, s = run(inp)
+    o_ref, s_ref = wkv6_oracle(**inp)
+    assert max_norm_err(o, o_ref) <= TOL_F32 and max_norm_err(s, s_ref) <= TOL_F32
+
+
+@pytest.mark.parametrize("name,value", [("v", np.inf), ("k", np.nan), ("r", np.inf), ("x", np.nan)])
+def test_a_value_that_is_not_finite_with_scores_handed_over(name, value):
+    """What came before the value has the bits that it has without it."""
+    inp = inputs(1, 320, 4, 5)
+    inp["x"] = inp["x"].clip(-6, -1)
+    clean = run(inp)
+    inp[name][0, 231, 2, 37] = value
+    o, s = run(inp)
+    with np.errstate(all="ignore"):
+        o_ref, s_ref = wkv6_oracle(**inp)
+    for got, ref in ((o, o_ref), (s, s_ref)):
+        assert (np.isfinite(got) == np.isfinite(ref)).all()
+        assert max_norm_err(got[np.isfinite(ref)], ref[np.isfinite(ref)]) <= TOL_F32
+    assert np.array_equal(o[0, :231], clean[0][0, :231])
+
+
 @pytest.mark.parametrize("B,H,T", [(25, 1, 33), (25, 1, 48), (5, 16, 49), (100, 1, 24), (100, 1, 25), (200, 1, 24), (200, 1, 31), (300, 1, 48), (300, 1, 63)])
 def test_shortest_sequences(B, H, T):
     inp = inputs(B, T, H, T)
@@ -85,8 +111,9 @@ def test_a_value_that_is_not_finite_reaches_only_what_depends_on_it(H, name, val
     assert np.array_equal(o[0, :t0, :, :] if name != "state_in" else o[0, :, :h0], clean[0][0, :t0] if name != "state_in" else clean[0][0, :, :h0])
 
 
-def test_result_is_the_same_under_capture():
-    B, T, H = 2, 200, 16
+@pytest.mark.parametrize("T", [200, 300])
+def test_result_is_the_same_under_capture(T):
+    B, H = 2, 16
     inp = inputs(B, T, H, 1)
     dev = {n: torch.from_numpy(np.ascontiguousarray(a)).cuda() for n, a in inp.items()}
     out, state = torch.empty_like(dev["r"]), torch.empty_like(dev["state_in"])

@@ -139,7 +139,7 @@ def test_cache_policies_of_a_call_inside_a_layer(fake, B, T, multi, traffic):
 @pytest.mark.parametrize("units,shortest,column_blocks", [(1, 97, 1), (24, 97, 1), (25, 33, 1), (64, 33, 1), (65, 33, 2), (96, 33, 2), (97, 24, 2), (128, 24, 2),
                                                           (129, 24, 4), (256, 24, 4), (257, 48, 4), (512, 48, 4)])
 def test_fp32_sequences_in_chunks_from_where_that_is_faster(fake, units, shortest, column_blocks):
-    calls = [lu.time_mix("wkv6_prefill_f32", 1, T, units) for T in (shortest - 1, shortest, 1024)]
+    calls = [lu.time_mix("wkv6_prefill_f32", 1, T, units) for T in (shortest - 1, shortest, 201)]
     below, *above = [[e for e in ev if e.kind == "launch"] for ev in lu.events(fake, calls)]
     assert "recurrent" in below[0].kernel
     for launch in above:
@@ -147,13 +147,27 @@ def test_fp32_sequences_in_chunks_from_where_that_is_faster(fake, units, shortes
         assert launch[0].grid[0] == (units + 7) // 8 * 8 * (4 // column_blocks)
 
 
-@pytest.mark.parametrize("first", [(1, 1, 4), (2, 20, 16), (4, 100, 4), (40, 100, 4), (3, 100, 32), (300, 100, 4)])
+@pytest.mark.parametrize("units,shortest", [(1, 202), (32, 264), (64, 328), (65, None), (256, None)])
+def test_fp32_scores_in_a_kernel_of_their_own(fake, units, shortest):
+    """A wave a chunk; the second kernel's grid as without them."""
+    lengths = [(shortest or 400) - 1, shortest or 400, 5000]
+    for T, ev in zip(lengths, lu.events(fake, [lu.time_mix("wkv6_prefill_f32", 1, T, units) for T in lengths])):
+        launch = [e for e in ev if e.kind == "launch"]
+        if shortest and T >= shortest:
+            assert [e.kernel for e in launch] == ["chunked_f32_scores_kernel", "chunked_f32_scored_kernel<1, 4>"]
+            assert launch[0].grid[0] * 4 - units * ((T + 15) // 16) in range(4)
+            assert launch[1].grid[0] == (units + 7) // 8 * 8 * 4
+        else:
+            assert [e.base for e in launch] == ["chunked_f32_kernel"]
+
+
+@pytest.mark.parametrize("first", [(1, 1, 4), (2, 20, 16), (4, 100, 4), (40, 100, 4), (3, 100, 32), (300, 100, 4), (4, 300, 4)])
 def test_first_fp32_call_raises_every_limit(fake, first):
-    sizes = [(4, 100, 4), (40, 100, 4), (3, 100, 32), (300, 100, 4)]
+    sizes = [(4, 100, 4), (40, 100, 4), (3, 100, 32), (300, 100, 4), (4, 300, 4)]
     per_call = lu.events(fake, [lu.time_mix("wkv6_prefill_f32", *first)] + [lu.time_mix("wkv6_prefill_f32", *s) for s in sizes])
     limit = {e.kernel: e.bytes for e in per_call[0] if e.kind == "attribute"}
     for ev in per_call[1:]:
-        assert [e.kind for e in ev] == ["launch"] and ev[0].bytes <= limit[ev[0].kernel]
+        assert {e.kind for e in ev} == {"launch"} and ev[-1].bytes <= limit[ev[-1].kernel]
 
 
 @pytest.mark.parametrize("M,D,kernel", [
