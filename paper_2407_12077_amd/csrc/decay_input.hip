@@ -385,30 +385,36 @@ __global__ __launch_bounds__(kDiThreads) void decay_input_kernel(DiArgs a) {
 // tile) and its waves take the 32-channel blocks of D in turn; the partial sums of q A_d and of z A_omega meet
 // through LDS, once each.  No barrier and no shared stage inside the walks: a wave brings its block's x rows and weight
 // slices from global memory in whole 64-byte pieces, passes them through a piece of LDS of its own into the operand
-// layouts, and has the loads of the next block (two for the small tiles) in flight.  A token's predecessor is an
+// layouts, and has the loads of the next block in flight.  A token's predecessor is an
 // LDS row as well: the row above it, or the carried row where a sequence starts.  Bound by the compute unit's L1
 // path (every workgroup takes all weights, 512 KB at D = 2048) and, at 64 rows, by the conversions and interpolations in the
-// vector ALU.  Straight operand loads from global memory (sixteen lines per quarter wave) took 26.4 us where this takes 16.6,
-// bf16 weights with the other operand as two bf16 values the same time, six waves instead of twelve 17.0, and 64
+// vector ALU.  One block in flight, not more: with
+// two the loop is twice as long and the last trip works on blocks that are not there (24 tokens 14.0 -> 12.0 us with four groups, below;
+// 3000 tokens 16.9 -> 14.7; D = 128, 300 tokens 6.2 -> 4.5; three in flight 14.9).  Straight operand loads from global memory (sixteen lines per quarter wave) took 26.4 us where this took 16.6,
+// bf16 weights with the other operand as two bf16 values the same time,  six waves instead of twelve 17.0, and 64
 // rows with four waves, two workgroups per compute unit, 36 instead of 31 (24 sequences of one token; 16384 tokens; D = 2048).
-template <int kTB, int kSplitWaves>
+//
+// With few tiles kGroups workgroups share a tile: each forms z from all of A_d and B_d, and 64 / kGroups of its outputs,
+// so that what a compute unit takes in and passes through its LDS is A_omega's part less (D = 2048: 512 -> 320 KB of weights at four
+// groups; 24 tokens 16.7 -> 14.0 us, 12.0 with one block in flight).  An output's sums are the same ones in the same order.
+template <int kTB, int kSplitWaves, int kGroups>
 struct SplitTile {
+    static constexpr int kCols = kOuterRank / kGroups;   // columns of A_omega, outputs of a token, of this workgroup
     static constexpr int kRows = 16 * kTB;
     static constexpr int kWaves = kSplitWaves;
     static constexpr int kThreads = 64 * kWaves;
-    static constexpr int kDepth = kTB == 4 ? 1 : 2;      // blocks of a wave in flight beside the one it works on
     static constexpr int kCarry = kTB == 1 ? 16 : 1;     // rows of a tile that can start a sequence (kTB > 1: T >= kRows)
     // a wave's piece of LDS: rows of 32 channels (64 bytes + 32 pad: full-rate 16-byte reads)
     static constexpr int kRow = 96;
     static constexpr int kXRows = 1 + kRows + kCarry;    // the row before the tile, the tile, the carried rows
-    static constexpr int kOffA = kXRows * kRow;          // walk 1: A_d slice [32 columns]; walk 2: A_omega slice [64 columns]
-    static constexpr int kOffB = kOffA + kOuterRank * kRow;   // walk 2: B_d slice [32 channels][32 ranks]
+    static constexpr int kOffA = kXRows * kRow;          // walk 1: A_d slice [32 columns]; walk 2: A_omega slice [kCols columns]
+    static constexpr int kOffB = kOffA + (kCols > kInnerRank ? kCols : kInnerRank) * kRow;   // walk 2: B_d slice [32 channels][32 ranks]
     static constexpr int kOffV = kOffB + 32 * kRow;      // mu_x or lambda_d slice, 32 fp32
     static constexpr int kPiece = kOffV + 128;
     static constexpr int kPRow = kInnerRank + 4;         // row strides (floats) of the waves' partial sums
-    static constexpr int kYRow = kOuterRank + 4;
+    static constexpr int kYRow = kCols + 4;
     static constexpr int kPtRow = kInnerRank * 2 + 16;   // row stride (bytes) of tanh(q A_d)
-    static constexpr int kYPart = kWaves * kRows * kYRow * 4;
+    static constexpr int kYPart = kWaves * kRows * (kYRow > kPRow ? kYRow : kPRow) * 4;
     static constexpr int kPtOff = kWaves * kPiece > kYPart ? kWaves * kPiece : kYPart;
     static constexpr int kLds = kPtOff + kRows * kPtRow;
     static_assert(kLds <= 160 * 1024, "LDS budget");
@@ -420,15 +426,17 @@ __device__ __forceinline__ void wave_lds_order() {       // a wave's own LDS wri
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int kTB, int kSplitWaves, bool kOutF32>
+template <int kTB, int kSplitWaves, bool kOutF32, int kGroups>
 __global__ __launch_bounds__(64 * kSplitWaves) void decay_input_split_kernel(DiArgs a) {
-    using TL = SplitTile<kTB, kSplitWaves>;
+    using TL = SplitTile<kTB, kSplitWaves, kGroups>;
+    constexpr int kNB = TL::kCols / 16;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     char* mine = lds + wave * TL::kPiece;
     const long long M = static_cast<long long>(a.B) * a.T;
-    const long long m0 = static_cast<long long>(blockIdx.x) * TL::kRows;
+    const unsigned tile = kGroups == 1 ? blockIdx.x : blockIdx.x / kGroups, group = kGroups == 1 ? 0 : blockIdx.x % kGroups;
+    const long long m0 = static_cast<long long>(tile) * TL::kRows;
     const int rows = M - m0 < TL::kRows ? static_cast<int>(M - m0) : TL::kRows;
     const long long row_bytes = static_cast<long long>(a.D) * 2;
     const int nkb = a.D / 32;
@@ -535,24 +543,20 @@ __global__ __launch_bounds__(64 * kSplitWaves) void decay_input_split_kernel(DiA
         }
     };
     {
-        W1 ring[TL::kDepth];
-#pragma unroll
-        for (int i = 0; i < TL::kDepth; ++i) fetch1(ring[i], wave + i * TL::kWaves);
+        W1 next;
+        fetch1(next, wave);
 #pragma clang loop unroll(disable)
-        for (int kb = wave; kb < nkb; kb += TL::kDepth * TL::kWaves) {   // blocks past the end add products of zeros
-#pragma unroll
-            for (int i = 0; i < TL::kDepth; ++i) {
-                park1(ring[i]);
-                fetch1(ring[i], kb + (TL::kDepth + i) * TL::kWaves);
-                step1();
-            }
+        for (int kb = wave; kb < nkb; kb += TL::kWaves) {
+            park1(next);
+            fetch1(next, kb + TL::kWaves);
+            step1();
         }
     }
 
     // walk 2's first blocks do not wait for the exchange
     struct W2 {
         X x;
-        uint4v bd[2], wo[4], lam;
+        uint4v bd[2], wo[kNB], lam;
     };
     auto fetch2 = [&](W2& s, int kb) {
         const bool live = kb >= 0;
@@ -561,15 +565,14 @@ __global__ __launch_bounds__(64 * kSplitWaves) void decay_input_split_kernel(DiA
         for (int i = 0; i < 2; ++i)                            // 32 channels x 64 bytes: one contiguous piece
             s.bd[i] = load(a.b_d, live ? a.D * kInnerRank * 2 : 0, 1024 * i + 16 * lane, kInnerRank * soff);
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
-            s.wo[nb] = load(a.a_omega + nb * 16 * row_bytes, live ? static_cast<int>(16 * row_bytes) : 0, w_voff, soff);
+        for (int nb = 0; nb < kNB; ++nb)
+            s.wo[nb] = load(a.a_omega + (group * TL::kCols + nb * 16) * row_bytes, live ? static_cast<int>(16 * row_bytes) : 0, w_voff, soff);
         s.lam = load(a.lambda_d, live ? a.D * 4 : 0, lane < 8 ? 16 * lane : kNowhere, 2 * soff);
         fetch_x(s.x, live, soff);
     };
     const int last = wave < nkb ? wave + (nkb - 1 - wave) / TL::kWaves * TL::kWaves : -1;   // this wave's last block
-    W2 ring[TL::kDepth];
-#pragma unroll
-    for (int i = 0; i < TL::kDepth; ++i) fetch2(ring[i], last - i * TL::kWaves);
+    W2 next;
+    fetch2(next, last);
 
     // the waves' shares of q A_d meet; p = tanh of the sum, as fp16
     float* part = reinterpret_cast<float*>(lds);
@@ -596,17 +599,17 @@ __global__ __launch_bounds__(64 * kSplitWaves) void decay_input_split_kernel(DiA
         pt[tb] = *reinterpret_cast<const half8*>(lds + TL::kPtOff + (16 * tb + l16) * TL::kPtRow + 16 * g4);
 
     // walk 2: this wave's share of z A_omega, from the blocks most recently brought into the caches down
-    float4v yacc[kTB][4];
+    float4v yacc[kTB][kNB];
 #pragma unroll
     for (int tb = 0; tb < kTB; ++tb)
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) yacc[tb][nb] = float4v{0.f, 0.f, 0.f, 0.f};
+        for (int nb = 0; nb < kNB; ++nb) yacc[tb][nb] = float4v{0.f, 0.f, 0.f, 0.f};
     auto park2 = [&](const W2& s) {
         wave_lds_order();
 #pragma unroll
         for (int i = 0; i < 2; ++i) store(TL::kOffB + (16 * i + lr) * TL::kRow + lp, bf16x8_to_f16x8(s.bd[i]));
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) store(TL::kOffA + (16 * nb + lr) * TL::kRow + lp, bf16x8_to_f16x8(s.wo[nb]));
+        for (int nb = 0; nb < kNB; ++nb) store(TL::kOffA + (16 * nb + lr) * TL::kRow + lp, bf16x8_to_f16x8(s.wo[nb]));
         if (lane < 8) store(TL::kOffV + 16 * lane, s.lam);
         park_x(s.x);
         wave_lds_order();
@@ -614,7 +617,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void decay_input_split_kernel(DiA
     auto step2 = [&] {
         // Which channel sits in which row of the B_d^T operand is free as long as z and A_omega agree: with row m of
         // block `half` holding channel 8*(m>>2) + 4*half + (m&3) a lane's results are its own channels 8*g4 .. +7
-        half8 bd[2], wo[4];
+        half8 bd[2], wo[kNB];
         float4v lam[2];
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
@@ -622,7 +625,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void decay_input_split_kernel(DiA
             lam[half] = read_f4(TL::kOffV + 32 * g4 + 16 * half);
         }
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) wo[nb] = read_half8(TL::kOffA + (16 * nb + l16) * TL::kRow + 16 * g4);
+        for (int nb = 0; nb < kNB; ++nb) wo[nb] = read_half8(TL::kOffA + (16 * nb + l16) * TL::kRow + 16 * g4);
 #pragma unroll
         for (int tb = 0; tb < kTB; ++tb) {
             const uint4v cur = read_u4(cur_off[tb]), prev = read_u4(prev_off[tb]);
@@ -636,35 +639,32 @@ __global__ __launch_bounds__(64 * kSplitWaves) void decay_input_split_kernel(DiA
                     z[2 * half + i] = interpolate(cur[2 * half + i], prev[2 * half + i], mix[2 * i], mix[2 * i + 1]);
             }
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb)
+            for (int nb = 0; nb < kNB; ++nb)
                 yacc[tb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wo[nb], __builtin_bit_cast(half8, z), yacc[tb][nb], 0, 0, 0);
         }
     };
 #pragma clang loop unroll(disable)
-    for (int kb = last; kb >= 0; kb -= TL::kDepth * TL::kWaves) {   // blocks before the first add products with zero weights
-#pragma unroll
-        for (int i = 0; i < TL::kDepth; ++i) {
-            park2(ring[i]);
-            fetch2(ring[i], kb - (TL::kDepth + i) * TL::kWaves);
-            step2();
-        }
+    for (int kb = last; kb >= 0; kb -= TL::kWaves) {
+        park2(next);
+        fetch2(next, kb - TL::kWaves);
+        step2();
     }
 
     __syncthreads();                                           // every wave is done with its piece
 #pragma unroll
     for (int tb = 0; tb < kTB; ++tb)
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
+        for (int nb = 0; nb < kNB; ++nb)
             *reinterpret_cast<float4v*>(part + (wave * TL::kRows + 16 * tb + l16) * TL::kYRow + 16 * nb + 4 * g4) = yacc[tb][nb];
     __syncthreads();
-    for (int i = tid; i < TL::kRows * (kOuterRank / 4); i += TL::kThreads) {
-        const int row = i / (kOuterRank / 4), c4 = 4 * (i % (kOuterRank / 4));
+    for (int i = tid; i < TL::kRows * (TL::kCols / 4); i += TL::kThreads) {
+        const int row = i / (TL::kCols / 4), c4 = 4 * (i % (TL::kCols / 4));
         float4v sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < TL::kWaves; ++w)
             sum += *reinterpret_cast<const float4v*>(part + (w * TL::kRows + row) * TL::kYRow + c4);
         if (row < rows) {
-            const long long e = (m0 + row) * kOuterRank + c4;
+            const long long e = (m0 + row) * kOuterRank + group * TL::kCols + c4;
 #pragma unroll
             for (int i2 = 0; i2 < 4; ++i2) sum[i2] = fast_tanh(sum[i2]);
             if constexpr (kOutF32) {
@@ -682,20 +682,22 @@ __global__ __launch_bounds__(64 * kSplitWaves) void decay_input_split_kernel(DiA
 
 namespace {
 
-template <int kTB, int kSplitWaves, bool kOutF32>
+template <int kTB, int kSplitWaves, bool kOutF32, int kGroups = 1>
 hipError_t launch_split(const DiArgs& a, hipStream_t stream) {
-    using TL = SplitTile<kTB, kSplitWaves>;
+    using TL = SplitTile<kTB, kSplitWaves, kGroups>;
     const long long M = static_cast<long long>(a.B) * a.T;
-    hipLaunchKernelGGL((decay_input_split_kernel<kTB, kSplitWaves, kOutF32>), dim3(static_cast<unsigned>((M + TL::kRows - 1) / TL::kRows)),
+    hipLaunchKernelGGL((decay_input_split_kernel<kTB, kSplitWaves, kOutF32, kGroups>), dim3(static_cast<unsigned>((M + TL::kRows - 1) / TL::kRows * kGroups)),
                        dim3(TL::kThreads), TL::kLds, stream, a);
     return hipGetLastError();
 }
 
 template <bool kOutF32>
 hipError_t raise_lds_limits() {
-    hipError_t err = set_lds_limit(&decay_input_split_kernel<1, 12, kOutF32>, SplitTile<1, 12>::kLds);
-    if (err == hipSuccess) err = set_lds_limit(&decay_input_split_kernel<2, 8, kOutF32>, SplitTile<2, 8>::kLds);
-    if (err == hipSuccess) err = set_lds_limit(&decay_input_split_kernel<4, 8, kOutF32>, SplitTile<4, 8>::kLds);
+    hipError_t err = set_lds_limit(&decay_input_split_kernel<1, 12, kOutF32, 1>, SplitTile<1, 12, 1>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&decay_input_split_kernel<1, 12, kOutF32, 2>, SplitTile<1, 12, 2>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&decay_input_split_kernel<1, 12, kOutF32, 4>, SplitTile<1, 12, 4>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&decay_input_split_kernel<2, 8, kOutF32, 1>, SplitTile<2, 8, 1>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&decay_input_split_kernel<4, 8, kOutF32, 1>, SplitTile<4, 8, 1>::kLds);
     if (err == hipSuccess) err = set_lds_limit(&decay_input_kernel<kOutF32>, kDiLds);
     return err;
 }
@@ -733,13 +735,23 @@ hipError_t launch_decay_input(int B, int T, int D, const void* x, const void* x_
     // one token 45.8 : 16.6, 300 of them 90 : 16.8, 8192 tokens 46.6 : 22, 16 384 tokens 47 : 31, 33 792 tokens 94 : 86, 24 000
     // tokens (a second round of 64 rows) 48 : 59; D = 128 one token 6.3 : 6.9, 300 sequences of one token 12.2 : 7.2, 33 792 tokens
     // 13.0 : 20.0; D = 256 33 792 tokens 19.3 : 23.6, 1000 sequences of 20 34.7 : 36.3; D = 768 49 152 tokens 41.0 : 42.6.
+    // These were fitted with two blocks of a wave in flight in the 16- and 32-row tiles, which now take about 2 us less a round
+    // (16 rows 4.2 us and 0.66 per 128 channels): the line still errs towards the 128-token tiles at D = 128 and 256.
     const long long cus = compute_units(), rows = static_cast<long long>(B) * T, blocks = D / 128;
     auto rounds = [&](long long groups) { return (groups + cus - 1) / cus; };
     const long long whole = (4300 + 2640 * blocks) * rounds(static_cast<long long>(B) * a.tiles_per_seq);
     const long long r64 = T >= 64 ? (5500 + 1550 * blocks) * rounds((rows + 63) / 64) : whole;
     const long long r32 = T >= 32 ? (6500 + 1000 * blocks) * rounds((rows + 31) / 32) : whole;
     const long long r16 = (6600 + 590 * blocks) * rounds((rows + 15) / 16);
-    if (r16 < whole && r16 <= r32 && r16 <= r64) return out_f32 ? launch_split<1, 12, true>(a, stream) : launch_split<1, 12, false>(a, stream);
+    if (r16 < whole && r16 <= r32 && r16 <= r64) {
+        // A tile's outputs over four or two workgroups while these still fit the chip once.  One, two, four of them (with two
+        // blocks of a wave in flight, 2 us more than now): D = 2048, 24 tokens 16.7, 14.9, 14.0 us; 1024 tokens 16.5, 14.7, 14.6; 2048
+        // tokens 16.9, 15.6, 26.4 (a second round); D = 128, 300 tokens 7.2, 6.6, 6.3; D = 768, 24 tokens 9.0, 8.2, 7.8; D = 4096 28.4, 22.7, 21.3.
+        const long long tiles = (rows + 15) / 16;
+        if (4 * tiles <= cus) return out_f32 ? launch_split<1, 12, true, 4>(a, stream) : launch_split<1, 12, false, 4>(a, stream);
+        if (2 * tiles <= cus) return out_f32 ? launch_split<1, 12, true, 2>(a, stream) : launch_split<1, 12, false, 2>(a, stream);
+        return out_f32 ? launch_split<1, 12, true>(a, stream) : launch_split<1, 12, false>(a, stream);
+    }
     if (r32 < whole && r32 <= r64) return out_f32 ? launch_split<2, 8, true>(a, stream) : launch_split<2, 8, false>(a, stream);
     if (r64 < whole) return out_f32 ? launch_split<4, 8, true>(a, stream) : launch_split<4, 8, false>(a, stream);
     const dim3 grid(static_cast<unsigned>(static_cast<long long>(B) * a.tiles_per_seq));

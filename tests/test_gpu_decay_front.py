@@ -194,3 +194,12 @@ def test_split_contraction_tiles_at_the_widths_that_take_them(gpu_device, B, T, 
         assert max_norm_err(y32, oracle_front(fi, with_prev)) <= TOL_BF16
         y16 = run_front(fi, torch.bfloat16, with_prev).float().cpu().numpy()
         assert np.array_equal(y16, round_to_bf16(y32))
+
+
+# the outputs of a tile over four, two and one workgroups: both sides of each line, ragged last tiles, sequences that start in a tile
+@pytest.mark.parametrize("B,T,H", [(1, 1024, 4), (1023, 1, 4), (1, 1025, 4), (205, 5, 4), (4, 512, 4), (2041, 1, 4), (1, 2049, 4)])
+def test_outputs_of_a_tile_over_several_workgroups(gpu_device, B, T, H):
+    fi = make_decay_front_inputs(scaled(CONFIGS[2], B=B, T=T, H=H), seed=70 + B + T)
+    y32 = run_front(fi, torch.float32).cpu().numpy()
+    assert max_norm_err(y32, oracle_front(fi)) <= TOL_BF16
+    assert np.array_equal(run_front(fi, torch.bfloat16).float().cpu().numpy(), round_to_bf16(y32))

@@ -70,6 +70,14 @@ def test_decay_front_tiles_by_width(fake, B, T, D, kernel):
     assert kernel in launch.kernel, launch.kernel
 
 
+@pytest.mark.parametrize("B,T,D,groups", [(1, 1, 2048, 4), (24, 1, 2048, 4), (1, 1024, 2048, 4), (1025, 1, 2048, 2), (4, 512, 768, 2), (1, 2049, 2048, 1), (4, 1024, 2048, 1)])
+def test_decay_front_outputs_of_a_tile_over_workgroups(fake, B, T, D, groups):
+    call = ("wkv6_decay_lora_input_bf16", [B, T, D, 32, 64] + [lu.at(i) for i in range(8)] + [0, None])
+    [launch] = [e for e in lu.events(fake, [call])[0] if e.kind == "launch"]
+    assert launch.kernel == "decay_input_split_kernel<1, 12, false, %d>" % groups
+    assert launch.grid[0] == (B * T + 15) // 16 * groups
+
+
 # shapes of tests/test_gpu_own_split.py beside those of the list
 ALSO_SPLIT = [(1, 1100, 4), (2, 1531, 12), (2, 1201, 6), (1, 1000, 4), (1, 1300, 8)]
 
