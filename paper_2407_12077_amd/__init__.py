@@ -1,4 +1,4 @@
-"""MI355X-native WKV6 prefill: HIP kernels behind a C ABI, with a thin ctypes binding."""
+"""MI355X-native WKV6 prefill: HIP kernels behind a C ABI, with a thin binding."""
 from .binding import (  # noqa: F401
     WKV6_DTYPE_BF16, WKV6_DTYPE_F32, Wkv6Error, load, status_string, wkv6_append_bf16, wkv6_decode_bf16,
     wkv6_decay_lora_input_bf16, wkv6_finch_c2_append_bf16, wkv6_finch_c2_decode_bf16, wkv6_finch_c2_prefill_bf16,
