@@ -47,7 +47,8 @@ void split_into_out(wkv6::Args& a, const wkv6::SplitPlan& p, bool out_f32) {
 
 // The passes of a prefill whose Args are complete but for the segments.  Sequences of one chunk go to the kernel that runs several
 // units per compute unit and not several chunks of one: at no number of units is it the slower one (figures there), and the bits
-// are the same.  The limits of the other kernels behind the entry point are raised all the same.
+// are the same.  More units than a launch has workgroups for (2^24; one token of them without states is 11 GB) stay with the
+// other kernel, whose workgroups take several.  The limits of the other kernels behind the entry point are raised all the same.
 hipError_t launch_prefill(wkv6::Args& a, wkv6::ChunkedMode mode, bool own_split, hipStream_t s) {
     const bool lora = mode == wkv6::ChunkedMode::kBf16OutLora || mode == wkv6::ChunkedMode::kBf16OutLoraMoments;
     if (own_split) {
@@ -55,7 +56,7 @@ hipError_t launch_prefill(wkv6::Args& a, wkv6::ChunkedMode mode, bool own_split,
         if (p.segs > 1) split_into_out(a, p, mode == wkv6::ChunkedMode::kF32Out);
     }
     hipError_t err = wkv6::launch_segment_states(a, lora, s);
-    if (a.segs == 1 && a.T <= wkv6::kChunkTokens) {
+    if (a.segs == 1 && a.T <= wkv6::kChunkTokens && wkv6::fits_a_launch(static_cast<long long>(a.B) * a.H, wkv6::kOneChunkThreads)) {
         if (err == hipSuccess) err = wkv6::raise_chunked_limits(a, mode);
         return err == hipSuccess ? wkv6::launch_one_chunk(a, mode, s) : err;
     }

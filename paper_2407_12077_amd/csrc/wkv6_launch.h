@@ -73,8 +73,8 @@ hipError_t raise_chunked_f32_limits();
 // kBf16OutLoraMoments: that plus a.moments (Finch-C2 form).
 hipError_t launch_chunked(const Args& a, ChunkedMode mode, hipStream_t stream);
 
-// The same, bit for bit, for sequences of at most kChunkTokens tokens.
-constexpr int kChunkTokens = 32;
+// The same, bit for bit, for sequences of at most kChunkTokens tokens; a workgroup of kOneChunkThreads per (batch, head) unit.
+constexpr int kChunkTokens = 32, kOneChunkThreads = 256;
 hipError_t launch_one_chunk(const Args& a, ChunkedMode mode, hipStream_t stream);
 
 // Raises the dynamic LDS limits that launch_chunked needs for this form and mode, without launching.
@@ -109,6 +109,9 @@ hipError_t launch_layernorm_apply(long long tokens, int D, const void* o, const 
 hipError_t launch_decay_input(int B, int T, int D, const void* x, const void* x_prev, const float* mu_x,
                               const float* lambda_d, const void* a_d, const void* b_d, const void* a_omega, void* y,
                               bool out_f32, hipStream_t stream);
+
+// Whether one launch holds `workgroups` of `threads` each: HIP takes fewer than 2^32 work items in a dimension.
+constexpr bool fits_a_launch(long long workgroups, int threads) { return workgroups * threads < 1ll << 32; }
 
 // The current device as an index below 64.  With one visible device there is nothing to ask (a short append of one user, where the
 // host bounds the call, checks two flags: 5.12 -> 5.00 us).

@@ -27,6 +27,8 @@ std::string& text() {
     return s;
 }
 thread_local Config pushed;
+thread_local int last_error = 0;
+constexpr int kInvalidConfiguration = 9;
 void* module = nullptr;
 alignas(256) char symbol[256];
 void line(const char* kind, const void* f, const Dim3& g, const Dim3& b, std::size_t bytes) {
@@ -57,7 +59,9 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, std::size_t* shared, void
     *stream = pushed.stream;
     return 0;
 }
+// the runtime takes fewer than 2^32 work items in a dimension
 int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void**, std::size_t shared, void*) {
+    if (1ull * grid.x * block.x >> 32 || 1ull * grid.y * block.y >> 32) return last_error = kInvalidConfiguration;
     line("launch", f, grid, block, shared);
     return 0;
 }
@@ -81,7 +85,11 @@ int hipGetSymbolAddress(void** address, const void*) {
     *address = symbol;
     return 0;
 }
-int hipGetLastError() { return 0; }
+int hipGetLastError() {
+    const int error = last_error;
+    last_error = 0;
+    return error;
+}
 
 const char* launch_log() { return text().c_str(); }
 void launch_log_clear() { text().clear(); }

@@ -107,3 +107,19 @@ def test_strided_batches_of_one_chunk():
     wkv.wkv6_finch_c2_prefill_bf16_strided(B, T, H, 64, t["r"], t["k"], t["v"], t["x"], t["uprime"], t["state_in"], out, s, 40 * H * 64, wkv.WKV6_DTYPE_BF16)
     torch.cuda.synchronize()
     assert torch.equal(out[:, :T], want) and torch.equal(s, s_want) and not out[:, T:].any()
+
+
+def test_more_units_than_a_launch_has_workgroups_for():
+    """2^24 (batch, head) units of one token: the kernel for longer sequences, whose workgroups take several units, with the same bits."""
+    B, T, H = 524288, 1, 32
+    g = torch.Generator(device="cuda").manual_seed(1)
+    r, k, v = (torch.randn((B, T, H, 64), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    x, u = r, torch.randn((H, 64), generator=g, device="cuda")
+    out = torch.full((B, T, H, 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wkv.wkv6_prefill_bf16(B, T, H, 64, r, k, v, x, u, None, out, None)
+    for b in (0, 131072, B - 3):                              # element offsets up to 2^30, bytes up to 2^31
+        sl = slice(b, b + 3)
+        few = torch.empty((3, T, H, 64), dtype=torch.bfloat16, device="cuda")
+        wkv.wkv6_prefill_bf16(3, T, H, 64, r[sl], k[sl], v[sl], x[sl], u, None, few, None)
+        torch.cuda.synchronize()
+        assert torch.equal(few, out[sl]), b

@@ -126,6 +126,18 @@ def test_sequences_of_one_chunk_take_four_waves_a_unit(fake, make, shortest, B, 
         assert T > 32 or run.grid[0] == B * H
 
 
+@pytest.mark.parametrize("make,lengths", [
+    (lambda B, T, H: lu.time_mix("wkv6_prefill_bf16", B, T, H, False), (1, 32)), (lambda B, T, H: lu.time_mix("wkv6_prefill_bf16_f32out", B, T, H, False), (1, 32)),
+    (lambda B, T, H: lu.time_mix("wkv6_finch_c2_append_bf16", B, T, H, False), (7, 32)), (lambda B, T, H: lu.fused_c2(B, T, H), (5, 32)),
+    (lambda B, T, H: lu.fused_finch(B, T, H), (5, 32))], ids=["prefill", "f32out", "c2_append", "fused_c2", "fused_finch"])
+@pytest.mark.parametrize("B,H", [(524287, 32), (524288, 32), (65537, 256), (174763, 96)])
+def test_one_chunk_of_more_units_than_a_grid_takes(fake, make, lengths, B, H):
+    """A launch holds fewer than 2^32 work items: from 2^24 units on, the several units of a workgroup of the kernel for longer sequences."""
+    for T, ev in zip(lengths, lu.events(fake, [make(B, T, H) for T in lengths])):
+        [run] = [e for e in ev if e.kind == "launch"]
+        assert run.grid[0] * run.block < 2 ** 32 and run.block == (256 if B * H < 2 ** 24 else 1024), T
+
+
 @pytest.mark.parametrize("entry,B,T,H,multi,traffic", [
     ("wkv6_prefill_bf16", 8, 33, 32, False, 0), ("wkv6_prefill_bf16", 8, 520, 32, False, 0), ("wkv6_prefill_bf16", 8, 530, 32, False, 1),
     ("wkv6_prefill_bf16", 8, 8000, 32, False, 1), ("wkv6_prefill_bf16", 16, 230, 32, True, 0), ("wkv6_prefill_bf16", 16, 240, 32, True, 1),
