@@ -76,7 +76,8 @@ hipError_t launch_f32(const wkv6::Args& a, hipStream_t s) {
     const hipError_t err = wkv6::raise_chunked_f32_limits();
     if (err != hipSuccess) return err;
     const long long units = static_cast<long long>(a.B) * a.H;
-    return a.T >= f32_chunked_tokens(units) ? wkv6::launch_chunked_f32(a, s) : wkv6::launch_recurrent(a, false, false, s);
+    const bool chunked = a.T >= f32_chunked_tokens(units) && wkv6::fits_a_launch(units + 7, wkv6::kChunkedF32Threads);
+    return chunked ? wkv6::launch_chunked_f32(a, s) : wkv6::launch_recurrent(a, false, false, s);
 }
 
 // `uprime` selects the form: nullptr = Finch (bonus u), otherwise Finch-C2 (u unused, may be null).

@@ -62,6 +62,7 @@ struct Shape {
     static constexpr int kLds = 2 * kProducers * kSlot;
     static constexpr int kThreads = 64 * (kProducers + kConsumers);
     static_assert(kLds <= 160 * 1024, "LDS budget");
+    static_assert(kThreads == kChunkedF32Threads, "what the callers count with");
 };
 
 // Rows of 16 tokens are four granules of 16 bytes: granule g holds tokens g, 4 + g, 8 + g, 12 + g, so that a lane's read is its

@@ -61,7 +61,8 @@ constexpr int kLoraRank = 64;   // R: the only rank of the decay path the fused 
 // from a.y, a.lambda, a.bw (bf16 in and out) and a.moments, if set, is written (Finch-C2 form).
 hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStream_t stream);
 
-// Chunked kernel of fp32 tensors (Finch form, fp32 throughout).
+// Chunked kernel of fp32 tensors (Finch form, fp32 throughout).  Units, to a multiple of eight, in workgroups of kChunkedF32Threads.
+constexpr int kChunkedF32Threads = 512;
 hipError_t launch_chunked_f32(const Args& a, hipStream_t stream);
 
 // Raises the dynamic LDS limits that launch_chunked_f32 needs, without launching.

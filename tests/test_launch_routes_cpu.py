@@ -167,6 +167,13 @@ def test_fp32_sequences_in_chunks_from_where_that_is_faster(fake, units, shortes
         assert launch[0].grid[0] == (units + 7) // 8 * 8 * (4 // column_blocks)
 
 
+@pytest.mark.parametrize("units,chunked", [(2 ** 23 - 8, True), (2 ** 23 - 7, False), (2 ** 23, False), (2 ** 24 - 1, False)])
+def test_fp32_of_more_units_than_a_grid_takes(fake, units, chunked):
+    """The token-by-token form has half as many threads a unit."""
+    [run] = [e for e in lu.events(fake, [lu.time_mix("wkv6_prefill_f32", units, 100, 1)])[0] if e.kind == "launch"]
+    assert run.base == ("chunked_f32_kernel" if chunked else "recurrent_wide_kernel")
+
+
 @pytest.mark.parametrize("units,shortest", [(1, 202), (32, 264), (64, 328), (65, None), (256, None)])
 def test_fp32_scores_in_a_kernel_of_their_own(fake, units, shortest):
     """A wave a chunk; the second kernel's grid as without them."""
