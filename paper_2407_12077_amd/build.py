@@ -20,8 +20,8 @@ SOURCE_FLAGS = {"wkv6_chunked.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
 
 
 def build(verbose=False, extra=()):
-    """Compile every source to an object of its own (in parallel), then link the shared library;
-    always recompiles."""
+    """Compile every source to an object of its own (in parallel), then link the shared library, then the binding's
+    extension; always recompiles."""
     objdir = os.path.join(PKG, "_build")
     os.makedirs(objdir, exist_ok=True)
     jobs = []
@@ -31,28 +31,34 @@ def build(verbose=False, extra=()):
         if verbose:
             print(" ".join(cmd))
         jobs.append((cmd, obj, subprocess.Popen(cmd)))
+    failed = [(cmd, proc.returncode) for cmd, _, proc in jobs if proc.wait() != 0]      # (every compiler has ended)
+    if failed:
+        raise subprocess.CalledProcessError(failed[0][1], failed[0][0])
+    link = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *(obj for _, obj, _ in jobs)]
+    if verbose:
+        print(" ".join(link))
+    subprocess.check_call(link)
+    build_call(verbose)
+    return LIB
+
+
+def build_call(verbose=False):
+    """The binding's extension.  It comes last: callers of the C ABI need neither g++ nor Python's headers, and have the library
+    whether or not this succeeds."""
     call = ["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_path("include"),
             "-I", os.path.join(os.path.dirname(PKG), "include"), os.path.join(CSRC, "binding_call.cpp"), "-o", CALL]
     if verbose:
         print(" ".join(call))
     subprocess.check_call(call)
-    objs = []
-    for cmd, obj, proc in jobs:
-        if proc.wait() != 0:
-            raise subprocess.CalledProcessError(proc.returncode, cmd)
-        objs.append(obj)
-    link = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
-    if verbose:
-        print(" ".join(link))
-    subprocess.check_call(link)
-    return LIB
 
 
 def ensure_built():
-    """For the harness entry points (tests, smoke, bench): compile only when no library is there.
+    """For the harness entry points (tests, smoke, bench): compile only what is not there.
     The binding itself never builds and never falls back: it raises when the library is missing."""
-    if not (os.path.exists(LIB) and os.path.exists(CALL)):
+    if not os.path.exists(LIB):
         build()
+    elif not os.path.exists(CALL):
+        build_call()
     return LIB
 
 
