@@ -20,15 +20,21 @@ enum class Path { kChunked, kRecurrent, kBySize, kF32 };
 // units; the one-chunk kernel would be the faster one from 4 tokens on, with fp16 operands.)
 constexpr int kRecurrentMaxTokens = 6;
 
-// fp32 tensors: sequences of at least this many tokens go to the chunked kernel.  It takes whole chunks of 16 tokens and a round to
+// fp32 tensors: whether the chunked kernel takes the sequences.  It takes whole chunks of 16 tokens, four at a time, and a round to
 // fill, the token-by-token kernels blocks of 8 to 32, so the line follows the form that those take at this number of units.  Measured,
-// microseconds, token by token : chunked: 4 units 64 tokens 7.6 : 7.6, 96 9.9 : 10.2, 112 12.2 : 10.5; 16 units 96 10.6 : 10.4; 32 units 32
-// tokens 5.8 : 7.3, 40 8.6 : 7.6; 64 units 32 6.5 : 7.4, 40 8.4 : 7.7; 96 units 24 7.8 : 8.1, 32 8.4 : 8.2; 128 units 24 8.8 : 8.2;
-// 256 units 24 10.2 : 9.0; 320 units (two rounds of workgroups) 40 18.3 : 18.5, 48 21.1 : 18.8; 512 units 40 19.5 : 19.3, 48 22.3 : 19.9.
-int f32_chunked_tokens(long long units) {
-    if (units <= 24) return 97;
-    if (units <= 96) return 33;
-    return units <= 256 ? 24 : 48;
+// microseconds, token by token : chunked: 24 units 64 tokens 8.9 : 8.6, 80 11.3 : 10.8, 96 11.2 : 11.2, 97 13.5 : 11.5; 32 units 32
+// tokens 6.8 : 8.1, 33 9.1 : 8.4; 96 units 32 8.6 : 8.9, 33 11.0 : 9.6; 128 units 24 8.8 : 9.1 with the inputs in the caches, 9.3 : 8.5 without;
+// 256 units 24 11.0 : 10.0; 320 units (two rounds of workgroups) 40 17.5 : 18.9, 48 20.1 : 19.2; 512 units 40 20.7 : 21.0, 48 23.8 : 21.8.
+// Beyond that both are in rounds, three units to a compute unit token by token, one here.  The fourth round of one is the second of the
+// other: 769 units 48 39.6 : 36.5, 65 53.4 : 49.6, 1024 units 48 44.2 : 39.4.  Elsewhere only long sequences and those that just
+// fill the four chunks: 513 units 48 26.6 : 27.5, 63 33.6 : 31.7, 72 37.1 : 37.9, 80 40.6 : 38.0; 2048 units 48 75 : 76, 64 95 : 92, 65
+// 99 : 106, 80 119 : 116; 4096 units 48 143 : 159, 56 169 : 174, 64 198 : 179, 72 219 : 220, 80 247 : 223.
+bool f32_in_chunks(long long units, int T) {
+    if (units <= 24) return T >= 97;
+    if (units <= 96) return T >= 33;
+    if (units <= 256) return T >= 24;
+    if (units <= 512 || (units > 768 && units <= 1024)) return T >= 48;
+    return T >= 80 || (T > 56 && T <= 64);
 }
 
 // Fills in the segments of `p` with their hand-over in the segments' own rows of out.
@@ -76,7 +82,7 @@ hipError_t launch_f32(const wkv6::Args& a, hipStream_t s) {
     const hipError_t err = wkv6::raise_chunked_f32_limits();
     if (err != hipSuccess) return err;
     const long long units = static_cast<long long>(a.B) * a.H;
-    const bool chunked = a.T >= f32_chunked_tokens(units) && wkv6::fits_a_launch(units + 7, wkv6::kChunkedF32Threads);
+    const bool chunked = f32_in_chunks(units, a.T) && wkv6::fits_a_launch(units + 7, wkv6::kChunkedF32Threads);
     return chunked ? wkv6::launch_chunked_f32(a, s) : wkv6::launch_recurrent(a, false, false, s);
 }
 

@@ -167,6 +167,16 @@ def test_fp32_sequences_in_chunks_from_where_that_is_faster(fake, units, shortes
         assert launch[0].grid[0] == (units + 7) // 8 * 8 * (4 // column_blocks)
 
 
+@pytest.mark.parametrize("units,chunked", [(512, (48, 56, 57, 64, 65, 79, 80)), (513, (57, 64, 80, 200)), (768, (57, 64, 80)), (769, (48, 56, 57, 64, 65, 79, 80)),
+                                           (1024, (48, 56, 57, 64, 65, 79, 80)), (1025, (57, 64, 80)), (2048, (57, 64, 80)), (4096, (57, 64, 80, 81))])
+def test_fp32_of_many_units_in_chunks_only_where_that_is_faster(fake, units, chunked):
+    """4096 units of 48 tokens took 159 us against 143 token by token, 2048 of 65 tokens 106 against 99."""
+    lengths = [47, 48, 56, 57, 64, 65, 79, 80, 81, 200]
+    for T, ev in zip(lengths, lu.events(fake, [lu.time_mix("wkv6_prefill_f32", 1, T, units) for T in lengths])):
+        [run] = [e for e in ev if e.kind == "launch"]
+        assert (run.base == "chunked_f32_kernel") == (T in chunked or T > 80), T
+
+
 @pytest.mark.parametrize("units,chunked", [(2 ** 23 - 8, True), (2 ** 23 - 7, False), (2 ** 23, False), (2 ** 24 - 1, False)])
 def test_fp32_of_more_units_than_a_grid_takes(fake, units, chunked):
     """The token-by-token form has half as many threads a unit."""
