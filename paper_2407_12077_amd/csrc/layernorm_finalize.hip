@@ -83,10 +83,15 @@ __global__ __launch_bounds__(256) void layernorm_finalize_few_kernel(long long t
 typedef unsigned uint4v __attribute__((ext_vector_type(4)));
 constexpr int kInFlight = 4;
 
-// Cache policy of the stores.  bf16 rows of up to 64 MiB leave through the L2 (sc1), as those of the prefill do, but not
-// non-temporal: the product that reads them next finds them in the memory-side cache.  Microseconds, five calls of a layer in a row:
-// 16 x 700 tokens, D = 2048 134 -> 133, 8 x 100 42.8 -> 41.6, 4 x 500 55.5 -> 54.0, 8 x 2048 (64 MiB)
-// 164.2 -> 162.8; alone 16 x 700 17.7 -> 16.2, 8 x 4096 46.9 -> 47.7.  fp32 rows, which leave half a line at a time, stay non-temporal (92 -> 206 written through).
+// Cache policy of the stores.  Written through the L2 (sc1), as those of the prefill, but not non-temporal, bf16 rows are in the
+// memory-side cache when the product that reads them next does, as long as that holds them beside what else the layer touches.
+// Five calls of a layer in a row, streamed -> through, microseconds, repeated on one set of tensors / on sets that no cache holds:
+// D = 2048 4 x 500 tokens (8 MiB of rows) 54.5 -> 53.4 / 56.0 -> 56.1, 8 x 2048 (64 MiB) 164 -> 158 / 165 -> 161, 9 x 2048 (72) 246 -> 242 /
+// 247 -> 244, 10 x 2048 (80) 249 -> 248 / 251 -> 253, 12 x 2048 (96) 262 -> 255 / 258 -> 265; D = 4096 4 x 1024 (32) 126 -> 123 / 125 -> 124,
+// 8 x 1024 (64) 186 -> 182 / 190 -> 190, 9 x 1024 (72) 233 -> 234 / 240 -> 243.  The kernel for other widths, whose workgroups write runs
+// across rows: D = 1024 8 x 2048 (32) 118 -> 114 / 117 -> 117, 12 x 2048 (48) 135 -> 134 / 135 -> 136, 16 x 2048 (64) 154 -> 156 / 157 -> 158;
+// few rows leave it later: D = 768 500 tokens (0.7 MiB) 40.7 -> 41.2 (alone 4.0 -> 4.3), 1000 (1.5) 42.0 -> 42.2, 1500 (2.2) 43.6 -> 43.1.
+// fp32 rows, which leave half a line at a time, stay non-temporal (92 -> 206 written through).
 constexpr int kStoreThrough = 16, kStoreStreamed = 2;
 
 // item `item` of the `items` from `first` on
@@ -178,7 +183,7 @@ hipError_t launch_layernorm_apply(long long tokens, int D, const void* o, const 
                                   const float* beta, void* y, bool out_f32, hipStream_t stream) {
     const int items_per_token = D / 8;
     const long long items = tokens * items_per_token;
-    const bool small = items * 16 <= 64ll << 20;
+    const long long bytes = items * 16;                       // of bf16 rows
     const int cus = compute_units();
     const uint4v* src = static_cast<const uint4v*>(o);
     const float2* ms = reinterpret_cast<const float2*>(mean_rstd);
@@ -197,7 +202,7 @@ hipError_t launch_layernorm_apply(long long tokens, int D, const void* o, const 
             hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, tokens, tokens_per_block, items_per_token, src, ms, gm, bt, y);
         };
         out_f32 ? go(&layernorm_apply_strip_kernel<true, kStoreStreamed>)
-                : small ? go(&layernorm_apply_strip_kernel<false, kStoreThrough>) : go(&layernorm_apply_strip_kernel<false, kStoreStreamed>);
+                : bytes <= 68ll << 20 ? go(&layernorm_apply_strip_kernel<false, kStoreThrough>) : go(&layernorm_apply_strip_kernel<false, kStoreStreamed>);
         return hipGetLastError();
     }
     const long long step = kInFlight * 256;
@@ -208,8 +213,9 @@ hipError_t launch_layernorm_apply(long long tokens, int D, const void* o, const 
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, items, items_per_block, items_per_token, src, ms, gm, bt, y);
     };
+    const bool through = bytes >= 2ll << 20 && bytes <= 36ll << 20;
     out_f32 ? go(&layernorm_apply_kernel<true, kStoreStreamed>)
-            : small ? go(&layernorm_apply_kernel<false, kStoreThrough>) : go(&layernorm_apply_kernel<false, kStoreStreamed>);
+            : through ? go(&layernorm_apply_kernel<false, kStoreThrough>) : go(&layernorm_apply_kernel<false, kStoreStreamed>);
     return hipGetLastError();
 }
 

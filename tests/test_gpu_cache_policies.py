@@ -29,3 +29,21 @@ def test_bits_do_not_depend_on_the_size_of_the_batch(c2, dtype, B, T, H):
         entry(1, T, H, 64, r[sl], k[sl], v[sl], x[sl], up[sl] if c2 else extra, state[sl], one, s1, code, 1, None, 0)
         torch.cuda.synchronize()
         assert torch.equal(one, out[sl]) and torch.equal(s1, s[sl]), b
+
+
+@pytest.mark.parametrize("H,tokens,piece", [(12, 1400, 700), (12, 25000, 5000), (32, 17409, 4099), (4, 4097, 1025)])
+def test_bits_of_normalised_rows_do_not_depend_on_the_number_of_tokens(H, tokens, piece):
+    """Whole: rows written through (1400 and 4097 tokens) or streamed; in pieces the other way."""
+    g = torch.Generator(device="cuda").manual_seed(tokens)
+    o = torch.randn((tokens, H * 64), generator=g, device="cuda").to(torch.bfloat16)
+    ms = torch.rand((tokens, 2), generator=g, device="cuda")
+    gain, offset = (torch.randn((H * 64,), generator=g, device="cuda") for _ in range(2))
+    whole, parts = torch.empty_like(o), torch.empty_like(o)
+    wkv.wkv6_layernorm_apply_bf16(1, tokens, H, 64, o, ms, gain, offset, whole, wkv.WKV6_DTYPE_BF16)
+    for t in range(0, tokens, piece):
+        sl = slice(t, min(t + piece, tokens))
+        wkv.wkv6_layernorm_apply_bf16(1, sl.stop - t, H, 64, o[sl], ms[sl], gain, offset, parts[sl], wkv.WKV6_DTYPE_BF16)
+    torch.cuda.synchronize()
+    assert torch.equal(whole, parts)
+    want = (o.double() - ms[:, :1]) * ms[:, 1:] * gain + offset      # fp32 arithmetic, one rounding to bf16
+    assert ((whole.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5).all()

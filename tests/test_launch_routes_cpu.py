@@ -54,6 +54,18 @@ def test_fold_by_wave_per_token_only_for_few_tokens_or_many_heads(fake, B, T, H,
     assert lu.launched(fake, [call])[0] == ["layernorm_finalize_few_kernel" if few else "layernorm_finalize_kernel"]
 
 
+@pytest.mark.parametrize("tokens,H,through", [(1, 32, True), (8 * 2048, 32, True), (17 * 1024, 32, True), (17 * 1024 + 1, 32, False), (10 * 2048, 32, False),
+                                              (8 * 1024, 64, True), (9 * 1024, 64, False), (24, 12, False), (1365, 12, False), (1366, 12, True), (24576, 12, True),
+                                              (24577, 12, False), (1023, 16, False), (1024, 16, True), (16384, 16, True), (18433, 16, False)])
+@pytest.mark.parametrize("f32", [False, True])
+def test_normalised_rows_written_through_only_while_that_is_faster(fake, tokens, H, through, f32):
+    """24 tokens of 12 heads written through took 4.3 us against 3.9."""
+    call = ("wkv6_layernorm_apply_bf16", [1, tokens, H, 64, lu.at(0), lu.at(1), lu.at(2), lu.at(3), lu.at(4), int(f32), None])
+    [run] = [e for e in lu.events(fake, [call])[0] if e.kind == "launch"]
+    name = "layernorm_apply_strip_kernel" if H % 32 == 0 else "layernorm_apply_kernel"
+    assert run.kernel.startswith("%s<%s, %d>(" % (name, str(f32).lower(), 16 if through and not f32 else 2)), run.kernel
+
+
 @pytest.mark.parametrize("B,T,D,kernel", [
     (1, 1, 128, "decay_input_kernel<"), (24, 1, 128, "decay_input_kernel<"), (300, 1, 128, "split_kernel<1, 12,"), (16, 1024, 128, "decay_input_kernel<"),
     (33, 1024, 128, "decay_input_kernel<"), (1000, 20, 128, "decay_input_kernel<"), (1000, 40, 256, "decay_input_kernel<"), (33, 1024, 256, "decay_input_kernel<"),
