@@ -67,10 +67,9 @@ __device__ __forceinline__ bf16x8 lds_read_column8(const char* lds, int off) {
     return __builtin_bit_cast(bf16x8, both);
 }
 
-// (The name is that of the kernel for longer sequences: the same step of the same entry points.)
 // kRows: cache policy of the rows' loads, kStreamOnce or 0 (temporal)
 template <bool kC2, bool kLora, bool kOutF32, bool kMoments, int kRows>
-__global__ __launch_bounds__(kOneChunkThreads, 4) void chunked_kernel(Args a) {
+__global__ __launch_bounds__(kOneChunkThreads, 4) void one_chunk_kernel(Args a) {
     using L = Lds<kC2>;
     constexpr bool kStageF32 = kOutF32 || kC2;
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -357,9 +356,9 @@ hipError_t go(const Args& a, hipStream_t stream) {
     // 13.8, 2048 x 24 (104 MB) 17.9 : 21.2, 4096 x 8 (159 MB) 28.7 : 29.3, 4096 x 24 (209 MB) 41.0 : 36.1.
     const long long bytes = static_cast<long long>(grid.x) * (2 * 4096 * 4 + a.T * (kHeadSize * 2) * (kC2 ? 6 : 5));
     if (bytes >= 32ll << 20 && bytes <= 160ll << 20)
-        hipLaunchKernelGGL((chunked_kernel<kC2, kLora, kOutF32, kMoments, 0>), grid, dim3(kOneChunkThreads), Lds<kC2>::kBytes, stream, a);
+        hipLaunchKernelGGL((one_chunk_kernel<kC2, kLora, kOutF32, kMoments, 0>), grid, dim3(kOneChunkThreads), Lds<kC2>::kBytes, stream, a);
     else
-        hipLaunchKernelGGL((chunked_kernel<kC2, kLora, kOutF32, kMoments, kStreamOnce>), grid, dim3(kOneChunkThreads), Lds<kC2>::kBytes, stream, a);
+        hipLaunchKernelGGL((one_chunk_kernel<kC2, kLora, kOutF32, kMoments, kStreamOnce>), grid, dim3(kOneChunkThreads), Lds<kC2>::kBytes, stream, a);
     return hipGetLastError();
 }
 

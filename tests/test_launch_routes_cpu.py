@@ -37,11 +37,11 @@ def test_first_call_raises_every_limit_of_its_entry(fake, make):
 @pytest.mark.parametrize("B,H,c2,longest", [(1, 4, True, 2), (8, 32, True, 2), (8, 32, False, 2), (9, 32, True, 3), (16, 32, False, 3),
                                             (17, 32, True, 4), (32, 32, True, 4), (33, 32, True, 2), (256, 32, True, 2), (17, 32, False, 4),
                                             (33, 32, False, 4), (256, 32, False, 4)])
-def test_fused_decay_calls_are_token_by_token_only_while_that_is_faster(fake, B, H, c2, longest):
-    """Up to 2 to 4 tokens by the number of units; 6 tokens of 32 units took twice as long token by token."""
+def test_fused_decay_calls_are_token_by_token_up_to_two_to_four_tokens(fake, B, H, c2, longest):
+    """By the number of units; 6 tokens of 32 units take twice as long token by token."""
     make = (lambda T: lu.fused_c2(B, T, H)) if c2 else (lambda T: lu.fused_finch(B, T, H))
     for T, kernels in zip(range(1, 9), lu.launched(fake, [make(T) for T in range(1, 9)])):
-        assert kernels == ["recurrent_kernel" if T <= longest else "chunked_kernel"], T
+        assert kernels == ["recurrent_kernel" if T <= longest else "one_chunk_kernel"], T
 
 
 @pytest.mark.parametrize("B,T,H,few", [(1, 1, 1, True), (24, 1, 32, True), (136, 15, 32, True), (137, 15, 32, False), (3, 16, 12, False),
@@ -134,7 +134,7 @@ def test_columns_of_few_units_over_workgroups(fake, entry, bf16, units, T, colum
 def test_sequences_of_one_chunk_take_four_waves_a_unit(fake, make, shortest, B, H):
     for T, ev in zip((shortest, 32, 33), lu.events(fake, [make(B, T, H) for T in (shortest, 32, 33)])):
         [run] = [e for e in ev if e.kind == "launch"]
-        assert run.base == "chunked_kernel" and (run.block, run.bytes <= 40 * 1024) == ((256, True) if T <= 32 else (1024, False))
+        assert (run.base, run.block, run.bytes <= 40 * 1024) == (("one_chunk_kernel", 256, True) if T <= 32 else ("chunked_kernel", 1024, False))
         assert T > 32 or run.grid[0] == B * H
 
 
@@ -147,7 +147,7 @@ def test_one_chunk_of_more_units_than_a_grid_takes(fake, make, lengths, B, H):
     """A launch holds fewer than 2^32 work items: from 2^24 units on, the several units of a workgroup of the kernel for longer sequences."""
     for T, ev in zip(lengths, lu.events(fake, [make(B, T, H) for T in lengths])):
         [run] = [e for e in ev if e.kind == "launch"]
-        assert run.grid[0] * run.block < 2 ** 32 and run.block == (256 if B * H < 2 ** 24 else 1024), T
+        assert run.grid[0] * run.block < 2 ** 32 and run.base == ("one_chunk_kernel" if B * H < 2 ** 24 else "chunked_kernel"), T
 
 
 @pytest.mark.parametrize("entry,B,T,H,multi,traffic", [
