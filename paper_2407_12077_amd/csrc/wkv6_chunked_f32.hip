@@ -27,7 +27,7 @@
 // workgroup issues about 2900 clocks of vector work, 1024 of scores and 1152 kCB / 4 of state work per wave, over four
 // SIMDs; a unit's column groups repeat the producers' part, so columns are spread only while compute units are idle.  The token-by-token
 // kernels it replaces need 196 clocks a token at few units and 4 instructions per state element and 64 lanes at many.  Microseconds,
-// token by token -> here: 32 units x 512 tokens 42.5 -> 30.9, x 128 14.4 -> 11.1; 128 x 512 75 -> 37.6; 256 x 512
+// token by token -> here: 32 units x 512 tokens 42.5 -> 31.7 (25.2 with the scores in a kernel of their own), x 128 14.4 -> 11.1; 128 x 512 75 -> 37.6; 256 x 512
 // 130 -> 52.6, x 1000 247 -> 95; 512 x 512 197 -> 101.  Error against 64 bits no larger: `out` 9.4e-8 (9.4e-8), state 5.8e-8 (6.0e-8);
 // that takes sums in pairs, tokens in their order, and decays from sums of exponents where the comments say so.
 // Also tried: six or eight producers (more registers than three waves a SIMD have: up to 1.6 times slower), one register set
@@ -592,15 +592,15 @@ hipError_t raise_chunked_f32_limits() {
 hipError_t launch_chunked_f32(const Args& a, hipStream_t stream) {
     const hipError_t err = raise_chunked_f32_limits();
     if (err != hipSuccess) return err;
-    // as many workgroups as fit the chip once
-    const long long units = static_cast<long long>(a.B) * a.H;
+    // Column groups while the workgroups fit the chip once
+    const long long cus = compute_units(), units = static_cast<long long>(a.B) * a.H;
     // Scores in a kernel of their own: a launch more (2 to 3 us) against 0.4 us a chunk, and the more units the longer that
     // kernel takes itself.  Microseconds, one kernel : two: 4 units 192 tokens 14.1 : 14.4, 224 16.9 : 15.7; 16 units 192
     // 14.4 : 14.7, 224 17.3 : 15.9; 32 units 224 17.4 : 16.5, 256 18.0 : 17.1, 512 31.7 : 25.3, 2048 112 : 76; 48 units 256 18.1 : 17.9,
     // 320 21.5 : 20.1; 64 units 256 18.4 : 18.5, 320 21.7 : 22.1, 512 32.1 : 28.8, 2048 122 : 102.  With two or four column blocks a workgroup
     // the producers' part is hardly repeated and one kernel is the better one: 128 units x 512 37.8 : 42.2, 256 x 512 52.5 : 75.
-    if (units <= 64) return launch_cb<1, 4>(a, a.T >= 200 + 2 * units, stream);
-    if (units <= 128) return launch_cb<2, 4>(a, false, stream);
+    if (4 * units <= cus) return launch_cb<1, 4>(a, a.T >= 200 + 2 * units, stream);
+    if (2 * units <= cus) return launch_cb<2, 4>(a, false, stream);
     return launch_cb<4, 4>(a, false, stream);
 }
 

@@ -78,7 +78,8 @@ int hipGetDeviceCount(int* count) {
     return 0;
 }
 int hipDeviceGetAttribute(int* value, int, int) {      // the library asks for the number of compute units only
-    *value = 256;
+    const char* units = std::getenv("FAKE_HIP_COMPUTE_UNITS");
+    *value = units ? std::atoi(units) : 256;
     return 0;
 }
 int hipGetSymbolAddress(void** address, const void*) {

@@ -39,9 +39,10 @@ class Event:
         self.base = self.kernel.split("<")[0]
 
 
-def events(fake, calls):
+def events(fake, calls, compute_units=256):
     """calls: [(entry, [arguments])]; per call the events in order.  All calls in one fresh process."""
-    out = subprocess.run([sys.executable, "-c", CHILD, ROOT, fake], input=json.dumps(calls), capture_output=True, text=True)
+    out = subprocess.run([sys.executable, "-c", CHILD, ROOT, fake], input=json.dumps(calls), capture_output=True, text=True,
+                         env={**os.environ, "FAKE_HIP_COMPUTE_UNITS": str(compute_units)})
     assert out.returncode == 0, out.stderr
     res = []
     for (name, args), (status, text) in zip(calls, json.loads(out.stdout)):

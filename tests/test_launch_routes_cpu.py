@@ -196,6 +196,12 @@ def test_fp32_of_more_units_than_a_grid_takes(fake, units, chunked):
     assert run.base == ("chunked_f32_kernel" if chunked else "recurrent_wide_kernel")
 
 
+@pytest.mark.parametrize("compute_units,units,column_blocks", [(256, 64, 1), (256, 65, 2), (256, 129, 4), (128, 32, 1), (128, 33, 2), (128, 64, 2), (128, 65, 4), (304, 76, 1), (304, 152, 2)])
+def test_fp32_column_groups_while_they_fit_the_chip(fake, compute_units, units, column_blocks):
+    [run] = [e for e in lu.events(fake, [lu.time_mix("wkv6_prefill_f32", 1, 150, units)], compute_units)[0] if e.kind == "launch"]
+    assert run.kernel == "chunked_f32_kernel<%d, 4>" % column_blocks
+
+
 @pytest.mark.parametrize("units,shortest", [(1, 202), (32, 264), (64, 328), (65, None), (256, None)])
 def test_fp32_scores_in_a_kernel_of_their_own(fake, units, shortest):
     """A wave a chunk; the second kernel's grid as without them."""
