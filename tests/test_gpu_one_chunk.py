@@ -63,12 +63,33 @@ ENTRIES = ["wkv6_prefill_bf16", "wkv6_prefill_bf16_f32out", "wkv6_finch_c2_prefi
            "wkv6_finch_c2_prefill_bf16_moments", "wkv6_finch_c2_prefill_lora_bf16", "wkv6_prefill_lora_bf16"]
 
 
-# up to 6 tokens of a fused call are token by token; 2048 and 8192 units lie on both sides of the rows' cache policy
+# (up to 2 to 4 tokens of a fused call are token by token); 2048 and 8192 units lie on both sides of the rows' cache policy
 @pytest.mark.parametrize("entry", ENTRIES)
 @pytest.mark.parametrize("B,T,H", [(1, 5, 1), (2, 7, 4), (3, 17, 8), (1, 31, 12), (2, 32, 3), (64, 20, 32), (256, 9, 32)])
 def test_bits_are_those_of_the_head_of_a_longer_sequence(entry, B, T, H):
-    longer = 33 + T % 3
-    t = tensors(B, longer, H, 7 * T + H)
+    compare_with_head_of_longer(entry, tensors(B, 33 + T % 3, H, 7 * T + H), B, T, H)
+
+
+@pytest.mark.parametrize("entry", ENTRIES)
+@pytest.mark.parametrize("B,T,H", [(2, 7, 4), (3, 17, 8), (2, 32, 3)])
+def test_bits_with_decays_of_nought_and_one_and_operands_beyond_fp16(entry, B, T, H):
+    """Logits at both ends of their range (w = 0 and w = 1 exactly) and keys and values that are clamped to +-65504."""
+    t = tensors(B, 33 + T % 3, H, T)
+    g = torch.Generator().manual_seed(T)
+    kind = torch.randint(0, 6, t["x"].shape, generator=g).cuda()
+    big = torch.randint(0, 8, t["k"].shape, generator=g).cuda()
+    column = torch.arange(H * 64, device="cuda") % 5
+    for i, value in enumerate((float("inf"), float("-inf"), 10., -20.)):
+        t["x"][kind == i] = value
+        t["lambda"][column == i] = value
+    for n, lo in (("k", 0), ("v", 2)):
+        t[n][big == lo], t[n][big == lo + 1] = 1e5, -1e5
+    o = compare_with_head_of_longer(entry, t, B, T, H)
+    assert torch.isfinite(o).all() and o.float().abs().max() > 65504
+
+
+def compare_with_head_of_longer(entry, t, B, T, H):
+    longer = t["k"].shape[1]
     # the head of the longer sequence; its tail brings a state of its own, so the states are compared through tokens that change nothing
     for n in ("k", "v"):
         t[n][:, T:] = 0
@@ -84,6 +105,7 @@ def test_bits_are_those_of_the_head_of_a_longer_sequence(entry, B, T, H):
         assert torch.equal(m_long[:, :, :T], m_short)
     if "lora" not in entry:                                   # (fused logits: the tail's decays are not 1)
         assert torch.equal(s_long, s_short)
+    return o_short
 
 
 def test_without_a_state_out_and_in_place():
