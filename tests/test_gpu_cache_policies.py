@@ -31,7 +31,40 @@ def test_bits_do_not_depend_on_the_size_of_the_batch(c2, dtype, B, T, H):
         assert torch.equal(one, out[sl]) and torch.equal(s1, s[sl]), b
 
 
-@pytest.mark.parametrize("H,tokens,piece", [(12, 1400, 700), (12, 25000, 5000), (32, 17409, 4099), (4, 4097, 1025)])
+@pytest.mark.parametrize("mode", ["moments", "lora", "lora_moments", "finch_lora"])
+def test_bits_of_the_modes_inside_a_layer_do_not_depend_on_the_size_of_the_batch(mode):
+    """140 MiB, several units a workgroup (a unit's logits are formed while the one before it is worked on), against calls of 28 MiB with
+    one unit a workgroup.  128 units of 300 tokens are not split."""
+    B, T, H, few = 20, 300, 32, 4
+    g = torch.Generator(device="cuda").manual_seed(3)
+    n = lambda *s: torch.randn(s, generator=g, device="cuda")  # noqa: E731
+    r, k, v, up = ((n(B, T, H, 64) / 8).to(torch.bfloat16) for _ in range(4))
+    x = (torch.rand((B, T, H, 64), generator=g, device="cuda") * 7 - 6).to(torch.bfloat16)
+    y, lam, b_omega = torch.tanh(n(B, T, 64)).to(torch.bfloat16), torch.rand((H * 64,), generator=g, device="cuda") * 6 - 5.5, (n(64, H * 64) / 5).to(torch.bfloat16)
+    u, state = n(H, 64) / 2, n(B, H, 64, 64) / 10
+
+    def call(sl):
+        b = sl.stop - sl.start
+        out = torch.full((b, T, H, 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+        s, m = torch.full((b, H, 64, 64), float("nan"), device="cuda"), torch.full((b, H, T, 2), float("nan"), device="cuda")
+        if mode == "moments":
+            wkv.wkv6_finch_c2_prefill_bf16_moments(b, T, H, 64, r[sl], k[sl], v[sl], x[sl], up[sl], state[sl], out, m, s)
+        elif mode == "finch_lora":
+            wkv.wkv6_prefill_lora_bf16(b, T, H, 64, 64, r[sl], k[sl], v[sl], y[sl], lam, b_omega, u, state[sl], out, s)
+        else:
+            wkv.wkv6_finch_c2_prefill_lora_bf16(b, T, H, 64, 64, r[sl], k[sl], v[sl], y[sl], lam, b_omega, up[sl], state[sl], out,
+                                                m if mode == "lora_moments" else None, s)
+        torch.cuda.synchronize()
+        return (out, s, m) if "moments" in mode else (out, s)
+
+    whole = call(slice(0, B))
+    for b in range(0, B, few):
+        sl = slice(b, b + few)
+        for got, part in zip(whole, call(sl)):
+            assert torch.isfinite(part).all() and torch.equal(got[sl], part), b
+
+
+@pytest.mark.parametrize("H,tokens,piece", [(12, 1400, 700), (12, 25000, 5000), (32, 17409, 4100), (4, 4097, 1026)])
 def test_bits_of_normalised_rows_do_not_depend_on_the_number_of_tokens(H, tokens, piece):
     """Whole: rows written through (1400 and 4097 tokens) or streamed; in pieces the other way."""
     g = torch.Generator(device="cuda").manual_seed(tokens)
