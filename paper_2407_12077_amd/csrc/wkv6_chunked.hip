@@ -668,7 +668,10 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
     // stays in registers for the whole kernel; y rows (128 bytes per token, shared by all heads, so served by L2) are
     // requested right behind the use of the chunk before: a load returns behind the chunk loads that the producers have
     // in flight, and one requested at the start of the window that uses it lengthens the window (8 sequences of 2048 tokens and
-    // 32 heads 86.7 -> 80.3 us, with no request at all 78.3; 4 x 3000 x 64 121 -> 115).
+    // 32 heads 86.7 -> 80.3 us, with no request at all 78.3; 4 x 3000 x 64 121 -> 115).  In the Finch form, whose windows are shorter, the
+    // request costs where everything lies in the caches (1 x 600 tokens x 32 heads 20.6 -> 21.6 us, 2 x 800 25.2 -> 26.6): there it goes out
+    // without a branch, past the end with an empty descriptor, while the products are formed (21.1, 25.7; 8 x 2048 74.4 -> 73.8; 1 x 100
+    // 9.3 -> 9.4, 9.5 with the request at the start).  In the Finch-C2 form the two are level, but for short sequences (1 x 100 10.8 -> 11.0).
     [[maybe_unused]] bf16x8 bw[2];
     [[maybe_unused]] bf16x8 ya[2][2];
     [[maybe_unused]] float lam = 0.f;
@@ -691,7 +694,7 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
         const long long batch = y_b0 + (kMulti ? static_cast<long long>(dn.ui) * y_bstep : 0);
         const __amdgpu_buffer_rsrc_t ry = chunk_rsrc(static_cast<const char*>(a.y) + (batch * a.T + un.t0) * (kLoraRank * 2),
                                                      static_cast<long long>(dn.c) * kChunk * (kLoraRank * 2),
-                                                     static_cast<long long>(un.tokens) * (kLoraRank * 2));
+                                                     kC2 || dn.live(un) ? static_cast<long long>(un.tokens) * (kLoraRank * 2) : 0);
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
@@ -699,23 +702,28 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
                 ya[rt][ks] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
                                                             ry, y_voff + 16 * rt * (kLoraRank * 2) + 64 * ks, 0, 0));
     };
-    auto d_finish = [&](int pos) {                   // pos: the chunk's position in the sequence (LDS parity)
+    auto d_finish = [&](int pos, auto request) {     // pos: the chunk's position in the sequence (LDS parity)
         char* dx = lds_all + kDx + (pos & 1) * kDxBuf + (8 * cw + (l16 >> 1)) * kDxPair + (l16 & 1) * (kChunk * 4) + 16 * g4;
+        float4v acc[2];
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt) {
-            float4v acc = {lam, lam, lam, lam};
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ya[rt][0], bw[0], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ya[rt][1], bw[1], acc, 0, 0, 0);
-            *reinterpret_cast<float4v*>(dx + 64 * rt) = acc;     // tokens 16rt + 4g4 .. +3 of this lane's channel
+            acc[rt] = float4v{lam, lam, lam, lam};
+            acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ya[rt][0], bw[0], acc[rt], 0, 0, 0);
+            acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ya[rt][1], bw[1], acc[rt], 0, 0, 0);
         }
+        if constexpr (!kC2) request();
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) *reinterpret_cast<float4v*>(dx + 64 * rt) = acc[rt];     // tokens 16rt + 4g4 .. +3 of this lane's channel
+        if constexpr (kC2) request();
     };
     Cursor<kMulti> dn{0, 0};                         // the chunk whose logits are formed next
     if constexpr (kLora) {
         if (total > 0) {
             y_fetch(dn);
-            d_finish(0);
-            dn.advance(1, un.nchunks);
-            if (total > 1) y_fetch(dn);
+            d_finish(0, [&] {
+                dn.advance(1, un.nchunks);
+                if (!kC2 || total > 1) y_fetch(dn);
+            });
         }
     }
 
@@ -810,9 +818,10 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
         }
         if constexpr (kLora) {
             if (dlive) {
-                d_finish(n + 1);
-                dn.advance(1, un.nchunks);
-                if (n + 2 < total) y_fetch(dn);
+                d_finish(n + 1, [&] {
+                    dn.advance(1, un.nchunks);
+                    if (!kC2 || n + 2 < total) y_fetch(dn);
+                });
             }
         }
         __syncthreads();                                                        // window barrier
