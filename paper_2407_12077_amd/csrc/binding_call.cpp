@@ -1,7 +1,8 @@
 // The calls of the Python binding in native code (CPython extension `_call`): arguments to C types, the current stream,
 // the call, the status.  Where a kernel takes three microseconds the host is what a call costs.  Measured, a decode step of
 // one user (32 heads): 5.2 us a call through ctypes, 4.2 here; of the host's part before the library's own checks and
-// launch 2.3 us became 0.85, and 0.5 of these are torch's seven data_ptr().  A first call on new buffers 25 -> 18 us.
+// launch 2.3 us became 0.85, and 0.5 of these are torch's seven data_ptr().  (A first call on new buffers takes 18 to 21 us
+// either way.)
 // The functions are those of the library that the binding has loaded, found in it by name; their types come from the header,
 // so a list of arguments that does not match does not compile.
 //

@@ -204,15 +204,14 @@ int wkv6_finch_c2_prefill_bf16_moments(int B, int T, int H, int N, const void* r
 
 namespace {
 
-// Fused decay path: sequences at most this long go to the token-by-token kernel.  It streams the states once, as for the
-// append entries, but a token costs it 64 more multiply-adds and a barrier, while the chunked kernel takes any of these
-// lengths in the time of one window per round of workgroups.  So the line lies the further out the more rounds that
-// would be, until the token-by-token kernel needs several rounds of waves itself (from one unit per SIMD on, sooner
-// with the registers of the Finch-C2 form).  Measured, microseconds, chunked against token by token, Finch-C2 with moments:
-// 256 units 2 tokens 6.9 : 7.0, 3 tokens 6.9 : 8.6; 512 units 3 tokens 9.7 : 9.4, 4 tokens 9.7 : 11.1; 1024 units 4 tokens
-// 15.2 : 13.5, 5 tokens 15.3 : 15.5; 2048 units 1 token 22.0 : 14.6, 2 tokens 22.1 : 18.7, 3 tokens 22.4 : 22.4; 8192 units 2
-// tokens 74.8 : 69.4, 3 tokens 74.9 : 85.6.  Finch: 256 units 2 tokens 6.4 : 6.1, 3 tokens 6.4 : 7.5; 512 units 3 tokens 9.0 : 8.1, 4
-// tokens 9.0 : 9.5; 768 units 4 tokens 12.2 : 10.5; 8192 units 4 tokens 73.7 : 68.2, 6 tokens 74.1 : 81.8.
+// Fused decay path: sequences at most this long go to the token-by-token kernel, which works on fp32 operands; the one-chunk kernel, which
+// takes the next longer ones, rounds its operands to fp16.  The lines were drawn as lines of speed against the chunked kernel, one
+// window per round of workgroups at any of these lengths.  Against the one-chunk kernel, which takes any of them in one pass over the states,
+// the token-by-token kernel is the faster one for a single token only, and the lines stay for the precision: a call of 2 to 4 tokens is not moved to
+// fewer bits.  Microseconds, token by token : one chunk, Finch-C2 with moments: 256 units 1 token 6.0 : 6.6, 2 tokens 7.6 : 6.5; 512 units 1 token
+// 6.6 : 7.5, 3 tokens 10.0 : 7.6; 1024 units 1 token 8.7 : 10.0, 4 tokens 14.7 : 10.2; 2048 units 1 token 15.9 : 17.5, 2 tokens 19.7 : 17.5;
+// 8192 units 1 token 54.6 : 63.3, 2 tokens 71.1 : 63.4.  Finch: 256 units 2 tokens 6.8 : 5.9; 1024 units 4 tokens 12.9 : 9.4; 2048 units 1
+// token 12.1 : 17.0, 3 tokens 15.9 : 16.1, 4 tokens 17.5 : 16.3; 8192 units 1 token 49.7 : 55.3, 2 tokens 55.6 : 55.1, 4 tokens 68.7 : 57.8.
 int fused_short_tokens(int B, int H, bool finch_c2) {
     const long long units = static_cast<long long>(B) * H;
     if (units <= 256) return 2;
