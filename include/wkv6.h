@@ -55,7 +55,9 @@
  * (1 + max|r|) max|S|).  Finch-C2 channels with decay logits below about -10
  * (1 - w < 5e-5) are the case that matters: scale kbar so that kbar (1 - w)
  * stays above 2^-14 if those state rows are needed to full relative accuracy.
- * The fp32 entry point and the decode entry points have no such limits.
+ * The fp32 entry point and the decode entry points have no such limits.  (Where the
+ * fp32 entry works in chunks it forms the scores, sums of r*k, before it takes
+ * them times v, so these have to stay inside the fp32 range as well.)
  *
  * Errors: every entry point returns a wkv6_status.  Arguments are validated
  * before anything is enqueued; on a non-zero status nothing was launched,
