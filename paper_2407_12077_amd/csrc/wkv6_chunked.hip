@@ -135,7 +135,9 @@ __device__ __forceinline__ int score_off(int t, int granule) {
 // The line between kCached and kLarge is drawn for rows that the caches hold, as those that a kernel has just written; rows that none holds
 // lose by kCached.  kLarge -> kCached, one set of tensors over and over / three sets in turn / sets that no cache holds: Finch 8 x 200 x 32
 // (39 MiB) 13.1 -> 11.8 / 14.8 -> 14.0 / 15.0 -> 15.3, 8 x 400 (70) 18.8 -> 19.3 / 20.5 -> 19.5 / 21.2 -> 22.3, 16 x 300 (110) 27.7 -> 27.2 /
-// 27.7 -> 28.4 / 27.9 -> 29.9.  The last pass of a split call, whose first pass has read k, v and x, has the same line: Finch-C2 1 x 2000
+// 27.7 -> 28.4 / 27.9 -> 29.9.  Behind copies that have just written the rows from elsewhere, the prefill's share: Finch 8 x 100 10.1 -> 9.6,
+// 8 x 300 15.9 -> 15.8, 8 x 400 18.4 -> 18.3, 12 x 250 21.7 -> 21.2, fp32 out 8 x 300 16.2 -> 16.6, fused Finch-C2 with moments 8 x 300
+// 20.0 -> 19.0.  The last pass of a split call, whose first pass has read k, v and x, has the same line: Finch-C2 1 x 2000
 // (48 MiB) 27.6 -> 26.5 / 27.5 -> 26.1 / 28.6 -> 28.6, 1 x 4096 (97) 43.3 -> 41.5 / 42.5 -> 42.2 / 41.8 -> 43.7, 1 x 5000 (118) 48.5 -> 46.9 /
 // 47.7 -> 48.4 / 48.0 -> 49.5.
 enum class Traffic { kCached, kLarge, kStreamed };
