@@ -107,6 +107,9 @@ constexpr int kDx = kLdsBytes;
 constexpr int kLdsBytesLora = kLdsBytes + 2 * kDxBuf;
 static_assert(kLdsBytesLora <= 160 * 1024, "LDS budget");
 
+// Units of several heads in a workgroup, Finch form: the bonus of all heads as fp16 pairs, behind the two main buffers.
+constexpr int kTurnHeads = (160 * 1024 - kLdsBytes) / (kHeadSize * 2);
+
 // Byte offset, inside a transposed tile, of the 16-byte granule `granule` (tokens 8*granule .. +7)
 // of row `row` (a channel).  The XOR with two row bits makes the producers' 8-byte stores (32
 // lanes on 32 different rows, two lanes per granule) and the consumers' 16-byte reads (16
@@ -191,8 +194,8 @@ __device__ __forceinline__ void load_rows_kv(Raw& d, const Streams& st, long lon
 // The units (batch, head) of one workgroup.  A workgroup keeps its pipeline running across unit
 // boundaries: its chunks form one sequence, unit after unit, and only the state (consumers) and
 // the base addresses change at a boundary, so short sequences do not pay the fill and drain of
-// the pipeline once per unit.  All units of a workgroup share the head (the stride between them
-// is a multiple of H), have the same length T, and lie `step` elements apart.
+// the pipeline once per unit.  The stride between the units of a workgroup is a multiple of H, so they share the head
+// unless they take the heads in turn (kTurn: the head moves on by one from each unit to the next); they have the same length T, and their token rows lie `step` elements apart.
 struct Units {
     int first;            // index (batch * H + head) of the first one: selects state_in / state_out / moments
     int stride;           // unit index stride
@@ -205,20 +208,24 @@ struct Units {
     int tokens;           // tokens of a unit
     const char* entering; // segment's entering state ([64][64] fp32 with the pitches below), or nullptr: state_in
     int pitch_row, pitch_half;
+    int heads, head0;     // heads of a token row; the first unit's
+    __device__ __forceinline__ int next_head(int hd) const { return hd + 1 == heads ? 0 : hd + 1; }
+    __device__ __forceinline__ long long index(int ui, int hd) const { return first + static_cast<long long>(ui) * stride + (hd - head0); }
 };
 
 // Position in the workgroup's chunk sequence: unit ui, chunk c of it.  Advanced without
 // divisions; c < 0 (before the start) and ui >= count (past the end) mean "no chunk".
-// With a single unit per workgroup (kMulti false) ui stays 0 and "past the end" is c >= nchunks.
-template <bool kMulti>
+// With a single unit per workgroup ui stays 0 and "past the end" is c >= nchunks.
+template <bool kTurn, bool kMulti>
 struct Cursor {
-    int ui, c;
-    __device__ __forceinline__ void advance(int by, int nchunks) {
+    int ui, c, hd;        // hd: the head of unit ui
+    __device__ __forceinline__ void advance(int by, const Units& un) {
         c += by;
         if constexpr (kMulti) {
-            while (c >= nchunks) {
-                c -= nchunks;
+            while (c >= un.nchunks) {
+                c -= un.nchunks;
                 ++ui;
+                if constexpr (kTurn) hd = un.next_head(hd);
             }
         }
     }
@@ -227,6 +234,7 @@ struct Cursor {
         return c < un.nchunks;
     }
     __device__ __forceinline__ long long unit_elems(const Units& un) const {
+        if constexpr (kTurn) return ui * un.step + (hd - un.head0) * kHeadSize;
         if constexpr (kMulti) return ui * un.step;
         return 0;
     }
@@ -235,7 +243,7 @@ struct Cursor {
 // ------------------------------------------------------------------------------------------
 // Producer waves: group pg (0..2) = chunk index mod 3, wq = wave inside the group
 // ------------------------------------------------------------------------------------------
-template <int kMode, bool kC2, bool kMulti, Traffic kTraffic>
+template <int kMode, bool kC2, bool kTurn, bool kMulti, Traffic kTraffic>
 __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, int pg, int wq, int h,
                                          const Units& un, long long tok_stride, int T) {
     constexpr int kRows = kTraffic == Traffic::kCached ? 0 : kStreamOnce;
@@ -254,7 +262,12 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
     const int g4 = lane >> 4;
 
     // the bonus u of this channel pair as an fp16 pair (Finch form only)
-    const unsigned hu = kC2 ? 0u : pack_h2(a.u[h * kHeadSize + 2 * cp], a.u[h * kHeadSize + 2 * cp + 1]);
+    [[maybe_unused]] unsigned hu = kC2 ? 0u : pack_h2(a.u[h * kHeadSize + 2 * cp], a.u[h * kHeadSize + 2 * cp + 1]);
+    constexpr bool kTurnU = kTurn && !kC2;  // all heads' u wait in LDS
+    if constexpr (kTurnU) {
+        for (int i = tid; i < a.H * (kHeadSize / 2); i += 4 * 64 * kProducerGroups)
+            lds_write_u32(lds_all, kLdsBytes + 4 * i, pack_h2(a.u[2 * i], a.u[2 * i + 1]));
+    }
 
     Streams st;
     st.r = static_cast<const char*>(a.r) + un.base0 * 2;
@@ -288,9 +301,12 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
 
     // Phase D.  Digest the raw inputs in `cur` (chunk c): decays, their products inside
     // the thread's 4-token group (published in G), and every operand that needs nothing else.
-    auto digest = [&](int g, int c, Raw& cur) {     // g: position in the sequence, c: chunk of its unit
+    auto digest = [&](int g, int c, int hd, Raw& cur) {     // g: position in the sequence, c: chunk of its unit, hd: head
         char* lds = lds_all + (g & 1) * kBuf;
         const int t0 = c * kChunk;
+        if constexpr (kTurnU) {                              // this group's first chunk of a unit is one of its first three
+            if (c < kProducerGroups) hu = *reinterpret_cast<const unsigned*>(lds_all + kLdsBytes + (hd * (kHeadSize / 2) + cp) * 4);
+        }
         if (t0 + kChunk > T) {
             // last, partial chunk: tokens past the end were read as zeros; give them w = 1
 #pragma unroll
@@ -465,7 +481,7 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
     // instruction), so thread j holds channels 4j .. and 32 + 4j ..; a bf16 row's threads hold channels 8j ..
     [[maybe_unused]] const int up_voff = static_cast<int>(srow * st.row_bytes + (kOutF32 ? scol : scol * 2));
     [[maybe_unused]] const char* up_base = kC2 ? static_cast<const char*>(a.uprime) + un.base0 * 2 : nullptr;
-    auto load_uprime = [&](const Cursor<kMulti>& at) {
+    auto load_uprime = [&](const Cursor<kTurn, kMulti>& at) {
         if constexpr (kC2) {
             // unconditional (exact wait counts): before the start it re-reads chunk 0, past the
             // end the descriptor is empty
@@ -489,7 +505,7 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
     [[maybe_unused]] const long long out_span = static_cast<long long>(T - 1) * out_row_bytes + kHeadSize * kOutElem;
     [[maybe_unused]] const int out_voff = static_cast<int>(srow * out_row_bytes + scol * kOutElem);
     [[maybe_unused]] const char* out_base = static_cast<const char*>(a.out) + un.base0 * kOutElem;
-    auto store_rows = [&](int g, const Cursor<kMulti>& at) {   // g: position in the sequence (LDS parity)
+    auto store_rows = [&](int g, const Cursor<kTurn, kMulti>& at) {   // g: position in the sequence (LDS parity)
         const char* lds = lds_all + (g & 1) * kBuf;
         const int t = at.c * kChunk + srow;
         const __amdgpu_buffer_rsrc_t ro = chunk_rsrc(out_base + at.unit_elems(un) * kOutElem,
@@ -506,8 +522,7 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
                 if constexpr (kMoments) {
                     const float2v pair = row_moments(q0, q1);        // the row's first thread writes it
                     if (scol == 0) {
-                        long long unit_index = un.first;
-                        if constexpr (kMulti) unit_index += static_cast<long long>(at.ui) * un.stride;
+                        const long long unit_index = kMulti ? un.index(at.ui, at.hd) : un.first;
                         // streamed like the output rows (measured: 7 % of the kernel's time on many
                         // short units against a plain store)
                         __builtin_nontemporal_store(pair, reinterpret_cast<float2v*>(a.moments + (unit_index * a.T + un.t0 + t) * 2));
@@ -544,15 +559,15 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
     // -3 %, config 5 -4 to -12 % depending on the box, fp32 output -8 %, nothing slower.
     const int total = un.count * un.nchunks;
     const int nwin = window_count(total);
-    Cursor<kMulti> cur{0, 0}, ld{0, 0}, stc{0, pg - 2};      // chunk g, chunk g+6 (loads), chunk g-2 (stores)
-    cur.advance(pg, un.nchunks);
-    ld.advance(pg, un.nchunks);
-    stc.advance(0, un.nchunks);
-    auto fetch_xr = [&](Raw& buf, const Cursor<kMulti>& at) {
+    Cursor<kTurn, kMulti> cur{0, 0, un.head0}, ld{0, 0, un.head0}, stc{0, pg - 2, un.head0};      // chunk g, chunk g+6 (loads), chunk g-2 (stores)
+    cur.advance(pg, un);
+    ld.advance(pg, un);
+    stc.advance(0, un);
+    auto fetch_xr = [&](Raw& buf, const Cursor<kTurn, kMulti>& at) {
         const bool live = at.live(un);                // uniform; dead: offset past the span = empty descriptor
         load_rows_xr<kLora, kRows>(buf, st, live ? at.unit_elems(un) * 2 : 0, live ? at.c * kChunk : T + kChunk, voff);
     };
-    auto fetch_kv = [&](Raw& buf, const Cursor<kMulti>& at) {
+    auto fetch_kv = [&](Raw& buf, const Cursor<kTurn, kMulti>& at) {
         const bool live = at.live(un);
         load_rows_kv<kRows>(buf, st, live ? at.unit_elems(un) * 2 : 0, live ? at.c * kChunk : T + kChunk, voff);
     };
@@ -561,7 +576,7 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
     auto cycle = [&](int g, Raw& buf) {
         const bool live = cur.live(un);
         __builtin_amdgcn_s_setprio(2);            // see the note on wave priorities above
-        if (live) digest(g, cur.c, buf);
+        if (live) digest(g, cur.c, cur.hd, buf);
         load_uprime(stc);                         // older than the chunk loads: waited for first
         fetch_xr(buf, ld);
         __syncthreads();                                                        // window barrier
@@ -573,16 +588,16 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
         if (live) scores(g);
         if (stc.c >= 0 && stc.live(un)) store_rows(g - 2, stc);
         __syncthreads();                                                        // window barrier
-        cur.advance(3, un.nchunks);
-        ld.advance(3, un.nchunks);
-        stc.advance(3, un.nchunks);
+        cur.advance(3, un);
+        ld.advance(3, un);
+        stc.advance(3, un);
     };
     fetch_xr(raw_a, ld);
     fetch_kv(raw_a, ld);
-    ld.advance(3, un.nchunks);
+    ld.advance(3, un);
     fetch_xr(raw_b, ld);
     fetch_kv(raw_b, ld);
-    ld.advance(3, un.nchunks);                    // now six chunks ahead of `cur`
+    ld.advance(3, un);                    // now six chunks ahead of `cur`
     __syncthreads();                                                            // start barrier
     int done = 0;                                                               // windows passed
     for (; done < pg; ++done) {
@@ -607,7 +622,7 @@ __device__ __forceinline__ void producer(const Args& a, char* lds_all, int tid, 
 // ------------------------------------------------------------------------------------------
 // Consumer waves
 // ------------------------------------------------------------------------------------------
-template <int kMode, bool kC2, bool kMulti, Traffic kTraffic>
+template <int kMode, bool kC2, bool kTurn, bool kMulti, Traffic kTraffic>
 __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane, int cw, const Units& un) {
     constexpr int kState = kTraffic == Traffic::kCached ? kStoreThrough | kStreamOnce : 0;
     constexpr bool kOutF32 = kMode == 1;
@@ -626,13 +641,13 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
     float4v S[4];
     [[maybe_unused]] float4v Snext[4];
     const int state_voff = (4 * g4 * 64 + j) * 4;
-    auto state_rsrc = [&](const float* base, int ui) {
-        const long long unit = static_cast<long long>(un.first) + static_cast<long long>(ui) * un.stride;
+    auto state_rsrc = [&](const float* base, int ui, int hd) {
+        const long long unit = un.index(ui, hd);
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base + unit * 4096), 0, 4096 * 4, 0x00020000);
     };
-    auto fetch_state = [&](float4v (&dst)[4], int ui) {
+    auto fetch_state = [&](float4v (&dst)[4], int ui, int hd) {
         if (a.state_in && ui < un.count) {
-            const __amdgpu_buffer_rsrc_t rs = state_rsrc(a.state_in, ui);
+            const __amdgpu_buffer_rsrc_t rs = state_rsrc(a.state_in, ui, hd);
 #pragma unroll
             for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
@@ -644,7 +659,7 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
         }
     };
     if constexpr (kMulti) {
-        fetch_state(Snext, 0);
+        fetch_state(Snext, 0, un.head0);
     } else if (un.entering) {
         // A token segment: its entering state, rows and half rows at the pitches of where it was left.  When
         // that is the segment's own rows of `out`, this load has returned before the first of them is
@@ -657,7 +672,7 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
             for (int e = 0; e < 4; ++e)
                 S[nb][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, (16 * nb + e) * un.pitch_row, 0));
     } else {
-        fetch_state(S, 0);
+        fetch_state(S, 0, un.head0);
     }
 
     // Output of the chunk whose state chain ran last, transposed: o[tq][e] belongs to token
@@ -698,7 +713,7 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
         y_b0 = un.first / a.H;
         y_bstep = un.stride / a.H;
     }
-    auto y_fetch = [&](const Cursor<kMulti>& dn) {
+    auto y_fetch = [&](const Cursor<kTurn, kMulti>& dn) {
         const long long batch = y_b0 + (kMulti ? static_cast<long long>(dn.ui) * y_bstep : 0);
         const __amdgpu_buffer_rsrc_t ry = chunk_rsrc(static_cast<const char*>(a.y) + (batch * a.T + un.t0) * (kLoraRank * 2),
                                                      static_cast<long long>(dn.c) * kChunk * (kLoraRank * 2),
@@ -724,19 +739,19 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
         for (int rt = 0; rt < 2; ++rt) *reinterpret_cast<float4v*>(dx + 64 * rt) = acc[rt];     // tokens 16rt + 4g4 .. +3 of this lane's channel
         if constexpr (kC2) request();
     };
-    Cursor<kMulti> dn{0, 0};                         // the chunk whose logits are formed next
+    Cursor<kTurn, kMulti> dn{0, 0, un.head0};                         // the chunk whose logits are formed next
     if constexpr (kLora) {
         if (total > 0) {
             y_fetch(dn);
             d_finish(0, [&] {
-                dn.advance(1, un.nchunks);
+                dn.advance(1, un);
                 if (!kC2 || total > 1) y_fetch(dn);
             });
         }
     }
 
     __syncthreads();                                                            // start barrier
-    Cursor<kMulti> at{0, 0};                         // chunk n-2 of the sequence: the state chain's
+    Cursor<kTurn, kMulti> at{0, 0, un.head0};                         // chunk n-2 of the sequence: the state chain's
 #pragma clang loop unroll(disable)
     for (int n = 0; n < nwin; ++n) {
         [[maybe_unused]] const bool dlive = kLora && n + 1 < total;
@@ -770,7 +785,7 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
                 if constexpr (kMulti) {
 #pragma unroll
                     for (int nb = 0; nb < 4; ++nb) S[nb] = Snext[nb];
-                    fetch_state(Snext, at.ui + 1);
+                    fetch_state(Snext, at.ui + 1, kTurn ? un.next_head(at.hd) : at.hd);
                 }
             }
             // inter-chunk read: o[t][j] = sum_n (r_t W(t,-1))[n] S[n][j]; the state registers,
@@ -811,7 +826,7 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
             if (at.c == un.nchunks - 1) {
                 // the unit ends: its final state
                 if (un.state_out) {
-                    const __amdgpu_buffer_rsrc_t rs = state_rsrc(un.state_out, at.ui);
+                    const __amdgpu_buffer_rsrc_t rs = state_rsrc(un.state_out, at.ui, at.hd);
 #pragma unroll
                     for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
@@ -822,12 +837,12 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
                         }
                 }
             }
-            at.advance(1, un.nchunks);
+            at.advance(1, un);
         }
         if constexpr (kLora) {
             if (dlive) {
                 d_finish(n + 1, [&] {
-                    dn.advance(1, un.nchunks);
+                    dn.advance(1, un);
                     if (!kC2 || n + 2 < total) y_fetch(dn);
                 });
             }
@@ -836,7 +851,7 @@ __device__ __forceinline__ void consumer(const Args& a, char* lds_all, int lane,
     }
 }
 
-template <int kMode, bool kC2, bool kMulti, Traffic kTraffic>
+template <int kMode, bool kC2, bool kTurn, bool kMulti, Traffic kTraffic>
 __global__ __launch_bounds__(kThreads) void chunked_kernel(Args a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     clamp_fp16_overflow();
@@ -856,7 +871,7 @@ __global__ __launch_bounds__(kThreads) void chunked_kernel(Args a) {
     const int seg = bs - b * a.segs;
     const long long tok_stride = static_cast<long long>(a.H) * kHeadSize;
     // The workgroup's units: this one and, when the launch gave a stride (a multiple of H, whole
-    // sequences only), every stride-th unit after it: same head, batch index advancing.
+    // sequences only), every stride-th unit after it, batch index advancing: same head, or the next one each time.
     Units un;
     un.t0 = seg * a.seg_len;
     const int T = a.T - un.t0 < a.seg_len ? a.T - un.t0 : a.seg_len;
@@ -868,6 +883,8 @@ __global__ __launch_bounds__(kThreads) void chunked_kernel(Args a) {
     if (a.segs > 1) un.entering = a.place.base + b * a.place.batch + seg * a.place.seg + h * a.place.head;
     un.pitch_row = a.place.row;
     un.pitch_half = a.place.half;
+    un.heads = a.H;
+    un.head0 = h;
     un.count = 1;
     un.nchunks = (T + kChunk - 1) / kChunk;
     un.base0 = static_cast<long long>(b) * a.batch_stride + un.t0 * tok_stride + static_cast<long long>(h) * kHeadSize;
@@ -878,24 +895,59 @@ __global__ __launch_bounds__(kThreads) void chunked_kernel(Args a) {
         un.step = static_cast<long long>(a.unit_stride / a.H) * a.batch_stride;
     }
     if (wid < 4 * kProducerGroups)
-        producer<kMode, kC2, kMulti, kTraffic>(a, lds, tid, wid >> 2, wid & 3, h, un, tok_stride, T);
+        producer<kMode, kC2, kTurn, kMulti, kTraffic>(a, lds, tid, wid >> 2, wid & 3, h, un, tok_stride, T);
     else
-        consumer<kMode, kC2, kMulti, kTraffic>(a, lds, tid & 63, wid - 4 * kProducerGroups, un);
+        consumer<kMode, kC2, kTurn, kMulti, kTraffic>(a, lds, tid & 63, wid - 4 * kProducerGroups, un);
 }
 
 template <int kMode, bool kC2>
+constexpr int lds_bytes_of(bool turn, int heads) {
+    return (kMode >= 4 ? kLdsBytesLora : kLdsBytes) + (turn && !kC2 ? heads * kHeadSize * 2 : 0);
+}
+
+// Which kernels take the heads in turn (heads_in_turn below): not those of a layer's modes, and in the Finch form with bf16 rows not
+// beyond a GiB.
+template <int kMode, bool kC2, Traffic kTraffic>
+constexpr bool kHasTurn = kMode < 3 && (kTraffic == Traffic::kLarge || (kTraffic == Traffic::kStreamed && (kMode == 1 || kC2)));
+
+template <int kMode, bool kC2>
 hipError_t raise_mode_limits() {
-    constexpr int lds_bytes = kMode >= 4 ? kLdsBytesLora : kLdsBytes;
     struct Tag {};
     return once_per_device<Tag>([] {
-        hipError_t e = set_lds_limit(&chunked_kernel<kMode, kC2, false, Traffic::kCached>, lds_bytes);
-        if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, true, Traffic::kCached>, lds_bytes);
-        if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, false, Traffic::kLarge>, lds_bytes);
-        if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, true, Traffic::kLarge>, lds_bytes);
+        constexpr int bytes = lds_bytes_of<kMode, kC2>(false, 0);
+        [[maybe_unused]] constexpr int turn = lds_bytes_of<kMode, kC2>(true, kTurnHeads);
+        hipError_t e = set_lds_limit(&chunked_kernel<kMode, kC2, false, false, Traffic::kCached>, bytes);
+        if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, false, true, Traffic::kCached>, bytes);
+        if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, false, false, Traffic::kLarge>, bytes);
+        if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, false, true, Traffic::kLarge>, bytes);
         if constexpr (kMode < 3)
-            if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, true, Traffic::kStreamed>, lds_bytes);
+            if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, false, true, Traffic::kStreamed>, bytes);
+        if constexpr (kHasTurn<kMode, kC2, Traffic::kLarge>)
+            if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, true, true, Traffic::kLarge>, turn);
+        if constexpr (kHasTurn<kMode, kC2, Traffic::kStreamed>)
+            if (e == hipSuccess) e = set_lds_limit(&chunked_kernel<kMode, kC2, true, true, Traffic::kStreamed>, turn);
         return e;
     });
+}
+
+// Whether the units of a workgroup take the heads in turn.  Where a token row is a multiple of 1 KiB, all rows of a head share
+// address bits 7 to 9, and so do all streams of a unit where the tensors start equally aligned, as an allocator has them.  The memory serves one of
+// the eight classes more slowly (a unit of it takes 7 % longer in the Finch form, 22 % in Finch-C2), so a workgroup that kept its
+// head would end last, or early; in turn, each takes its share of every class.  Same head -> in turn, us, tensors of one allocation each:
+// Finch-C2 256 x 512 tokens x 32 heads 688 -> 628, 16 x 4096 x 32 364 -> 351, 10 x 4000 x 40 317 -> 296, 32 x 300 x 32 54.1 -> 53.0; Finch
+// 16 x 4096 x 32 323 -> 311, 10 x 5000 x 64 459 -> 436, 32 x 1000 x 32 140 -> 134, fp32 out 64 x 2500 x 32 804 -> 753.  Not taken: bf16 rows whose
+// streams start 128 bytes apart, which lie in every class by themselves (Finch-C2 64 x 1000 x 32 298 -> 306; fp32 rows, of 256
+// bytes, gain there too: 341 -> 323, Finch 64 x 2500 755 -> 727); Finch, bf16 out, from 1 GiB on, which the kernel's own cycles bound (64 x 1000 x
+// 32 255 -> 257, 12 x 12 000 x 32 698 -> 700); calls that the memory-side cache holds (20 x 60 x 32 13.6 -> 13.8, 30 x 100 x 32
+// 21.0 -> 21.5); and not with fused logits, whose consumers hold their head's slice of B in registers.
+template <int kMode, bool kC2>
+bool heads_in_turn(const Args& a) {
+    if (a.H % 8 != 0 || (!kC2 && a.H > kTurnHeads)) return false;
+    if (kMode == 1) return true;
+    const auto address_class = [](const void* p) { return reinterpret_cast<unsigned long long>(p) >> 7 & 7; };
+    const auto c = address_class(a.r);
+    return address_class(a.k) == c && address_class(a.v) == c && address_class(a.x) == c && address_class(a.out) == c &&
+           (!kC2 || address_class(a.uprime) == c);
 }
 
 template <int kMode, bool kC2>
@@ -908,30 +960,32 @@ hipError_t launch_mode(const Args& args, hipStream_t stream) {
     // With more (batch, head) units than compute units each workgroup takes several of them back to back.
     const int cus = compute_units();
     if (a.segs == 1 && a.H <= cus) {
-        const int per_round = a.H * (cus / a.H);                 // a multiple of H: the head stays fixed
+        const int per_round = a.H * (cus / a.H);                 // a multiple of H: every round begins with head 0
         if (units > per_round) {
             a.unit_stride = per_round;
             units = per_round;
         }
     }
     const dim3 grid(static_cast<unsigned>(units));
-    constexpr int lds_bytes = kMode >= 4 ? kLdsBytesLora : kLdsBytes;
     const long long row_bytes = kHeadSize * 2 * (kMode >= 4 ? 3 : 4) + kHeadSize * (kMode == 1 ? 4 : 2) + (kC2 ? kHeadSize * 2 : 0);
     const long long mib = static_cast<long long>(a.B) * a.H * (a.T * row_bytes + 2 * 4096 * 4) >> 20;     // the call's rows and states
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds_bytes, stream, a); };
-    const bool cached = mib < (kMode >= 3 ? 64 : 90);
-    if (a.unit_stride == 0) {
-        cached ? go(&chunked_kernel<kMode, kC2, false, Traffic::kCached>) : go(&chunked_kernel<kMode, kC2, false, Traffic::kLarge>);
+    auto go = [&](auto kernel, bool turn = false) {
+        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), (lds_bytes_of<kMode, kC2>(turn, a.H)), stream, a);
         return hipGetLastError();
-    }
-    if constexpr (kMode < 3) {
-        if (mib >= 1024) {
-            go(&chunked_kernel<kMode, kC2, true, Traffic::kStreamed>);
-            return hipGetLastError();
-        }
-    }
-    cached ? go(&chunked_kernel<kMode, kC2, true, Traffic::kCached>) : go(&chunked_kernel<kMode, kC2, true, Traffic::kLarge>);
-    return hipGetLastError();
+    };
+    const bool cached = mib < (kMode >= 3 ? 64 : 90);
+    if (a.unit_stride == 0)
+        return cached ? go(&chunked_kernel<kMode, kC2, false, false, Traffic::kCached>) : go(&chunked_kernel<kMode, kC2, false, false, Traffic::kLarge>);
+    if (cached) return go(&chunked_kernel<kMode, kC2, false, true, Traffic::kCached>);
+    auto several = [&](auto traffic) {
+        constexpr Traffic kTraffic = decltype(traffic)::value;
+        if constexpr (kHasTurn<kMode, kC2, kTraffic>)
+            if (heads_in_turn<kMode, kC2>(a)) return go(&chunked_kernel<kMode, kC2, true, true, kTraffic>, true);
+        return go(&chunked_kernel<kMode, kC2, false, true, kTraffic>);
+    };
+    if constexpr (kMode < 3)
+        if (mib >= 1024) return several(std::integral_constant<Traffic, Traffic::kStreamed>{});
+    return several(std::integral_constant<Traffic, Traffic::kLarge>{});
 }
 
 }  // namespace
