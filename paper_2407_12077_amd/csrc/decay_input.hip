@@ -384,19 +384,22 @@ __global__ __launch_bounds__(kDiThreads) void decay_input_kernel(DiArgs a) {
 // A workgroup owns 16 kTB consecutive rows of the flattened [B * T] tokens (so sequences of a token or two share a
 // tile) and its waves take the 32-channel blocks of D in turn; the partial sums of q A_d and of z A_omega meet
 // through LDS, once each.  No barrier and no shared stage inside the walks: a wave brings its block's x rows and weight
-// slices from global memory in whole 64-byte pieces, passes them through a piece of LDS of its own into the operand
-// layouts, and has the loads of the next block in flight.  A token's predecessor is an
-// LDS row as well: the row above it, or the carried row where a sequence starts.  Bound by the compute unit's L1
-// path (every workgroup takes all weights, 512 KB at D = 2048) and, at 64 rows, by the conversions and interpolations in the
-// vector ALU.  One block in flight, not more: with
-// two the loop is twice as long and the last trip works on blocks that are not there (24 tokens 14.0 -> 12.0 us with four groups, below;
-// 3000 tokens 16.9 -> 14.7; D = 128, 300 tokens 6.2 -> 4.5; three in flight 14.9).  Straight operand loads from global memory (sixteen lines per quarter wave) took 26.4 us where this took 16.6,
-// bf16 weights with the other operand as two bf16 values the same time,  six waves instead of twelve 17.0, and 64
-// rows with four waves, two workgroups per compute unit, 36 instead of 31 (24 sequences of one token; 16384 tokens; D = 2048).
+// slices in whole 64-byte pieces straight into a piece of LDS of its own (loads that bypass the registers), reads them from there as
+// operands, and asks for what comes next in the places that these have left: the weights one block ahead, x two.  A token's
+// predecessor is an LDS row as well: the row above it, or the carried row where a sequence starts.
+// What bounds it.  64 rows: walk 1 streams x at 5.1 TB/s, the rate of a large copy; walk 2 reads it again from the last-level cache, as
+// long as its conversions and interpolations keep the vector ALUs; together 24 of 34 us at 16 384 tokens and D = 2048.  16 rows: what
+// one compute unit takes in of the weights (18 bytes a clock), and both exchanges, 1.5 us each.  Through registers and LDS stores, with
+// one block ahead of both, a kernel of more code: 16 384 tokens x 2048 35.3 -> 33.6 us, 33 792 x 4096 169 -> 157, 24 x 2048 12.2 -> 11.0, 24 x
+// 768 7.05 -> 6.3, 1000 x 128 4.7 -> 4.1, 6000 x 1024 11.8 -> 10.7.  One place more for weights and x: 24 x 2048 12.0, 6000 x 1024 11.4, 16 384 x
+// 768 15.1 -> 15.5: short calls pay for every line of code that they pass once.  Straight operand loads from global memory
+// (sixteen lines per quarter wave) took 26.4 us where the register form took 16.6, bf16 weights with the other operand as two bf16
+// values the same time, six waves instead of twelve 17.0, 64 rows with four waves, two workgroups per compute unit, 36 instead of 31
+// (24 sequences of one token; 16 384 tokens; D = 2048).
 //
 // With few tiles kGroups workgroups share a tile: each forms z from all of A_d and B_d, and 64 / kGroups of its outputs,
 // so that what a compute unit takes in and passes through its LDS is A_omega's part less (D = 2048: 512 -> 320 KB of weights at four
-// groups; 24 tokens 16.7 -> 14.0 us, 12.0 with one block in flight).  An output's sums are the same ones in the same order.
+// groups; 24 tokens 16.7 -> 14.0 us when this was added).  An output's sums are the same ones in the same order.
 template <int kTB, int kSplitWaves, int kGroups>
 struct SplitTile {
     static constexpr int kCols = kOuterRank / kGroups;   // columns of A_omega, outputs of a token, of this workgroup
@@ -404,275 +407,316 @@ struct SplitTile {
     static constexpr int kWaves = kSplitWaves;
     static constexpr int kThreads = 64 * kWaves;
     static constexpr int kCarry = kTB == 1 ? 16 : 1;     // rows of a tile that can start a sequence (kTB > 1: T >= kRows)
-    // a wave's piece of LDS: rows of 32 channels (64 bytes + 32 pad: full-rate 16-byte reads)
-    static constexpr int kRow = 96;
-    static constexpr int kXRows = 1 + kRows + kCarry;    // the row before the tile, the tile, the carried rows
-    static constexpr int kOffA = kXRows * kRow;          // walk 1: A_d slice [32 columns]; walk 2: A_omega slice [kCols columns]
-    static constexpr int kOffB = kOffA + (kCols > kInnerRank ? kCols : kInnerRank) * kRow;   // walk 2: B_d slice [32 channels][32 ranks]
-    static constexpr int kOffV = kOffB + 32 * kRow;      // mu_x or lambda_d slice, 32 fp32
-    static constexpr int kPiece = kOffV + 128;
+    // A block's x in LDS: the tile's rows (32 channels, 64 bytes each), the row before the tile, mu_x or lambda_d
+    // (128 bytes), one carried row; kTB == 1: sixteen carried rows behind them.
+    static constexpr int kOffP = 1024 * kTB, kOffV = kOffP + 64, kOffC1 = kOffV + 128, kOffC = kOffP + 256;
+    static constexpr int kXBytes = kOffC + (kCarry > 1 ? 1024 : 0);
+    static constexpr int kXLoads = kTB + 1;              // (and one for the carried rows of kTB == 1)
+    // its weights: A_d (32 columns of 64 bytes), or B_d (32 channels of 64 bytes) and A_omega (kCols columns)
+    static constexpr int kWBytes1 = 2048, kWBytes2 = 2048 + 64 * kCols;
+    // a wave's piece: two places for x, one for weights
+    static constexpr int kPiece1 = 2 * kXBytes + kWBytes1;
+    // values of the exchanged sums that a thread adds up: few, where the rows are, so that most waves take part (16 rows 0.25 us faster
+    // with two than with four; 64 rows 0.1 slower)
+    static constexpr int kSum = kTB == 4 ? 4 : 2;
     static constexpr int kPRow = kInnerRank + 4;         // row strides (floats) of the waves' partial sums
     static constexpr int kYRow = kCols + 4;
     static constexpr int kPtRow = kInnerRank * 2 + 16;   // row stride (bytes) of tanh(q A_d)
-    static constexpr int kYPart = kWaves * kRows * (kYRow > kPRow ? kYRow : kPRow) * 4;
-    static constexpr int kPtOff = kWaves * kPiece > kYPart ? kWaves * kPiece : kYPart;
+    // Walk 2's first block is on its way while the waves' partial sums of walk 1 meet, so it lies behind these; the other place
+    // for x lies where they were.
+    static constexpr int kPPart = kWaves * kRows * kPRow * 4;
+    static constexpr int kYPart = kWaves * kRows * kYRow * 4;
+    static constexpr int kFirst2 = kXBytes + kWBytes2;                       // a wave's first block of walk 2
+    static constexpr int kMeet = kPPart > kWaves * kXBytes ? kPPart : kWaves * kXBytes;
+    static constexpr int kWalk1 = kWaves * kPiece1, kWalk2 = kMeet + kWaves * kFirst2;
+    static constexpr int kMost = kWalk1 > kWalk2 ? kWalk1 : kWalk2;
+    static constexpr int kZero = kMost > kYPart ? kMost : kYPart;            // 64 bytes of zeros a wave
+    static constexpr int kPtOff = kZero + 64 * kWaves;
     static constexpr int kLds = kPtOff + kRows * kPtRow;
     static_assert(kLds <= 160 * 1024, "LDS budget");
 };
 
-__device__ __forceinline__ void wave_lds_order() {       // a wave's own LDS writes before its own reads, and back
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// Loads straight into LDS are outside the compiler's view of a wave's own LDS accesses: at most `kYounger` of the wave's
+// youngest loads may still be on their way behind this, and no LDS access moves across it.
+template <int kYounger>
+__device__ __forceinline__ void wait_loads() {
+    static_assert(kYounger < 64, "vmcnt");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt((kYounger & 15) | (kYounger >> 4) << 14 | 7 << 4 | 15 << 8);
+    __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ void wait_lds() {             // the wave's own LDS reads and writes
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(15 | 3 << 14 | 7 << 4);
+    __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ void lds_barrier() {          // all waves; loads into LDS stay on their way
+    wait_lds();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 template <int kTB, int kSplitWaves, bool kOutF32, int kGroups>
 __global__ __launch_bounds__(64 * kSplitWaves) void decay_input_split_kernel(DiArgs a) {
     using TL = SplitTile<kTB, kSplitWaves, kGroups>;
-    constexpr int kNB = TL::kCols / 16;
+    constexpr int kNB = TL::kCols / 16, kW = TL::kWaves;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    char* mine = lds + wave * TL::kPiece;
     const long long M = static_cast<long long>(a.B) * a.T;
     const unsigned tile = kGroups == 1 ? blockIdx.x : blockIdx.x / kGroups, group = kGroups == 1 ? 0 : blockIdx.x % kGroups;
     const long long m0 = static_cast<long long>(tile) * TL::kRows;
     const int rows = M - m0 < TL::kRows ? static_cast<int>(M - m0) : TL::kRows;
-    const long long row_bytes = static_cast<long long>(a.D) * 2;
+    const int row_bytes = a.D * 2;
     const int nkb = a.D / 32;
-    const long long b0 = m0 / a.T;                             // sequence of the tile's first row
-    const unsigned T = static_cast<unsigned>(a.T), t0 = static_cast<unsigned>(m0 - b0 * a.T);
-    const unsigned first_start = t0 == 0 ? 0 : 1;              // first sequence, counted from b0, whose start can lie in the tile
+    const int mine = wave < nkb ? (nkb - 1 - wave) / kW + 1 : 0;      // this wave's blocks: wave, wave + kW, ...
+    // sequence of the tile's first row (fewer than 2^32 tokens: a row has at least 256 bytes)
+    const unsigned T = static_cast<unsigned>(a.T);
+    const int b0 = __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<unsigned>(m0) / T));
+    const unsigned t0 = static_cast<unsigned>(m0) - static_cast<unsigned>(b0) * T;
+    const int first_start = t0 == 0 ? 0 : 1;                   // first sequence, counted from b0, whose start can lie in the tile
     const bool has_start = t0 == 0 || t0 + rows > T;           // some row starts a sequence
 
-    constexpr int kNowhere = 0x7ffffff0;                       // an offset that no descriptor covers: reads zero
-    auto load = [](const char* base, int bytes, int voff, int soff) {
-        return __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(
-                                              __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, bytes, 0x00020000),
-                                              voff, soff, 0));
-    };
-    auto store = [&](int off, uint4v q) { *reinterpret_cast<uint4v*>(mine + off) = q; };
     // Global loads go by rows, four lanes to the 64 bytes of a row's 32 channels (sixteen different lines per
-    // quarter wave, as the operand layout would have it, cost four times as much in the L1's tag lookups).
-    const int lr = lane >> 2, lp = 16 * (lane & 3);
+    // quarter wave, as the operand layout would have it, cost four times as much in the L1's tag lookups), straight into LDS, where lane
+    // i's 16 bytes lie 16 i behind the wave's address.  Rows lie 64 bytes apart there, their 16-byte granules XOR-ed by
+    // bits 2 and 3 of the row (B_d: 3 and 4), so that both the lanes' reads of sixteen rows, at one granule each, and the loads take every
+    // bank once: lane i asks for the granule that belongs in its place.
+    const int lr = lane >> 2, lp = 16 * ((lane & 3) ^ ((lane >> 4) & 3));
+    typedef __attribute__((address_space(3))) char* lds_ptr;
+    auto load = [&](const char* base, int bytes, int voff, int soff, int to) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, bytes, 0x00020000),
+                                                 (lds_ptr)(lds + to), 16, voff, soff, 0, 0);
+    };
     const char* x_base = a.x + m0 * row_bytes;
-    const int x_bytes = static_cast<int>(rows * row_bytes), x_voff = static_cast<int>(lr * row_bytes) + lp;
-    const int x_pass = static_cast<int>(16 * row_bytes);
-    const char* p_base = t0 > 0 ? x_base - row_bytes : a.x;    // the row before the tile, if it belongs to the sequence
-    const int p_bytes = t0 > 0 ? static_cast<int>(row_bytes) : 0, p_voff = lane < 4 ? lp : kNowhere;
-    const long long c0 = b0 + first_start;                     // carried rows of the sequences that start in the tile
-    const long long c_rows = a.B - c0 < TL::kCarry ? a.B - c0 : TL::kCarry;
-    const char* c_base = a.x_prev && c_rows > 0 ? a.x_prev + c0 * row_bytes : a.x;
-    const int c_bytes = a.x_prev && c_rows > 0 ? static_cast<int>(c_rows * row_bytes) : 0;
-    const int w_voff = static_cast<int>(lr * row_bytes) + lp;  // columns of A_d, A_omega
+    const int x_bytes = rows * row_bytes;
+    int x_voff[kTB];                                           // rows past the tile's end: the last one again, whose result is not stored
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb) x_voff[tb] = (16 * tb + lr < rows ? 16 * tb + lr : rows - 1) * row_bytes + lp;
+    const int w_voff = lr * row_bytes + lp, w_pass = 16 * row_bytes;   // columns of A_d, A_omega
+    const int b_voff = lr * 64 + 16 * ((lane & 3) ^ (lane >> 5));      // channels of B_d; the second pass: granule ^ 2
 
-    struct X {
-        uint4v x[kTB], p, c;
-    };
-    auto fetch_x = [&](X& s, bool live, int soff) {            // live: uniform; dead: empty descriptors
+    // The row before the tile, the vector and the carried row come with one load of sixteen lanes with addresses of their own (a
+    // row that is not there is not asked for below: its reads go to the zeros).
+    const bool has_before = t0 > 0;
+    const int c0 = b0 + first_start;                           // carried rows of the sequences that start in the tile
+    const bool has_carry = a.x_prev && has_start && c0 < a.B;
+    const char* misc = lane < 4 ? x_base - (has_before ? row_bytes : 0) + 16 * lane
+                                : a.x_prev && lane >= 12 ? a.x_prev + static_cast<long long>(has_carry ? c0 : 0) * row_bytes + 16 * (lane - 12) : a.x;
+    const bool misc_x = lane < 4 || lane >= 12;
+    const int c_rows = a.B - c0 < TL::kCarry ? a.B - c0 : TL::kCarry;
+    const int c_voff = (lr < c_rows ? lr : c_rows - 1) * row_bytes + lp;
+
+    auto fetch_x = [&](int kb, const char* vec, int to) {
+        const int soff = kb * 64;
 #pragma unroll
-        for (int tb = 0; tb < kTB; ++tb) s.x[tb] = load(x_base, live ? x_bytes : 0, x_voff + tb * x_pass, soff);
-        s.p = load(p_base, live ? p_bytes : 0, p_voff, soff);
-        s.c = uint4v{0u, 0u, 0u, 0u};
-        if (has_start) s.c = load(c_base, live ? c_bytes : 0, lr < TL::kCarry ? x_voff : kNowhere, soff);
+        for (int tb = 0; tb < kTB; ++tb) load(x_base, x_bytes, x_voff[tb], soff, to + 1024 * tb);
+        if (lane < 16) {
+            const char* from = misc_x ? misc + soff : vec + 2 * soff + 16 * (lane - 4);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)from, (lds_ptr)(lds + to + TL::kOffP), 16, 0, 0);
+        }
+        if constexpr (TL::kCarry > 1)
+            if (has_carry) load(a.x_prev + static_cast<long long>(c0) * row_bytes, c_rows * row_bytes, c_voff, soff, to + TL::kOffC);
     };
-    auto park_x = [&](const X& s) {
+    auto fetch1 = [&](int kb, int to) {
 #pragma unroll
-        for (int tb = 0; tb < kTB; ++tb) store((1 + 16 * tb + lr) * TL::kRow + lp, s.x[tb]);
-        if (lane < 4) store(lp, s.p);
-        if (has_start && lr < TL::kCarry) store((1 + TL::kRows + lr) * TL::kRow + lp, s.c);
+        for (int nb = 0; nb < 2; ++nb) load(a.a_d, kInnerRank * row_bytes, w_voff + nb * w_pass, kb * 64, to + 1024 * nb);
     };
-    // LDS rows of this lane's tokens and of their predecessors
-    int cur_off[kTB], prev_off[kTB];
+    const char* omega = a.a_omega + static_cast<long long>(group) * TL::kCols * row_bytes;
+    auto fetch2 = [&](int kb, int to) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) load(a.b_d, a.D * kInnerRank * 2, (b_voff ^ 32 * i) + 1024 * i, kb * 2048, to + 1024 * i);
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb) load(omega, TL::kCols * row_bytes, w_voff + nb * w_pass, kb * 64, to + 2048 + 1024 * nb);
+    };
+    // A walk: trip i reads the operands of this wave's i-th block from LDS, asks for the weights of block i + 1 and the x of block i + 2 in
+    // the places that these have left, and computes.
+    const int piece = wave * TL::kPiece1;
+    auto ask_w1 = [&](int i) { if (i < mine) fetch1(wave + i * kW, piece + 2 * TL::kXBytes); };
+    auto ask_x1 = [&](int i) { if (i < mine) fetch_x(wave + i * kW, a.mu_x, piece + (i & 1) * TL::kXBytes); };
+    ask_x1(0);
+    ask_w1(0);
+    ask_x1(1);
+
+    auto row_off = [](int row, int granule) { return 64 * row + 16 * (granule ^ ((row >> 2) & 3)); };
+
+    const int zeros = TL::kZero + 64 * wave;
+    if (lane < 4) *reinterpret_cast<uint4v*>(lds + zeros + 16 * lane) = uint4v{0u, 0u, 0u, 0u};
+    // LDS places of this lane's tokens, within a block's x, and of their predecessors (kInZeros: none)
+    constexpr int kInZeros = -1;
+    int prev_off[kTB];
 #pragma unroll
     for (int tb = 0; tb < kTB; ++tb) {
-        const unsigned row = 16 * tb + l16, db = (t0 + row) / T;
+        // (kTB > 1: T >= kRows, so that at most one sequence starts in the tile)
+        const unsigned row = 16 * tb + l16, db = kTB == 1 ? (t0 + row) / T : t0 + row >= T ? 1 : 0;
         const bool start = t0 + row == db * T;
-        cur_off[tb] = (1 + row) * TL::kRow + 16 * g4;
-        // (a row past the end of the tile may find a sequence past the carried rows: its result is not stored)
-        const unsigned slot = db - first_start < TL::kCarry ? db - first_start : TL::kCarry - 1;
-        prev_off[tb] = (start ? 1 + TL::kRows + static_cast<int>(slot) : static_cast<int>(row)) * TL::kRow + 16 * g4;
+        prev_off[tb] = row > 0 ? row_off(row - 1, g4) : TL::kOffP + 16 * g4;
+        if (start) {
+            // (a row past the end of the tile may find a sequence past the carried rows: its result is not stored)
+            const int slot = static_cast<int>(db) - first_start;
+            prev_off[tb] = !has_carry || slot >= c_rows ? kInZeros : TL::kCarry > 1 ? TL::kOffC + row_off(slot, g4) : TL::kOffC1 + 16 * g4;
+        }
     }
+    const int cur0 = row_off(l16, g4);                         // a block's rows 16 tb + l16, and columns 16 nb + l16 of its weights
+    auto read_u4 = [&](int off) { return *reinterpret_cast<const uint4v*>(lds + off); };
+    auto read_f4 = [&](int off) { return *reinterpret_cast<const float4v*>(lds + off); };
     auto interpolate = [](unsigned cur, unsigned prev, float w0, float w1) {   // two channels, fp32, rounded to fp16
         const float c0 = lo_f(cur), c1 = hi_f(cur);
         return pack_h2f(__builtin_fmaf(lo_f(prev) - c0, w0, c0), __builtin_fmaf(hi_f(prev) - c1, w1, c1));
     };
-    auto read_half8 = [&](int off) { return *reinterpret_cast<const half8*>(mine + off); };
-    auto read_u4 = [&](int off) { return *reinterpret_cast<const uint4v*>(mine + off); };
-    auto read_f4 = [&](int off) { return *reinterpret_cast<const float4v*>(mine + off); };
-
-    // walk 1: this wave's share of q A_d
-    struct W1 {
-        X x;
-        uint4v wgt[2], mu;
+    struct X {
+        uint4v cur[kTB], prev[kTB];
+        float4v vec[2];
     };
-    auto fetch1 = [&](W1& s, int kb) {
-        const bool live = kb < nkb;
-        const int soff = live ? kb * 64 : 0;
+    auto read_x = [&](X& s, int at) {
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-            s.wgt[nb] = load(a.a_d + nb * 16 * row_bytes, live ? static_cast<int>(16 * row_bytes) : 0, w_voff, soff);
-        s.mu = load(a.mu_x, live ? a.D * 4 : 0, lane < 8 ? 16 * lane : kNowhere, 2 * soff);
-        fetch_x(s.x, live, soff);
+        for (int tb = 0; tb < kTB; ++tb) {
+            s.cur[tb] = read_u4(at + cur0 + 1024 * tb);
+            s.prev[tb] = read_u4(prev_off[tb] == kInZeros ? zeros : at + prev_off[tb]);
+        }
+        s.vec[0] = read_f4(at + TL::kOffV + 32 * g4);
+        s.vec[1] = read_f4(at + TL::kOffV + 32 * g4 + 16);
     };
+    // walk 1: this wave's share of q A_d
     float4v pacc[kTB][2];
 #pragma unroll
     for (int tb = 0; tb < kTB; ++tb) pacc[tb][0] = pacc[tb][1] = float4v{0.f, 0.f, 0.f, 0.f};
-    auto park1 = [&](const W1& s) {
-        wave_lds_order();
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) store(TL::kOffA + (16 * nb + lr) * TL::kRow + lp, bf16x8_to_f16x8(s.wgt[nb]));
-        if (lane < 8) store(TL::kOffV + 16 * lane, s.mu);
-        park_x(s.x);
-        wave_lds_order();
+    auto wait_block = [&](int i) {                             // only the x of block i + 1 is behind block i's weights
+        if (i + 1 >= mine) wait_loads<0>();
+        else if (TL::kCarry > 1 && has_carry) wait_loads<TL::kXLoads + 1>();
+        else wait_loads<TL::kXLoads>();
     };
-    auto step1 = [&] {
-        half8 wgt[2];
+#pragma clang loop unroll(disable)
+    for (int i = 0; i < mine; ++i) {
+        wait_block(i);
+        X x;
+        uint4v wgt[2];
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) wgt[nb] = read_half8(TL::kOffA + (16 * nb + l16) * TL::kRow + 16 * g4);
-        const float4v mu[2] = {read_f4(TL::kOffV + 32 * g4), read_f4(TL::kOffV + 32 * g4 + 16)};
+        for (int nb = 0; nb < 2; ++nb) wgt[nb] = read_u4(piece + 2 * TL::kXBytes + cur0 + 1024 * nb);
+        read_x(x, piece + (i & 1) * TL::kXBytes);
+        wait_lds();                                            // the operands are in registers: their places may be written again
+        ask_w1(i + 1);
+        ask_x1(i + 2);
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) wgt[nb] = bf16x8_to_f16x8(wgt[nb]);
 #pragma unroll
         for (int tb = 0; tb < kTB; ++tb) {
-            const uint4v cur = read_u4(cur_off[tb]), prev = read_u4(prev_off[tb]);
             uint4v q;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) q[i] = interpolate(cur[i], prev[i], mu[i >> 1][2 * (i & 1)], mu[i >> 1][2 * (i & 1) + 1]);
+            for (int e = 0; e < 4; ++e) q[e] = interpolate(x.cur[tb][e], x.prev[tb][e], x.vec[e >> 1][2 * (e & 1)], x.vec[e >> 1][2 * (e & 1) + 1]);
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb)
-                pacc[tb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wgt[nb], __builtin_bit_cast(half8, q), pacc[tb][nb], 0, 0, 0);
-        }
-    };
-    {
-        W1 next;
-        fetch1(next, wave);
-#pragma clang loop unroll(disable)
-        for (int kb = wave; kb < nkb; kb += TL::kWaves) {
-            park1(next);
-            fetch1(next, kb + TL::kWaves);
-            step1();
+                pacc[tb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, wgt[nb]), __builtin_bit_cast(half8, q), pacc[tb][nb], 0, 0, 0);
         }
     }
 
-    // walk 2's first blocks do not wait for the exchange
-    struct W2 {
-        X x;
-        uint4v bd[2], wo[kNB], lam;
-    };
-    auto fetch2 = [&](W2& s, int kb) {
-        const bool live = kb >= 0;
-        const int soff = live ? kb * 64 : 0;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)                            // 32 channels x 64 bytes: one contiguous piece
-            s.bd[i] = load(a.b_d, live ? a.D * kInnerRank * 2 : 0, 1024 * i + 16 * lane, kInnerRank * soff);
-#pragma unroll
-        for (int nb = 0; nb < kNB; ++nb)
-            s.wo[nb] = load(a.a_omega + (group * TL::kCols + nb * 16) * row_bytes, live ? static_cast<int>(16 * row_bytes) : 0, w_voff, soff);
-        s.lam = load(a.lambda_d, live ? a.D * 4 : 0, lane < 8 ? 16 * lane : kNowhere, 2 * soff);
-        fetch_x(s.x, live, soff);
-    };
-    const int last = wave < nkb ? wave + (nkb - 1 - wave) / TL::kWaves * TL::kWaves : -1;   // this wave's last block
-    W2 next;
-    fetch2(next, last);
+    // walk 2, from the blocks most recently brought into the caches down; its first block does not wait for the exchange
+    const int first2 = TL::kMeet + wave * TL::kFirst2;
+    auto x_place = [&](int i) { return i & 1 ? wave * TL::kXBytes : first2; };
+    auto ask_w2 = [&](int i) { if (i < mine) fetch2(wave + (mine - 1 - i) * kW, first2 + TL::kXBytes); };
+    auto ask_x2 = [&](int i) { if (i < mine) fetch_x(wave + (mine - 1 - i) * kW, a.lambda_d, x_place(i)); };
 
     // the waves' shares of q A_d meet; p = tanh of the sum, as fp16
     float* part = reinterpret_cast<float*>(lds);
-    __syncthreads();                                           // every wave is done with its piece
+    lds_barrier();                                             // every wave is done with its piece
+    ask_x2(0);
+    ask_w2(0);
 #pragma unroll
     for (int tb = 0; tb < kTB; ++tb)
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
             *reinterpret_cast<float4v*>(part + (wave * TL::kRows + 16 * tb + l16) * TL::kPRow + 16 * nb + 4 * g4) = pacc[tb][nb];
-    __syncthreads();
-    for (int i = tid; i < TL::kRows * (kInnerRank / 4); i += TL::kThreads) {
-        const int row = i / (kInnerRank / 4), c4 = 4 * (i % (kInnerRank / 4));
-        float4v sum = {0.f, 0.f, 0.f, 0.f};
+    lds_barrier();
+    constexpr int kSum = TL::kSum;
+    typedef float floats __attribute__((ext_vector_type(kSum)));
+    for (int i = tid; i < TL::kRows * (kInnerRank / kSum); i += TL::kThreads) {
+        const int row = i / (kInnerRank / kSum), c = kSum * (i % (kInnerRank / kSum));
+        floats sum = 0.f;
 #pragma unroll
         for (int w = 0; w < TL::kWaves; ++w)
-            sum += *reinterpret_cast<const float4v*>(part + (w * TL::kRows + row) * TL::kPRow + c4);
-        *reinterpret_cast<uint2v*>(lds + TL::kPtOff + row * TL::kPtRow + 2 * c4) =
-            uint2v{pack_h2f(fast_tanh(sum[0]), fast_tanh(sum[1])), pack_h2f(fast_tanh(sum[2]), fast_tanh(sum[3]))};
+            sum += *reinterpret_cast<const floats*>(part + (w * TL::kRows + row) * TL::kPRow + c);
+#pragma unroll
+        for (int e = 0; e < kSum; e += 2)
+            *reinterpret_cast<unsigned*>(lds + TL::kPtOff + row * TL::kPtRow + 2 * (c + e)) = pack_h2f(fast_tanh(sum[e]), fast_tanh(sum[e + 1]));
     }
-    __syncthreads();
+    lds_barrier();
+    ask_x2(1);
     half8 pt[kTB];                                             // ranks 8*g4 .. +7 of this lane's tokens
 #pragma unroll
     for (int tb = 0; tb < kTB; ++tb)
         pt[tb] = *reinterpret_cast<const half8*>(lds + TL::kPtOff + (16 * tb + l16) * TL::kPtRow + 16 * g4);
 
-    // walk 2: this wave's share of z A_omega, from the blocks most recently brought into the caches down
+    // this wave's share of z A_omega
     float4v yacc[kTB][kNB];
 #pragma unroll
     for (int tb = 0; tb < kTB; ++tb)
 #pragma unroll
         for (int nb = 0; nb < kNB; ++nb) yacc[tb][nb] = float4v{0.f, 0.f, 0.f, 0.f};
-    auto park2 = [&](const W2& s) {
-        wave_lds_order();
+    // Which channel sits in which row of the B_d^T operand is free as long as z and A_omega agree: with row m of
+    // block `half` holding channel 8*(m>>2) + 4*half + (m&3) a lane's results are its own channels 8*g4 .. +7
+    int bd_off[2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) store(TL::kOffB + (16 * i + lr) * TL::kRow + lp, bf16x8_to_f16x8(s.bd[i]));
+    for (int half = 0; half < 2; ++half) {
+        const int ch = 8 * (l16 >> 2) + 4 * half + (l16 & 3);
+        bd_off[half] = 64 * ch + 16 * (g4 ^ ((ch >> 3) & 3));
+    }
+#pragma clang loop unroll(disable)
+    for (int i = 0; i < mine; ++i) {
+        wait_block(i);
+        const int wat = first2 + TL::kXBytes;
+        X x;
+        uint4v bd[2], wo[kNB];
 #pragma unroll
-        for (int nb = 0; nb < kNB; ++nb) store(TL::kOffA + (16 * nb + lr) * TL::kRow + lp, bf16x8_to_f16x8(s.wo[nb]));
-        if (lane < 8) store(TL::kOffV + 16 * lane, s.lam);
-        park_x(s.x);
-        wave_lds_order();
-    };
-    auto step2 = [&] {
-        // Which channel sits in which row of the B_d^T operand is free as long as z and A_omega agree: with row m of
-        // block `half` holding channel 8*(m>>2) + 4*half + (m&3) a lane's results are its own channels 8*g4 .. +7
-        half8 bd[2], wo[kNB];
-        float4v lam[2];
+        for (int half = 0; half < 2; ++half) bd[half] = read_u4(wat + bd_off[half]);
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            bd[half] = read_half8(TL::kOffB + (8 * (l16 >> 2) + 4 * half + (l16 & 3)) * TL::kRow + 16 * g4);
-            lam[half] = read_f4(TL::kOffV + 32 * g4 + 16 * half);
-        }
+        for (int nb = 0; nb < kNB; ++nb) wo[nb] = read_u4(wat + 2048 + cur0 + 1024 * nb);
+        read_x(x, x_place(i));
+        wait_lds();                                            // the operands are in registers: their places may be written again
+        ask_w2(i + 1);
+        ask_x2(i + 2);
 #pragma unroll
-        for (int nb = 0; nb < kNB; ++nb) wo[nb] = read_half8(TL::kOffA + (16 * nb + l16) * TL::kRow + 16 * g4);
+        for (int half = 0; half < 2; ++half) bd[half] = bf16x8_to_f16x8(bd[half]);
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb) wo[nb] = bf16x8_to_f16x8(wo[nb]);
 #pragma unroll
         for (int tb = 0; tb < kTB; ++tb) {
-            const uint4v cur = read_u4(cur_off[tb]), prev = read_u4(prev_off[tb]);
             uint4v z;
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 // mix[e] = lambda_d + sum_k B_d[k][channel 8*g4 + 4*half + e] p[token][k]
-                const float4v mix = __builtin_amdgcn_mfma_f32_16x16x32_f16(bd[half], pt[tb], lam[half], 0, 0, 0);
+                const float4v mix = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, bd[half]), pt[tb], x.vec[half], 0, 0, 0);
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    z[2 * half + i] = interpolate(cur[2 * half + i], prev[2 * half + i], mix[2 * i], mix[2 * i + 1]);
+                for (int e = 0; e < 2; ++e)
+                    z[2 * half + e] = interpolate(x.cur[tb][2 * half + e], x.prev[tb][2 * half + e], mix[2 * e], mix[2 * e + 1]);
             }
 #pragma unroll
             for (int nb = 0; nb < kNB; ++nb)
-                yacc[tb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wo[nb], __builtin_bit_cast(half8, z), yacc[tb][nb], 0, 0, 0);
+                yacc[tb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, wo[nb]), __builtin_bit_cast(half8, z), yacc[tb][nb], 0, 0, 0);
         }
-    };
-#pragma clang loop unroll(disable)
-    for (int kb = last; kb >= 0; kb -= TL::kWaves) {
-        park2(next);
-        fetch2(next, kb - TL::kWaves);
-        step2();
     }
 
-    __syncthreads();                                           // every wave is done with its piece
+    lds_barrier();                                             // every wave is done with its piece
 #pragma unroll
     for (int tb = 0; tb < kTB; ++tb)
 #pragma unroll
         for (int nb = 0; nb < kNB; ++nb)
             *reinterpret_cast<float4v*>(part + (wave * TL::kRows + 16 * tb + l16) * TL::kYRow + 16 * nb + 4 * g4) = yacc[tb][nb];
     __syncthreads();
-    for (int i = tid; i < TL::kRows * (TL::kCols / 4); i += TL::kThreads) {
-        const int row = i / (TL::kCols / 4), c4 = 4 * (i % (TL::kCols / 4));
-        float4v sum = {0.f, 0.f, 0.f, 0.f};
+    for (int i = tid; i < TL::kRows * (TL::kCols / kSum); i += TL::kThreads) {
+        const int row = i / (TL::kCols / kSum), c = kSum * (i % (TL::kCols / kSum));
+        floats sum = 0.f;
 #pragma unroll
         for (int w = 0; w < TL::kWaves; ++w)
-            sum += *reinterpret_cast<const float4v*>(part + (w * TL::kRows + row) * TL::kYRow + c4);
+            sum += *reinterpret_cast<const floats*>(part + (w * TL::kRows + row) * TL::kYRow + c);
         if (row < rows) {
-            const long long e = (m0 + row) * kOuterRank + group * TL::kCols + c4;
+            const long long e = (m0 + row) * kOuterRank + group * TL::kCols + c;
 #pragma unroll
-            for (int i2 = 0; i2 < 4; ++i2) sum[i2] = fast_tanh(sum[i2]);
+            for (int i2 = 0; i2 < kSum; ++i2) sum[i2] = fast_tanh(sum[i2]);
             if constexpr (kOutF32) {
-                *reinterpret_cast<float4v*>(static_cast<float*>(a.y) + e) = sum;
+                *reinterpret_cast<floats*>(static_cast<float*>(a.y) + e) = sum;
             } else {
-                typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-                *reinterpret_cast<uint2v*>(static_cast<unsigned short*>(a.y) + e) =
-                    __builtin_bit_cast(uint2v, __builtin_convertvector(sum, bf16x4));
+                typedef __bf16 bf16s __attribute__((ext_vector_type(kSum)));
+                *reinterpret_cast<bf16s*>(static_cast<unsigned short*>(a.y) + e) = __builtin_convertvector(sum, bf16s);
             }
         }
     }
@@ -735,8 +779,8 @@ hipError_t launch_decay_input(int B, int T, int D, const void* x, const void* x_
     // one token 45.8 : 16.6, 300 of them 90 : 16.8, 8192 tokens 46.6 : 22, 16 384 tokens 47 : 31, 33 792 tokens 94 : 86, 24 000
     // tokens (a second round of 64 rows) 48 : 59; D = 128 one token 6.3 : 6.9, 300 sequences of one token 12.2 : 7.2, 33 792 tokens
     // 13.0 : 20.0; D = 256 33 792 tokens 19.3 : 23.6, 1000 sequences of 20 34.7 : 36.3; D = 768 49 152 tokens 41.0 : 42.6.
-    // These were fitted with two blocks of a wave in flight in the 16- and 32-row tiles, which now take about 2 us less a round
-    // (16 rows 4.2 us and 0.66 per 128 channels): the line still errs towards the 128-token tiles at D = 128 and 256.
+    // These were fitted with two blocks of a wave in flight in the 16- and 32-row tiles; 16 rows now take 3.7 us and 0.46 per
+    // 128 channels, 64 rows 7 % less: the line still errs towards the 128-token tiles at D = 128 and 256.
     const long long cus = compute_units(), rows = static_cast<long long>(B) * T, blocks = D / 128;
     auto rounds = [&](long long groups) { return (groups + cus - 1) / cus; };
     const long long whole = (4300 + 2640 * blocks) * rounds(static_cast<long long>(B) * a.tiles_per_seq);

@@ -54,6 +54,16 @@ def test_matches_oracle(gpu_device, B, T, H, with_prev):
     assert np.array_equal(y16, round_to_bf16(y32))
 
 
+# tiles of 16, 32 and 64 rows over whole and parts of sequences, fewer blocks than waves, a last tile of one row
+@pytest.mark.parametrize("B,T,H", [(17, 1, 6), (9, 2, 10), (33, 15, 2), (33, 16, 4), (31, 17, 12), (1, 33, 2), (131, 33, 4), (127, 65, 4), (2, 4097, 4)])
+@pytest.mark.parametrize("with_prev", [True, False])
+def test_rows_of_a_tile_and_their_predecessors(gpu_device, B, T, H, with_prev):
+    fi = make_decay_front_inputs(scaled(CONFIGS[2], B=B, T=T, H=H), seed=500 + B)
+    y32 = run_front(fi, torch.float32, with_prev).cpu().numpy()
+    assert max_norm_err(y32, oracle_front(fi, with_prev)) <= TOL_BF16
+    assert np.array_equal(run_front(fi, torch.bfloat16, with_prev).float().cpu().numpy(), round_to_bf16(y32))
+
+
 def test_special_weights(gpu_device):
     """B_d = 0 and lambda_d = 1: z is the previous token, so y_t = tanh(x_{t-1} A_omega); lambda_d = 0: y_t =
     tanh(x_t A_omega), whatever mu_x and A_d are."""
