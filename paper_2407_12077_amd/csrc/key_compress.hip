@@ -5,7 +5,7 @@
 // by the HBM read of x; all arithmetic is on the matrix cores (v_mfma_f32_16x16x32_bf16, fp32
 // accumulation, bf16 products are exact in fp32).
 //
-// Two kernels.  With enough tokens to fill the chip with large tiles (the rule is at the launch): one workgroup
+// Three kernels; the rules are at the launch.  With more large tiles than compute units: one workgroup
 // owns 128 tokens x kBN output columns (kBN = 128 up to D = 2048, 256 above that if there are more tiles than
 // compute units, so that up to D = 4096 a workgroup has all columns and x passes through a compute unit's vector
 // memory path once; fewer columns in the last tile when D/16 is not a multiple of kBN) and walks the D
@@ -18,9 +18,9 @@
 //               Rows past M and steps past D go through shrunk raw buffer descriptors and read
 //               as zero without touching memory, so no load is predicated and the wait counters
 //               stay exact.
-//   kBN/32 MFMA waves (or twice as many): each owns a 64 x 64 (64 x 32) block of the result in accumulator
-//               registers; per step 8 row reads of x (row stride 160 B: full-rate 16-byte LDS reads), 16 (8)
-//               transposing reads of W (its contraction index is the tile's row) and 32 (16) MFMAs.
+//   kBN/32 MFMA waves: each owns a 64 x 64 block of the result in accumulator
+//               registers; per step 8 row reads of x (row stride 160 B: full-rate 16-byte LDS reads), 16
+//               transposing reads of W (its contraction index is the tile's row) and 32 MFMAs.
 //               They issue no global loads, so nothing but LDS latency sits between their MFMAs.
 // With kBN = 128 registers and LDS are sized so that two workgroups share a compute unit: the
 // waits, prologue and epilogue of one overlap the steady state of the other.  With kBN = 256 a
@@ -42,8 +42,9 @@ constexpr int kXRow = 160;          // LDS row stride of the x tile (64 bf16 + 3
 constexpr int kXTile = kBM * kXRow; // 20480
 constexpr int kCRow = 128 * 4 + 16; // staging row of 128 columns of the fp32 result tile
 
-// per width of the workgroup's column tile (kBN = 128 or 256) and 16-column blocks of an MFMA wave (kWNB = 4 or 2)
-template <int kBN, int kWNB>
+// per width of the workgroup's column tile (kBN = 128 or 256)
+constexpr int kWNB = 4;             // 16-column blocks of an MFMA wave
+template <int kBN>
 struct Tile {
     static constexpr int kWRow = kBN * 2 + 32;          // LDS row stride of the W tile (kBN bf16 + 32 B pad)
     static constexpr int kWTile = kBK * kWRow;
@@ -57,7 +58,7 @@ struct Tile {
     // steps a loader has in flight: two when two workgroups share a compute unit (they overlap each
     // other's waits), four when one workgroup has it alone
     static constexpr int kDepth = kBN == 128 ? 2 : 4;
-    static constexpr int kPerCu = kBN == 128 && kWNB == 4 ? 2 : 1;
+    static constexpr int kPerCu = kBN == 128 ? 2 : 1;
     static constexpr int kHalves = kBN / 128;           // the result leaves through LDS 128 columns at a time
     static_assert(kLds >= kBM * kCRow, "result staging reuses the operand buffers");
 };
@@ -101,10 +102,10 @@ struct StepRegs {          // a loader thread's share of one step, 16 bytes each
 // ------------------------------------------------------------------------------------------
 // loader waves (256 threads): tiles of step s+2 into registers, tiles of step s+1 into LDS
 // ------------------------------------------------------------------------------------------
-template <int kBN, int kWNB>
+template <int kBN>
 __device__ __forceinline__ void kc_loader(const KcArgs& a, char* lds, int lt, long long m0, int n0, int rows,
                                           int nsteps, int first) {
-    using TL = Tile<kBN, kWNB>;
+    using TL = Tile<kBN>;
     constexpr int kWRow = TL::kWRow, kStage = TL::kStage, kXLoads = TL::kXLoads, kWLoads = TL::kWLoads;
     constexpr int kXRowsPerPass = TL::kLoaders / 8;
     constexpr int kLanesPerWRow = kBN / 8, kWRowsPerPass = TL::kLoaders / kLanesPerWRow;
@@ -205,10 +206,10 @@ __device__ __forceinline__ void kc_loader(const KcArgs& a, char* lds, int lt, lo
 // ------------------------------------------------------------------------------------------
 // MFMA waves (256 threads)
 // ------------------------------------------------------------------------------------------
-template <int kBN, int kWNB, bool kOutF32>
+template <int kBN, bool kOutF32>
 __device__ __forceinline__ void kc_worker(const KcArgs& a, char* lds, int tid, int wave, long long m0, int n0,
                                           int rows, int nsteps) {
-    using TL = Tile<kBN, kWNB>;
+    using TL = Tile<kBN>;
     constexpr int kWRow = TL::kWRow, kStage = TL::kStage, kColBlocks = kBN / (16 * kWNB);
     const int lane = tid & 63;
     const int l16 = lane & 15;
@@ -296,10 +297,9 @@ __device__ __forceinline__ void kc_worker(const KcArgs& a, char* lds, int tid, i
     }
 }
 
-template <int kBN, int kWNB, bool kOutF32>
-__global__ __launch_bounds__((Tile<kBN, kWNB>::kThreads), (Tile<kBN, kWNB>::kPerCu)) void key_compress_kernel(KcArgs a) {
-    using TL = Tile<kBN, kWNB>;
-    extern __shared__ __attribute__((aligned(16))) char lds[];
+template <bool kOutF32, int kBN>
+__device__ __forceinline__ void kc_roles(const KcArgs& a, char* lds) {
+    using TL = Tile<kBN>;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Block -> tile map.  With more than one column tile (D > 16 kBN: 2048 or 4096) the column tiles of one row tile
@@ -326,11 +326,192 @@ __global__ __launch_bounds__((Tile<kBN, kWNB>::kThreads), (Tile<kBN, kWNB>::kPer
     // priority is an issue-arbitration hint): measured 2-3 % on the benchmark shapes
     if (wave >= TL::kMfmaWaves) {
         __builtin_amdgcn_s_setprio(2);
-        kc_loader<kBN, kWNB>(a, lds, tid - 64 * TL::kMfmaWaves, m0, n0, rows, nsteps, first);
+        kc_loader<kBN>(a, lds, tid - 64 * TL::kMfmaWaves, m0, n0, rows, nsteps, first);
     } else {
         __builtin_amdgcn_s_setprio(1);
-        kc_worker<kBN, kWNB, kOutF32>(a, lds, tid, wave, m0, n0, rows, nsteps);
+        kc_worker<kBN, kOutF32>(a, lds, tid, wave, m0, n0, rows, nsteps);
     }
+}
+
+// ------------------------------------------------------------------------------------------
+// At most one large tile per compute unit: loads straight into LDS, all waves load and multiply
+// ------------------------------------------------------------------------------------------
+// A workgroup owns kRowTile tokens x 128 columns and walks D in steps of 64 channels, cyclically from a start of its own.  Its eight waves each
+// bring an eighth of a step's x and W tiles straight into LDS, two steps ahead, and multiply: four waves the first 32 channels of a step,
+// four the second, 32 columns each, so that a step's x is read from LDS four times and its W once.  One barrier a step.  No registers hold loads
+// on their way and no LDS stores stand in the way of the operand reads.  What bounds it at 16 384 tokens and D = 2048 (15.0 us; the 67 MB of x
+// alone take 13 at the copy rate): what a compute unit takes in, 768 KB of x and W.
+template <int kRowTile>
+struct DmaTile {
+    static constexpr int kX = kRowTile * 128, kStage = kX + 64 * 256;
+    static constexpr int kStages = 3;                                       // steps in LDS: as many as fit were 5 to 10 % slower, the later the first step begins
+    static constexpr int kXLoads = kRowTile / 64, kLoads = kXLoads + 2;      // of a wave and step
+    static constexpr int kRB = kRowTile / 16;                               // 16-row blocks
+    static constexpr int kPRow = 128 + 4;                                   // row stride (floats) of the two partial results
+    static constexpr int kLds = kStages * kStage > 2 * kRowTile * kPRow * 4 ? kStages * kStage : 2 * kRowTile * kPRow * 4;
+    static_assert(kLds <= 160 * 1024 && kLoads * (kStages - 2) < 64, "LDS budget, vmcnt");
+};
+
+// At most kYounger of the wave's youngest loads are still on their way behind this; no LDS access moves across it.
+template <int kYounger>
+__device__ __forceinline__ void wait_loads() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt((kYounger & 15) | (kYounger >> 4) << 14 | 7 << 4 | 15 << 8);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Two operands of a tile with rows of 256 bytes, as lds_read_tr8, from the addresses of their first four rows; waits for all LDS accesses of the wave.
+__device__ __forceinline__ void lds_read_tr8_pair(__attribute__((address_space(3))) const char* p0, __attribute__((address_space(3))) const char* p1,
+                                                  bf16x8& q0, bf16x8& q1) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    short4v lo0, hi0, lo1, hi1;
+    asm volatile("ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %4 offset:1024\n\t"
+                 "ds_read_b64_tr_b16 %2, %5\n\tds_read_b64_tr_b16 %3, %5 offset:1024\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(lo0), "=&v"(hi0), "=&v"(lo1), "=&v"(hi1)
+                 : "v"(static_cast<unsigned>(reinterpret_cast<unsigned long long>(p0))), "v"(static_cast<unsigned>(reinterpret_cast<unsigned long long>(p1)))
+                 : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    typedef short short8v __attribute__((ext_vector_type(8)));
+    const short8v both0 = __builtin_shufflevector(lo0, hi0, 0, 1, 2, 3, 4, 5, 6, 7), both1 = __builtin_shufflevector(lo1, hi1, 0, 1, 2, 3, 4, 5, 6, 7);
+    q0 = __builtin_bit_cast(bf16x8, both0);
+    q1 = __builtin_bit_cast(bf16x8, both1);
+#endif
+}
+
+template <bool kOutF32, int kRowTile>
+__device__ __forceinline__ void kc_direct(const KcArgs& a, char* lds) {
+    using TL = DmaTile<kRowTile>;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the column tiles of a row tile in consecutive slots of one XCD, as above
+    const int nct = (a.C + 127) / 128;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const long long m0 = (static_cast<long long>(slot / nct) * 8 + xcd) * kRowTile;
+    const int n0 = slot % nct * 128;
+    if (m0 >= a.M) return;                     // padding of the row tiles to a multiple of 8
+    const int rows = a.M - m0 < kRowTile ? static_cast<int>(a.M - m0) : kRowTile;
+    const int nsteps = a.D / kBK;
+    int at = (slot / nct + 4 * xcd) % nsteps;  // the channel block asked for next
+
+    // A load brings 1 KiB: lane i's 16 bytes lie 16 i behind the wave's LDS address.  x: eight rows of 128 bytes, the granule of a row r at
+    // place (granule ^ (r >> 1 & 7)); W: four rows k of 256 bytes, the 32-byte pair p of a row at place p ^ (k & 3 | k >> 1 & 4).  With these the
+    // reads of an operand, sixteen rows at one granule or pair, take every bank equally often.  Rows past the end of x are the last one again, columns
+    // past C lie at an offset that no descriptor covers: their results are not stored.
+    const int x_row_bytes = a.D * 2, w_row_bytes = a.C * 2;
+    const char* x_base = static_cast<const char*>(a.x) + m0 * x_row_bytes;
+    int x_voff[TL::kXLoads], w_voff[2];
+#pragma unroll
+    for (int p = 0; p < TL::kXLoads; ++p) {
+        const int r = 8 * (wave + 8 * p) + (lane >> 3);
+        x_voff[p] = (r < rows ? r : rows - 1) * x_row_bytes + 16 * ((lane & 7) ^ (r >> 1 & 7));
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int k = 4 * (wave + 8 * p) + (lane >> 4);
+        const int col = n0 + 16 * ((lane & 15) >> 1 ^ ((k & 3) | (k >> 1 & 4))) + 8 * (lane & 1);
+        w_voff[p] = col < a.C ? k * w_row_bytes + col * 2 : 0x7ffffff0;
+    }
+    typedef __attribute__((address_space(3))) char* lds_ptr;
+    const __amdgpu_buffer_rsrc_t rx = rsrc_of(x_base, static_cast<long long>(rows) * x_row_bytes);
+    const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.w, static_cast<long long>(a.D) * w_row_bytes);
+    auto ask = [&](int place) {
+        const int to = place * TL::kStage + 1024 * wave;
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_ptr)(lds + to + TL::kX + 8192 * p), 16, w_voff[p], at * (kBK * w_row_bytes), 0, 0);
+#pragma unroll
+        for (int p = 0; p < TL::kXLoads; ++p)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_ptr)(lds + to + 8192 * p), 16, x_voff[p], at * (kBK * 2), 0, 0);
+        at = at + 1 == nsteps ? 0 : at + 1;
+    };
+
+    const int kb = wave >> 2, wc = wave & 3;   // this wave's half of a step's channels, and its 32 columns
+    int a_off[2], b_off[2];                    // rows l16 and 16 + l16 (the others 32 rows further); columns 16 nb, channels 8 g4 .. +3 (and 1024 further the next four)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = 16 * i + l16;
+        a_off[i] = r * 128 + 16 * ((4 * kb + g4) ^ (r >> 1 & 7));
+    }
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+        const int k = 32 * kb + 8 * g4 + (l16 >> 2);
+        b_off[nb] = TL::kX + k * 256 + 32 * ((2 * wc + nb) ^ ((k & 3) | (k >> 1 & 4))) + 8 * (l16 & 3);
+    }
+    float4v acc[TL::kRB][2];
+#pragma unroll
+    for (int rb = 0; rb < TL::kRB; ++rb) acc[rb][0] = acc[rb][1] = float4v{0.f, 0.f, 0.f, 0.f};
+
+    int asked = 0;
+    for (; asked < TL::kStages - 1 && asked < nsteps; ++asked) ask(asked);
+    int place = 0, free_place = TL::kStages - 1;
+#pragma clang loop unroll(disable)
+    for (int step = 0; step < nsteps; ++step) {
+        if (asked - step == TL::kStages - 1) wait_loads<TL::kLoads * (TL::kStages - 2)>();     // the younger steps are on their way
+        else wait_loads<0>();
+        __builtin_amdgcn_s_barrier();          // the step's tiles are there, and all waves are done with the place of the one before
+        __builtin_amdgcn_sched_barrier(0);
+        if (asked < nsteps) {
+            ask(free_place);
+            ++asked;
+        }
+        free_place = place;
+        const char* b = lds + place * TL::kStage;
+        place = place + 1 == TL::kStages ? 0 : place + 1;
+        if (n0 + 32 * wc >= a.C) continue;     // no columns: the wave only loads
+        bf16x8 av[TL::kRB];
+#pragma unroll
+        for (int rb = 0; rb < TL::kRB; ++rb) av[rb] = lds_read_b8(b, a_off[rb & 1] + 4096 * (rb >> 1));
+        // The transposing reads with their own wait, which is the wave's last LDS access of the step.  (Before the builtin the compiler waits for
+        // every load into LDS.)
+        bf16x8 wt[2];
+        lds_read_tr8_pair((lds_ptr)(b + b_off[0]), (lds_ptr)(b + b_off[1]), wt[0], wt[1]);
+#pragma unroll
+        for (int rb = 0; rb < TL::kRB; ++rb)
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)     // columns as the rows of the product: a lane ends with four neighbouring columns of its token
+                acc[rb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[nb], av[rb], acc[rb][nb], 0, 0, 0);
+    }
+
+    // the two halves meet in LDS; whole rows leave
+    __syncthreads();
+    float* part = reinterpret_cast<float*>(lds);
+#pragma unroll
+    for (int rb = 0; rb < TL::kRB; ++rb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+            *reinterpret_cast<float4v*>(part + (kb * kRowTile + 16 * rb + l16) * TL::kPRow + 32 * wc + 16 * nb + 4 * g4) = acc[rb][nb];
+    __syncthreads();
+    constexpr int kPer = kOutF32 ? 4 : 8, kLanes = 128 / kPer;   // columns of a thread's 16 bytes, threads of a row
+    const int cr = tid / kLanes, col = tid % kLanes * kPer;
+    if (n0 + col >= a.C) return;
+#pragma unroll
+    for (int p = 0; p < kRowTile * kLanes / 512; ++p) {
+        const int row = cr + 512 / kLanes * p;
+        if (row >= rows) break;
+        float4v q[kPer / 4];
+#pragma unroll
+        for (int i = 0; i < kPer / 4; ++i)
+            q[i] = *reinterpret_cast<const float4v*>(part + row * TL::kPRow + col + 4 * i) +
+                   *reinterpret_cast<const float4v*>(part + (kRowTile + row) * TL::kPRow + col + 4 * i);
+        const long long e = (m0 + row) * a.C + n0 + col;
+        if constexpr (kOutF32) {
+            *reinterpret_cast<float4v*>(static_cast<float*>(a.c) + e) = q[0];
+        } else {
+            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+            typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+            const uint2v lo = __builtin_bit_cast(uint2v, __builtin_convertvector(q[0], bf16x4)), hi = __builtin_bit_cast(uint2v, __builtin_convertvector(q[1], bf16x4));
+            *reinterpret_cast<uint4v*>(static_cast<unsigned short*>(a.c) + e) = uint4v{lo[0], lo[1], hi[0], hi[1]};
+        }
+    }
+}
+
+// kRowTile tokens x kBN columns; kWNB: 16-column blocks of a multiplying wave, and with it the form: 4 with loader waves, 2 with all waves alike.
+template <int kBN, int kWNB, bool kOutF32, int kRowTile>
+__global__ __launch_bounds__(kWNB == 2 ? 512 : Tile<kBN>::kThreads, kWNB == 2 ? 128 / kRowTile : Tile<kBN>::kPerCu) void key_compress_kernel(KcArgs a) {
+    static_assert(kWNB == 2 ? kBN == 128 : kRowTile == kBM, "forms");
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    if constexpr (kWNB == 2) kc_direct<kOutF32, kRowTile>(a, lds);
+    else kc_roles<kOutF32, kBN>(a, lds);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -491,12 +672,12 @@ hipError_t launch_few(const KcArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <int kBN, int kWNB, bool kOutF32>
+template <int kBN, int kWNB, bool kOutF32, int kRowTile = kBM>
 hipError_t launch_tile(const KcArgs& a, hipStream_t stream) {
-    using TL = Tile<kBN, kWNB>;
-    const long long row_tiles = (a.M + kBM - 1) / kBM;
+    constexpr int threads = kWNB == 2 ? 512 : Tile<kBN>::kThreads, bytes = kWNB == 2 ? DmaTile<kRowTile>::kLds : Tile<kBN>::kLds;
+    const long long row_tiles = (a.M + kRowTile - 1) / kRowTile;
     const dim3 grid(static_cast<unsigned>((row_tiles + 7) / 8 * 8 * ((a.C + kBN - 1) / kBN)));
-    hipLaunchKernelGGL((key_compress_kernel<kBN, kWNB, kOutF32>), grid, dim3(TL::kThreads), TL::kLds, stream, a);
+    hipLaunchKernelGGL((key_compress_kernel<kBN, kWNB, kOutF32, kRowTile>), grid, dim3(threads), bytes, stream, a);
     return hipGetLastError();
 }
 
@@ -510,9 +691,10 @@ hipError_t raise_lds_limits() {
     if (err == hipSuccess) err = set_lds_limit(&key_compress_few_kernel<1, 2, kOutF32>, FewTile<1, 2>::kLds);
     if (err == hipSuccess) err = set_lds_limit(&key_compress_few_kernel<1, 4, kOutF32>, FewTile<1, 4>::kLds);
     if (err == hipSuccess) err = set_lds_limit(&key_compress_few_kernel<2, 4, kOutF32>, FewTile<2, 4>::kLds);
-    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, 4, kOutF32>, Tile<128, 4>::kLds);
-    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, 2, kOutF32>, Tile<128, 2>::kLds);
-    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<256, 4, kOutF32>, Tile<256, 4>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, 4, kOutF32, kBM>, Tile<128>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<256, 4, kOutF32, kBM>, Tile<256>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, 2, kOutF32, 64>, DmaTile<64>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, 2, kOutF32, 128>, DmaTile<128>::kLds);
     return err;
 }
 
@@ -549,11 +731,19 @@ hipError_t launch_key_compress(long long M, int D, const void* x, const void* w,
     if (groups(1, 4) <= cus) return out_f32 ? launch_few<1, 4, true>(a, stream) : launch_few<1, 4, false>(a, stream);
     if (3 * groups(2, 4) <= (a.C > 128 ? 6 : a.C == 128 ? 5 : 3) * cus)
         return out_f32 ? launch_few<2, 4, true>(a, stream) : launch_few<2, 4, false>(a, stream);
-    // At most one large tile per compute unit: 128 columns a tile, also above D = 2048 (x then comes from L2 the second
-    // time), and eight MFMA waves instead of four, since no second workgroup is there to overlap with.  Microseconds, before -> here:
-    // D = 4096 6000 tokens 58.6 -> 37.1, 16 384 (256 tiles) 64.8 -> 50.8, and at 24 000 71 against 79; D = 8192 8192 tokens 116 -> 88;
-    // D = 2048 16 384 tokens 22.6 -> 21.5.
-    if ((M + kBM - 1) / kBM * ((a.C + 127) / 128) <= cus) return out_f32 ? launch_tile<128, 2, true>(a, stream) : launch_tile<128, 2, false>(a, stream);
+    // At most one large tile per compute unit: 128 columns a tile, also above D = 2048 (x then comes from L2 the second time), loads
+    // straight into LDS by all waves, 64 tokens a tile while these fit the chip once (twice with at most 64 columns, whose tiles share a compute
+    // unit), which doubles the compute units of the shorter calls.  Microseconds, loader waves and 128 tokens -> here: D = 2048, 7000 tokens
+    // 20.3 -> 13.3, 16 384 20.8 -> 15.0, with 128 tokens a tile 17 000 20.9 -> 19.0, 20 000 22.7 -> 21.8, 32 768 30.1 -> 29.4; D = 4096 5000 36.7 -> 24.0,
+    // 8192 37.1 -> 24.7, 16 000 47.5 -> 45.4; D = 1024 12 000 11.8 -> 8.4, 20 000 12.2 -> 10.6, D = 768 30 000 10.9 -> 10.1.  64 tokens a tile in two rounds
+    // take all of W again: D = 2048 20 000 27.2, 32 768 36.9.  Beyond, two workgroups of loader waves share a compute unit and overlap: 131 072
+    // tokens 114 against 119 (128 tokens a tile), D = 1024 57 against 58 (64), D = 4096 65 536 160 against 226, D = 256 500 000 60 against 70.
+    // (The direct form addresses W with 32 bits.)
+    if (D <= 32768) {
+        const long long col_tiles = (a.C + 127) / 128;
+        if ((M + 63) / 64 * col_tiles <= (a.C <= 64 ? 2 : 1) * cus) return out_f32 ? launch_tile<128, 2, true, 64>(a, stream) : launch_tile<128, 2, false, 64>(a, stream);
+        if ((M + 127) / 128 * col_tiles <= cus) return out_f32 ? launch_tile<128, 2, true, 128>(a, stream) : launch_tile<128, 2, false, 128>(a, stream);
+    }
     if (a.C > 128) return out_f32 ? launch_tile<256, 4, true>(a, stream) : launch_tile<256, 4, false>(a, stream);
     return out_f32 ? launch_tile<128, 4, true>(a, stream) : launch_tile<128, 4, false>(a, stream);
 }

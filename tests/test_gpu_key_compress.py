@@ -36,6 +36,17 @@ def test_matches_oracle(gpu_device, M, D):
     assert np.array_equal(c16, round_to_bf16(c32))
 
 
+# tiles of 64 and 128 tokens with all waves alike: a last tile of one row, fewer steps than places, column tiles of 16, 48 and 64 columns, a
+# third column tile of 16
+@pytest.mark.parametrize("M,D", [(6849, 2048), (16384, 2048), (16385, 2048), (8200, 256), (16321, 256), (9000, 768), (30000, 768), (12000, 1024), (5400, 4352)])
+def test_tiles_that_fill_the_chip_at_most_once(gpu_device, M, D):
+    x, w = make_key_compress_inputs(M, D, seed=900 + M)
+    ref = key_compress_oracle(x, w)
+    c32 = run(x, w, torch.float32)
+    assert max_norm_err(c32, ref) <= 1e-5
+    assert np.array_equal(run(x, w, torch.bfloat16), round_to_bf16(c32))
+
+
 def test_selector_matrix_copies_channels(gpu_device):
     """W with one 1 per column: every output is one bf16 input copied exactly."""
     M, D = 200, 2048
