@@ -938,11 +938,15 @@ hipError_t raise_mode_limits() {
 // 16 x 4096 x 32 323 -> 311, 10 x 5000 x 64 459 -> 436, 32 x 1000 x 32 140 -> 134, fp32 out 64 x 2500 x 32 804 -> 753.  Not taken: bf16 rows whose
 // streams start 128 bytes apart, which lie in every class by themselves (Finch-C2 64 x 1000 x 32 298 -> 306; fp32 rows, of 256
 // bytes, gain there too: 341 -> 323, Finch 64 x 2500 755 -> 727); Finch, bf16 out, from 1 GiB on, which the kernel's own cycles bound (64 x 1000 x
-// 32 255 -> 257, 12 x 12 000 x 32 698 -> 700); calls that the memory-side cache holds (20 x 60 x 32 13.6 -> 13.8, 30 x 100 x 32
-// 21.0 -> 21.5); and not with fused logits, whose consumers hold their head's slice of B in registers.
+// 32 255 -> 257, 12 x 12 000 x 32 698 -> 700); calls that the memory-side cache holds for the most part, to 300 MiB in the Finch form with bf16
+// rows (10 x 412 x 64 40.4 -> 41.0, 20 x 700 x 16 44.7 -> 45.1; at 306 MiB 24 x 600 x 32 65.5 -> 62.9), to 150 MiB in the others (20 x 60 x
+// 32 13.6 -> 13.8, 9 x 500 x 32 39.4 -> 39.9; at 213 10 x 412 x 64 49.8 -> 49.2, fp32 out 20 x 300 x 32 36.8 -> 35.3); fewer units than one and a
+// half rounds, most of whose workgroups have one (9 x 1500 x 32 85.2 -> 85.9); and fused logits, whose consumers hold their head's slice of B in
+// registers.
 template <int kMode, bool kC2>
-bool heads_in_turn(const Args& a) {
-    if (a.H % 8 != 0 || (!kC2 && a.H > kTurnHeads)) return false;
+bool heads_in_turn(const Args& a, long long units, long long mib) {
+    if (a.H % 8 != 0 || (!kC2 && a.H > kTurnHeads) || 2 * units < 3ll * a.unit_stride) return false;
+    if (mib < (kMode == 1 || kC2 ? 150 : 300)) return false;
     if (kMode == 1) return true;
     const auto address_class = [](const void* p) { return reinterpret_cast<unsigned long long>(p) >> 7 & 7; };
     const auto c = address_class(a.r);
@@ -980,7 +984,7 @@ hipError_t launch_mode(const Args& args, hipStream_t stream) {
     auto several = [&](auto traffic) {
         constexpr Traffic kTraffic = decltype(traffic)::value;
         if constexpr (kHasTurn<kMode, kC2, kTraffic>)
-            if (heads_in_turn<kMode, kC2>(a)) return go(&chunked_kernel<kMode, kC2, true, true, kTraffic>, true);
+            if (heads_in_turn<kMode, kC2>(a, static_cast<long long>(a.B) * a.H, mib)) return go(&chunked_kernel<kMode, kC2, true, true, kTraffic>, true);
         return go(&chunked_kernel<kMode, kC2, false, true, kTraffic>);
     };
     if constexpr (kMode < 3)
