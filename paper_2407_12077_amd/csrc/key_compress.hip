@@ -360,21 +360,38 @@ __device__ __forceinline__ void wait_loads() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Two operands of a tile with rows of 256 bytes, as lds_read_tr8, from the addresses of their first four rows; waits for all LDS accesses of the wave.
-__device__ __forceinline__ void lds_read_tr8_pair(__attribute__((address_space(3))) const char* p0, __attribute__((address_space(3))) const char* p1,
-                                                  bf16x8& q0, bf16x8& q1) {
+// kCount operands as lds_read_tr8 reads them, from the byte offsets of their first four rows behind `base`, the next four kHi bytes further; waits for all
+// LDS accesses of the wave.  (Before the builtin the compiler waits for every load into LDS.)
+template <int kCount, int kHi = 4 * 32 * kCount>
+__device__ __forceinline__ void lds_read_tr8_all(__attribute__((address_space(3))) const char* base, const int (&off)[kCount], bf16x8 (&q)[kCount]) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    short4v lo0, hi0, lo1, hi1;
-    asm volatile("ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %4 offset:1024\n\t"
-                 "ds_read_b64_tr_b16 %2, %5\n\tds_read_b64_tr_b16 %3, %5 offset:1024\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&v"(lo0), "=&v"(hi0), "=&v"(lo1), "=&v"(hi1)
-                 : "v"(static_cast<unsigned>(reinterpret_cast<unsigned long long>(p0))), "v"(static_cast<unsigned>(reinterpret_cast<unsigned long long>(p1)))
-                 : "memory");
-    __builtin_amdgcn_sched_barrier(0);
     typedef short short8v __attribute__((ext_vector_type(8)));
-    const short8v both0 = __builtin_shufflevector(lo0, hi0, 0, 1, 2, 3, 4, 5, 6, 7), both1 = __builtin_shufflevector(lo1, hi1, 0, 1, 2, 3, 4, 5, 6, 7);
-    q0 = __builtin_bit_cast(bf16x8, both0);
-    q1 = __builtin_bit_cast(bf16x8, both1);
+    unsigned p[kCount];
+    short4v lo[kCount], hi[kCount];
+#pragma unroll
+    for (int i = 0; i < kCount; ++i) p[i] = static_cast<unsigned>(reinterpret_cast<unsigned long long>(base)) + off[i];
+    if constexpr (kCount == 1) {
+        asm volatile("ds_read_b64_tr_b16 %0, %2\n\tds_read_b64_tr_b16 %1, %2 offset:%3\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(lo[0]), "=&v"(hi[0]) : "v"(p[0]), "n"(kHi) : "memory");
+    } else if constexpr (kCount == 2) {
+        asm volatile("ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %4 offset:%6\n\t"
+                     "ds_read_b64_tr_b16 %2, %5\n\tds_read_b64_tr_b16 %3, %5 offset:%6\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(lo[0]), "=&v"(hi[0]), "=&v"(lo[1]), "=&v"(hi[1]) : "v"(p[0]), "v"(p[1]), "n"(kHi) : "memory");
+    } else {
+        static_assert(kCount == 4, "1, 2 or 4 operands");
+        asm volatile("ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:%12\n\t"
+                     "ds_read_b64_tr_b16 %2, %9\n\tds_read_b64_tr_b16 %3, %9 offset:%12\n\t"
+                     "ds_read_b64_tr_b16 %4, %10\n\tds_read_b64_tr_b16 %5, %10 offset:%12\n\t"
+                     "ds_read_b64_tr_b16 %6, %11\n\tds_read_b64_tr_b16 %7, %11 offset:%12\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(lo[0]), "=&v"(hi[0]), "=&v"(lo[1]), "=&v"(hi[1]), "=&v"(lo[2]), "=&v"(hi[2]), "=&v"(lo[3]), "=&v"(hi[3])
+                     : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "n"(kHi) : "memory");
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < kCount; ++i) {
+        const short8v both = __builtin_shufflevector(lo[i], hi[i], 0, 1, 2, 3, 4, 5, 6, 7);
+        q[i] = __builtin_bit_cast(bf16x8, both);
+    }
 #endif
 }
 
@@ -461,10 +478,8 @@ __device__ __forceinline__ void kc_direct(const KcArgs& a, char* lds) {
         bf16x8 av[TL::kRB];
 #pragma unroll
         for (int rb = 0; rb < TL::kRB; ++rb) av[rb] = lds_read_b8(b, a_off[rb & 1] + 4096 * (rb >> 1));
-        // The transposing reads with their own wait, which is the wave's last LDS access of the step.  (Before the builtin the compiler waits for
-        // every load into LDS.)
         bf16x8 wt[2];
-        lds_read_tr8_pair((lds_ptr)(b + b_off[0]), (lds_ptr)(b + b_off[1]), wt[0], wt[1]);
+        lds_read_tr8_all<2, 1024>((lds_ptr)b, b_off, wt);      // with a wait for all of the step's LDS reads: after the next barrier its place is free
 #pragma unroll
         for (int rb = 0; rb < TL::kRB; ++rb)
 #pragma unroll
@@ -516,24 +531,23 @@ __global__ __launch_bounds__(kWNB == 2 ? 512 : Tile<kBN>::kThreads, kWNB == 2 ? 
 
 // ------------------------------------------------------------------------------------------
 // Few tokens (a decode batch, short prompts): the contraction split over the waves.  Bound by latency up to a
-// few hundred tokens (launch, two rounds of loads, the reduction: 4 to 6 us), then by W through L2.
+// few hundred tokens (launch, two rounds of loads, the reduction: 3.7 to 5.6 us), then by W through L2.
 // ------------------------------------------------------------------------------------------
-// The tiles above need 128 tokens per workgroup to be worth their loads: with a few row tiles most
+// The tiles above need 64 tokens per workgroup to be worth their loads: with a few row tiles most
 // compute units have nothing to do and the others walk D / 64 dependent steps.  Here a workgroup owns a
 // small tile, 16 kTB tokens x 16 kNB columns, and its sixteen waves take the 32-channel blocks of D in
-// turn (wave w: blocks w, w + 16, ...), so that a walk is D / 512 steps long, with the loads of
-// kFewDepth of them in flight, and needs no barrier: a wave passes its x and W blocks through a piece of LDS of its
-// own (x loaded straight into operand layout touches sixteen lines per quarter wave, which the L1's tag lookups
-// charge four times: D = 2048, 16 tokens 5.1 -> 4.5 us, 4096 tokens 11.1 -> 10.6).  The sixteen partial results are added in wave order, in fp32, at the end.
+// turn (wave w: blocks w, w + 16, ...), so that a walk is D / 512 steps long and needs no barrier: a wave brings its x and W blocks straight into a
+// piece of LDS of its own, W kAhead blocks ahead and x one more (x loaded into operand layout from global memory touches sixteen lines per quarter
+// wave, which the L1's tag lookups charge four times), and reads them from there as operands.  The sixteen partial results are added in wave
+// order, in fp32, at the end.  Through registers and LDS stores, two blocks ahead of both, the same sums took longer: D = 2048, 24 tokens 4.55 us against 3.85 now,
+// 2048 tokens 7.4 against 6.3, 4096 11.7 against 10.5, 6500 19.0 against 16.7; D = 768 3000 tokens 4.8 against 3.7; D = 4096 16 tokens 6.0 against 5.1.
 constexpr int kFewWaves = 16;
-constexpr int kFewDepth = 2;
 
 template <int kTB, int kNB>
 struct FewTile {
-    static constexpr int kWRow = 32 * kNB + 32;         // LDS row stride of a wave's W block [32][16 kNB] bf16
-    static constexpr int kXOff = 32 * kWRow;            // then its x block [16 kTB][32] bf16, 64-byte rows
-    static constexpr int kFewXRow = 96;
-    static constexpr int kPiece = kXOff + 16 * kTB * kFewXRow;
+    static constexpr int kX = 1024 * kTB, kW = 1024 * kNB;                  // bytes of a block: rows of 64 bytes; 32 rows of 32 kNB bytes
+    static constexpr int kAhead = kNB == 4 ? 1 : 2;                         // places for W blocks; one more for x
+    static constexpr int kPiece = (kAhead + 1) * kX + kAhead * kW;
     static constexpr int kPRow = 16 * kNB + 4;          // row stride (floats) of a wave's partial result
     static constexpr int kPart = 16 * kTB * kPRow;      // floats per wave
     static constexpr int kWBytes = kFewWaves * kPiece, kPBytes = kFewWaves * kPart * 4;
@@ -542,89 +556,87 @@ struct FewTile {
 };
 
 template <int kTB, int kNB, bool kOutF32>
-__global__ __launch_bounds__(64 * kFewWaves) void key_compress_few_kernel(KcArgs a) {
+__device__ __forceinline__ void kc_few(const KcArgs& a, char* lds) {
     using TL = FewTile<kTB, kNB>;
-    extern __shared__ __attribute__((aligned(16))) char lds[];
+    constexpr int kA = TL::kAhead;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nct = (a.C + 16 * kNB - 1) / (16 * kNB);
     const long long m0 = static_cast<long long>(blockIdx.x / nct) * (16 * kTB);
     const int n0 = static_cast<int>(blockIdx.x % nct) * (16 * kNB);
-    const long long rows_left = a.M - m0;
-    const int rows = rows_left < 16 * kTB ? static_cast<int>(rows_left) : 16 * kTB;
-    const long long x_row_bytes = static_cast<long long>(a.D) * 2, w_row_bytes = static_cast<long long>(a.C) * 2;
-    const char* x_base = static_cast<const char*>(a.x) + m0 * x_row_bytes;
-    const long long x_bytes = rows * x_row_bytes, w_bytes = static_cast<long long>(a.D) * w_row_bytes;
-    const int nkb = a.D / 32;
+    const int rows = a.M - m0 < 16 * kTB ? static_cast<int>(a.M - m0) : 16 * kTB;
+    const int x_row_bytes = a.D * 2, w_row_bytes = a.C * 2;
+    const int nkb = a.D / 32, mine = wave < nkb ? (nkb - 1 - wave) / kFewWaves + 1 : 0;     // this wave's blocks
 
-    // W block: 2 kNB lanes per row piece of 16 kNB columns, 32 / kNB rows per pass; columns past C (a
-    // partial last column tile) lie at an offset that no descriptor covers
-    constexpr int kLanesPerRow = 2 * kNB, kRowsPerPass = 64 / kLanesPerRow;
-    const int wr = lane / kLanesPerRow, wg = lane % kLanesPerRow;
-    const int w_voff = n0 + 8 * wg < a.C ? static_cast<int>(wr * w_row_bytes + (n0 + 8 * wg) * 2) : 0x7ffffff0;
-    const int w_pass = n0 + 8 * wg < a.C ? static_cast<int>(kRowsPerPass * w_row_bytes) : 0;
-    // x block: 4 lanes per 64-byte row piece, 16 rows per pass
-    const int xr = lane >> 2, xg = 16 * (lane & 3);
-    const int x_voff = static_cast<int>(xr * x_row_bytes) + xg, x_pass = static_cast<int>(16 * x_row_bytes);
-
-    struct Regs {
-        uint4v x[kTB], w[kNB];
-    };
-    auto fetch = [&](Regs& s, int kb) {
-        const bool live = kb < nkb;                    // uniform; past the end the descriptors are empty
-        const long long xs = static_cast<long long>(kb) * 64, ws = static_cast<long long>(kb) * 32 * w_row_bytes;
-        const __amdgpu_buffer_rsrc_t rx = rsrc_of(x_base + (live ? xs : 0), live ? x_bytes - xs : 0);
-        const __amdgpu_buffer_rsrc_t rw = rsrc_of(static_cast<const char*>(a.w) + (live ? ws : 0), live ? w_bytes - ws : 0);
+    // A load brings 1 KiB, lane i's 16 bytes 16 i behind the wave's LDS address.  x: sixteen rows, granules XOR-ed by two row bits; W: rows of kNB
+    // 32-byte pairs, the pairs XOR-ed by row bits, so that the reads of an operand take every bank equally often.  Rows past the end are
+    // the last one again, columns past C lie at an offset that no descriptor covers: their results are not stored.
+    typedef __attribute__((address_space(3))) char* lds_ptr;
+    auto pair_of = [](int k) { return kNB == 4 ? (k >> 1 & 1) | (k >> 2 & 2) : kNB == 2 ? k >> 3 & 1 : 0; };
+    int x_voff[kTB], w_voff[kNB];
 #pragma unroll
-        for (int nb = 0; nb < kNB; ++nb)
-            s.w[nb] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(rw, w_voff + nb * w_pass, 0, 0));
+    for (int tb = 0; tb < kTB; ++tb) {
+        const int r = 16 * tb + (lane >> 2);
+        x_voff[tb] = (r < rows ? r : rows - 1) * x_row_bytes + 16 * ((lane & 3) ^ (r >> 2 & 3));
+    }
+#pragma unroll
+    for (int nb = 0; nb < kNB; ++nb) {
+        const int k = (64 * nb + lane) / (2 * kNB), at = lane % (2 * kNB);
+        const int col = n0 + 16 * (at >> 1 ^ pair_of(k)) + 8 * (at & 1);
+        w_voff[nb] = col < a.C ? k * w_row_bytes + col * 2 : 0x7ffffff0;
+    }
+    const char* x_base = static_cast<const char*>(a.x) + m0 * x_row_bytes;
+    const __amdgpu_buffer_rsrc_t rx = rsrc_of(x_base, static_cast<long long>(rows) * x_row_bytes);
+    const int piece = wave * TL::kPiece;
+    auto x_place = [&](int i) { return piece + i % (kA + 1) * TL::kX; };
+    auto w_place = [&](int i) { return piece + (kA + 1) * TL::kX + i % kA * TL::kW; };
+    auto ask_x = [&](int i) {
+        if (i >= mine) return;
 #pragma unroll
         for (int tb = 0; tb < kTB; ++tb)
-            s.x[tb] = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(rx, x_voff + tb * x_pass, 0, 0));
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_ptr)(lds + x_place(i) + 1024 * tb), 16, x_voff[tb], (wave + i * kFewWaves) * 64, 0, 0);
     };
+    auto ask_w = [&](int i) {
+        if (i >= mine) return;
+        const long long ws = static_cast<long long>(wave + i * kFewWaves) * 32 * w_row_bytes;
+        const __amdgpu_buffer_rsrc_t rw = rsrc_of(static_cast<const char*>(a.w) + ws, 32 * w_row_bytes);
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_ptr)(lds + w_place(i) + 1024 * nb), 16, w_voff[nb], 0, 0, 0);
+    };
+    ask_x(0);
+#pragma clang loop unroll(disable)
+    for (int i = 0; i < kA; ++i) {
+        ask_w(i);
+        ask_x(i + 1);
+    }
 
     float4v acc[kTB][kNB];
 #pragma unroll
     for (int tb = 0; tb < kTB; ++tb)
 #pragma unroll
         for (int nb = 0; nb < kNB; ++nb) acc[tb][nb] = float4v{0.f, 0.f, 0.f, 0.f};
-    char* mine = lds + wave * TL::kPiece;
-    const int b_lane = (8 * g4 + (l16 >> 2)) * TL::kWRow + 8 * (l16 & 3);
-    auto step = [&](const Regs& s) {
-        // the wave alone touches its piece: the fences keep the order of its own accesses
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+    const int a_off = 64 * l16 + 16 * (g4 ^ (l16 >> 2 & 3));
+    const int k0 = 8 * g4 + (l16 >> 2);                  // this lane's row of W, and the one four further (the same pair_of)
+    int b_off[kNB];
+#pragma unroll
+    for (int nb = 0; nb < kNB; ++nb) b_off[nb] = k0 * 32 * kNB + 32 * (nb ^ pair_of(k0)) + 8 * (l16 & 3);
+#pragma clang loop unroll(disable)
+    for (int i = 0; i < mine; ++i) {
+        // behind block i's W: the x of the next block and what follows
+        if (i + kA < mine) wait_loads<(kA - 1) * kNB + kA * kTB>();
+        else wait_loads<0>();
+        bf16x8 xv[kTB], wt[kNB];
+#pragma unroll
+        for (int tb = 0; tb < kTB; ++tb) xv[tb] = lds_read_b8(lds + x_place(i), a_off + 1024 * tb);
+        lds_read_tr8_all<kNB>((lds_ptr)(lds + w_place(i)), b_off, wt);      // (and a wait for all LDS reads: the places are free)
+        ask_w(i + kA);
+        ask_x(i + kA + 1);
 #pragma unroll
         for (int nb = 0; nb < kNB; ++nb)
-            *reinterpret_cast<uint4v*>(mine + (wr + kRowsPerPass * nb) * TL::kWRow + 16 * wg) = s.w[nb];
 #pragma unroll
-        for (int tb = 0; tb < kTB; ++tb)
-            *reinterpret_cast<uint4v*>(mine + TL::kXOff + (16 * tb + xr) * TL::kFewXRow + xg) = s.x[tb];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        bf16x8 xv[kTB];
-#pragma unroll
-        for (int tb = 0; tb < kTB; ++tb) xv[tb] = lds_read_b8(mine, TL::kXOff + (16 * tb + l16) * TL::kFewXRow + 16 * g4);
-#pragma unroll
-        for (int nb = 0; nb < kNB; ++nb) {
-            // columns as the rows of the product: a lane ends with four neighbouring columns of its token
-            const bf16x8 wt = lds_read_tr8<TL::kWRow>(mine, b_lane + 32 * nb);
-#pragma unroll
-            for (int tb = 0; tb < kTB; ++tb)
-                acc[tb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt, xv[tb], acc[tb][nb], 0, 0, 0);
-        }
-    };
-    Regs ring[kFewDepth];
-#pragma unroll
-    for (int i = 0; i < kFewDepth; ++i) fetch(ring[i], wave + kFewWaves * i);
-#pragma clang loop unroll(disable)
-    for (int kb = wave; kb < nkb; kb += kFewWaves * kFewDepth) {
-#pragma unroll
-        for (int i = 0; i < kFewDepth; ++i) {          // blocks past the end add products of zeros
-            step(ring[i]);
-            fetch(ring[i], kb + kFewWaves * (kFewDepth + i));
-        }
+            for (int tb = 0; tb < kTB; ++tb)   // columns as the rows of the product: a lane ends with four neighbouring columns of its token
+                acc[tb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[nb], xv[tb], acc[tb][nb], 0, 0, 0);
     }
 
     // the partial results meet in LDS
@@ -657,6 +669,12 @@ __global__ __launch_bounds__(64 * kFewWaves) void key_compress_few_kernel(KcArgs
                     (static_cast<unsigned>(__builtin_bit_cast(unsigned short, static_cast<__bf16>(hi))) << 16);
         }
     }
+}
+
+template <int kTB, int kNB, bool kOutF32>
+__global__ __launch_bounds__(64 * kFewWaves) void key_compress_few_kernel(KcArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    kc_few<kTB, kNB, kOutF32>(a, lds);
 }
 
 }  // namespace
@@ -720,7 +738,7 @@ hipError_t launch_key_compress(long long M, int D, const void* x, const void* w,
     // or tie: 18.5 against 19.9 at 4200 tokens, 19.5 against 20.1 at 6200 and 19.8 against 20.1 at 6700, but 20.4 against 20.1
     // at 7200 and 21.6 against 20.2 at 8192, so up to five thirds of a round there (six to seven thousand tokens); wider models
     // the whole second round: D = 2304 20.5 against 22.0 at 3000 tokens, 3072 24.0 against 28.2 at 4096 and 25.0 against 28.3 at 5200,
-    // 4096 33.6 against 36.4 at 4096.  Beyond that the W traffic of the small tiles (all of W per 32 tokens) loses: D = 2048,
+    // 4096 33.6 against 36.4 at 4096 (all of these with loads through registers in both; now 15.8 us at 4500 tokens, 16.7 at 6500).  Beyond that the W traffic of the small tiles (all of W per 32 tokens) loses: D = 2048,
     // 16 384 tokens 37 against 21.
     const int cus = compute_units();
     auto groups = [&](int tb, int nb) {

@@ -37,8 +37,8 @@ def test_matches_oracle(gpu_device, M, D):
 
 
 # tiles of 64 and 128 tokens with all waves alike: a last tile of one row, fewer steps than places, column tiles of 16, 48 and 64 columns, a
-# third column tile of 16
-@pytest.mark.parametrize("M,D", [(6849, 2048), (16384, 2048), (16385, 2048), (8200, 256), (16321, 256), (9000, 768), (30000, 768), (12000, 1024), (5400, 4352)])
+# third column tile of 16; smaller tiles, the contraction over the waves: waves without a block, a last block of one row, 16 of 64 columns
+@pytest.mark.parametrize("M,D", [(6849, 2048), (16384, 2048), (16385, 2048), (8200, 256), (16321, 256), (9000, 768), (30000, 768), (12000, 1024), (5400, 4352), (17, 2048), (2100, 2048), (4097, 2048), (3001, 768), (8191, 256), (1500, 2304)])
 def test_tiles_that_fill_the_chip_at_most_once(gpu_device, M, D):
     x, w = make_key_compress_inputs(M, D, seed=900 + M)
     ref = key_compress_oracle(x, w)
