@@ -1,5 +1,5 @@
-// Token-by-token WKV6 kernel for gfx950: one wavefront per (batch, head), lane j owns
-// column j of the state (64 fp32 registers), r/k/w of the current token are exchanged
+// Token-by-token WKV6 kernel for gfx950: one wavefront per (batch, head), or four that share its key rows; lane j owns
+// column j of the state (64 or 16 fp32 registers), r/k/w of the current token are exchanged
 // through LDS and read back as broadcasts.  Follows the recurrence one step at a time
 // (Finch-C2 Time Mixing: decay map, wkv_t, read-out; plus the Finch bonus u):
 //     o_t[j] = sum_i r_t[i] S[i][j]  +  (sum_i r_t[i] u[i] k_t[i]) v_t[j]
@@ -7,7 +7,7 @@
 // It is bound by the fp32 vector ALUs (about 3*N*N operations per token and head), which
 // is why the chunked kernel exists; this one serves the decode / short-append shapes (one or a
 // few tokens per sequence, many sequences), where the work is streaming the fp32 state through
-// once: 64 row loads of 256 contiguous bytes per wave, all in flight together.  Long sequences
+// once: 64 (16) row loads of 256 contiguous bytes per wave, all in flight together.  Long sequences
 // of the fp32 and cross-check entry points take the four-wave form or, with few units, the form that spreads a
 // unit's columns over the chip, both further down.
 // Finch-C2 form (template flag): k = kbar (1 - w), no bonus, second value u' added to o.
@@ -40,39 +40,54 @@ __device__ __forceinline__ float wave_sum(float a) {
 // kLora: the decay logit is formed here, lambda + y B, from the token's 64 low-rank activations and this channel's column of
 // B (32 registers of bf16 pairs; products exact and sums in fp32, as on the matrix cores).  With a.moments
 // (Finch-C2) the wave also leaves the head's LayerNorm partials of every token.
-template <bool kInBf16, bool kOutBf16, bool kC2, bool kLora>
-__global__ __launch_bounds__(64) void recurrent_kernel(Args a) {
-    constexpr int N = kHeadSize;
+// kWaves: 1 or 4 (the rule is at the launch).  Wave q of four holds the key rows 16 q .. 16 q + 15 of the state and sums its sixteen terms of a read-out, and with kLora of a
+// logit; they meet in LDS, one barrier each, and wave 0 writes the row.  Everything else of a token each wave does by itself.
+template <bool kInBf16, bool kOutBf16, bool kC2, bool kLora, int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void recurrent_kernel(Args a) {
+    constexpr int N = kHeadSize, kRows = N / kWaves;
     const int unit = blockIdx.x;           // b * H + h
     const int b = unit / a.H;
     const int h = unit - b * a.H;
-    const int j = threadIdx.x;
+    const int j = threadIdx.x & 63;
+    const int q = kWaves == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-    __shared__ __attribute__((aligned(16))) float s_r[N];
-    __shared__ __attribute__((aligned(16))) float s_k[N];
-    __shared__ __attribute__((aligned(16))) float s_w[N];
-    __shared__ __attribute__((aligned(16))) float s_y[kLora ? N : 4];
+    __shared__ __attribute__((aligned(16))) float s_in[kWaves][3][N];      // r, k, w of the token, a copy for each wave
+    __shared__ __attribute__((aligned(16))) float s_y[kLora ? kWaves : 1][kLora ? N : 4];
+    // partial logits and read-outs by token parity: a wave writes a slot again two barriers after the last read of it
+    __shared__ float s_logit[2][kWaves > 1 && kLora ? kWaves : 1][N], s_out[2][kWaves][N];
+    float(&s_r)[N] = s_in[q][0];
+    float(&s_k)[N] = s_in[q][1];
+    float(&s_w)[N] = s_in[q][2];
     static_assert(!kLora || kLoraRank == kHeadSize, "a lane brings in one activation");
+    auto order = [] {                      // this wave's LDS accesses before and behind it
+        if constexpr (kWaves == 1) {
+            __syncthreads();
+        } else {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+    };
 
-    [[maybe_unused]] unsigned bw[kLora ? N / 2 : 1];
+    [[maybe_unused]] unsigned bw[kLora ? kRows / 2 : 1];
     [[maybe_unused]] float lam = 0.f;
     if constexpr (kLora) {
         const long long width = static_cast<long long>(a.H) * N;
-        const unsigned short* col = static_cast<const unsigned short*>(a.bw) + h * N + j;
+        const unsigned short* col = static_cast<const unsigned short*>(a.bw) + q * kRows * width + h * N + j;
 #pragma unroll
-        for (int i = 0; i < N / 2; ++i)
+        for (int i = 0; i < kRows / 2; ++i)
             bw[i] = static_cast<unsigned>(col[2 * i * width]) | (static_cast<unsigned>(col[(2 * i + 1) * width]) << 16);
         lam = a.lambda[h * N + j];
     }
 
-    float S[N];
+    float S[kRows];
     if (a.state_in) {
-        const float* s0 = a.state_in + static_cast<long long>(unit) * N * N;
+        const float* s0 = a.state_in + static_cast<long long>(unit) * N * N + q * kRows * N;
 #pragma unroll
-        for (int i = 0; i < N; ++i) S[i] = __builtin_nontemporal_load(&s0[i * N + j]);   // streamed once
+        for (int i = 0; i < kRows; ++i) S[i] = __builtin_nontemporal_load(&s0[i * N + j]);   // streamed once
     } else {
 #pragma unroll
-        for (int i = 0; i < N; ++i) S[i] = 0.f;
+        for (int i = 0; i < kRows; ++i) S[i] = 0.f;
     }
 
     const float uj = kC2 ? 0.f : a.u[h * N + j];
@@ -105,34 +120,42 @@ __global__ __launch_bounds__(64) void recurrent_kernel(Args a) {
         }
         float logit = x_cur;
         if constexpr (kLora) {
-            s_y[j] = x_cur;                    // (the last token's reads are behind its second barrier)
-            __syncthreads();
-            logit = lam;
+            s_y[q][j] = x_cur;                 // (the last token's reads are behind its second barrier)
+            order();
+            logit = q == 0 ? lam : 0.f;
 #pragma unroll
-            for (int i = 0; i < N; i += 4) {
-                const float4 y4 = *reinterpret_cast<const float4*>(&s_y[i]);
+            for (int i = 0; i < kRows; i += 4) {
+                const float4 y4 = *reinterpret_cast<const float4*>(&s_y[q][q * kRows + i]);
                 logit = fmaf(y4.x, __uint_as_float(bw[i / 2] << 16), logit);
                 logit = fmaf(y4.y, __uint_as_float(bw[i / 2] & 0xffff0000u), logit);
                 logit = fmaf(y4.z, __uint_as_float(bw[i / 2 + 1] << 16), logit);
                 logit = fmaf(y4.w, __uint_as_float(bw[i / 2 + 1] & 0xffff0000u), logit);
             }
+            if constexpr (kWaves > 1) {
+                s_logit[t & 1][q][j] = logit;
+                __syncthreads();
+                logit = (s_logit[t & 1][0][j] + s_logit[t & 1][1][j]) + (s_logit[t & 1][2][j] + s_logit[t & 1][3][j]);
+            }
         }
         const float w_cur = expf(-expf(logit));
         // Finch-C2 key factor 1 - w = -expm1(-exp(x)): no cancellation for decays close to 1
         const float k_cur = kC2 ? kraw * -expm1f(-expf(logit)) : kraw;
-        __syncthreads();                       // previous token's LDS reads are done
+        order();                               // previous token's LDS reads are done
         s_r[j] = r_cur;
         s_k[j] = k_cur;
         s_w[j] = w_cur;
-        float o = p_cur;                       // Finch-C2: the second value; Finch: the bonus term
-        if constexpr (!kC2) o = wave_sum(r_cur * uj * k_cur) * v_cur;
-        __syncthreads();
+        float o = 0.f;                         // Finch-C2: the second value; Finch: the bonus term
+        if (q == 0) {
+            o = p_cur;
+            if constexpr (!kC2) o = wave_sum(r_cur * uj * k_cur) * v_cur;
+        }
+        order();
 
 #pragma unroll
-        for (int i4 = 0; i4 < N; i4 += 4) {
-            const float4 r4 = *reinterpret_cast<const float4*>(&s_r[i4]);
-            const float4 k4 = *reinterpret_cast<const float4*>(&s_k[i4]);
-            const float4 w4 = *reinterpret_cast<const float4*>(&s_w[i4]);
+        for (int i4 = 0; i4 < kRows; i4 += 4) {
+            const float4 r4 = *reinterpret_cast<const float4*>(&s_r[q * kRows + i4]);
+            const float4 k4 = *reinterpret_cast<const float4*>(&s_k[q * kRows + i4]);
+            const float4 w4 = *reinterpret_cast<const float4*>(&s_w[q * kRows + i4]);
             o = fmaf(r4.x, S[i4 + 0], o);
             S[i4 + 0] = fmaf(w4.x, S[i4 + 0], k4.x * v_cur);
             o = fmaf(r4.y, S[i4 + 1], o);
@@ -141,6 +164,12 @@ __global__ __launch_bounds__(64) void recurrent_kernel(Args a) {
             S[i4 + 2] = fmaf(w4.z, S[i4 + 2], k4.z * v_cur);
             o = fmaf(r4.w, S[i4 + 3], o);
             S[i4 + 3] = fmaf(w4.w, S[i4 + 3], k4.w * v_cur);
+        }
+        if constexpr (kWaves > 1) {
+            s_out[t & 1][q][j] = o;
+            __syncthreads();
+            if (q != 0) continue;
+            o = (o + s_out[t & 1][1][j]) + (s_out[t & 1][2][j] + s_out[t & 1][3][j]);
         }
         if constexpr (kOutBf16)
             static_cast<unsigned short*>(a.out)[idx_cur] =
@@ -157,9 +186,9 @@ __global__ __launch_bounds__(64) void recurrent_kernel(Args a) {
     }
 
     if (a.state_out) {
-        float* so = a.state_out + static_cast<long long>(unit) * N * N;
+        float* so = a.state_out + static_cast<long long>(unit) * N * N + q * kRows * N;
 #pragma unroll
-        for (int i = 0; i < N; ++i) __builtin_nontemporal_store(S[i], &so[i * N + j]);
+        for (int i = 0; i < kRows; ++i) __builtin_nontemporal_store(S[i], &so[i * N + j]);
     }
 }
 
@@ -503,11 +532,27 @@ constexpr int kWideMinTokens = 16;
 hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStream_t stream) {
     const dim3 grid(static_cast<unsigned>(a.B) * static_cast<unsigned>(a.H));
     const bool c2 = a.finch_c2;
+    // Four waves a unit or one.  Four hold a quarter of the state and of a token's work each, so that few units keep more of the chip busy;
+    // one needs no exchange.  One -> four, us: decode 1024 units 6.3 -> 5.9, with up to 512 4.7 -> 4.6; appends 32 units x 6 tokens 7.6 -> 5.2,
+    // 256 x 4 6.2 -> 4.6, 1024 x 6 11.8 -> 9.4, 1536 x 2 9.8 -> 8.2; fp32 32 units x 12 tokens 14.5 -> 10.1; with fused logits 768 units x 1 in a
+    // layer 29.6 -> 28.0, 2048 x 2 42.7 -> 38.0.  With 1025 to 2500 units eight workgroups of four waves do not fit a compute unit beside one
+    // another: decode 1280 7.1 -> 7.8, 1792 9.1 -> 11.1, 2048 11.8 -> 12.5.  From there on a step streams the states at the memory's rate, and the
+    // shorter waves keep it busier: 2560 15.4 -> 15.2, 8192 46.1 -> 43.7, 32 768 177 -> 170; longer appends, whose waves wait for one another
+    // at every token, lose: 2048 x 2 11.8 -> 13.4, 3200 x 3 18.8 -> 21.8, 8192 x 6 54 -> 60.
+    const long long units = grid.x;
+    auto shared_work = [&] {
+        const long long cus = compute_units();
+        return units <= 4 * cus || (a.y ? units <= 8 * cus : a.T > 1 ? units <= 6 * cus : units >= 10 * cus);
+    };
+    const bool four = units <= 64 || (fits_a_launch(units, 256) && shared_work());
+    auto step = [&](auto one_wave, auto four_waves) {
+        hipLaunchKernelGGL(four ? four_waves : one_wave, grid, dim3(four ? 256 : 64), 0, stream, a);
+    };
     if (a.y) {                                 // fused decay path: bf16 in and out
         if (c2)
-            hipLaunchKernelGGL((recurrent_kernel<true, true, true, true>), grid, dim3(64), 0, stream, a);
+            step(&recurrent_kernel<true, true, true, true, 1>, &recurrent_kernel<true, true, true, true, 4>);
         else
-            hipLaunchKernelGGL((recurrent_kernel<true, true, false, true>), grid, dim3(64), 0, stream, a);
+            step(&recurrent_kernel<true, true, false, true, 1>, &recurrent_kernel<true, true, false, true, 4>);
         return hipGetLastError();
     }
     if (a.T >= kWideMinTokens && !c2 && !out_bf16) {
@@ -518,7 +563,6 @@ hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStrea
         // Short sequences, four waves -> here: 32 units x 16 tokens 6.7 -> 5.6, 128 x 17 8.5 -> 7.5; eight columns (blocks of 8
         // tokens) 256 units x 16 7.8 -> 7.2, x 17 9.0 -> 9.4, x 18 9.2 -> 9.4, x 20 9.7 -> 9.5 to 10.0, x 22 10.1 -> 9.7, x 33 13.9 -> 13.7,
         // 192 x 17 8.8 -> 9.0, x 18 9.0 -> 9.0: a third block for a few tokens is what loses.
-        const long long units = grid.x;
         auto columns = [&](auto bf16) {
             constexpr bool kIn = decltype(bf16)::value;
             if (units <= 32)
@@ -542,15 +586,15 @@ hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStrea
         return hipGetLastError();
     }
     if (!in_bf16)
-        hipLaunchKernelGGL((recurrent_kernel<false, false, false, false>), grid, dim3(64), 0, stream, a);
+        step(&recurrent_kernel<false, false, false, false, 1>, &recurrent_kernel<false, false, false, false, 4>);
     else if (!out_bf16 && !c2)
-        hipLaunchKernelGGL((recurrent_kernel<true, false, false, false>), grid, dim3(64), 0, stream, a);
+        step(&recurrent_kernel<true, false, false, false, 1>, &recurrent_kernel<true, false, false, false, 4>);
     else if (!out_bf16 && c2)
-        hipLaunchKernelGGL((recurrent_kernel<true, false, true, false>), grid, dim3(64), 0, stream, a);
+        step(&recurrent_kernel<true, false, true, false, 1>, &recurrent_kernel<true, false, true, false, 4>);
     else if (!c2)
-        hipLaunchKernelGGL((recurrent_kernel<true, true, false, false>), grid, dim3(64), 0, stream, a);
+        step(&recurrent_kernel<true, true, false, false, 1>, &recurrent_kernel<true, true, false, false, 4>);
     else
-        hipLaunchKernelGGL((recurrent_kernel<true, true, true, false>), grid, dim3(64), 0, stream, a);
+        step(&recurrent_kernel<true, true, true, false, 1>, &recurrent_kernel<true, true, true, false, 4>);
     return hipGetLastError();
 }
 

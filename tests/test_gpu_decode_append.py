@@ -112,3 +112,31 @@ def test_decode_requires_a_state(gpu_device):
     with pytest.raises(wkv.Wkv6Error) as e:
         wkv.wkv6_decode_bf16(2, 3, 64, z, z, z, z, u, None, z.clone())
     assert e.value.status == 1
+
+
+@pytest.mark.parametrize("c2", [False, True])
+@pytest.mark.parametrize("B,T,H", [(33, 1, 32), (79, 1, 32), (81, 1, 32), (48, 2, 32), (49, 2, 32), (50, 6, 32), (3, 5, 12)])
+def test_both_forms_of_a_unit_agree(gpu_device, c2, B, T, H):
+    """One wave or four a unit, by the number of units and tokens, against calls of two sequences (four): states take the same operations, bit for
+    bit; a read-out's 64 fp32 products are summed in another order (64 x 2^-24 of their magnitudes) before its rounding to bf16."""
+    g = torch.Generator(device="cuda").manual_seed(B + T)
+    r, k, v, up = ((torch.randn((B, T, H, 64), generator=g, device="cuda") / 8).to(torch.bfloat16) for _ in range(4))
+    x = (torch.rand((B, T, H, 64), generator=g, device="cuda") * 7 - 6).to(torch.bfloat16)
+    extra = up if c2 else torch.randn((H, 64), generator=g, device="cuda") / 2
+    state = torch.randn((B, H, 64, 64), generator=g, device="cuda") / 10
+    entry = wkv.wkv6_finch_c2_append_bf16 if c2 else wkv.wkv6_append_bf16
+
+    def call(sl):
+        n = len(range(*sl.indices(B)))
+        out = torch.full((n, T, H, 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+        s = torch.full((n, H, 64, 64), float("nan"), device="cuda")
+        entry(n, T, H, 64, r[sl], k[sl], v[sl], x[sl], up[sl] if c2 else extra, state[sl], out, s)
+        torch.cuda.synchronize()
+        return out, s
+
+    whole, s_whole = call(slice(0, B))
+    for b in range(0, B, 2):
+        part, s_part = call(slice(b, b + 2))
+        assert torch.equal(s_whole[b:b + 2], s_part), b
+        diff = (whole[b:b + 2].double() - part.double()).abs()
+        assert (diff <= 2.0 ** -7 * part.double().abs() + 1e-5).all(), b
