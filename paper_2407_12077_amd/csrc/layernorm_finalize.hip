@@ -2,74 +2,84 @@
 // the per-head partial moments the prefill kernel emits next to its output.
 //
 // Each (batch, head, token) contributes the sum s of its N values and the squared deviations m2
-// from its own mean.  Groups of values combine exactly (Chan, Golub, LeVeque): with counts n_a,
-// n_b, means mu_a, mu_b:  M2 = M2_a + M2_b + (mu_b - mu_a)^2 n_a n_b / (n_a + n_b).  A workgroup
-// takes 64 consecutive tokens of one batch; each of its four waves folds every fourth head (a
-// lane per token, so every read is a contiguous run of 8-byte pairs), then the first wave
-// combines the four partial results.
+// from its own mean.  With the mean mu of the token known from the sums, the heads' deviations about it add up without
+// cancellation: M2 = sum of m2_h + N (s_h / N - mu)^2 (Chan, Golub, LeVeque).  A workgroup
+// takes 64 consecutive tokens of one batch; each of its four waves has every fourth head (a
+// lane per token, so every read is a contiguous run of 8-byte pairs); sums and then deviations meet in LDS.  Bound by latency: the
+// first 16 to 64 of a wave's heads stay in registers, all asked for at once, and no step divides.  Folding the pairs one after the
+// other, with two divisions each, the calls of a layer took 156.4 us where they take 153.9 (8 x 2048 tokens x 32 heads) and 27.8 where they
+// take 26.9 (24 x 1), alone 4 x 3000 x 64 3.8 against 3.4.
 #include "wkv6_launch.h"
 
 namespace wkv6 {
 namespace {
 
-struct Group {
-    float count, mean, m2;
-};
+constexpr float kInvN = 1.f / kHeadSize;
 
-__device__ __forceinline__ Group combine(const Group& a, const Group& b) {
-    if (b.count == 0.f) return a;
-    const float total = a.count + b.count;
-    const float delta = b.mean - a.mean;
-    return Group{total, fmaf(delta, b.count / total, a.mean),
-                 a.m2 + b.m2 + delta * delta * (a.count * b.count / total)};
+// deviations of a head's values about the token's mean
+__device__ __forceinline__ float deviations(const float2 p, float mean) {
+    const float d = fmaf(p.x, kInvN, -mean);
+    return fmaf(d * kHeadSize, d, p.y);
 }
 
+// kKept: heads of a wave in registers; 16 up to 64 heads, 32 up to 128, 64 above (2 x 300 tokens x 100 heads with 16 4.15 us, with 32 3.4; one
+// pair after the other 3.9; 250 heads with 32 8.0, one after the other 6.7)
+template <int kKept>
 __global__ __launch_bounds__(256) void layernorm_finalize_kernel(int T, int H, const float2* moments, float eps,
                                                                  float2* mean_rstd) {
-    __shared__ Group part[3][64];
+    __shared__ float part[2][4][64];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int t = blockIdx.x * 64 + lane;
     const int b = blockIdx.y;
-    Group g{0.f, 0.f, 0.f};
-    if (t < T) {
-        const float2* src = moments + static_cast<long long>(b) * H * T + t;
-#pragma unroll 4
-        for (int h = wave; h < H; h += 4) {
-            const float2 p = src[static_cast<long long>(h) * T];
-            g = combine(g, Group{static_cast<float>(kHeadSize), p.x * (1.f / kHeadSize), p.y});
-        }
-    }
-    if (wave > 0) part[wave - 1][lane] = g;
+    const float2* src = moments + static_cast<long long>(b) * H * T + (t < T ? t : T - 1);
+    float2 kept[kKept];
+    float sums[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < kKept; ++i) kept[i] = wave + 4 * i < H ? src[static_cast<long long>(wave + 4 * i) * T] : make_float2(0.f, 0.f);
+#pragma unroll
+    for (int i = 0; i < kKept; ++i) sums[i % 4] += kept[i].x;
+#pragma unroll 8
+    for (int h = wave + 4 * kKept; h < H; h += 4) sums[0] += src[static_cast<long long>(h) * T].x;
+    part[0][wave][lane] = (sums[0] + sums[1]) + (sums[2] + sums[3]);
+    __syncthreads();
+    const float count = static_cast<float>(H) * kHeadSize;
+    const float mean = ((part[0][0][lane] + part[0][1][lane]) + (part[0][2][lane] + part[0][3][lane])) / count;
+    float m2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < kKept; ++i)
+        if (wave + 4 * i < H) m2 += deviations(kept[i], mean);
+#pragma unroll 8
+    for (int h = wave + 4 * kKept; h < H; h += 4) m2 += deviations(src[static_cast<long long>(h) * T], mean);
+    part[1][wave][lane] = m2;
     __syncthreads();
     if (wave == 0 && t < T) {
-#pragma unroll
-        for (int w = 0; w < 3; ++w) g = combine(g, part[w][lane]);
-        mean_rstd[static_cast<long long>(b) * T + t] = make_float2(g.mean, 1.f / sqrtf(g.m2 / g.count + eps));
+        m2 = (part[1][0][lane] + part[1][1][lane]) + (part[1][2][lane] + part[1][3][lane]);
+        mean_rstd[static_cast<long long>(b) * T + t] = make_float2(mean, 1.f / sqrtf(m2 / count + eps));
     }
 }
 
 // Sequences of a few tokens: a wave per token with the heads on its lanes, since a lane per token would leave
-// most lanes without one.  Partial results meet in pairs over the lanes (the order of the fold is free).
+// most lanes without one.  Partial results meet in pairs over the lanes.
 __global__ __launch_bounds__(256) void layernorm_finalize_few_kernel(long long tokens, int T, int H, const float2* moments,
                                                                      float eps, float2* mean_rstd) {
     const int lane = threadIdx.x & 63;
     const long long token = static_cast<long long>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (token >= tokens) return;
-    const long long b = token / T;
-    const float2* src = moments + b * H * T + (token - b * T);
-    Group g{0.f, 0.f, 0.f};
-    for (int h = lane; h < H; h += 64) {
-        const float2 p = src[static_cast<long long>(h) * T];
-        g = combine(g, Group{static_cast<float>(kHeadSize), p.x * (1.f / kHeadSize), p.y});
-    }
+    // (fewer than 2^32 tokens: a token has at least 8 bytes of partials and 128 of values)
+    const unsigned b = static_cast<unsigned>(token) / static_cast<unsigned>(T);
+    const float2* src = moments + static_cast<long long>(b) * H * T + (token - static_cast<long long>(b) * T);
+    const float2 mine = lane < H ? src[static_cast<long long>(lane) * T] : make_float2(0.f, 0.f);
+    float sum = mine.x;
+    for (int h = lane + 64; h < H; h += 64) sum += src[static_cast<long long>(h) * T].x;
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        const Group other{__shfl_xor(g.count, m, 64), __shfl_xor(g.mean, m, 64), __shfl_xor(g.m2, m, 64)};
-        // the same order of the pair on both sides, so that every lane ends with the same values
-        g = lane & m ? combine(other, g) : combine(g, other);
-    }
-    if (lane == 0) mean_rstd[token] = make_float2(g.mean, 1.f / sqrtf(g.m2 / g.count + eps));
+    for (int m = 32; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, 64);
+    const float count = static_cast<float>(H) * kHeadSize, mean = sum / count;
+    float m2 = lane < H ? deviations(mine, mean) : 0.f;
+    for (int h = lane + 64; h < H; h += 64) m2 += deviations(src[static_cast<long long>(h) * T], mean);
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) m2 += __shfl_xor(m2, m, 64);
+    if (lane == 0) mean_rstd[token] = make_float2(mean, 1.f / sqrtf(m2 / count + eps));
 }
 
 // The normalisation itself, for callers whose projection GEMM has no row-scaling epilogue:
@@ -236,7 +246,7 @@ hipError_t launch_layernorm_finalize(int B, int T, int H, const float* moments, 
         return hipGetLastError();
     }
     const dim3 grid(static_cast<unsigned>((T + 63) / 64), static_cast<unsigned>(B));
-    hipLaunchKernelGGL(layernorm_finalize_kernel, grid, dim3(256), 0, stream, T, H,
+    hipLaunchKernelGGL(H <= 64 ? &layernorm_finalize_kernel<16> : H <= 128 ? &layernorm_finalize_kernel<32> : &layernorm_finalize_kernel<64>, grid, dim3(256), 0, stream, T, H,
                        reinterpret_cast<const float2*>(moments), eps, reinterpret_cast<float2*>(mean_rstd));
     return hipGetLastError();
 }
