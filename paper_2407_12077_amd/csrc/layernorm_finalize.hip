@@ -23,7 +23,7 @@ __device__ __forceinline__ float deviations(const float2 p, float mean) {
 }
 
 // kKept: heads of a wave in registers; 16 up to 64 heads, 32 up to 128, 64 above (2 x 300 tokens x 100 heads with 16 4.15 us, with 32 3.4; one
-// pair after the other 3.9; 250 heads with 32 8.0, one after the other 6.7)
+// pair after the other 3.9; 250 heads with 32 8.0, with 64 4.8, one after the other 6.7)
 template <int kKept>
 __global__ __launch_bounds__(256) void layernorm_finalize_kernel(int T, int H, const float2* moments, float eps,
                                                                  float2* mean_rstd) {
