@@ -532,17 +532,26 @@ constexpr int kWideMinTokens = 16;
 hipError_t launch_recurrent(const Args& a, bool in_bf16, bool out_bf16, hipStream_t stream) {
     const dim3 grid(static_cast<unsigned>(a.B) * static_cast<unsigned>(a.H));
     const bool c2 = a.finch_c2;
-    // Four waves a unit or one.  Four hold a quarter of the state and of a token's work each, so that few units keep more of the chip busy;
-    // one needs no exchange.  One -> four, us: decode 1024 units 6.3 -> 5.9, with up to 512 4.7 -> 4.6; appends 32 units x 6 tokens 7.6 -> 5.2,
-    // 256 x 4 6.2 -> 4.6, 1024 x 6 11.8 -> 9.4, 1536 x 2 9.8 -> 8.2; fp32 32 units x 12 tokens 14.5 -> 10.1; with fused logits 768 units x 1 in a
-    // layer 29.6 -> 28.0, 2048 x 2 42.7 -> 38.0.  With 1025 to 2500 units eight workgroups of four waves do not fit a compute unit beside one
-    // another: decode 1280 7.1 -> 7.8, 1792 9.1 -> 11.1, 2048 11.8 -> 12.5.  From there on a step streams the states at the memory's rate, and the
-    // shorter waves keep it busier: 2560 15.4 -> 15.2, 8192 46.1 -> 43.7, 32 768 177 -> 170; longer appends, whose waves wait for one another
-    // at every token, lose: 2048 x 2 11.8 -> 13.4, 3200 x 3 18.8 -> 21.8, 8192 x 6 54 -> 60.
+    // Four waves a unit or one.  Four hold a quarter of the state and of a token's work each, so that few units keep more of
+    // the chip busy; one needs no exchange.  One -> four, us, the same tensors again and again:
+    // decode: 1024 units 5.7 -> 5.4.  With 1025 to 2500 units eight workgroups of four waves do not fit a compute unit beside
+    // one another: 1536 7.0 -> 8.4, 2048 8.9 -> 11.4.  From there on a step streams the states at the memory's rate, and the
+    // shorter waves keep it busier: with states that no cache holds 2560 15.9 -> 15.6, 3200 19.7 -> 19.1, 8192 46.7 -> 44.2,
+    // 32 768 177 -> 170 (2560 units whose 42 MB stay in the memory-side cache lose, 13.5 -> 13.8).
+    // Appends: 256 units x 6 tokens 8.6 -> 7.2, 1024 x 6 11.5 -> 9.7, 1056 x 4 9.4 -> 8.9, 1280 x 3 9.0 -> 8.6, 1536 x 2 9.1 -> 8.1,
+    // x 6 13.4 -> 11.9; fp32 32 units x 12 tokens 14.6 -> 10.2, 1536 x 15 26.1 -> 24.2.  With more units than six a compute
+    // unit the waves wait for one another at every token in a second round: 1600 x 2 9.3 -> 11.1, x 6 13.8 -> 16.7; 2560 x 3
+    // 13.8 -> 16.1; fp32 1568 x 12 21.9 -> 26.2.
+    // Fused logits, Finch-C2 (with one wave its registers leave four units a compute unit): 1024 units x 1 token 7.8 -> 6.6,
+    // 1056 x 2 14.2 -> 10.7, 2048 x 1 14.7 -> 13.4, x 2 18.5 -> 14.0.  Finch (eight units of one wave, five of four): 1024 x 1
+    // 7.2 -> 6.2, x 4 11.4 -> 9.2, 1280 x 2 9.5 -> 8.1, x 4 12.3 -> 10.6; but 1056 x 1 7.3 -> 7.6, 1408 x 2 10.2 -> 11.4, 1536 x 4
+    // 13.4 -> 15.8, 2048 x 1 10.4 -> 13.2, x 4 15.6 -> 17.8.
     const long long units = grid.x;
     auto shared_work = [&] {
         const long long cus = compute_units();
-        return units <= 4 * cus || (a.y ? units <= 8 * cus : a.T > 1 ? units <= 6 * cus : units >= 10 * cus);
+        if (units <= 4 * cus) return true;
+        if (a.y) return units <= (c2 ? 8 : a.T > 1 ? 5 : 4) * cus;
+        return a.T > 1 ? units <= 6 * cus : units >= 10 * cus;
     };
     const bool four = units <= 64 || (fits_a_launch(units, 256) && shared_work());
     auto step = [&](auto one_wave, auto four_waves) {
