@@ -245,3 +245,9 @@ def test_few_tokens_on_both_sides_of_the_kernel_switch(gpu_device, B, T, H):
     delta = TOL_BF16 * np.abs(o_ref).max()
     assert np.abs(mom[..., 0] - sum_ref).max() <= 64 * delta
     assert (np.abs(mom[..., 1] - m2_ref) <= 4 * delta * np.sqrt(64 * m2_ref) + 4 * 64 * delta ** 2).all()
+
+
+@pytest.mark.parametrize("B,T,H", [(32, 1, 32), (33, 1, 32), (64, 1, 32), (65, 1, 32), (64, 2, 32), (65, 2, 32), (40, 4, 32), (41, 4, 32), (65, 4, 32)])
+def test_one_and_four_waves_a_unit(gpu_device, B, T, H):
+    """Both sides of the lines between one wave a unit and four (Finch 1024 units for one token, 1280 for several; Finch-C2 2048)."""
+    test_few_tokens_on_both_sides_of_the_kernel_switch(gpu_device, B, T, H)

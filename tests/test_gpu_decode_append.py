@@ -9,7 +9,7 @@ import paper_2407_12077_amd as wkv
 from oracle import finch_c2_oracle, wkv6_oracle
 from paper_2407_12077_amd.workloads import CONFIGS, make_inputs, make_uprime, round_to_bf16, scaled
 
-from gpu_util import BF16_OUT_ROUNDING, TOL_BF16, max_norm_err, to_dev
+from gpu_util import BF16_OUT_ROUNDING, TOL_BF16, TOL_F32, max_norm_err, run_entry, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -140,3 +140,12 @@ def test_both_forms_of_a_unit_agree(gpu_device, c2, B, T, H):
         assert torch.equal(s_whole[b:b + 2], s_part), b
         diff = (whole[b:b + 2].double() - part.double()).abs()
         assert (diff <= 2.0 ** -7 * part.double().abs() + 1e-5).all(), b
+
+
+@pytest.mark.parametrize("B,T,H", [(48, 3, 32), (49, 3, 32), (48, 15, 32), (49, 15, 32), (131, 7, 12), (33, 1, 32)])
+def test_fp32_one_and_four_waves_a_unit(gpu_device, B, T, H):
+    """Both sides of the line (1536 units), every unit against the oracle at the bar of fp32 tensors."""
+    inp = make_inputs(scaled(CONFIGS[4], B=B, T=T, H=H), seed=B + T)
+    o_ref, s_ref = wkv6_oracle(**inp)
+    o, s = run_entry("wkv6_prefill_f32", inp, in_dtype=torch.float32)
+    assert max_norm_err(o, o_ref) <= TOL_F32 and max_norm_err(s, s_ref) <= TOL_F32
