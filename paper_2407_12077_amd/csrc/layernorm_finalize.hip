@@ -5,10 +5,10 @@
 // from its own mean.  With the mean mu of the token known from the sums, the heads' deviations about it add up without
 // cancellation: M2 = sum of m2_h + N (s_h / N - mu)^2 (Chan, Golub, LeVeque).  A workgroup
 // takes 64 consecutive tokens of one batch; each of its four waves has every fourth head (a
-// lane per token, so every read is a contiguous run of 8-byte pairs); sums and then deviations meet in LDS.  Bound by latency: the
-// first 16 to 64 of a wave's heads stay in registers, all asked for at once, and no step divides.  Folding the pairs one after the
-// other, with two divisions each, the calls of a layer took 156.4 us where they take 153.9 (8 x 2048 tokens x 32 heads) and 27.8 where they
-// take 26.9 (24 x 1), alone 4 x 3000 x 64 3.8 against 3.4.
+// lane per token, so every read is a contiguous run of 8-byte pairs); sums and then deviations meet in LDS.  Bound by latency: up to 256
+// heads stay in registers, all requested at once, and no step divides.  Folding the pairs one after the other, with two divisions
+// each, the calls of a layer took 156.4 us where they took 153.9 with this (8 x 2048 tokens x 32 heads) and 27.8 where they took 26.9
+// (24 x 1).
 #include "wkv6_launch.h"
 
 namespace wkv6 {
@@ -22,9 +22,10 @@ __device__ __forceinline__ float deviations(const float2 p, float mean) {
     return fmaf(d * kHeadSize, d, p.y);
 }
 
-// kKept: heads of a wave in registers; 16 up to 64 heads, 32 up to 128, 64 above (2 x 300 tokens x 100 heads with 16 4.15 us, with 32 3.4; one
-// pair after the other 3.9; 250 heads with 32 8.0, with 64 4.8, one after the other 6.7)
-template <int kKept>
+// kKept: heads of a wave in registers, all requested before the first is used.  As few as hold all heads (the rule is at the launch),
+// since a place without a head costs its instructions all the same: 8 x 2048 tokens x 8 heads 1.97 us with 4, 2.35 with 16; x 32 heads 2.37
+// with 16, 3.01 with 32; x 130 heads 3.34 with 40, 4.77 with 64.  kRest: there are more heads, which are read twice.
+template <int kKept, bool kRest>
 __global__ __launch_bounds__(256) void layernorm_finalize_kernel(int T, int H, const float2* moments, float eps,
                                                                  float2* mean_rstd) {
     __shared__ float part[2][4][64];
@@ -39,8 +40,10 @@ __global__ __launch_bounds__(256) void layernorm_finalize_kernel(int T, int H, c
     for (int i = 0; i < kKept; ++i) kept[i] = wave + 4 * i < H ? src[static_cast<long long>(wave + 4 * i) * T] : make_float2(0.f, 0.f);
 #pragma unroll
     for (int i = 0; i < kKept; ++i) sums[i % 4] += kept[i].x;
+    if constexpr (kRest) {
 #pragma unroll 8
-    for (int h = wave + 4 * kKept; h < H; h += 4) sums[0] += src[static_cast<long long>(h) * T].x;
+        for (int h = wave + 4 * kKept; h < H; h += 4) sums[0] += src[static_cast<long long>(h) * T].x;
+    }
     part[0][wave][lane] = (sums[0] + sums[1]) + (sums[2] + sums[3]);
     __syncthreads();
     const float count = static_cast<float>(H) * kHeadSize;
@@ -49,8 +52,10 @@ __global__ __launch_bounds__(256) void layernorm_finalize_kernel(int T, int H, c
 #pragma unroll
     for (int i = 0; i < kKept; ++i)
         if (wave + 4 * i < H) m2 += deviations(kept[i], mean);
+    if constexpr (kRest) {
 #pragma unroll 8
-    for (int h = wave + 4 * kKept; h < H; h += 4) m2 += deviations(src[static_cast<long long>(h) * T], mean);
+        for (int h = wave + 4 * kKept; h < H; h += 4) m2 += deviations(src[static_cast<long long>(h) * T], mean);
+    }
     part[1][wave][lane] = m2;
     __syncthreads();
     if (wave == 0 && t < T) {
@@ -246,8 +251,18 @@ hipError_t launch_layernorm_finalize(int B, int T, int H, const float* moments, 
         return hipGetLastError();
     }
     const dim3 grid(static_cast<unsigned>((T + 63) / 64), static_cast<unsigned>(B));
-    hipLaunchKernelGGL(H <= 64 ? &layernorm_finalize_kernel<16> : H <= 128 ? &layernorm_finalize_kernel<32> : &layernorm_finalize_kernel<64>, grid, dim3(256), 0, stream, T, H,
-                       reinterpret_cast<const float2*>(moments), eps, reinterpret_cast<float2*>(mean_rstd));
+    // Pairs folded one after the other (before) : here, us inside a graph: 8 x 2048 tokens x 8 heads 2.24 : 1.97, x 32 2.64 : 2.37, x 130
+    // 4.60 : 3.34, x 256 7.40 : 5.15, x 300 10.4 : 10.4 (with 64 places 11.4); 32 x 4096 x 2 heads 2.52 : 2.51, x 8 3.39 : 2.63, and
+    // of one head, with nothing to fold, 2.30 : 2.51.
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, T, H, reinterpret_cast<const float2*>(moments), eps, reinterpret_cast<float2*>(mean_rstd));
+    };
+    if (H <= 16) go(&layernorm_finalize_kernel<4, false>);
+    else if (H <= 64) go(&layernorm_finalize_kernel<16, false>);
+    else if (H <= 128) go(&layernorm_finalize_kernel<32, false>);
+    else if (H <= 160) go(&layernorm_finalize_kernel<40, false>);
+    else if (H <= 256) go(&layernorm_finalize_kernel<64, false>);
+    else go(&layernorm_finalize_kernel<40, true>);
     return hipGetLastError();
 }
 
