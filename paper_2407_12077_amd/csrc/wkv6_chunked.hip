@@ -940,12 +940,14 @@ hipError_t raise_mode_limits() {
 // bytes, gain there too: 341 -> 323, Finch 64 x 2500 755 -> 727); Finch, bf16 out, from 1 GiB on, which the kernel's own cycles bound (64 x 1000 x
 // 32 255 -> 257, 12 x 12 000 x 32 698 -> 700); calls that the memory-side cache holds for the most part, to 300 MiB in the Finch form with bf16
 // rows (10 x 412 x 64 40.4 -> 41.0, 20 x 700 x 16 44.7 -> 45.1; at 306 MiB 24 x 600 x 32 65.5 -> 62.9), to 150 MiB in the others (20 x 60 x
-// 32 13.6 -> 13.8, 9 x 500 x 32 39.4 -> 39.9; at 213 10 x 412 x 64 49.8 -> 49.2, fp32 out 20 x 300 x 32 36.8 -> 35.3); fewer units than one and a
-// half rounds, most of whose workgroups have one (9 x 1500 x 32 85.2 -> 85.9); and fused logits, whose consumers hold their head's slice of B in
-// registers.
+// 32 13.6 -> 13.8, 9 x 500 x 32 39.4 -> 39.9; at 213 10 x 412 x 64 49.8 -> 49.2, fp32 out 20 x 300 x 32 36.8 -> 35.3); fewer units than one and
+// three quarters rounds, most of whose workgroups have one (bf16 rows, 256 a round: Finch-C2 384 units x 900 tokens 70.9 -> 72.3, x 6000
+// 425 -> 431, 416 x 2000 140.2 -> 141.2, 448 x 900 75.0 -> 73.5; Finch 384 x 1500 86.0 -> 86.5, 416 x 2000 113.5 -> 114.2, 448 x 2000 126 ->
+// 123; fp32 rows gain or tie from one and a half rounds on: Finch-C2 384 x 600 53.4 -> 49.7, Finch 384 x 900 60.4 -> 59.8); and fused
+// logits, whose consumers hold their head's slice of B in registers.
 template <int kMode, bool kC2>
 bool heads_in_turn(const Args& a, long long units, long long mib) {
-    if (a.H % 8 != 0 || (!kC2 && a.H > kTurnHeads) || 2 * units < 3ll * a.unit_stride) return false;
+    if (a.H % 8 != 0 || (!kC2 && a.H > kTurnHeads) || 4 * units < (kMode == 1 ? 6ll : 7ll) * a.unit_stride) return false;
     if (mib < (kMode == 1 || kC2 ? 150 : 300)) return false;
     if (kMode == 1) return true;
     const auto address_class = [](const void* p) { return reinterpret_cast<unsigned long long>(p) >> 7 & 7; };
