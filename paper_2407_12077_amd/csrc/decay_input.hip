@@ -774,23 +774,24 @@ hipError_t launch_decay_input(int B, int T, int D, const void* x, const void* x_
     // takes as long with one token as with 128 and serves one sequence, so it is the better one only when it fills the
     // chip; the split tiles take rows of any sequences, but every tile takes all weights and the launch, the two exchanges
     // and the last reduction weigh more the narrower the model is.  Nanoseconds a round, a fixed part and one per 128
-    // channels, fitted to D = 128, 256, 768, 2048, 4096: 128 tokens 6.7, 9.5, 20.3, 46.5, 89 us; split 64 rows 6.8, 8, 14.5, 30,
-    // 56, 32 rows 7.4, 8.9, 12.9, 21.6, 39, 16 rows 7.0, 7.9, 9.0, 16.5, 25.5.  128 tokens against the split: D = 2048 24 sequences of
-    // one token 45.8 : 16.6, 300 of them 90 : 16.8, 8192 tokens 46.6 : 22, 16 384 tokens 47 : 31, 33 792 tokens 94 : 86, 24 000
-    // tokens (a second round of 64 rows) 48 : 59; D = 128 one token 6.3 : 6.9, 300 sequences of one token 12.2 : 7.2, 33 792 tokens
-    // 13.0 : 20.0; D = 256 33 792 tokens 19.3 : 23.6, 1000 sequences of 20 34.7 : 36.3; D = 768 49 152 tokens 41.0 : 42.6.
-    // These were fitted with two blocks of a wave in flight in the 16- and 32-row tiles; 16 rows now take 3.7 us and 0.46 per
-    // 128 channels, 64 rows 7 % less: the line still errs towards the 128-token tiles at D = 128 and 256.
+    // channels, fitted to a full round at D = 128, 256, 768, 1024, 2048, 4096: 128 tokens 7.0, 9.6, 20.2, 25.4, 46.4, 88 us; split 64 rows
+    // 7.1, 8.3, 13.5, 16.1, 27.2, 52, 32 rows 5.1, 6.0, 9.2, 10.7, 17.4, 29 to 37, 16 rows 4.5, 5.2, 7.5, 8.3, 13.4, 22.7.  Where a line lies,
+    // measured on both sides: 128 tokens : 16 rows: D = 128 24 x 1 token 6.7 : 4.0, 1000 x 20 24.4 : 18.0, D = 256 1000 x 20 34.7 : 21.3, D =
+    // 2048 24 x 1 46 : 10.1; 16 : 32 rows: 4000 tokens 4.6 : 5.0, 8.9 : 10.4, 13.9 : 16.3 and 4200 7.4 : 5.0, 15.3 : 10.4, 24.5 : 16.3 (D = 128,
+    // 1024, 2048); 32 : 64 rows: 8192 tokens 10.7 : 15.5, 17.5 : 25.1 and 8320 19.2 : 15.6, 30.7 : 25.1 (1024, 2048); 128 tokens : 32 rows:
+    // 1000 x 40 24.9 : 20.2 (128), 35.2 : 24.5 (256), 500 x 50 13.3 : 16.3 (128), 28.9 : 26.1 (512, the rule errs), 39.1 : 32.7 (768), 49.6 : 38.9
+    // (1024); 128 tokens : 64 rows: 16 384 tokens 7.4 : 7.1 (128, the rule errs), 10.0 : 8.3 (256), 46.7 : 27.2 (2048); 20 000 26.0 : 30.1 (1024),
+    // 47 : 50 (2048), 33 792 13.9 : 18.4 (128), 19.4 : 21.7 (256), 40.1 : 39.1 (768, the rule errs), 50.4 : 46.8 (1024), 92.6 : 76.5 (2048).
     const long long cus = compute_units(), rows = static_cast<long long>(B) * T, blocks = D / 128;
     auto rounds = [&](long long groups) { return (groups + cus - 1) / cus; };
     const long long whole = (4300 + 2640 * blocks) * rounds(static_cast<long long>(B) * a.tiles_per_seq);
-    const long long r64 = T >= 64 ? (5500 + 1550 * blocks) * rounds((rows + 63) / 64) : whole;
-    const long long r32 = T >= 32 ? (6500 + 1000 * blocks) * rounds((rows + 31) / 32) : whole;
-    const long long r16 = (6600 + 590 * blocks) * rounds((rows + 15) / 16);
+    const long long r64 = T >= 64 ? (5600 + 1360 * blocks) * rounds((rows + 63) / 64) : whole;
+    const long long r32 = T >= 32 ? (4400 + 810 * blocks) * rounds((rows + 31) / 32) : whole;
+    const long long r16 = (3900 + 585 * blocks) * rounds((rows + 15) / 16);
     if (r16 < whole && r16 <= r32 && r16 <= r64) {
-        // A tile's outputs over four or two workgroups while these still fit the chip once.  One, two, four of them (with two
-        // blocks of a wave in flight, 2 us more than now): D = 2048, 24 tokens 16.7, 14.9, 14.0 us; 1024 tokens 16.5, 14.7, 14.6; 2048
-        // tokens 16.9, 15.6, 26.4 (a second round); D = 128, 300 tokens 7.2, 6.6, 6.3; D = 768, 24 tokens 9.0, 8.2, 7.8; D = 4096 28.4, 22.7, 21.3.
+        // A tile's outputs over four or two workgroups while these still fit the chip once.  One, two, four of them, us: D = 128, 256
+        // x 1 token 4.4, 4.2, 4.1; D = 768, 24 x 1 7.1, 6.5, 6.3; D = 2048, 24 x 1 12.1, 10.7, 10.1; 1000 tokens 12.0, 10.7, 10.8; 2000 12.2,
+        // 11.2; 4000 13.4, 20.6 (a second round); D = 4096, 24 x 1 19.2, 16.9, 15.8.
         const long long tiles = (rows + 15) / 16;
         if (4 * tiles <= cus) return out_f32 ? launch_split<1, 12, true, 4>(a, stream) : launch_split<1, 12, false, 4>(a, stream);
         if (2 * tiles <= cus) return out_f32 ? launch_split<1, 12, true, 2>(a, stream) : launch_split<1, 12, false, 2>(a, stream);

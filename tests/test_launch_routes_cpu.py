@@ -67,15 +67,18 @@ def test_normalised_rows_written_through_only_while_that_is_faster(fake, tokens,
 
 
 @pytest.mark.parametrize("B,T,D,kernel", [
-    (1, 1, 128, "decay_input_kernel<"), (24, 1, 128, "decay_input_kernel<"), (300, 1, 128, "split_kernel<1, 12,"), (16, 1024, 128, "decay_input_kernel<"),
-    (33, 1024, 128, "decay_input_kernel<"), (1000, 20, 128, "decay_input_kernel<"), (1000, 40, 256, "decay_input_kernel<"), (33, 1024, 256, "decay_input_kernel<"),
+    (1, 1, 128, "split_kernel<1, 12,"), (24, 1, 128, "split_kernel<1, 12,"), (300, 1, 128, "split_kernel<1, 12,"), (16, 1024, 128, "decay_input_kernel<"),
+    (33, 1024, 128, "decay_input_kernel<"), (1000, 20, 128, "split_kernel<1, 12,"), (1000, 40, 256, "split_kernel<2, 8,"), (33, 1024, 256, "decay_input_kernel<"),
     (24, 1, 256, "split_kernel<1, 12,"), (300, 129, 256, "split_kernel<4, 8,"), (33, 1024, 768, "decay_input_kernel<"), (16, 1024, 768, "split_kernel<4, 8,"),
     (24, 1, 2048, "split_kernel<1, 12,"), (8, 1000, 2048, "split_kernel<2, 8,"), (16, 1024, 2048, "split_kernel<4, 8,"), (24, 1000, 2048, "decay_input_kernel<"),
     (33, 1024, 2048, "split_kernel<4, 8,"), (33, 1024, 4096, "split_kernel<4, 8,"), (32, 1024, 2048, "decay_input_kernel<"),
     (130, 31, 256, "split_kernel<1, 12,"), (131, 33, 256, "split_kernel<2, 8,"), (256, 32, 256, "split_kernel<2, 8,"), (2, 4097, 256, "split_kernel<4, 8,"),
-    (3, 5461, 256, "split_kernel<4, 8,"), (1, 16385, 256, "decay_input_kernel<"), (600, 3, 128, "split_kernel<1, 12,"), (1000, 40, 2048, "split_kernel<2, 8,")])
+    (3, 5461, 256, "split_kernel<4, 8,"), (1, 16385, 256, "decay_input_kernel<"), (600, 3, 128, "split_kernel<1, 12,"), (1000, 40, 2048, "split_kernel<2, 8,"),
+    (4, 1000, 128, "split_kernel<1, 12,"), (2, 2100, 128, "split_kernel<2, 8,"), (8, 1000, 128, "split_kernel<2, 8,"), (500, 50, 128, "decay_input_kernel<"),
+    (500, 50, 768, "split_kernel<2, 8,"), (33, 1024, 1024, "split_kernel<4, 8,"), (5, 4000, 1024, "decay_input_kernel<")])
 def test_decay_front_tiles_by_width(fake, B, T, D, kernel):
-    """What a round of each tile takes depends on the width: at D = 128, 33 x 1024 tokens in 64-row tiles took 20 us against 13."""
+    """What a round of each tile takes depends on the width: at D = 128, 33 x 1024 tokens in 64-row tiles take 18 us against 14, and one token
+    in a tile of 128 tokens 6.5 against 3.9."""
     call = ("wkv6_decay_lora_input_bf16", [B, T, D, 32, 64] + [lu.at(i) for i in range(8)] + [0, None])
     [ev] = lu.events(fake, [call])
     [launch] = [e for e in ev if e.kind == "launch"]
