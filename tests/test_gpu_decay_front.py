@@ -14,6 +14,7 @@ from oracle import decay_logits_numpy, decay_lora_input_numpy, finch_c2_oracle
 from paper_2407_12077_amd.workloads import (CONFIGS, make_decay_front_inputs, make_inputs, make_uprime, round_to_bf16,
                                             scaled)
 
+import front_shapes
 from gpu_util import BF16_OUT_ROUNDING, TOL_BF16, error_report, fmt_report, max_norm_err, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -54,7 +55,7 @@ def test_matches_oracle(gpu_device, B, T, H, with_prev):
     assert np.array_equal(y16, round_to_bf16(y32))
 
 
-# tiles of 16, 32 and 64 rows over whole and parts of sequences, fewer blocks than waves, a last tile of one row
+# tiles of 16, 32 and 64 rows over whole and parts of sequences, one block of channels a wave or fewer (two with 10 and 12 heads), a last tile of one row
 @pytest.mark.parametrize("B,T,H", [(17, 1, 6), (9, 2, 10), (33, 15, 2), (33, 16, 4), (31, 17, 12), (1, 33, 2), (131, 33, 4), (127, 65, 4), (2, 4097, 4)])
 @pytest.mark.parametrize("with_prev", [True, False])
 def test_rows_of_a_tile_and_their_predecessors(gpu_device, B, T, H, with_prev):
@@ -196,8 +197,8 @@ def test_split_contraction_tiles(gpu_device, B, T, H):
 @pytest.mark.parametrize("B,T,H", [(17, 1, 4), (300, 1, 2), (600, 3, 2), (9, 17, 4), (130, 31, 4), (131, 33, 4), (4, 1100, 4), (70, 60, 4),
                                    (256, 32, 4), (2, 4097, 4), (3, 5461, 4), (128, 127, 4), (1, 16385, 4)])
 def test_split_contraction_tiles_at_the_widths_that_take_them(gpu_device, B, T, H):
-    """The same places of a tile as above at D = 256, where 16-, 32- and 64-row tiles are taken (at D = 128 only many short
-    sequences take the split form).  Bar and rounding as above."""
+    """The same places of a tile as above at D = 256, where 16-, 32- and 64-row tiles are taken (at D = 128
+    tiles of 128 tokens are the faster ones where 64 rows would fit).  Bar and rounding as above."""
     fi = make_decay_front_inputs(scaled(CONFIGS[2], B=B, T=T, H=H), seed=1700 + T)
     for with_prev in (True, False):
         y32 = run_front(fi, torch.float32, with_prev).cpu().numpy()
@@ -213,3 +214,15 @@ def test_outputs_of_a_tile_over_several_workgroups(gpu_device, B, T, H):
     y32 = run_front(fi, torch.float32).cpu().numpy()
     assert max_norm_err(y32, oracle_front(fi)) <= TOL_BF16
     assert np.array_equal(run_front(fi, torch.bfloat16).float().cpu().numpy(), round_to_bf16(y32))
+
+
+@pytest.mark.parametrize("B,T,H", [s for shapes in front_shapes.SEVERAL_BLOCKS.values() for s in shapes] + front_shapes.WHOLE)
+def test_several_blocks_a_wave(gpu_device, B, T, H):
+    """Each tile with two to eight blocks of channels a wave, sequences that start in a tile, ragged last tiles, with and without carried rows; and
+    tiles of 128 tokens with short sequences."""
+    fi = make_decay_front_inputs(scaled(CONFIGS[2], B=B, T=T, H=H), seed=2100 + B + T)
+    for with_prev in (True, False):
+        y32 = run_front(fi, torch.float32, with_prev).cpu().numpy()
+        assert max_norm_err(y32, oracle_front(fi, with_prev)) <= TOL_BF16
+        y16 = run_front(fi, torch.bfloat16, with_prev).float().cpu().numpy()
+        assert np.array_equal(y16, round_to_bf16(y32))

@@ -3,6 +3,7 @@ point's first call whatever its size, since a later call may be captured, and ea
 pinned on both sides of its line."""
 import pytest
 
+import front_shapes
 import launch_util as lu
 from split_shapes import SPLIT, WHOLE
 
@@ -83,6 +84,15 @@ def test_decay_front_tiles_by_width(fake, B, T, D, kernel):
     [ev] = lu.events(fake, [call])
     [launch] = [e for e in ev if e.kind == "launch"]
     assert kernel in launch.kernel, launch.kernel
+
+
+@pytest.mark.parametrize("f32", [False, True])
+def test_decay_front_shapes_of_the_gpu_tests(fake, f32):
+    wanted = [(s, k % str(f32).lower()) for k, shapes in front_shapes.SEVERAL_BLOCKS.items() for s in shapes]
+    wanted += [(s, "decay_input_kernel<%s>" % str(f32).lower()) for s in front_shapes.WHOLE]
+    calls = [("wkv6_decay_lora_input_bf16", [B, T, 64 * H, 32, 64] + [lu.at(i) for i in range(8)] + [int(f32), None]) for (B, T, H), _ in wanted]
+    for (shape, kernel), ev in zip(wanted, lu.events(fake, calls)):
+        assert [e.kernel for e in ev if e.kind == "launch"] == [kernel], shape
 
 
 @pytest.mark.parametrize("B,T,D,groups", [(1, 1, 2048, 4), (24, 1, 2048, 4), (1, 1024, 2048, 4), (1025, 1, 2048, 2), (4, 512, 768, 2), (1, 2049, 2048, 1), (4, 1024, 2048, 1)])
