@@ -35,6 +35,7 @@
 // Weight layouts are the ones an MFMA operand can be read from with the contraction index
 // contiguous: A_d and A_omega column by column ([r][D]), B_d column by column ([D][r]).
 #include "wkv6_launch.h"
+#include "wkv6_lds_loads.h"
 
 namespace wkv6 {
 namespace {
@@ -436,15 +437,6 @@ struct SplitTile {
     static_assert(kLds <= 160 * 1024, "LDS budget");
 };
 
-// Loads straight into LDS are outside the compiler's view of a wave's own LDS accesses: at most `kYounger` of the wave's
-// youngest loads may still be on their way behind this, and no LDS access moves across it.
-template <int kYounger>
-__device__ __forceinline__ void wait_loads() {
-    static_assert(kYounger < 64, "vmcnt");
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt((kYounger & 15) | (kYounger >> 4) << 14 | 7 << 4 | 15 << 8);
-    __builtin_amdgcn_sched_barrier(0);
-}
 __device__ __forceinline__ void wait_lds() {             // the wave's own LDS reads and writes
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(15 | 3 << 14 | 7 << 4);

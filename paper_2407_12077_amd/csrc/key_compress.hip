@@ -27,6 +27,7 @@
 // compute unit holds one workgroup of sixteen waves, and its loaders keep four steps in flight
 // instead (in-flight bytes, not arithmetic, limit this shape).
 #include "wkv6_launch.h"
+#include "wkv6_lds_loads.h"
 
 namespace wkv6 {
 namespace {
@@ -344,21 +345,13 @@ __device__ __forceinline__ void kc_roles(const KcArgs& a, char* lds) {
 template <int kRowTile>
 struct DmaTile {
     static constexpr int kX = kRowTile * 128, kStage = kX + 64 * 256;
-    static constexpr int kStages = 3;                                       // steps in LDS: as many as fit were 5 to 10 % slower, the later the first step begins
+    static constexpr int kStages = 3;                                       // steps in LDS: as many as fit, whose first step begins later, were 5 to 10 % slower
     static constexpr int kXLoads = kRowTile / 64, kLoads = kXLoads + 2;      // of a wave and step
     static constexpr int kRB = kRowTile / 16;                               // 16-row blocks
     static constexpr int kPRow = 128 + 4;                                   // row stride (floats) of the two partial results
     static constexpr int kLds = kStages * kStage > 2 * kRowTile * kPRow * 4 ? kStages * kStage : 2 * kRowTile * kPRow * 4;
     static_assert(kLds <= 160 * 1024 && kLoads * (kStages - 2) < 64, "LDS budget, vmcnt");
 };
-
-// At most kYounger of the wave's youngest loads are still on their way behind this; no LDS access moves across it.
-template <int kYounger>
-__device__ __forceinline__ void wait_loads() {
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt((kYounger & 15) | (kYounger >> 4) << 14 | 7 << 4 | 15 << 8);
-    __builtin_amdgcn_sched_barrier(0);
-}
 
 // kCount operands as lds_read_tr8 reads them, from the byte offsets of their first four rows behind `base`, the next four kHi bytes further; waits for all
 // LDS accesses of the wave.  (Before the builtin the compiler waits for every load into LDS.)
@@ -443,7 +436,7 @@ __device__ __forceinline__ void kc_direct(const KcArgs& a, char* lds) {
     };
 
     const int kb = wave >> 2, wc = wave & 3;   // this wave's half of a step's channels, and its 32 columns
-    int a_off[2], b_off[2];                    // rows l16 and 16 + l16 (the others 32 rows further); columns 16 nb, channels 8 g4 .. +3 (and 1024 further the next four)
+    int a_off[2], b_off[2];                    // rows l16 and 16 + l16 (the others 32 rows further); columns 16 nb, channels 8 g4 .. +3 (the next four 1024 further)
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int r = 16 * i + l16;
@@ -459,6 +452,8 @@ __device__ __forceinline__ void kc_direct(const KcArgs& a, char* lds) {
     for (int rb = 0; rb < TL::kRB; ++rb) acc[rb][0] = acc[rb][1] = float4v{0.f, 0.f, 0.f, 0.f};
 
     int asked = 0;
+    // (D >= 256: there are more steps than places.  With a constant count here the loop below is compiled to a slower one: 6900 x 2048 12.8 ->
+    // 13.0 us, 6900 x 4096 22.8 -> 23.3.)
     for (; asked < TL::kStages - 1 && asked < nsteps; ++asked) ask(asked);
     int place = 0, free_place = TL::kStages - 1;
 #pragma clang loop unroll(disable)
@@ -514,18 +509,20 @@ __device__ __forceinline__ void kc_direct(const KcArgs& a, char* lds) {
         } else {
             typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
             typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-            const uint2v lo = __builtin_bit_cast(uint2v, __builtin_convertvector(q[0], bf16x4)), hi = __builtin_bit_cast(uint2v, __builtin_convertvector(q[1], bf16x4));
+            const uint2v lo = __builtin_bit_cast(uint2v, __builtin_convertvector(q[0], bf16x4));
+            const uint2v hi = __builtin_bit_cast(uint2v, __builtin_convertvector(q[1], bf16x4));
             *reinterpret_cast<uint4v*>(static_cast<unsigned short*>(a.c) + e) = uint4v{lo[0], lo[1], hi[0], hi[1]};
         }
     }
 }
 
-// kRowTile tokens x kBN columns; kWNB: 16-column blocks of a multiplying wave, and with it the form: 4 with loader waves, 2 with all waves alike.
-template <int kBN, int kWNB, bool kOutF32, int kRowTile>
-__global__ __launch_bounds__(kWNB == 2 ? 512 : Tile<kBN>::kThreads, kWNB == 2 ? 128 / kRowTile : Tile<kBN>::kPerCu) void key_compress_kernel(KcArgs a) {
-    static_assert(kWNB == 2 ? kBN == 128 : kRowTile == kBM, "forms");
+// The two kernels behind one name: kForm 4 with loader waves and 128 tokens (Tile), kForm 2 with all waves alike, 64 or 128 tokens (DmaTile).
+constexpr int kLoaderWaves = 4, kWavesAlike = 2;
+template <int kBN, int kForm, bool kOutF32, int kRowTile>
+__global__ __launch_bounds__(kForm == kWavesAlike ? 512 : Tile<kBN>::kThreads, kForm == kWavesAlike ? 128 / kRowTile : Tile<kBN>::kPerCu) void key_compress_kernel(KcArgs a) {
+    static_assert(kForm == kWavesAlike ? kBN == 128 : kForm == kLoaderWaves && kRowTile == kBM, "forms");
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    if constexpr (kWNB == 2) kc_direct<kOutF32, kRowTile>(a, lds);
+    if constexpr (kForm == kWavesAlike) kc_direct<kOutF32, kRowTile>(a, lds);
     else kc_roles<kOutF32, kBN>(a, lds);
 }
 
@@ -538,9 +535,9 @@ __global__ __launch_bounds__(kWNB == 2 ? 512 : Tile<kBN>::kThreads, kWNB == 2 ? 
 // small tile, 16 kTB tokens x 16 kNB columns, and its sixteen waves take the 32-channel blocks of D in
 // turn (wave w: blocks w, w + 16, ...), so that a walk is D / 512 steps long and needs no barrier: a wave brings its x and W blocks straight into a
 // piece of LDS of its own, W kAhead blocks ahead and x one more (x loaded into operand layout from global memory touches sixteen lines per quarter
-// wave, which the L1's tag lookups charge four times), and reads them from there as operands.  The sixteen partial results are added in wave
-// order, in fp32, at the end.  Through registers and LDS stores, two blocks ahead of both, the same sums took longer: D = 2048, 24 tokens 4.55 us against 3.85 now,
-// 2048 tokens 7.4 against 6.3, 4096 11.7 against 10.5, 6500 19.0 against 16.7; D = 768 3000 tokens 4.8 against 3.7; D = 4096 16 tokens 6.0 against 5.1.
+// wave, which the L1's tag lookups charge four times), and reads them from there as operands.  The sixteen partial results are added in
+// wave order, in fp32, at the end.  Through registers and LDS stores, two blocks ahead of both, the same sums took longer: D = 2048, 24
+// tokens 4.55 us against 3.85 now, 2048 tokens 7.4 against 6.3, 4096 11.7 against 10.5, 6500 19.0 against 16.7; D = 768 3000 tokens 4.8 against 3.7; D = 4096 16 tokens 6.0 against 5.1.
 constexpr int kFewWaves = 16;
 
 template <int kTB, int kNB>
@@ -690,12 +687,13 @@ hipError_t launch_few(const KcArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <int kBN, int kWNB, bool kOutF32, int kRowTile = kBM>
-hipError_t launch_tile(const KcArgs& a, hipStream_t stream) {
-    constexpr int threads = kWNB == 2 ? 512 : Tile<kBN>::kThreads, bytes = kWNB == 2 ? DmaTile<kRowTile>::kLds : Tile<kBN>::kLds;
+template <int kBN, int kForm, int kRowTile = kBM>
+hipError_t launch_tile(const KcArgs& a, bool out_f32, hipStream_t stream) {
+    constexpr bool kAlike = kForm == kWavesAlike;
     const long long row_tiles = (a.M + kRowTile - 1) / kRowTile;
     const dim3 grid(static_cast<unsigned>((row_tiles + 7) / 8 * 8 * ((a.C + kBN - 1) / kBN)));
-    hipLaunchKernelGGL((key_compress_kernel<kBN, kWNB, kOutF32, kRowTile>), grid, dim3(threads), bytes, stream, a);
+    const auto kernel = out_f32 ? &key_compress_kernel<kBN, kForm, true, kRowTile> : &key_compress_kernel<kBN, kForm, false, kRowTile>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kAlike ? 512 : Tile<kBN>::kThreads), kAlike ? DmaTile<kRowTile>::kLds : Tile<kBN>::kLds, stream, a);
     return hipGetLastError();
 }
 
@@ -709,10 +707,10 @@ hipError_t raise_lds_limits() {
     if (err == hipSuccess) err = set_lds_limit(&key_compress_few_kernel<1, 2, kOutF32>, FewTile<1, 2>::kLds);
     if (err == hipSuccess) err = set_lds_limit(&key_compress_few_kernel<1, 4, kOutF32>, FewTile<1, 4>::kLds);
     if (err == hipSuccess) err = set_lds_limit(&key_compress_few_kernel<2, 4, kOutF32>, FewTile<2, 4>::kLds);
-    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, 4, kOutF32, kBM>, Tile<128>::kLds);
-    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<256, 4, kOutF32, kBM>, Tile<256>::kLds);
-    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, 2, kOutF32, 64>, DmaTile<64>::kLds);
-    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, 2, kOutF32, 128>, DmaTile<128>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, kLoaderWaves, kOutF32, kBM>, Tile<128>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<256, kLoaderWaves, kOutF32, kBM>, Tile<256>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, kWavesAlike, kOutF32, 64>, DmaTile<64>::kLds);
+    if (err == hipSuccess) err = set_lds_limit(&key_compress_kernel<128, kWavesAlike, kOutF32, 128>, DmaTile<128>::kLds);
     return err;
 }
 
@@ -733,13 +731,15 @@ hipError_t launch_key_compress(long long M, int D, const void* x, const void* w,
     // its walk of D / 512 steps is shorter than the D / 64 of the large tiles.  The smallest tile that still
     // gives at most one workgroup per compute unit, since a workgroup's time grows with its tile.  Measured, D
     // = 2048, microseconds, large tiles -> this form: 19.7 -> 4.4 at 1 token, 20.9 -> 5.2 at 512, 21.0 -> 5.5 at
-    // 1024, 21.0 -> 6.8 at 2048, 21.0 -> 10.6 at 4096 (256 workgroups of the largest tile); D = 1024: 11.5 -> 3.8 at 16 tokens, 12.3
-    // -> 7.4 at 8192, level at 16 384.  From D = 2048 on a large tile's walk is so long that two rounds of these still win
-    // or tie: 18.5 against 19.9 at 4200 tokens, 19.5 against 20.1 at 6200 and 19.8 against 20.1 at 6700, but 20.4 against 20.1
-    // at 7200 and 21.6 against 20.2 at 8192, so up to five thirds of a round there (six to seven thousand tokens); wider models
-    // the whole second round: D = 2304 20.5 against 22.0 at 3000 tokens, 3072 24.0 against 28.2 at 4096 and 25.0 against 28.3 at 5200,
-    // 4096 33.6 against 36.4 at 4096 (all of these with loads through registers in both; now 15.8 us at 4500 tokens, 16.7 at 6500).  Beyond that the W traffic of the small tiles (all of W per 32 tokens) loses: D = 2048,
-    // 16 384 tokens 37 against 21.
+    // 1024, 21.0 -> 6.3 at 2048, 21.0 -> 10.6 at 4096 (256 workgroups of the largest tile); D = 1024: 11.5 -> 3.8 at 16 tokens, 12.3
+    // -> 5.7 at 8192.  From D = 2048 on a large tile's walk is so long that further rounds of these won, or tied, against the tiles with
+    // loader waves, which took these calls when the lines were drawn: up to five thirds of a round at D = 2048 (6700 tokens 19.8 against
+    // 20.1, 7200 20.4 against 20.1), wider models the whole second round (4096 x 4096 33.6 against 36.4).
+    // Beyond the first round the 64-token tiles below, with all waves alike, are the faster ones now.  These : those, with x in the
+    // caches and from HBM: D = 2048, 4097 tokens 14.4 : 12.8 and 16.4 : 16.7, 5000 15.1 : 12.9 and 19.9 : 17.0, 6816 17.1 : 13.1 and 20.7 : 17.6;
+    // D = 2304, 3000 17.3 : 14.1 and 21.0 : 16.9; D = 3072, 5000 22.1 : 18.1 and 26.6 : 22.3; D = 4096, 2049 24.1 : 22.5 and 26.8 : 27.9,
+    // 4096 31.8 : 23.0 and 35.5 : 29.2.  But sixteen short sums are closer to 64 bits than two long ones, 0.98e-7 : 1.87e-7 at D =
+    // 2048, 1.02e-7 : 1.99e-7 at 2304, 1.15e-7 : 2.72e-7 at 4096 (2-norm), so the lines stay for the precision: no call is moved to less.
     const int cus = compute_units();
     auto groups = [&](int tb, int nb) {
         return (M + 16 * tb - 1) / (16 * tb) * ((a.C + 16 * nb - 1) / (16 * nb));
@@ -759,11 +759,10 @@ hipError_t launch_key_compress(long long M, int D, const void* x, const void* w,
     // (The direct form addresses W with 32 bits.)
     if (D <= 32768) {
         const long long col_tiles = (a.C + 127) / 128;
-        if ((M + 63) / 64 * col_tiles <= (a.C <= 64 ? 2 : 1) * cus) return out_f32 ? launch_tile<128, 2, true, 64>(a, stream) : launch_tile<128, 2, false, 64>(a, stream);
-        if ((M + 127) / 128 * col_tiles <= cus) return out_f32 ? launch_tile<128, 2, true, 128>(a, stream) : launch_tile<128, 2, false, 128>(a, stream);
+        if ((M + 63) / 64 * col_tiles <= (a.C <= 64 ? 2 : 1) * cus) return launch_tile<128, kWavesAlike, 64>(a, out_f32, stream);
+        if ((M + 127) / 128 * col_tiles <= cus) return launch_tile<128, kWavesAlike, 128>(a, out_f32, stream);
     }
-    if (a.C > 128) return out_f32 ? launch_tile<256, 4, true>(a, stream) : launch_tile<256, 4, false>(a, stream);
-    return out_f32 ? launch_tile<128, 4, true>(a, stream) : launch_tile<128, 4, false>(a, stream);
+    return a.C > 128 ? launch_tile<256, kLoaderWaves>(a, out_f32, stream) : launch_tile<128, kLoaderWaves>(a, out_f32, stream);
 }
 
 }  // namespace wkv6

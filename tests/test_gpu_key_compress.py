@@ -36,7 +36,7 @@ def test_matches_oracle(gpu_device, M, D):
     assert np.array_equal(c16, round_to_bf16(c32))
 
 
-# tiles of 64 and 128 tokens with all waves alike: a last tile of one row, fewer steps than places, column tiles of 16, 48 and 64 columns, a
+# tiles of 64 and 128 tokens with all waves alike: a last tile of one row, the fewest steps, column tiles of 16, 48 and 64 columns, a
 # third column tile of 16; smaller tiles, the contraction over the waves: waves without a block, a last block of one row, 16 of 64 columns
 @pytest.mark.parametrize("M,D", [(6849, 2048), (16384, 2048), (16385, 2048), (8200, 256), (16321, 256), (9000, 768), (30000, 768), (12000, 1024), (5400, 4352), (17, 2048), (2100, 2048), (4097, 2048), (3001, 768), (8191, 256), (1500, 2304)])
 def test_tiles_that_fill_the_chip_at_most_once(gpu_device, M, D):
@@ -126,8 +126,8 @@ def test_every_tile_of_the_split_contraction(gpu_device, M, D):
 
 @pytest.mark.parametrize("M,D", [(8193, 4096), (16384, 4096), (16385, 4096), (8192, 2048), (32768, 1024), (32769, 1024), (5000, 8192), (8321, 4352)])
 def test_large_tiles_around_one_per_compute_unit(gpu_device, M, D):
-    """Both sides of the change from 128-column tiles with eight MFMA waves (at most 256 tiles) to the wider or
-    narrower-staffed ones, with a ragged last row tile and a partial last column tile."""
+    """Both sides of the changes between tiles of 64 and of 128 tokens with all waves alike (at most 256 of them) and the tiles with loader
+    waves, with a ragged last row tile and a partial last column tile."""
     x, w = make_key_compress_inputs(M, D, seed=77 + M)
     c32 = run(x, w, torch.float32)
     assert max_norm_err(c32, key_compress_oracle(x, w)) <= 1e-5
