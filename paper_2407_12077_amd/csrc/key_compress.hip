@@ -345,7 +345,8 @@ __device__ __forceinline__ void kc_roles(const KcArgs& a, char* lds) {
 template <int kRowTile>
 struct DmaTile {
     static constexpr int kX = kRowTile * 128, kStage = kX + 64 * 256;
-    static constexpr int kStages = 3;                                       // steps in LDS: as many as fit, whose first step begins later, were 5 to 10 % slower
+    // steps in LDS: with as many as fit the first one begins later (5 to 10 % slower)
+    static constexpr int kStages = 3;
     static constexpr int kXLoads = kRowTile / 64, kLoads = kXLoads + 2;      // of a wave and step
     static constexpr int kRB = kRowTile / 16;                               // 16-row blocks
     static constexpr int kPRow = 128 + 4;                                   // row stride (floats) of the two partial results
@@ -436,7 +437,8 @@ __device__ __forceinline__ void kc_direct(const KcArgs& a, char* lds) {
     };
 
     const int kb = wave >> 2, wc = wave & 3;   // this wave's half of a step's channels, and its 32 columns
-    int a_off[2], b_off[2];                    // rows l16 and 16 + l16 (the others 32 rows further); columns 16 nb, channels 8 g4 .. +3 (the next four 1024 further)
+    // rows l16 and 16 + l16 (the others 32 rows further); columns 16 nb, channels 8 g4 .. +3 (the next four 1024 further)
+    int a_off[2], b_off[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int r = 16 * i + l16;
@@ -519,7 +521,8 @@ __device__ __forceinline__ void kc_direct(const KcArgs& a, char* lds) {
 // The two kernels behind one name: kForm 4 with loader waves and 128 tokens (Tile), kForm 2 with all waves alike, 64 or 128 tokens (DmaTile).
 constexpr int kLoaderWaves = 4, kWavesAlike = 2;
 template <int kBN, int kForm, bool kOutF32, int kRowTile>
-__global__ __launch_bounds__(kForm == kWavesAlike ? 512 : Tile<kBN>::kThreads, kForm == kWavesAlike ? 128 / kRowTile : Tile<kBN>::kPerCu) void key_compress_kernel(KcArgs a) {
+__global__ __launch_bounds__(kForm == kWavesAlike ? 512 : Tile<kBN>::kThreads, kForm == kWavesAlike ? 128 / kRowTile : Tile<kBN>::kPerCu)
+void key_compress_kernel(KcArgs a) {
     static_assert(kForm == kWavesAlike ? kBN == 128 : kForm == kLoaderWaves && kRowTile == kBM, "forms");
     extern __shared__ __attribute__((aligned(16))) char lds[];
     if constexpr (kForm == kWavesAlike) kc_direct<kOutF32, kRowTile>(a, lds);
@@ -537,7 +540,8 @@ __global__ __launch_bounds__(kForm == kWavesAlike ? 512 : Tile<kBN>::kThreads, k
 // piece of LDS of its own, W kAhead blocks ahead and x one more (x loaded into operand layout from global memory touches sixteen lines per quarter
 // wave, which the L1's tag lookups charge four times), and reads them from there as operands.  The sixteen partial results are added in
 // wave order, in fp32, at the end.  Through registers and LDS stores, two blocks ahead of both, the same sums took longer: D = 2048, 24
-// tokens 4.55 us against 3.85 now, 2048 tokens 7.4 against 6.3, 4096 11.7 against 10.5, 6500 19.0 against 16.7; D = 768 3000 tokens 4.8 against 3.7; D = 4096 16 tokens 6.0 against 5.1.
+// tokens 4.55 us against 3.85 now, 2048 tokens 7.4 against 6.3, 4096 11.7 against 10.5, 6500 19.0 against 16.7; D = 768 3000 tokens
+// 4.8 against 3.7; D = 4096 16 tokens 6.0 against 5.1.
 constexpr int kFewWaves = 16;
 
 template <int kTB, int kNB>

@@ -195,7 +195,8 @@ __device__ __forceinline__ void load_rows_kv(Raw& d, const Streams& st, long lon
 // boundaries: its chunks form one sequence, unit after unit, and only the state (consumers) and
 // the base addresses change at a boundary, so short sequences do not pay the fill and drain of
 // the pipeline once per unit.  The stride between the units of a workgroup is a multiple of H, so they share the head
-// unless they take the heads in turn (kTurn: the head moves on by one from each unit to the next); they have the same length T, and their token rows lie `step` elements apart.
+// unless they take the heads in turn (kTurn: the head moves on by one from each unit to the next); they have the same length T, and
+// their token rows lie `step` elements apart.
 struct Units {
     int first;            // index (batch * H + head) of the first one: selects state_in / state_out / moments
     int stride;           // unit index stride
