@@ -1,14 +1,16 @@
 // Token statistics of the LayerNorm over all heads (Finch-C2 Time Mixing, output equation) from
 // the per-head partial moments the prefill kernel emits next to its output.
 //
-// Each (batch, head, token) contributes the sum s of its N values and the squared deviations m2
-// from its own mean.  With the mean mu of the token known from the sums, the heads' deviations about it add up without
-// cancellation: M2 = sum of m2_h + N (s_h / N - mu)^2 (Chan, Golub, LeVeque).  A workgroup
-// takes 64 consecutive tokens of one batch; each of its four waves has every fourth head (a
-// lane per token, so every read is a contiguous run of 8-byte pairs); sums and then deviations meet in LDS.  Bound by latency: up to 256
-// heads stay in registers, all requested at once, and no step divides.  Folding the pairs one after the other, with two divisions
-// each, the calls of a layer took 156.4 us where they took 153.9 with this (8 x 2048 tokens x 32 heads) and 27.8 where they took 26.9
-// (24 x 1).
+// Each (batch, head, token) contributes the sum s of its N values and the squared deviations m2 from its own mean.  With the mean
+// mu of the token known from the sums, the heads' deviations d_h = s_h / N - mu about it add up without cancellation: M2 = sum of m2_h +
+// N d_h^2 (Chan, Golub, LeVeque).  What mu lacks for rounding is the mean of the d_h, which then corrects both (the corrected two-pass
+// form): heads of equal sums s have the mean s / N and no deviation, whatever their number, and a common offset of 1e5 standard
+// deviations leaves rstd its 5e-8 (without the correction 1e-5, pair after pair 3e-4).
+//
+// A workgroup takes 64 consecutive tokens of one batch; each of its four waves has every fourth head (a lane per token, so every read
+// is a contiguous run of 8-byte pairs); sums and then deviations meet in LDS.  Bound by latency: up to 256 heads stay in
+// registers, all requested at once, and nothing but the result is divided.  Folding the pairs one after the other, with two divisions each,
+// took longer (figures at the launch); the calls of a layer 156.4 us where they take 153.9 (8 x 2048 tokens x 32 heads), 27.8 and 26.9 (24 x 1).
 #include "wkv6_launch.h"
 
 namespace wkv6 {
@@ -16,51 +18,81 @@ namespace {
 
 constexpr float kInvN = 1.f / kHeadSize;
 
-// deviations of a head's values about the token's mean
-__device__ __forceinline__ float deviations(const float2 p, float mean) {
-    const float d = fmaf(p.x, kInvN, -mean);
-    return fmaf(d * kHeadSize, d, p.y);
-}
+// deviations of the heads about the token's mean as it was first rounded
+struct Deviations {
+    float m2 = 0.f, left = 0.f;
+    __device__ __forceinline__ void add(const float2 p, float mean) {
+        const float d = fmaf(p.x, kInvN, -mean);
+        m2 += fmaf(d * kHeadSize, d, p.y);
+        left += d;
+    }
+    __device__ __forceinline__ float2 mean_rstd(float mean, float heads, float per_head, float eps) const {
+        const float by = left * per_head;
+        float m = fmaf(by * -kHeadSize, left, m2);
+        if (m < 0.f) m = 0.f;              // (NaN stays)
+        return make_float2(mean + by, 1.f / sqrtf(m / (heads * kHeadSize) + eps));
+    }
+};
 
 // kKept: heads of a wave in registers, all requested before the first is used.  As few as hold all heads (the rule is at the launch),
-// since a place without a head costs its instructions all the same: 8 x 2048 tokens x 8 heads 1.97 us with 4, 2.35 with 16; x 32 heads 2.37
-// with 16, 3.01 with 32; x 130 heads 3.34 with 40, 4.77 with 64.  kRest: there are more heads, which are read twice.
+// since a place without a head costs its instructions all the same: 8 x 2048 tokens x 8 heads 2.00 us with 4, 2.49 with 16; x 32 heads 2.14
+// with 8, 2.49 with 16; x 130 heads 3.6 with 40, 4.9 with 64.  (Branches around absent heads took longer where all are there: x 64
+// 2.72 against 2.51.)  kRest: there are more heads, which are read twice.
 template <int kKept, bool kRest>
 __global__ __launch_bounds__(256) void layernorm_finalize_kernel(int T, int H, const float2* moments, float eps,
                                                                  float2* mean_rstd) {
-    __shared__ float part[2][4][64];
+    __shared__ float part[4][64];
+    __shared__ float2 devs[4][64];
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int t = blockIdx.x * 64 + lane;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t0 = blockIdx.x * 64, t = t0 + lane;
     const int b = blockIdx.y;
-    const float2* src = moments + static_cast<long long>(b) * H * T + (t < T ? t : T - 1);
+    // A head's pairs of the 64 tokens, from a descriptor of their own, which is empty for a head that is not there: zeros, without a branch.
+    float2* src = const_cast<float2*>(moments) + static_cast<long long>(b) * H * T + t0;
+    const int bytes = (T - t0 < 64 ? T - t0 : 64) * 8;
+    auto pair_of = [&](int h) {
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(src + (h < H ? static_cast<long long>(h) * T : 0), 0, h < H ? bytes : 0, 0x00020000);
+        return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, lane * 8, 0, 0));
+    };
     float2 kept[kKept];
     float sums[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < kKept; ++i) kept[i] = wave + 4 * i < H ? src[static_cast<long long>(wave + 4 * i) * T] : make_float2(0.f, 0.f);
+    for (int i = 0; i < kKept; ++i) kept[i] = pair_of(wave + 4 * i);
 #pragma unroll
-    for (int i = 0; i < kKept; ++i) sums[i % 4] += kept[i].x;
+    for (int i = 0; i < kKept; ++i) sums[i % 4] = fmaf(kept[i].x, kInvN, sums[i % 4]);
+    constexpr int kAtOnce = 8;             // of the heads that are not kept
     if constexpr (kRest) {
-#pragma unroll 8
-        for (int h = wave + 4 * kKept; h < H; h += 4) sums[0] += src[static_cast<long long>(h) * T].x;
+        for (int h = wave + 4 * kKept; h < H; h += 4 * kAtOnce) {
+            float2 p[kAtOnce];
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i) p[i] = pair_of(h + 4 * i);
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i) sums[i % 4] = fmaf(p[i].x, kInvN, sums[i % 4]);
+        }
     }
-    part[0][wave][lane] = (sums[0] + sums[1]) + (sums[2] + sums[3]);
+    part[wave][lane] = (sums[0] + sums[1]) + (sums[2] + sums[3]);
+    const float heads = static_cast<float>(H), per_head = __builtin_amdgcn_rcpf(heads);
     __syncthreads();
-    const float count = static_cast<float>(H) * kHeadSize;
-    const float mean = ((part[0][0][lane] + part[0][1][lane]) + (part[0][2][lane] + part[0][3][lane])) / count;
-    float m2 = 0.f;
+    const float mean = ((part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane])) * per_head;
+    Deviations dev;
 #pragma unroll
-    for (int i = 0; i < kKept; ++i)
-        if (wave + 4 * i < H) m2 += deviations(kept[i], mean);
+    for (int i = 0; i < kKept; ++i) dev.add(kept[i], wave + 4 * i < H ? mean : 0.f);
     if constexpr (kRest) {
-#pragma unroll 8
-        for (int h = wave + 4 * kKept; h < H; h += 4) m2 += deviations(src[static_cast<long long>(h) * T], mean);
+        for (int h = wave + 4 * kKept; h < H; h += 4 * kAtOnce) {
+            float2 p[kAtOnce];
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i) p[i] = pair_of(h + 4 * i);
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i) dev.add(p[i], h + 4 * i < H ? mean : 0.f);
+        }
     }
-    part[1][wave][lane] = m2;
+    devs[wave][lane] = make_float2(dev.m2, dev.left);
     __syncthreads();
     if (wave == 0 && t < T) {
-        m2 = (part[1][0][lane] + part[1][1][lane]) + (part[1][2][lane] + part[1][3][lane]);
-        mean_rstd[static_cast<long long>(b) * T + t] = make_float2(mean, 1.f / sqrtf(m2 / count + eps));
+        dev.m2 = (devs[0][lane].x + devs[1][lane].x) + (devs[2][lane].x + devs[3][lane].x);
+        dev.left = (devs[0][lane].y + devs[1][lane].y) + (devs[2][lane].y + devs[3][lane].y);
+        mean_rstd[static_cast<long long>(b) * T + t] = dev.mean_rstd(mean, heads, per_head, eps);
     }
 }
 
@@ -71,20 +103,26 @@ __global__ __launch_bounds__(256) void layernorm_finalize_few_kernel(long long t
     const int lane = threadIdx.x & 63;
     const long long token = static_cast<long long>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (token >= tokens) return;
-    // (fewer than 2^32 tokens: a token has at least 8 bytes of partials and 128 of values)
+    // (fewer than 2^32 tokens: at most 65 535 sequences, of fewer than 16)
     const unsigned b = static_cast<unsigned>(token) / static_cast<unsigned>(T);
     const float2* src = moments + static_cast<long long>(b) * H * T + (token - static_cast<long long>(b) * T);
     const float2 mine = lane < H ? src[static_cast<long long>(lane) * T] : make_float2(0.f, 0.f);
-    float sum = mine.x;
-    for (int h = lane + 64; h < H; h += 64) sum += src[static_cast<long long>(h) * T].x;
+    float sum = mine.x * kInvN;
+    for (int h = lane + 64; h < H; h += 64) sum = fmaf(src[static_cast<long long>(h) * T].x, kInvN, sum);
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, 64);
-    const float count = static_cast<float>(H) * kHeadSize, mean = sum / count;
-    float m2 = lane < H ? deviations(mine, mean) : 0.f;
-    for (int h = lane + 64; h < H; h += 64) m2 += deviations(src[static_cast<long long>(h) * T], mean);
+    const float heads = static_cast<float>(H), per_head = __builtin_amdgcn_rcpf(heads), mean = sum * per_head;
+    Deviations dev;
+    if (lane < H) dev.add(mine, mean);
+    for (int h = lane + 64; h < H; h += 64) dev.add(src[static_cast<long long>(h) * T], mean);
+    // both at once: the lower half of the lanes adds up m2, the upper one what is left of the mean
+    float half = lane < 32 ? dev.m2 : dev.left;
+    half += __shfl_xor(lane < 32 ? dev.left : dev.m2, 32, 64);
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) m2 += __shfl_xor(m2, m, 64);
-    if (lane == 0) mean_rstd[token] = make_float2(mean, 1.f / sqrtf(m2 / count + eps));
+    for (int m = 16; m >= 1; m >>= 1) half += __shfl_xor(half, m, 64);
+    dev.m2 = half;
+    dev.left = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(half), 32));
+    if (lane == 0) mean_rstd[token] = dev.mean_rstd(mean, heads, per_head, eps);
 }
 
 // The normalisation itself, for callers whose projection GEMM has no row-scaling epilogue:
@@ -251,18 +289,23 @@ hipError_t launch_layernorm_finalize(int B, int T, int H, const float* moments, 
         return hipGetLastError();
     }
     const dim3 grid(static_cast<unsigned>((T + 63) / 64), static_cast<unsigned>(B));
-    // Pairs folded one after the other (before) : here, us inside a graph: 8 x 2048 tokens x 8 heads 2.24 : 1.97, x 32 2.64 : 2.37, x 130
-    // 4.60 : 3.34, x 256 7.40 : 5.15, x 300 10.4 : 10.4 (with 64 places 11.4); 32 x 4096 x 2 heads 2.52 : 2.51, x 8 3.39 : 2.63, and
-    // of one head, with nothing to fold, 2.30 : 2.51.
+    // Pairs folded one after the other : here, us inside a graph: 8 x 2048 tokens x 8 heads 2.24 : 2.00, x 16 2.33 : 2.00, x 32 2.62 : 2.14,
+    // x 64 3.21 : 2.51, x 128 4.43 : 3.30, x 256 7.32 : 5.15, x 300 10.5 : 9.4; 1024 x 11 x 32 4.02 : 2.93, 32 x 4096 x 2 2.50 : 2.43, and of
+    // one head, with nothing to fold, 2.29 : 2.41.
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, T, H, reinterpret_cast<const float2*>(moments), eps, reinterpret_cast<float2*>(mean_rstd));
     };
-    if (H <= 16) go(&layernorm_finalize_kernel<4, false>);
+    if (H <= 4) go(&layernorm_finalize_kernel<1, false>);
+    else if (H <= 16) go(&layernorm_finalize_kernel<4, false>);
+    else if (H <= 32) go(&layernorm_finalize_kernel<8, false>);
+    else if (H <= 48) go(&layernorm_finalize_kernel<12, false>);
     else if (H <= 64) go(&layernorm_finalize_kernel<16, false>);
+    else if (H <= 96) go(&layernorm_finalize_kernel<24, false>);
     else if (H <= 128) go(&layernorm_finalize_kernel<32, false>);
     else if (H <= 160) go(&layernorm_finalize_kernel<40, false>);
+    else if (H <= 192) go(&layernorm_finalize_kernel<48, false>);
     else if (H <= 256) go(&layernorm_finalize_kernel<64, false>);
-    else go(&layernorm_finalize_kernel<40, true>);
+    else go(&layernorm_finalize_kernel<64, true>);
     return hipGetLastError();
 }
 

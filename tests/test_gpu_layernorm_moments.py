@@ -266,10 +266,32 @@ def test_fold_of_short_sequences(gpu_device, B, T, H):
     assert (np.abs(got[..., 1] * np.sqrt(var + EPS) - 1) <= 3e-5).all()
 
 
-@pytest.mark.parametrize("B,T,H", [(2, 40, 1), (3, 65, 4), (2, 100, 16), (2, 40, 17), (1, 130, 33), (1, 70, 65), (2, 40, 128), (2, 40, 130), (1, 64, 160),
-                                   (1, 70, 161), (1, 70, 200), (2, 33, 256), (2, 33, 257), (1, 65, 300), (2, 17, 1000)])
+@pytest.mark.parametrize("B,T,H", [(2, 40, 1), (3, 65, 4), (3, 20, 5), (2, 100, 16), (2, 40, 17), (1, 40, 32), (1, 130, 33), (2, 40, 49), (1, 70, 65), (1, 40, 97),
+                                   (2, 40, 128), (2, 40, 130), (1, 64, 160), (1, 70, 161), (1, 70, 193), (1, 70, 200), (2, 33, 256), (2, 33, 257), (1, 65, 300),
+                                   (2, 17, 1000)])
 def test_fold_of_every_number_of_heads_kept(gpu_device, B, T, H):
     """Both sides of each number of heads that a wave keeps, and heads beyond the most that it does, at the bars of the other folds.  The longest
-    sum, 1000 heads, has 220 additions in a row, 220 x 2^-24 = 1.3e-5: of the heads' means (0.1 here) that is 1.3e-6, against
-    1e-5 of a standard deviation of 0.7; of the variance it is 0.7e-5 in the reciprocal, against 3e-5."""
+    sum, 1000 heads, has 250 additions in a row, 250 x 2^-24 = 1.5e-5: of the heads' means (0.1 here) that is 1.5e-6, against
+    1e-5 of a standard deviation of 0.7; of the variance it is 0.8e-5 in the reciprocal, against 3e-5."""
     test_fold_of_short_sequences(gpu_device, B, T, H)
+
+
+@pytest.mark.parametrize("B,T,H", [(2, 1, 12), (3, 2, 40), (2, 5, 130), (1, 70, 3), (2, 40, 12), (1, 65, 40), (1, 70, 100), (2, 40, 130), (1, 65, 300)])
+def test_heads_of_equal_sums(gpu_device, B, T, H):
+    """Constant rows, of any value and number of heads: the mean is that value to two roundings (2^-23 of it), and no deviation is left beside
+    eps (the mean's first rounding, squared, would be: 1000 with 12 heads 7e-4 of rstd).  The same with a spread of one about the value:
+    what is left of the mean's rounding is some 2^-24 of it times itself, so rstd keeps its bar."""
+    rng = np.random.default_rng(H)
+    value = (rng.uniform(0.5, 2.0, (B, 1, T)) * 10.0 ** rng.integers(0, 6, (B, 1, T))).astype(np.float32)
+    got = torch.empty((B, T, 2), device="cuda")
+    for spread in (0.0, 1.0):
+        sums = np.broadcast_to(value * np.float32(64), (B, H, T)) + (rng.standard_normal((B, H, T)) * 8 * spread).astype(np.float32)
+        mom = np.stack([sums, np.full((B, H, T), 64 * spread)], axis=-1).astype(np.float32)
+        wkv.wkv6_layernorm_finalize(B, T, H, 64, to_dev(mom, torch.float32), EPS, got)
+        torch.cuda.synchronize()
+        m = mom.astype(np.float64)
+        mean = m[..., 0].sum(1) / (64 * H)
+        var = (m[..., 1] + 64 * (m[..., 0] / 64 - mean[:, None]) ** 2).sum(1) / (64 * H)
+        g = got.cpu().numpy()
+        assert (np.abs(g[..., 0] - mean) <= 2.0 ** -23 * np.abs(mean)).all()
+        assert (np.abs(g[..., 1] * np.sqrt(var + EPS) - 1) <= (1e-6 if spread == 0 else 3e-5)).all()
