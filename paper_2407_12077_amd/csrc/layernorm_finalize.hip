@@ -277,10 +277,11 @@ hipError_t launch_layernorm_finalize(int B, int T, int H, const float* moments, 
     // Below 16 tokens a sequence the lane-per-token form uses fewer than a quarter of its lanes and one workgroup per
     // sequence, but it reads a line of a head's pairs once where a wave per token reads it for every token again.  So
     // the wave per token takes launches of up to 2048 tokens (one round of waves) and, with more, the lengths where the
-    // heads make the other form's chain the longer one.  Microseconds, lane per token : wave per token: 24 sequences of one
-    // token, 32 heads, 4.6 : 3.9 inside a layer's calls (4.5 : 4.6 repeated alone), 1024 x 8 tokens x 12 heads 4.5 : 6.5, x 15 4.5 :
-    // 10; 4096 x 2 x 32 8.8 : 7.1, x 4 8.8 : 11.8, x 15 8.9 : 38; 65 535 x 1 x 12 54 : 35, x 2 54 : 68; 1024 x 4 x 64 5.8 : 5.1,
-    // x 6 5.8 : 6.6; 1024 x 8 x 128 9.9 : 8.3, x 11 9.4 : 12.6; 4096 x 8 x 256 54 : 32, x 15 53 : 81.
+    // heads make the other form's chain the longer one.  Lane per token : wave per token, us inside a graph: 24 sequences of one token
+    // 2.09 : 2.21 (12 heads), 2.29 : 2.24 (32), 2.62 : 2.24 (64); 136 x 15 x 32 2.22 : 2.34, 1024 x 2 x 12 2.55 : 2.32, 2048 x 1 x 32 4.1 : 2.3; 1024 x
+    // 8 x 12 2.5 : 3.4, x 15 2.5 : 4.7; 4096 x 2 x 32 6.0 : 3.3, x 15 5.9 : 14.6; 65 535 x 1 x 12 38 : 13; 1024 x 4 x 64 3.7 : 2.6; 1024 x 8 x 128
+    // 5.8 : 4.1, x 11 5.8 : 8.7; 4096 x 8 x 256 32 : 27, x 9 32 : 43.  The lines were drawn when both folded pair after pair and err towards
+    // the lanes where sequences of 2 to 6 tokens are many: 4096 x 3 x 32 5.9 : 4.0, x 4 5.8 : 4.8, 1024 x 6 x 64 3.9 : 2.9, 65 535 x 2 x 12 38 : 24.
     const long long tokens = static_cast<long long>(B) * T;
     const int longest = H / 16 < 8 ? H / 16 : 8;
     if (T < 16 && (tokens <= 2048 || T == 1 || T <= longest)) {
