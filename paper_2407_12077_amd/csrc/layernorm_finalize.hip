@@ -96,6 +96,28 @@ __global__ __launch_bounds__(256) void layernorm_finalize_kernel(int T, int H, c
     }
 }
 
+// The two halves of a wave added: the sum of a's in the lower half of the lanes, of b's in the upper one.
+__device__ __forceinline__ float add_halves(float a, float b) {
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
+
+template <int kBy>
+__device__ __forceinline__ float rotated(float v) {        // within a row of sixteen lanes
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + kBy, 0xf, 0xf, false));
+}
+
+// Sum over the 32 lanes of a half, in every lane of it, in pairs of lanes 16, 8, 4, 2 and 1 apart (a rotation by as much as the period
+// to which the sums are equal already).  No step passes LDS; through shuffles 65 535 x 1 token x 12 heads took 13.1 us where this takes 11.0.
+__device__ __forceinline__ float half_sum(float v) {
+    const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+    v += rotated<8>(v);
+    v += rotated<4>(v);
+    v += rotated<2>(v);
+    return v + rotated<1>(v);
+}
+
 // Sequences of a few tokens: a wave per token with the heads on its lanes, since a lane per token would leave
 // most lanes without one.  Partial results meet in pairs over the lanes.
 __global__ __launch_bounds__(256) void layernorm_finalize_few_kernel(long long tokens, int T, int H, const float2* moments,
@@ -109,19 +131,14 @@ __global__ __launch_bounds__(256) void layernorm_finalize_few_kernel(long long t
     const float2 mine = lane < H ? src[static_cast<long long>(lane) * T] : make_float2(0.f, 0.f);
     float sum = mine.x * kInvN;
     for (int h = lane + 64; h < H; h += 64) sum = fmaf(src[static_cast<long long>(h) * T].x, kInvN, sum);
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, 64);
+    sum = half_sum(add_halves(sum, sum));
     const float heads = static_cast<float>(H), per_head = __builtin_amdgcn_rcpf(heads), mean = sum * per_head;
     Deviations dev;
     if (lane < H) dev.add(mine, mean);
     for (int h = lane + 64; h < H; h += 64) dev.add(src[static_cast<long long>(h) * T], mean);
-    // both at once: the lower half of the lanes adds up m2, the upper one what is left of the mean
-    float half = lane < 32 ? dev.m2 : dev.left;
-    half += __shfl_xor(lane < 32 ? dev.left : dev.m2, 32, 64);
-#pragma unroll
-    for (int m = 16; m >= 1; m >>= 1) half += __shfl_xor(half, m, 64);
-    dev.m2 = half;
-    dev.left = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(half), 32));
+    const float both = half_sum(add_halves(dev.m2, dev.left));
+    dev.m2 = both;
+    dev.left = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(both), 32));
     if (lane == 0) mean_rstd[token] = dev.mean_rstd(mean, heads, per_head, eps);
 }
 
@@ -278,10 +295,10 @@ hipError_t launch_layernorm_finalize(int B, int T, int H, const float* moments, 
     // sequence, but it reads a line of a head's pairs once where a wave per token reads it for every token again.  So
     // the wave per token takes launches of up to 2048 tokens (one round of waves) and, with more, the lengths where the
     // heads make the other form's chain the longer one.  Lane per token : wave per token, us inside a graph: 24 sequences of one token
-    // 2.09 : 2.21 (12 heads), 2.29 : 2.24 (32), 2.62 : 2.24 (64); 136 x 15 x 32 2.22 : 2.34, 1024 x 2 x 12 2.55 : 2.32, 2048 x 1 x 32 4.1 : 2.3; 1024 x
-    // 8 x 12 2.5 : 3.4, x 15 2.5 : 4.7; 4096 x 2 x 32 6.0 : 3.3, x 15 5.9 : 14.6; 65 535 x 1 x 12 38 : 13; 1024 x 4 x 64 3.7 : 2.6; 1024 x 8 x 128
-    // 5.8 : 4.1, x 11 5.8 : 8.7; 4096 x 8 x 256 32 : 27, x 9 32 : 43.  The lines were drawn when both folded pair after pair and err towards
-    // the lanes where sequences of 2 to 6 tokens are many: 4096 x 3 x 32 5.9 : 4.0, x 4 5.8 : 4.8, 1024 x 6 x 64 3.9 : 2.9, 65 535 x 2 x 12 38 : 24.
+    // 2.15 : 1.91 (12 heads), 2.26 : 1.90 (32), 2.60 : 1.90 (64); 136 x 15 x 12 2.07 : 2.04, 1024 x 2 x 12 2.57 : 2.03, 2048 x 1 x 32 4.1 : 2.0; 1024 x
+    // 8 x 12 2.5 : 2.9, x 15 2.5 : 4.0; 4096 x 2 x 32 6.0 : 2.9, x 15 6.0 : 14.0; 65 535 x 1 x 12 38 : 11; 1024 x 4 x 64 3.8 : 2.3; 1024 x 8 x 128
+    // 5.8 : 3.8, x 11 5.8 : 8.2; 4096 x 8 x 256 32 : 27, x 9 32 : 43.  The lines were drawn when both folded pair after pair and err towards
+    // the lanes where sequences of 2 to 6 tokens are many: 4096 x 3 x 32 6.0 : 3.5, x 4 5.9 : 4.1, 1024 x 6 x 64 3.8 : 2.7, 65 535 x 2 x 12 38 : 21.
     const long long tokens = static_cast<long long>(B) * T;
     const int longest = H / 16 < 8 ? H / 16 : 8;
     if (T < 16 && (tokens <= 2048 || T == 1 || T <= longest)) {
